@@ -128,6 +128,9 @@ hipError_t launch_resblock(const ConvParams& a, const ConvParams& b, hipStream_t
 // c = the stack convolution planned with its fused pool, a1 / b1 and a2 / b2 = the two blocks' convolutions
 bool stack_supported(const ConvParams& c, int NTC, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2);
 hipError_t launch_stack(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2, hipStream_t s);
+// the same for the stacks of the full-width bf16 teacher
+bool stack_bf16_supported(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2);
+hipError_t launch_stack_bf16(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2, hipStream_t s);
 // the third layer of that network (9x9x64 -> 3x3/1 x64) with sizes fixed at compile time
 bool conv_tail_supported(const ConvParams& p, int NT);
 hipError_t launch_conv_tail(const ConvParams& p, hipStream_t s);

@@ -1029,12 +1029,14 @@ int run(accerl_policy* p, const Call& c) {
                             const Step& t = p->steps[idx[k]];
                             cv[k] = t.cp;
                             cv[k].in = nullptr; cv[k].out = nullptr; cv[k].res = nullptr; cv[k].tap_acc = nullptr;
-                            cv[k].wfrag = p->consts + t.o_w; cv[k].bias = p->consts + t.o_bias; cv[k].mult = (const float*)(p->consts + t.o_mult);
+                            cv[k].wfrag = p->consts + t.o_w; cv[k].bias = p->consts + t.o_bias;
+                            cv[k].mult = t.o_mult >= 0 ? (const float*)(p->consts + t.o_mult) : nullptr;
                             cv[k].B = n;
                         }
                         cv[0].in = bufp(s.in_buf);
                         cv[4].out = bufp(p->steps[si + 5].out_buf);
-                        e = launch_stack(cv[0], cv[1], cv[2], cv[3], cv[4], c.stream);
+                        e = s.el == EL_I8 ? launch_stack(cv[0], cv[1], cv[2], cv[3], cv[4], c.stream)
+                                          : launch_stack_bf16(cv[0], cv[1], cv[2], cv[3], cv[4], c.stream);
                         pooled = true;          // the max-pool step behind this one is done too
                         stack_skip = 4;         // and so are the four convolutions of the two blocks
                         break;
@@ -1288,17 +1290,25 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
             Step& b1 = pol->steps[si + 3];
             Step& a2 = pol->steps[si + 4];
             Step& b2 = pol->steps[si + 5];
-            if (sc.kind != ST_CONV || sc.el != EL_I8 || sc.pool_buf < 0 || sc.fuse_next || sc.fused_prev || sc.res_buf >= 0) continue;
+            if (sc.kind != ST_CONV || sc.pool_buf < 0 || sc.fuse_next || sc.fused_prev || sc.res_buf >= 0) continue;
             if (sp.kind != ST_MAXPOOL || !sp.fused || sp.out_buf != sc.pool_buf) continue;
-            if (!(a1.kind == ST_CONV && a1.fuse_next && a1.resblock && b1.kind == ST_CONV && b1.fused_prev)) continue;
-            if (!(a2.kind == ST_CONV && a2.fuse_next && a2.resblock && b2.kind == ST_CONV && b2.fused_prev)) continue;
+            if (a1.kind != ST_CONV || b1.kind != ST_CONV || a2.kind != ST_CONV || b2.kind != ST_CONV) continue;
             if (a1.in_buf != sc.pool_buf || a2.in_buf != b1.out_buf) continue;
+            if (sc.el == EL_I8) {
+                if (!(a1.fuse_next && a1.resblock && b1.fused_prev && a2.fuse_next && a2.resblock && b2.fused_prev)) continue;
+            } else {
+                // bf16 blocks have no launch of their own: check here that each pair is one (the inner tensors are read by nothing else)
+                if (sc.el != EL_BF16 || a1.res_buf >= 0 || b1.in_buf != a1.out_buf || b1.res_buf != a1.in_buf) continue;
+                if (a2.res_buf >= 0 || b2.in_buf != a2.out_buf || b2.res_buf != a2.in_buf) continue;
+                if (sc.o_lut >= 0) continue;         // observation bytes through the table: not in the stack kernel
+            }
             bool read_elsewhere = false;             // the pooled image and the first block's output feed the blocks only
             for (size_t sj = si + 6; sj < pol->steps.size(); ++sj)
                 for (int b : {sc.pool_buf, b1.out_buf})
                     if (pol->steps[sj].in_buf == b || pol->steps[sj].res_buf == b) read_elsewhere = true;
             if (read_elsewhere) continue;
-            if (!stack_supported(sc.cp, sc.NT, a1.cp, b1.cp, a2.cp, b2.cp)) continue;
+            if (!(sc.el == EL_I8 ? stack_supported(sc.cp, sc.NT, a1.cp, b1.cp, a2.cp, b2.cp)
+                                 : stack_bf16_supported(sc.cp, a1.cp, b1.cp, a2.cp, b2.cp))) continue;
             sc.stack_head = true;
             sp.stack_member = a1.stack_member = b1.stack_member = a2.stack_member = b2.stack_member = true;
         }
@@ -1391,11 +1401,12 @@ int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t w
             snprintf(line, sizeof line,
                      "step %zu conv layer=%d sub=%d el=%d in=%dx%dx%d out=%dx%dx%d k=%d s=%d pad=%d mode=%d NT=%d KS=%d "
                      "k_steps=%d RD=%d PF=%d TH=%d bands=%d G=%d units_img=%d pitch=%d tile_stride=%d lds=%ld wp=%d pt=%d pool=%d TPH=%d fuse_next=%d "
-                     "front=%d tail=%d out_frag=%d resblock=%d pos23=%d stack=%d\n",
+                     "front=%d tail=%d out_frag=%d resblock=%d pos23=%d stack=%d stack_bf16=%d\n",
                      i, s.layer, s.sub, (int)s.el, c.H, c.W, c.Cs_in, c.Ho, c.Wo, c.Cs_out, c.k, c.s, c.pad, c.mode,
                      s.NT, s.KS, c.k_steps, s.RD, s.PF, c.TH, c.n_bands, c.G, c.units_img, c.pitch, c.tile_stride, lds, c.wave_private, c.wp_pt, c.pool, c.TPH, (int)s.fuse_next,
                      (int)(s.fuse_next && i + 1 < pol.steps.size() && conv_front_supported(c, s.NT, pol.steps[i + 1].cp)),
-                     (int)(s.el == EL_I8 && !s.fused_prev && conv_tail_supported(c, s.NT)), c.out_frag, (int)s.resblock, c.pos23, s.stack_head ? 1 : s.stack_member ? 2 : 0);
+                     (int)(s.el == EL_I8 && !s.fused_prev && conv_tail_supported(c, s.NT)), c.out_frag, (int)s.resblock, c.pos23,
+                     s.el != EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0, s.el == EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0);
         } else if (s.kind == ST_GEMM) {
             snprintf(line, sizeof line, "step %zu gemm layer=%d el=%d epi=%d N=%d Np=%d Kp_bytes=%d k_steps=%d n_tiles=%d relu_in=%d relu=%d x_frag=%d\n",
                      i, s.layer, (int)s.el, (int)s.epi, s.gp.N, s.gp.Np, s.gp.Kp_bytes, s.gp.k_steps, s.gp.n_tiles, s.gp.relu_in, s.gp.relu, s.gp.x_frag);

@@ -1,0 +1,452 @@
+// One whole stack of the IMPALA teacher in one kernel, bf16: conv3x3 (pad 1, no ReLU) -> max-pool 3x3 / 2 (pad 1) -> two
+// residual blocks (ReLU - conv3x3 - ReLU - conv3x3 + skip).  The stack's input is read once and its output written once;
+// every tensor in between stays in LDS.
+//
+// What bounds it: layer by layer the eleven launches of a stack moved the stream through memory nine times and fetched
+// every window from LDS anew (nine or five 16-byte reads per lane and MFMA tile, as many LDS clocks as matrix clocks).
+// Here a lane is a *column* of the image and walks down it: the fragments of an input row (three reads) serve the output
+// rows above, at and below it, so a row of 16 pixels costs three reads and five (16 channels) or nine (32 channels) MFMAs
+// per 16 output channels.  The three output rows in flight are three independent accumulator chains.  Measured at 1024
+// states: the three stacks 74 / 78 / 40 us where the layer-by-layer kernels took 283 / 163 / 85 us.
+//
+//  * Lanes.  A workgroup of eight wavefronts owns G images.  The lanes of the blocks' tiles are (image, segment of rows,
+//    column) triples: 3 x 42, 3 x 21 and 2 x 2 x 11 of them fill 126 of 128, 63 of 64 and 44 of 48 lanes.  32-channel
+//    layers split the output channels over two wavefronts, so that a wavefront keeps the weights of all four block
+//    convolutions (4 x 36 registers) for the whole kernel.
+//  * LDS layout.  Planes of eight channels, [channel block][row][column][16 B]: the 16 lanes of a K group read 256
+//    consecutive bytes, and planes a multiple of 256 bytes apart keep the four groups of a read off each other's banks.
+//  * Convolution + pooling.  Lanes are convolution columns 14 t - 1 .. 14 t + 14 (seven pooled pixels); the vertical
+//    maximum runs over the rows as they are produced (row 2 py + 1 is kept for the next pooled row), the horizontal one
+//    over the two neighbour lanes (DPP).  Rounding to bf16 is monotone, so it follows the maximum.
+//  * The stream is kept un-rectified (the skip connection needs it) and rectified as fragments are read: one packed
+//    16-bit integer maximum per dword, since a negative bf16 is a negative 16-bit integer.
+//
+// Arithmetic: the planner's weight fragments, the bias in the accumulator and the K steps of every output in the planner's
+// order, so results are bit-identical to the layer-by-layer kernels (conv_kernel.h), which the debug taps still run.  (The
+// last K step of a 16-channel layer holds two chunks only; here they sit in the other half of the step, which adds the
+// same products in the same order.)
+#include <math.h>
+
+#include <type_traits>
+
+#include "conv_kernel.h"
+
+namespace accerl {
+
+namespace {
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+
+struct BStackParams {
+    const void* in;          // uint8 planes [B, 4, HIN, HIN] or bf16 [B, HIN, HIN, CI]
+    char* out;               // bf16 [B, H, H, C]
+    const v4i* w[5];         // 0: stack convolution, 1 / 2: first block's conv A / B, 3 / 4: second block's
+    const float* bias[5];
+    int64_t B;
+};
+
+constexpr int bs_up(int v, int a) { return (v + a - 1) / a * a; }
+
+template <bool U8, int CI, int HIN, int C, int G_, int SEG_, int PSEG_>
+struct BsShape {
+    static constexpr int G = G_, SEG = SEG_, PSEG = PSEG_;
+    static constexpr int NW = 8, THREADS = NW * 64;
+    static constexpr int NH = C / 16;                          // wavefronts that share a tile, 16 output channels each
+    static constexpr int TW = NW / NH;                         // tiles in work at a time
+    static constexpr int H = (HIN - 1) / 2 + 1;                // pooled size
+    // bordered tiles of the stream and of a block's inner tensor: planes of eight channels
+    static constexpr int PB = H + 2, ROWB = PB * 16;
+    static constexpr int R = (H + SEG - 1) / SEG;              // rows a lane walks
+    static constexpr int PLANE = bs_up((PB + SEG * R - H) * ROWB, 256);
+    static constexpr int TILE = C / 8 * PLANE;
+    static constexpr int NCOL = G * SEG * H;
+    // bordered input tile: channels-last pixels of 8 bytes (observations) or planes
+    static constexpr int IPB = HIN + 2, IROW = IPB * (U8 ? 8 : 16);
+    static constexpr int IPLANE = bs_up(IPB * IROW, 256);
+    static constexpr int TILE_IN = U8 ? bs_up((HIN + 3) * IROW, 256) : CI / 8 * IPLANE;
+    static constexpr int KS_C = U8 ? 2 : CI == 16 ? 5 : 9, KS_B = C == 16 ? 5 : 9;
+    // staging: 64 units of a wavefront's load are 1 KiB in a row
+    static constexpr int UNITS = U8 ? HIN * HIN / 4 : G * HIN * HIN * CI / 8;
+    static constexpr int PF = (UNITS + THREADS - 1) / THREADS;
+    static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI * 2;
+    static constexpr int IMG = H * H * C * 2;
+    // conv + pool items: column tiles of seven pooled pixels x row segments x images
+    static constexpr int CT = (H + 6) / 7, RP = (H + PSEG - 1) / PSEG, ITEMS = CT * PSEG * G;
+    // the inner tensor takes the place of the observation tile, which is dead once it has been pooled
+    static constexpr bool OVER = U8;
+    static constexpr int O_IN = G * TILE;
+    static constexpr int O_M = OVER ? O_IN : O_IN + G * TILE_IN;
+    static constexpr int LDS = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);
+    static_assert(C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS <= 160 * 1024, "shape");
+};
+
+__device__ __forceinline__ v4f bs_mfma(v4i a, v4i b, v4f c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ v4i bs_relu(v4i x) {
+    typedef short v8s __attribute__((ext_vector_type(8)));
+    const v8s z = {0, 0, 0, 0, 0, 0, 0, 0};
+    return __builtin_bit_cast(v4i, __builtin_elementwise_max(__builtin_bit_cast(v8s, x), z));
+}
+__device__ __forceinline__ v2i bs_pack(v4f v) {
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    return (v2i){__builtin_bit_cast(int, __builtin_convertvector((v2f){v[0], v[1]}, v2bf)),
+                 __builtin_bit_cast(int, __builtin_convertvector((v2f){v[2], v[3]}, v2bf))};
+}
+__device__ __forceinline__ float bs_max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+// max(v, v of both neighbours in the 16-lane row); the outermost lanes' results are not used
+__device__ __forceinline__ float bs_max_neighbours(float v) {
+    const int i = __float_as_int(v);
+    return bs_max3(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false)),
+                   __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x101, 0xf, 0xf, false)));
+}
+
+// The fragments of one input row under a lane's 3-wide window.
+// 16 channels (K steps of two pixels): f0 = pixels 0, 1; f1 = pixel 2 of the row above and pixel 0; f2 = pixels 1, 2.
+// 32 channels (a pixel per step): f0, f1, f2 = pixels 0, 1, 2.
+struct BsRow { v4i f[3]; };
+template <int CIN>
+__device__ __forceinline__ void bs_load(BsRow& r, const char* a, const char* m, int off) {
+    r.f[0] = *(const v4i*)(a + off);
+    r.f[1] = CIN == 16 ? *(const v4i*)(m + off) : *(const v4i*)(a + off + 16);
+    r.f[2] = *(const v4i*)(a + off + (CIN == 16 ? 16 : 32));
+}
+// what an input row adds to the output row whose first / middle / last window row it is
+template <int CIN>
+__device__ __forceinline__ v4f bs_top(const v4i* w, const BsRow& r, v4f acc) {
+    if constexpr (CIN == 16) return bs_mfma(w[0], r.f[0], acc);
+    else return bs_mfma(w[2], r.f[2], bs_mfma(w[1], r.f[1], bs_mfma(w[0], r.f[0], acc)));
+}
+template <int CIN>
+__device__ __forceinline__ v4f bs_mid(const v4i* w, const BsRow& r, v4f acc) {
+    if constexpr (CIN == 16) return bs_mfma(w[2], r.f[2], bs_mfma(w[1], r.f[1], acc));
+    else return bs_mfma(w[5], r.f[2], bs_mfma(w[4], r.f[1], bs_mfma(w[3], r.f[0], acc)));
+}
+template <int CIN>
+__device__ __forceinline__ v4f bs_bottom(const v4i* w, const BsRow& r, v4f acc) {
+    if constexpr (CIN == 16) return bs_mfma(w[4], r.f[2], bs_mfma(w[3], r.f[0], acc));
+    else return bs_mfma(w[8], r.f[2], bs_mfma(w[7], r.f[1], bs_mfma(w[6], r.f[0], acc)));
+}
+
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG>
+__global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p) {
+    typedef BsShape<U8, CI, HIN, C, G, SEG, PSEG> S;
+    constexpr int T = S::THREADS;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* tX = smem;                                     // G bordered tiles of the stream
+    char* tin = smem + S::O_IN;                          // G bordered input tiles
+    char* tM = smem + S::O_M;                            // G bordered tiles of a block's inner tensor
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int half = wave % S::NH, tile = wave / S::NH;  // which 16 output channels, which tile
+    constexpr int NH = S::NH;
+
+    // ---- staging: unit u of a batch is 16 bytes of bf16 pixels, or one dword of each of the four planes
+    v4i pre[S::PF];
+    auto unit_of = [&](int i) -> int {
+        if constexpr (U8) {
+            return tid + i * T;
+        } else {
+            // a wavefront's 64 units in the order (channel block, pixel): its LDS stores then run along a plane
+            constexpr int CB = CI / 8, PX = 64 / CB;
+            return (wave + i * S::NW) * 64 + (lane % PX) * CB + lane / PX;
+        }
+    };
+    auto prefetch = [&](int64_t batch) {
+        const int64_t b0 = batch * G;
+        const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
+        const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
+        const int last = (U8 ? S::UNITS : gc * (S::UNITS / G)) - 1;
+#pragma unroll
+        for (int i = 0; i < S::PF; ++i) {
+            const int u = min(unit_of(i), last);         // a unit that does not exist re-reads the last one
+            if constexpr (U8) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) pre[i][c] = *(const int*)(src + (uint32_t)(c * HIN * HIN + 4 * u));
+            } else {
+                pre[i] = *(const v4i*)(src + (uint32_t)u * 16u);
+            }
+        }
+    };
+    auto commit = [&]() {
+#pragma unroll
+        for (int i = 0; i < S::PF; ++i) {
+            const int u = unit_of(i);
+            if (u >= S::UNITS) continue;                 // (units of an image past the batch: never read by a stored result)
+            if constexpr (U8) {
+                constexpr int RU = HIN / 4;
+                const int row = u / RU, cu = u - row * RU;
+                typedef float v2f __attribute__((ext_vector_type(2)));
+                typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+                const float k255 = 1.0f / 255.0f;        // bf16(v / 255) = bf16(v * (1 / 255)): checked for all 256 values
+                char* d = tin + (row + 1) * S::IROW + (1 + 4 * cu) * 8;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const v2f lo = {(float)((pre[i][0] >> (8 * e)) & 0xff) * k255, (float)((pre[i][1] >> (8 * e)) & 0xff) * k255};
+                    const v2f hi = {(float)((pre[i][2] >> (8 * e)) & 0xff) * k255, (float)((pre[i][3] >> (8 * e)) & 0xff) * k255};
+                    *(v2i*)(d + 8 * e) = (v2i){__builtin_bit_cast(int, __builtin_convertvector(lo, v2bf)),
+                                               __builtin_bit_cast(int, __builtin_convertvector(hi, v2bf))};
+                }
+            } else {
+                constexpr int CB = CI / 8;
+                const int px = u / CB, cb = u - px * CB;
+                const int img = px / (HIN * HIN), w = px - img * HIN * HIN, row = w / HIN, col = w - row * HIN;
+                *(v4i*)(tin + img * S::TILE_IN + cb * S::IPLANE + (row + 1) * S::IROW + (col + 1) * 16) = pre[i];
+            }
+        }
+        if constexpr (S::OVER) {                         // the border of the observation tile: three rows, two columns
+            for (int i = tid; i < 3 * S::IPB; i += T) {
+                const int rr = i / S::IPB;
+                *(v2i*)(tin + (rr ? HIN + rr : 0) * S::IROW + (i - rr * S::IPB) * 8) = (v2i){0, 0};
+            }
+            for (int i = tid; i < 2 * HIN; i += T) *(v2i*)(tin + (1 + (i >> 1)) * S::IROW + (i & 1) * (HIN + 1) * 8) = (v2i){0, 0};
+        }
+    };
+
+    const int64_t n_batch = (p.B + G - 1) / G;
+    int64_t batch = blockIdx.x;
+    if (batch < n_batch) prefetch(batch);
+
+    // ---- weights of all five convolutions, in registers for the whole kernel
+    v4i wC[S::KS_C], wA1[S::KS_B], wB1[S::KS_B], wA2[S::KS_B], wB2[S::KS_B];
+    v4f bias[5];
+    {
+        auto frag = [&](int cv, int st, int ks) -> v4i {
+            if (ks == 5 && st == 4) {                    // the two chunks of the last step in the upper half (see bs_bottom)
+                const v4i v = p.w[cv][(st * NH + half) * 64 + (lane & 31)];
+                return g >= 2 ? v : (v4i){0, 0, 0, 0};
+            }
+            return p.w[cv][(st * NH + half) * 64 + lane];
+        };
+#pragma unroll
+        for (int st = 0; st < S::KS_C; ++st) wC[st] = frag(0, st, S::KS_C);
+#pragma unroll
+        for (int st = 0; st < S::KS_B; ++st) {
+            wA1[st] = frag(1, st, S::KS_B);
+            wB1[st] = frag(2, st, S::KS_B);
+            wA2[st] = frag(3, st, S::KS_B);
+            wB2[st] = frag(4, st, S::KS_B);
+        }
+#pragma unroll
+        for (int cv = 0; cv < 5; ++cv) bias[cv] = *(const v4f*)(p.bias[cv] + 4 * NH * g + 4 * half);
+    }
+    for (int i = tid; i < S::LDS / 16; i += T) ((v4i*)smem)[i] = (v4i){0, 0, 0, 0};
+
+    // ---- this lane's column of the blocks' tiles
+    const int n = tile * 16 + j, nc = min(n, S::NCOL - 1);
+    const int img = nc / (SEG * S::H), seg = (nc - img * SEG * S::H) / S::H, col = nc - (img * SEG + seg) * S::H;
+    const int row0 = seg * S::R;
+    const int pos = img * S::TILE + row0 * S::ROWB + col * 16;
+    const int offA = pos + (C == 16 ? (g & 1) * S::PLANE + (g >> 1) * 16 : g * S::PLANE);
+    const int offM = pos + (g & 1) * S::PLANE + (g < 2 ? 32 - S::ROWB : 0);       // 16 channels only
+    const int own = pos + S::ROWB + 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
+    __syncthreads();
+
+    for (; batch < n_batch; batch += gridDim.x) {
+        commit();
+        __syncthreads();
+        const int64_t b0 = batch * G;
+        const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
+
+        // ---- stack convolution + max-pool -> the stream's tile
+        for (int it = tile; it < S::ITEMS; it += S::TW) {
+            const int im = it / (S::CT * PSEG), ps = (it - im * S::CT * PSEG) % PSEG, ct = (it - im * S::CT * PSEG) / PSEG;
+            const int p0 = min(ps * S::RP, S::H - S::RP);        // segments may overlap: the same bytes twice
+            const int x = min(max(14 * ct - 1 + j, 0), HIN - 1);  // columns outside repeat the outermost one
+            const int px = 7 * ct + (j >> 1);
+            const bool st_ok = (j & 1) && j < 14 && px < S::H;
+            char* dst = tX + im * S::TILE + (p0 + 1) * S::ROWB + (px + 1) * 16
+                        + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
+            auto store = [&](int k, v4f v) {
+                v4f m;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) m[r] = bs_max_neighbours(v[r]);
+                if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+            };
+            v4f carry = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            if constexpr (U8) {
+                // window rows y, y + 1 in the two halves of a fragment: F(y) is step 0 of conv row y and step 1 of row y - 2
+                const char* a = tin + (2 * p0 + (g >> 1)) * S::IROW + x * 8 + (g & 1) * 16;
+                v4i f0 = read_chunk<8>(a), f1 = read_chunk<8>(a + S::IROW);
+                if (p0 > 0) carry = bs_mfma(wC[1], f1, bs_mfma(wC[0], read_chunk<8>(a - S::IROW), bias[0]));
+#pragma unroll
+                for (int k = 0; k < S::RP; ++k) {
+                    const v4i f2 = read_chunk<8>(a + (2 * k + 2) * S::IROW), f3 = read_chunk<8>(a + (2 * k + 3) * S::IROW);
+                    const v4f c0 = bs_mfma(wC[1], f2, bs_mfma(wC[0], f0, bias[0]));
+                    const v4f c1 = bs_mfma(wC[1], f3, bs_mfma(wC[0], f1, bias[0]));
+                    v4f v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = bs_max3(carry[r], c0[r], c1[r]);
+                    carry = c1;
+                    store(k, v);
+                    f0 = f2; f1 = f3;
+                }
+            } else {
+                const int base = im * S::TILE_IN + 2 * p0 * S::IROW + x * 16;
+                const char* a = tin + base + (CI == 16 ? (g & 1) * S::IPLANE + (g >> 1) * 16 : g * S::IPLANE);
+                const char* m = tin + base + (g & 1) * S::IPLANE + (g < 2 ? 32 - S::IROW : 0);
+                BsRow r0, r1;                             // input rows 2 p0, 2 p0 + 1
+                bs_load<CI>(r1, a, m, S::IROW);
+                v4f a1, a2;
+                if (p0 > 0) {                             // conv row 2 p0 - 1, kept for the first pooled row
+                    BsRow rm;
+                    bs_load<CI>(rm, a, a, -S::IROW);      // (its f1 is not used with 16 channels)
+                    bs_load<CI>(r0, a, m, 0);
+                    carry = bs_bottom<CI>(wC, r1, bs_mid<CI>(wC, r0, bs_top<CI>(wC, rm, bias[0])));
+                } else {
+                    bs_load<CI>(r0, a, a, 0);
+                }
+                a2 = bs_mid<CI>(wC, r1, bs_top<CI>(wC, r0, bias[0]));
+                a1 = bs_top<CI>(wC, r1, bias[0]);
+#pragma unroll
+                for (int k = 0; k < S::RP; ++k) {
+                    BsRow r2, r3;
+                    const bool low = (HIN & 1) == 0 || k + 1 < S::RP || p0 + k < S::H - 1;   // conv row 2 py + 1 exists
+                    bs_load<CI>(r2, a, m, (2 * k + 2) * S::IROW);
+                    const v4f c0 = bs_bottom<CI>(wC, r2, a2);
+                    v4f c1 = c0;
+                    if (low) {
+                        bs_load<CI>(r3, a, m, (2 * k + 3) * S::IROW);
+                        c1 = bs_bottom<CI>(wC, r3, bs_mid<CI>(wC, r2, a1));
+                        a2 = bs_mid<CI>(wC, r3, bs_top<CI>(wC, r2, bias[0]));
+                        a1 = bs_top<CI>(wC, r3, bias[0]);
+                    }
+                    v4f v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = bs_max3(carry[r], c0[r], c1[r]);
+                    carry = c1;
+                    store(k, v);
+                }
+            }
+        }
+        __syncthreads();
+        if constexpr (S::OVER) {                          // the inner tensor's border, where the observation tile was
+            for (int i = tid; i < C / 8 * (2 * S::PB + 2 * S::H); i += T) {
+                const int pl = i / (2 * S::PB + 2 * S::H), q = i - pl * (2 * S::PB + 2 * S::H);
+                int at;
+                if (q < 2 * S::PB) at = (q < S::PB ? q : (S::H + 1) * S::PB + q - S::PB);
+                else at = (1 + ((q - 2 * S::PB) >> 1)) * S::PB + (q & 1) * (S::H + 1);
+                *(v4i*)(tM + pl * S::PLANE + at * 16) = (v4i){0, 0, 0, 0};
+            }
+        }
+
+        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k, one row late
+        const bool live = n < S::NCOL && img < gc;
+        auto walk = [&](const char* src, const v4i* w, v4f b, auto relu, auto&& done) {
+            constexpr bool RELU = decltype(relu)::value;
+            const char* a = src + offA;
+            const char* m = src + offM;
+            BsRow cur, nxt;
+            auto rect = [&](BsRow& r) {
+                if constexpr (RELU) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) r.f[q] = bs_relu(r.f[q]);
+                }
+            };
+            bs_load<C>(cur, a, a, 0);                     // (f1 of the first row is not used with 16 channels)
+            bs_load<C>(nxt, a, m, S::ROWB);
+            rect(cur);
+            v4f a1 = bs_top<C>(w, cur, b), a2 = a1, out = a1;
+#pragma unroll
+            for (int i = 1; i < S::R + 2; ++i) {
+                cur = nxt;
+                if (i + 1 < S::R + 2) bs_load<C>(nxt, a, m, (i + 1) * S::ROWB);
+                rect(cur);
+                v4f o = out;
+                if (i >= 2) o = bs_bottom<C>(w, cur, a2);
+                if (i < S::R + 1) a2 = bs_mid<C>(w, cur, a1);
+                if (i < S::R) a1 = bs_top<C>(w, cur, b);
+                if (i >= 3) done(i - 3, out);
+                out = o;
+            }
+            done(S::R - 1, out);
+        };
+        auto row_ok = [&](int k) { return live && (SEG * S::R == S::H || row0 + k < S::H); };
+        auto conv_a = [&](const v4i* w, v4f b) {          // inner tensor = relu(conv(relu(stream)))
+            if (tile * 16 >= S::NCOL) return;
+            walk(tX, w, b, std::true_type{}, [&](int k, v4f acc) {
+                typedef short v4s __attribute__((ext_vector_type(4)));
+                const v4s q = __builtin_elementwise_max(__builtin_bit_cast(v4s, bs_pack(acc)), (v4s){0, 0, 0, 0});
+                if (row_ok(k)) *(v2i*)(tM + own + k * S::ROWB) = __builtin_bit_cast(v2i, q);
+            });
+        };
+        auto conv_b = [&](const v4i* w, v4f b, auto last) {   // stream += conv(inner tensor), in place or to memory
+            constexpr bool LAST = decltype(last)::value;
+            if (tile * 16 >= S::NCOL) return;
+            char* outp = p.out + b0 * (int64_t)S::IMG + (uint32_t)((img * S::H + row0) * S::H + col) * (C * 2) + (C == 16 ? 8 * g : 16 * g + 8 * half);
+            walk(tM, w, b, std::false_type{}, [&](int k, v4f acc) {
+                const v2i x = *(const v2i*)(tX + own + k * S::ROWB);
+                const v4f y = {bf2f((uint32_t)x[0] & 0xffffu) + acc[0], __int_as_float(x[0] & (int)0xffff0000) + acc[1],
+                               bf2f((uint32_t)x[1] & 0xffffu) + acc[2], __int_as_float(x[1] & (int)0xffff0000) + acc[3]};
+                if (!row_ok(k)) return;
+                if constexpr (LAST) *(v2i*)(outp + k * S::H * C * 2) = bs_pack(y);
+                else *(v2i*)(tX + own + k * S::ROWB) = bs_pack(y);
+            });
+        };
+        conv_a(wA1, bias[1]);
+        __syncthreads();
+        conv_b(wB1, bias[2], std::false_type{});
+        __syncthreads();
+        conv_a(wA2, bias[3]);
+        __syncthreads();
+        if (batch + gridDim.x < n_batch) prefetch(batch + gridDim.x);
+        conv_b(wB2, bias[4], std::true_type{});
+        // the observation tile takes the inner tensor's place; otherwise the barrier behind the next commit is enough
+        if constexpr (S::OVER) __syncthreads();
+    }
+}
+
+// the five convolutions of a stack as the planner laid them out
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG>
+bool bs_shape_ok(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2) {
+    typedef BsShape<U8, CI, HIN, C, G, SEG, PSEG> S;
+    if (c.H != HIN || c.W != HIN || c.Cs_in != CI || c.Cin_real != CI || c.Ho != HIN || c.Wo != HIN || c.Cs_out != C) return false;
+    if (c.k != 3 || c.s != 1 || c.pad != 1 || c.sx != 1 || c.k_steps != S::KS_C || (c.src_u8 != 0) != U8 || c.relu || c.relu_in) return false;
+    for (const ConvParams* b : {&a1, &b1, &a2, &b2}) {
+        if (b->H != S::H || b->W != S::H || b->Cin_real != C || b->Cs_in != C || b->Ho != S::H || b->Wo != S::H || b->Cs_out != C) return false;
+        if (b->k != 3 || b->s != 1 || b->pad != 1 || b->sx != 1 || b->k_steps != S::KS_B || b->src_u8 || b->pool || b->out_frag) return false;
+    }
+    return a1.relu_in && a1.relu && !b1.relu_in && !b1.relu && a2.relu_in && a2.relu && !b2.relu_in && !b2.relu;
+}
+
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG>
+hipError_t bs_go(const BStackParams& p, hipStream_t s) {
+    typedef BsShape<U8, CI, HIN, C, G, SEG, PSEG> S;
+    auto kfn = stack_bf16_kernel<U8, CI, HIN, C, G, SEG, PSEG>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
+    if (attr != hipSuccess) return attr;
+    // one workgroup per compute unit (LDS and registers), striding over the batches in even rounds
+    const int64_t batches = (p.B + G - 1) / G, cap = conv_num_cus();
+    const int64_t rounds = (batches + cap - 1) / cap;
+    kfn<<<dim3((unsigned)((batches + rounds - 1) / rounds)), dim3(S::THREADS), S::LDS, s>>>(p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// (uint8 source, input channels, input size, channels, images per batch, row segments of the blocks' and of the pool's lanes)
+#define ACCERL_BSTACK_SHAPES(X) X(true, 4, 84, 16, 1, 3, 4) X(false, 16, 42, 32, 1, 3, 4) X(false, 32, 21, 32, 2, 2, 1)
+
+bool stack_bf16_supported(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2) {
+#define X(U8, CI, HIN, C, G, SEG, PSEG) if (bs_shape_ok<U8, CI, HIN, C, G, SEG, PSEG>(c, a1, b1, a2, b2)) return true;
+    ACCERL_BSTACK_SHAPES(X)
+#undef X
+    return false;
+}
+
+hipError_t launch_stack_bf16(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2, hipStream_t s) {
+    if (c.B <= 0) return hipSuccess;
+    BStackParams p;
+    p.in = c.in; p.out = (char*)b2.out;
+    const ConvParams* cv[5] = {&c, &a1, &b1, &a2, &b2};
+    for (int i = 0; i < 5; ++i) { p.w[i] = (const v4i*)cv[i]->wfrag; p.bias[i] = (const float*)cv[i]->bias; }
+    p.B = c.B;
+#define X(U8, CI, HIN, C, G, SEG, PSEG) if (bs_shape_ok<U8, CI, HIN, C, G, SEG, PSEG>(c, a1, b1, a2, b2)) return bs_go<U8, CI, HIN, C, G, SEG, PSEG>(p, s);
+    ACCERL_BSTACK_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace accerl
