@@ -201,6 +201,24 @@ struct GemmF32Params {
 };
 hipError_t launch_gemm_f32(const GemmF32Params& p, hipStream_t s);
 
+// the whole fp32 teacher in one kernel: hidden layers of at most 256 units, at most 256 observation features
+constexpr int MLP_F32_MAX_LAYERS = 8;
+struct MlpF32Params {
+    const float* obs;        // [B, D]
+    const float* uniforms;   // [B]
+    float* logits; float* value; int32_t* action;
+    int64_t B;
+    int D, A, n_hidden;
+    int nt;                  // 1, 2 or 4: every hidden layer is computed as 64 * nt units
+    int kb0;                 // first layer's K in blocks of 16 (even, at most 4 * nt); later layers have 4 * nt blocks
+    const v4f* wfrag;        // [layer][block][unit tile][64 lanes]: W[16 * tile + lane % 16][16 * block + 4 * (lane / 16) ..]; 4 spare blocks at the end
+    const float* bias;       // [layer][64 * nt]
+    const v4f* whead;        // [head tile][block][64 lanes]
+    const float* bhead;      // [A + 1]
+    int N[MLP_F32_MAX_LAYERS], relu[MLP_F32_MAX_LAYERS];
+};
+hipError_t launch_mlp_f32(const MlpF32Params& p, hipStream_t s);
+
 // LSTM operand packing: xh[b] = [bf16(x[b]) , bf16(done ? 0 : h[b])], and h,c zeroed where done
 struct LstmPackParams {
     const void* x; int x_elem; float x_scale; int x_pitch_bytes; int x_relu; int In;

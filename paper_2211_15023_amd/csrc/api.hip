@@ -166,6 +166,7 @@ struct Step {
     bool fused_prev = false;    // conv: normally done by the conv step before it
     bool resblock = false;      // conv with fuse_next: the pair is a residual block (skip connection from this step's input)
     bool stack_head = false;    // conv: normally runs together with its max-pool and the two residual blocks behind it (steps +1 .. +5)
+    bool mlp_head = false;      // fp32 dense: normally runs the whole network (all steps behind it are then skipped)
     bool stack_member = false;  // max-pool / conv: normally done by the stack kernel of an earlier step
     ConvParams cp{};
     Elem el = EL_I8;
@@ -175,6 +176,9 @@ struct Step {
     GemmF32Params fp{};
     LstmPackParams lp{};
     MlpParams mp{};
+    MlpF32Params mf{};
+    int64_t o_whead = -1, o_bhead = -1;   // mlp_head: head fragments and biases; its o_wall / o_ball are the hidden layers'
+    int64_t o_wall = -1, o_ball = -1;
     // maxpool
     int H = 0, W = 0, Cs = 0, Ho = 0, Wo = 0, k = 0, s = 0, pad = 0;
     float inv_s0 = 0.f;
@@ -658,6 +662,45 @@ int build_plan(Builder& B) {
         }
         Step ss; ss.kind = ST_SAMPLE; ss.layer = a->n_layers;
         pol->steps.push_back(ss);
+        // One kernel for the whole chain when a workgroup's activations fit: see kernels_mlp_f32.hip.  Wider networks (and
+        // the debug taps) run layer by layer.
+        int widest = a->obs_c;
+        for (int i = 0; i < a->n_layers; ++i) widest = std::max(widest, (int)a->layers[i].cout);
+        if (a->n_layers >= 1 && a->n_layers <= MLP_F32_MAX_LAYERS && widest <= 256 && !getenv("ACCERL_NO_MLP_F32_FUSE")) {
+            Step& st = pol->steps.front();
+            MlpF32Params& m = st.mf;
+            st.mlp_head = true;
+            m.D = a->obs_c; m.A = a->n_actions; m.n_hidden = a->n_layers;
+            m.nt = widest <= 64 ? 1 : widest <= 128 ? 2 : 4;
+            m.kb0 = (int)up((a->obs_c + 15) / 16, 2);
+            const int ut = 4 * m.nt;
+            // fragments of 16 units x 16 inputs: lane holds inputs 4 * (lane / 16) .. + 3 of unit lane % 16
+            auto put_tile = [&](float* dst, const TensorSpec& t, int tile, int block) {
+                for (int lane = 0; lane < 64; ++lane)
+                    for (int e = 0; e < 4; ++e) {
+                        const int64_t n = 16 * tile + (lane & 15), k = 16 * block + 4 * (lane >> 4) + e;
+                        if (n < t.rows && k < t.cols) dst[4 * lane + e] = B.wf(t)[n * t.cols + k];
+                    }
+            };
+            std::vector<float> w((size_t)(m.kb0 + (m.n_hidden - 1) * ut + 4) * ut * 256, 0.f), b((size_t)m.n_hidden * 16 * ut, 0.f);
+            size_t at = 0;
+            for (int l = 0; l < m.n_hidden; ++l) {
+                const TensorSpec& t = B.tensor(l, 0);
+                m.N[l] = (int)t.rows; m.relu[l] = a->layers[l].relu;
+                for (int block = 0; block < (l ? ut : m.kb0); ++block)
+                    for (int tile = 0; tile < ut; ++tile, at += 256) put_tile(&w[at], t, tile, block);
+                for (int n = 0; n < m.N[l]; ++n) b[(size_t)l * 16 * ut + n] = B.bias(t)[n];
+            }
+            const TensorSpec& th = B.tensor(a->n_layers, 0);
+            const int ht = (a->n_actions + 16) / 16;
+            std::vector<float> wh((size_t)ht * ut * 256, 0.f);
+            for (int h = 0; h < ht; ++h)
+                for (int block = 0; block < ut; ++block) put_tile(&wh[(size_t)(h * ut + block) * 256], th, h, block);
+            st.o_wall = B.put(w.data(), (int64_t)w.size() * 4);
+            st.o_ball = B.put(b.data(), (int64_t)b.size() * 4);
+            st.o_whead = B.put(wh.data(), (int64_t)wh.size() * 4);
+            st.o_bhead = B.put(B.bias(th), th.rows * 4);
+        }
         return ACCERL_OK;
     }
 
@@ -975,8 +1018,12 @@ int run(accerl_policy* p, const Call& c) {
     }
     int64_t chunk = p->chunk > 0 ? p->chunk : c.B;
     if (chunk > c.B) chunk = c.B;
-    int rc = ensure_workspace(p, chunk, c.debug ? 1 : 0, c.stream);
-    if (rc) return rc;
+    if (p->steps[0].mlp_head && !c.debug) {          // nothing of the network leaves the chip: no workspace, no passes
+        chunk = c.B;
+    } else {
+        int rc = ensure_workspace(p, chunk, c.debug ? 1 : 0, c.stream);
+        if (rc) return rc;
+    }
     for (int64_t c0 = 0; c0 < c.B; c0 += chunk) {
         const int64_t n = (c.B - c0 < chunk) ? (c.B - c0) : chunk;
         const char* states = (const char*)c.states + c0 * p->obs_bytes;
@@ -1092,6 +1139,16 @@ int run(accerl_policy* p, const Call& c) {
                     break;
                 }
                 case ST_GEMM_F32: {
+                    if (s.mlp_head && !c.debug) {
+                        MlpF32Params m = s.mf;
+                        m.obs = (const float*)states; m.uniforms = uni; m.logits = logits; m.value = value; m.action = action;
+                        m.B = n;
+                        m.wfrag = (const v4f*)(p->consts + s.o_wall); m.bias = (const float*)(p->consts + s.o_ball);
+                        m.whead = (const v4f*)(p->consts + s.o_whead); m.bhead = (const float*)(p->consts + s.o_bhead);
+                        e = launch_mlp_f32(m, c.stream);
+                        last_step = si;
+                        break;
+                    }
                     GemmF32Params f = s.fp;
                     f.x = (const float*)bufp(s.in_buf);
                     f.w = (const float*)(p->consts + s.o_w);
@@ -1193,6 +1250,7 @@ static void assign_slots(accerl_policy* pol, int layout) {
         int touched[4] = {st.in_buf, st.res_buf, st.out_buf, -1};
         if (layout == 0 && st.kind == ST_CONV && st.pool_buf >= 0 && !st.stack_head) touched[2] = st.pool_buf;   // writes the pooled image only
         if (layout == 1 && st.kind == ST_CONV) touched[3] = st.pool_buf;                       // may run either way
+        if (layout == 0 && pol->steps[0].mlp_head) continue;                                    // the whole network is one launch
         if (layout == 0 && st.stack_member) continue;                                           // done by the stack kernel
         if (layout == 0 && st.stack_head) touched[2] = pol->steps[si + 5].out_buf;              // reads its input, writes the stack's output
         if (layout == 0 && st.kind == ST_MAXPOOL && st.fused) continue;                         // never launched
@@ -1341,7 +1399,7 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
     assign_slots(pol, 0);
     assign_slots(pol, 1);
     pol->ws_per_state = 0;
-    for (const int64_t sz : pol->slots[0]) pol->ws_per_state += sz;
+    for (const int64_t sz : pol->slots[pol->steps[0].mlp_head ? 1 : 0]) pol->ws_per_state += sz;
     // states per pass: about 1 GiB of intermediates, so that every launch still fills the chip
     pol->chunk = 0;
     if (pol->ws_per_state > 0) {
@@ -1411,7 +1469,7 @@ int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t w
             snprintf(line, sizeof line, "step %zu gemm layer=%d el=%d epi=%d N=%d Np=%d Kp_bytes=%d k_steps=%d n_tiles=%d relu_in=%d relu=%d x_frag=%d\n",
                      i, s.layer, (int)s.el, (int)s.epi, s.gp.N, s.gp.Np, s.gp.Kp_bytes, s.gp.k_steps, s.gp.n_tiles, s.gp.relu_in, s.gp.relu, s.gp.x_frag);
         } else {
-            snprintf(line, sizeof line, "step %zu %s layer=%d\n", i, kinds[s.kind], s.layer);
+            snprintf(line, sizeof line, "step %zu %s layer=%d%s\n", i, kinds[s.kind], s.layer, s.mlp_head ? " whole_network=1" : "");
         }
         out += line;
     }
