@@ -179,6 +179,10 @@ hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s)
 bool gemm_stream_supported(const GemmParams& p);
 hipError_t launch_gemm_stream(const GemmParams& p, hipStream_t s);
 
+// the wavefronts of a workgroup split K (launch_gemm picks it)
+bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi);
+hipError_t launch_gemm_ksplit(const GemmParams& p, Elem el, hipStream_t s);
+
 // policy heads + sampler in one kernel (K up to 16 MFMA steps; wider inputs go through launch_gemm + launch_sample)
 struct HeadsParams {
     const void* x;           // [B, Kp] elements

@@ -1,0 +1,87 @@
+// What the dense kernels share: operand fix-ups and the epilogues.
+#pragma once
+#include "accerl_internal.h"
+
+namespace accerl {
+
+__device__ __forceinline__ uint32_t g_relu_i8x4(uint32_t x) {
+    const uint32_t neg = (x & 0x80808080u) >> 7;
+    return x & ~(neg * 0xffu);
+}
+__device__ __forceinline__ uint32_t g_relu_bf16x2(uint32_t x) {
+    const uint32_t neg = (x & 0x80008000u) >> 15;
+    return x & ~(neg * 0xffffu);
+}
+__device__ __forceinline__ uint32_t g_f2bf(float x) {
+    uint32_t u = __float_as_uint(x);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return u >> 16;
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return u >> 16;
+}
+__device__ __forceinline__ float g_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
+
+
+// Results of features n0 .. n0 + 3 of state b (sums with the bias): requantized int8, bf16, head outputs or the LSTM cell.
+template <int EPI, typename ACC>
+__device__ __forceinline__ void gemm_finish(const GemmParams& p, const ACC& acc, int64_t b, int n0) {
+    if constexpr (EPI == EPI_REQUANT) {
+        const v4f ml = *(const v4f*)(p.mult + n0);
+        uint32_t pk = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int v = acc[r];
+            if (p.tap_acc && n0 + r < p.N) p.tap_acc[b * p.N + n0 + r] = v;
+            if (p.relu) {   // clamp(rint(y), 0, 127): the pack instruction rounds to nearest even, saturates at 0
+                pk = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f((float)v * ml[r], 0.0f, 127.0f), r, pk);
+            } else {
+                const float y = __builtin_amdgcn_fmed3f(rintf((float)v * ml[r]), -127.0f, 127.0f);
+                pk |= ((uint32_t)(int)y & 0xffu) << (8 * r);
+            }
+        }
+        *(uint32_t*)((int8_t*)p.out + b * p.Np + n0) = pk;
+    } else if constexpr (EPI == EPI_HEADS_I8) {
+        const v4f ml = *(const v4f*)(p.mult + n0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = n0 + r;
+            if (n > p.A) continue;
+            const int v = acc[r];
+            if (p.tap_acc) p.tap_acc[b * (p.A + 1) + n] = v;
+            const float o = (float)v * ml[r];
+            if (p.logits) { if (n < p.A) p.logits[b * p.A + n] = o; else p.value[b] = o; }
+        }
+    } else if constexpr (EPI == EPI_BF16) {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            v[r] = acc[r];
+            if (p.relu) v[r] = fmaxf(v[r], 0.0f);
+        }
+        uint32_t* d = (uint32_t*)((uint16_t*)p.out + b * p.Np + n0);
+        d[0] = g_f2bf(v[0]) | (g_f2bf(v[1]) << 16);
+        d[1] = g_f2bf(v[2]) | (g_f2bf(v[3]) << 16);
+    } else if constexpr (EPI == EPI_HEADS_F32ACC) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int n = n0 + r;
+            if (n > p.A) continue;
+            const float o = acc[r];
+            if (p.logits) { if (n < p.A) p.logits[b * p.A + n] = o; else p.value[b] = o; }
+        }
+    } else {   // EPI_LSTM: rows 4*unit + {i,f,g,o}
+        const int unit = n0 >> 2;
+        const float pi = acc[0], pf = acc[1];
+        const float pg = acc[2], po = acc[3];
+        const float si = g_sigmoid(pi), sf = g_sigmoid(pf), tg = tanhf(pg), so = g_sigmoid(po);
+        const float c_old = p.c[b * p.Hd + unit];
+        const float t1 = sf * c_old;
+        const float t2 = si * tg;
+        const float cn = t1 + t2;
+        const float hn = so * tanhf(cn);
+        p.c[b * p.Hd + unit] = cn;
+        p.h[b * p.Hd + unit] = hn;
+        ((uint16_t*)p.out)[b * p.Np + unit] = (uint16_t)g_f2bf(hn);   // bf16 copy for the heads
+    }
+}
+
+}  // namespace accerl
