@@ -135,6 +135,12 @@ hipError_t launch_stack_bf16(const ConvParams& c, const ConvParams& a1, const Co
 bool conv_tail_supported(const ConvParams& p, int NT);
 hipError_t launch_conv_tail(const ConvParams& p, hipStream_t s);
 
+// the three layers for the bf16 teacher: first two in one kernel, then the third
+bool conv_front_bf16_supported(const ConvParams& a, int NTA, const ConvParams& b);
+hipError_t launch_conv_front_bf16(const ConvParams& a, const ConvParams& b, hipStream_t s);
+bool conv_tail_bf16_supported(const ConvParams& p, int NT);
+hipError_t launch_conv_tail_bf16(const ConvParams& p, hipStream_t s);
+
 // ---------------------------------------------------------------- max pooling on NHWC
 hipError_t launch_maxpool(const void* in, void* out, int64_t B, int H, int W, int Cs, int Ho, int Wo,
                           int k, int s, int pad, Elem el, hipStream_t stream);

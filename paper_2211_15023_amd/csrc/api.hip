@@ -1093,12 +1093,13 @@ int run(accerl_policy* p, const Call& c) {
                         const Step& nx = p->steps[si + 1];
                         ConvParams ca = s.cp, cb = nx.cp;
                         ca.in = bufp(s.in_buf); ca.out = nullptr; ca.res = nullptr; ca.tap_acc = nullptr;
-                        ca.wfrag = p->consts + s.o_w; ca.bias = p->consts + s.o_bias; ca.mult = (const float*)(p->consts + s.o_mult);
+                        ca.wfrag = p->consts + s.o_w; ca.bias = p->consts + s.o_bias; ca.mult = s.o_mult >= 0 ? (const float*)(p->consts + s.o_mult) : nullptr;
                         ca.B = n;
                         cb.in = nullptr; cb.out = bufp(nx.out_buf); cb.res = nullptr; cb.tap_acc = nullptr;
-                        cb.wfrag = p->consts + nx.o_w; cb.bias = p->consts + nx.o_bias; cb.mult = (const float*)(p->consts + nx.o_mult);
+                        cb.wfrag = p->consts + nx.o_w; cb.bias = p->consts + nx.o_bias; cb.mult = nx.o_mult >= 0 ? (const float*)(p->consts + nx.o_mult) : nullptr;
                         cb.B = n;
-                        e = s.resblock ? launch_resblock(ca, cb, c.stream) : launch_conv_fused(ca, s.NT, cb, c.stream);
+                        e = s.resblock ? launch_resblock(ca, cb, c.stream)
+                          : s.el == EL_BF16 ? launch_conv_front_bf16(ca, cb, c.stream) : launch_conv_fused(ca, s.NT, cb, c.stream);
                         conv_pair_done = true;
                         break;
                     }
@@ -1313,13 +1314,16 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
         for (size_t si = 0; si + 1 < pol->steps.size(); ++si) {
             Step& sa = pol->steps[si];
             Step& sb = pol->steps[si + 1];
-            if (sa.kind != ST_CONV || sb.kind != ST_CONV || sa.el != EL_I8 || sb.el != EL_I8) continue;
+            if (sa.kind != ST_CONV || sb.kind != ST_CONV || sa.el != sb.el) continue;
             if (sa.fused_prev || sa.res_buf >= 0 || sb.res_buf >= 0 || sb.in_buf != sa.out_buf) continue;
             bool read_elsewhere = false;             // the first layer's output must have no other reader
             for (size_t sj = si + 2; sj < pol->steps.size(); ++sj)
                 if (pol->steps[sj].in_buf == sa.out_buf || pol->steps[sj].res_buf == sa.out_buf) read_elsewhere = true;
             if (read_elsewhere) continue;
-            if (conv_fused_supported(sa.cp, sa.NT, sa.KS, sa.RD, sb.cp, sb.NT, sb.KS, sb.RD)) { sa.fuse_next = true; sb.fused_prev = true; }
+            if (sa.el == EL_BF16) {                  // (observation bytes through the table: not in the fused kernel)
+                if (sa.o_lut >= 0 || getenv("ACCERL_NO_CONV_FRONT") || !conv_front_bf16_supported(sa.cp, sa.NT, sb.cp)) continue;
+                sa.fuse_next = true; sb.fused_prev = true;
+            } else if (conv_fused_supported(sa.cp, sa.NT, sa.KS, sa.RD, sb.cp, sb.NT, sb.KS, sb.RD)) { sa.fuse_next = true; sb.fused_prev = true; }
         }
     }
     // Residual blocks of the shapes the block kernel covers: both convolutions in one launch (the first one's output
@@ -1377,7 +1381,7 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
     if (!getenv("ACCERL_NO_FRAG_HANDOFF")) {
         for (size_t gi = 0; gi < pol->steps.size(); ++gi) {
             Step& sg = pol->steps[gi];
-            if (sg.kind != ST_GEMM || sg.el != EL_I8 || sg.epi != EPI_REQUANT || sg.in_buf < 0) continue;
+            if (sg.kind != ST_GEMM || (sg.epi != EPI_REQUANT && sg.epi != EPI_BF16) || sg.in_buf < 0) continue;
             if (sg.gp.Kp_bytes != sg.gp.k_steps * 64) continue;
             int writer = -1, readers = 0;
             for (size_t sj = 0; sj < pol->steps.size(); ++sj) {
@@ -1387,8 +1391,14 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
             }
             if (writer < 0 || readers != 1) continue;
             Step& sc = pol->steps[writer];
-            if (sc.kind != ST_CONV || sc.el != EL_I8 || sc.out_buf != sg.in_buf || sc.fused_prev || sc.fuse_next) continue;
+            if (sc.kind != ST_CONV || sc.el != sg.el || sc.out_buf != sg.in_buf || sc.fused_prev || sc.fuse_next) continue;
             if (sc.res_buf >= 0 || sc.cp.pool || sc.cp.n_bands != 1 || sc.cp.sx != sc.cp.s) continue;
+            if (sc.el == EL_BF16) {                  // bf16: only the kernel of the paper's third layer writes that order
+                if (getenv("ACCERL_NO_CONV_TAIL") || !conv_tail_bf16_supported(sc.cp, sc.NT) || sg.gp.k_steps != 98) continue;
+                sc.cp.out_frag = 1; sc.cp.frag_ks = sg.gp.k_steps;
+                sg.gp.x_frag = 1;
+                continue;
+            }
             const int cs = sc.cp.Cs_out;                                   // a pixel's channels must not straddle 16-byte blocks
             if (cs != 4 && cs != 8 && cs != 16 && cs != 32 && cs != 64) continue;
             if ((int64_t)sc.cp.Ho * sc.cp.Wo * sc.cp.Cs_out != sg.gp.Kp_bytes || sc.cp.G >= 2048) continue;
@@ -1462,8 +1472,8 @@ int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t w
                      "front=%d tail=%d out_frag=%d resblock=%d pos23=%d stack=%d stack_bf16=%d\n",
                      i, s.layer, s.sub, (int)s.el, c.H, c.W, c.Cs_in, c.Ho, c.Wo, c.Cs_out, c.k, c.s, c.pad, c.mode,
                      s.NT, s.KS, c.k_steps, s.RD, s.PF, c.TH, c.n_bands, c.G, c.units_img, c.pitch, c.tile_stride, lds, c.wave_private, c.wp_pt, c.pool, c.TPH, (int)s.fuse_next,
-                     (int)(s.fuse_next && i + 1 < pol.steps.size() && conv_front_supported(c, s.NT, pol.steps[i + 1].cp)),
-                     (int)(s.el == EL_I8 && !s.fused_prev && conv_tail_supported(c, s.NT)), c.out_frag, (int)s.resblock, c.pos23,
+                     (int)(s.fuse_next && i + 1 < pol.steps.size() && (s.el == EL_I8 ? conv_front_supported(c, s.NT, pol.steps[i + 1].cp) : conv_front_bf16_supported(c, s.NT, pol.steps[i + 1].cp))),
+                     (int)(!s.fused_prev && (s.el == EL_I8 ? conv_tail_supported(c, s.NT) : conv_tail_bf16_supported(c, s.NT))), c.out_frag, (int)s.resblock, c.pos23,
                      s.el != EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0, s.el == EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0);
         } else if (s.kind == ST_GEMM) {
             snprintf(line, sizeof line, "step %zu gemm layer=%d el=%d epi=%d N=%d Np=%d Kp_bytes=%d k_steps=%d n_tiles=%d relu_in=%d relu=%d x_frag=%d\n",

@@ -52,6 +52,8 @@ hipError_t launch_conv(const ConvParams& p, Elem el, int NT, int KS, int RD, int
     if (p.B <= 0) return hipSuccess;
     static const bool no_tail = getenv("ACCERL_NO_CONV_TAIL") != nullptr;
     if (el == EL_I8 && !no_tail && conv_tail_supported(p, NT)) return launch_conv_tail(p, s);
+    if (el == EL_BF16 && (!no_tail || p.out_frag) && conv_tail_bf16_supported(p, NT)) return launch_conv_tail_bf16(p, s);
+    if (el == EL_BF16 && p.out_frag) return hipErrorInvalidValue;
     const size_t lds = (KS > 0 ? 0 : (size_t)p.w_bytes + (size_t)p.k_steps * 16 + CONV_LDS_CONST) + (size_t)p.lds_tiles + (size_t)(p.pool ? p.lds_otile : 0) + (size_t)p.lds_tab;
     dim3 grid((unsigned)p.n_bands, 1);
     if (p.wave_private) {
