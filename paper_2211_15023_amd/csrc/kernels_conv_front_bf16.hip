@@ -4,36 +4,44 @@
 // A workgroup of eight wavefronts (one per compute unit, two per SIMD) walks over observations.  In one tick wavefronts
 // 4..7 compute the first convolution of observation n+1 from its bf16 copy in LDS and write the 20x20x32 image to LDS,
 // wavefronts 0..3 compute the second convolution of observation n from the image written in the tick before, and the bytes
-// of observation n+2 are in flight; then the first-layer wavefronts convert those bytes to bf16 (v / 255) into LDS while the
-// second-layer wavefronts finish their last two tiles.  The first layer's output never leaves the chip.
+// of observation n+2 are in flight; then all eight convert those bytes to bf16 (v / 255) into LDS.  The first layer's output
+// never leaves the chip.
 //
 //  * Weights stay in registers: 8 K steps x 2 channel tiles for the first layer (64), 16 x 2 for one half of the second
 //    layer's filters (128).
-//  * Observation copy.  A unit is 4 horizontally adjacent pixels of all four planes; its 16 values are two chunks, channels
-//    0, 1 and channels 2, 3, each [channel][pixel] as the plane's bytes arrive, and the two kinds of chunk lie in planes of
-//    their own.  A K step of the first layer is one kernel row: lane group g reads chunk kind g & 1 of unit ox + g / 2, so 16
-//    pixels of an output row are 256 consecutive bytes.  The weight fragments are brought to that order once.
+//  * Observation copy.  A unit is 4 horizontally adjacent pixels of all four planes; its 16 values are two chunks of two
+//    pixels, and the first and the second chunks of all units lie in planes of their own.  A K step of the first layer is one
+//    kernel row: lane group g reads chunk kind g & 1 of unit ox + g / 2, so 16 pixels of an output row are 256 consecutive
+//    bytes.
 //  * The first 16 output columns are tiled by output rows, five in a row per wavefront: rows 4..7 of a window are rows 0..3
 //    of the window below, so a tile fetches four of its eight fragments; the other 4 columns are five 4 x 4 tiles.
-//  * First-layer image: [8 channels][column parity][row][column / 2][16 B], rows of 12 columns: the stride-2 second layer
-//    reads consecutive chunks, and the second of two output rows starts 128 bytes further round the banks.
+//  * First-layer image: [8 channels][row parity][row / 2][column parity][column / 2][16 B], rows of 25 chunks (ten columns of
+//    either parity and a gap): the stride-2 second layer's output pixels 9 oy + ox read chunks 25 oy + ox, which are the same
+//    modulo the 16 chunks of a bank round, so any 16 consecutive pixels are free of conflicts.  All planes are multiples of
+//    256 bytes apart, since a pass of a 16-byte read mixes lanes of neighbouring groups.
+//  * K steps, weight fragments and bias are the planner's, in its order: results are bit-identical to conv_kernel.h.
 //  * The second layer's 81 pixels are the tiles 0..47 and 33..80; the overlap is stored twice with the same bytes.
 //
-// What bounds it: LDS (410 KB per observation) and the matrix cores (784 MFMAs per observation, 3 136 clocks per SIMD) about
-// equally.
+// What bounds it (clocks per observation inside the kernel): the two layers 3 900, 3 330 of them at the matrix cores' rate; the
+// conversion 1 400 to 1 600, at the vector ALUs' rate, with the matrix cores idle.  4096 states: 56 us (the generic kernels
+// 82 + 98 us).  Without effect on the time: bank conflicts of the fragment reads (six million clocks of 15 removed), the
+// order of the loads, two accumulator chains or four in the first layer.
+#include <type_traits>
+
 #include "conv_kernel.h"
 
 namespace accerl {
 
 namespace {
 
-constexpr int FB_THREADS = 512, FB_STAGERS = 256;
+constexpr int FB_THREADS = 512;
 constexpr int FB_PLANE_IN = 84 * 84;                     // bytes of a channel plane of the observation
 constexpr int FB_UNITS = FB_PLANE_IN / 4;                // 1764
-constexpr int FB_PF = (FB_UNITS + FB_STAGERS - 1) / FB_STAGERS;   // 7
-constexpr int FB_ROW_A = 21 * 16, FB_KIND_A = FB_UNITS * 16, FB_TILE_A = 2 * FB_KIND_A;
-constexpr int FB_ROW_B = 12 * 16, FB_PAR_B = 20 * FB_ROW_B + 128, FB_CH_B = 2 * FB_PAR_B, FB_TILE_B = 4 * FB_CH_B;
-constexpr int FB_LDS = FB_TILE_A + 2 * FB_TILE_B;
+constexpr int FB_RAW = (4 * FB_PLANE_IN + 4095) / 4096 * 4096;   // the observation's bytes as they are, whole KiB per wavefront
+constexpr int FB_ROW_A = 21 * 16, FB_KIND_A = (FB_UNITS * 16 + 255) / 256 * 256, FB_TILE_A = 2 * FB_KIND_A;
+constexpr int FB_ROW_B = 25 * 16, FB_XPAR_B = 10 * 16, FB_YPAR_B = 10 * FB_ROW_B, FB_CH_B = 8192, FB_TILE_B = 4 * FB_CH_B;
+static_assert(2 * FB_YPAR_B <= FB_CH_B, "two row parities of ten rows");
+constexpr int FB_LDS = FB_TILE_A + 2 * FB_TILE_B;      // besides FB_RAW
 constexpr int FB_NPIX2 = 81, FB_PIX2_BYTES = 128;
 
 struct FrontBParams {
@@ -59,11 +67,12 @@ __device__ __forceinline__ v4i fb_relu_pack(v4f a, v4f b) {
     const v4i v = {fb_pack2(a[0], a[1]), fb_pack2(a[2], a[3]), fb_pack2(b[0], b[1]), fb_pack2(b[2], b[3])};
     return __builtin_bit_cast(v4i, __builtin_elementwise_max(__builtin_bit_cast(v8s, v), z));
 }
-// bf16(v / 255) of two bytes of a dword
+// two pixels of four channels, bf16(v / 255): bytes LO and LO + 1 of the four planes' dwords
 template <int LO>
-__device__ __forceinline__ int fb_obs2(uint32_t d) {
+__device__ __forceinline__ v4i fb_obs(const uint32_t (&d)[4]) {
     constexpr float k = 1.0f / 255.0f;
-    return fb_pack2((float)((d >> (8 * LO)) & 0xffu) * k, (float)((d >> (8 * LO + 8)) & 0xffu) * k);
+    auto v = [&](int c, int px) { return (float)((d[c] >> (8 * (LO + px))) & 0xffu) * k; };
+    return (v4i){fb_pack2(v(0, 0), v(1, 0)), fb_pack2(v(2, 0), v(3, 0)), fb_pack2(v(0, 1), v(1, 1)), fb_pack2(v(2, 1), v(3, 1))};
 }
 
 __global__ __launch_bounds__(FB_THREADS, 2) void conv_front_bf16_kernel(const FrontBParams p) {
@@ -77,106 +86,146 @@ __global__ __launch_bounds__(FB_THREADS, 2) void conv_front_bf16_kernel(const Fr
     int64_t img = blockIdx.x;                            // the observation whose second convolution runs this tick
     if (img >= p.B) return;
 
-    if (wave >= 4) {
-        const int aw = wave - 4, stid = tid - FB_STAGERS;
-        uint32_t pre[FB_PF][4];
-        auto obs_of = [&](int64_t im) { return p.obs + min(im, p.B - 1) * (int64_t)(4 * FB_PLANE_IN); };   // past the batch: the last observation, never used
-        auto stage_load_part = [&](const uint8_t* src, int k) {
-            const int u = min(stid + k * FB_STAGERS, FB_UNITS - 1);
+    // Staging.  The second-layer wavefronts, which have time to spare, send the bytes of an observation straight from memory
+    // to `raw` (the memory queue of a compute unit fills up and holds the wavefront that issues into it); from there all eight
+    // wavefronts convert their share.
+    __shared__ __attribute__((aligned(16))) uint8_t raw[FB_RAW];
+    auto fetch = [&](int64_t im) {
+        const uint8_t* src = p.obs + im * (int64_t)(4 * FB_PLANE_IN);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) pre[k][c] = *(const uint32_t*)(src + c * FB_PLANE_IN + 4 * u);
-        };
-        auto stage_commit = [&]() {
+        for (int k = 0; k < FB_RAW / 4096; ++k) {
+            const uint32_t at = (wave + 4 * k) * 1024;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + min(at + lane * 16, (uint32_t)(4 * FB_PLANE_IN - 16))),
+                                             (__attribute__((address_space(3))) void*)(raw + at), 16, 0, 0);
+        }
+    };
+    auto fetched = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };   // by the wavefronts that fetch, before the barrier
+    auto convert = [&]() {
 #pragma unroll
-            for (int k = 0; k < FB_PF; ++k) {
-                const int u = stid + k * FB_STAGERS;
-                if (u < FB_UNITS) {
+        for (int k = 0; k < (FB_UNITS + FB_THREADS - 1) / FB_THREADS; ++k) {
+            const int u = tid + k * FB_THREADS;
+            if (u < FB_UNITS) {
+                uint32_t d[4];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        *(v4i*)(tileA + h * FB_KIND_A + 16 * u) = (v4i){fb_obs2<0>(pre[k][2 * h]), fb_obs2<2>(pre[k][2 * h]),
-                                                                         fb_obs2<0>(pre[k][2 * h + 1]), fb_obs2<2>(pre[k][2 * h + 1])};
-                }
+                for (int c = 0; c < 4; ++c) d[c] = *(const uint32_t*)(raw + c * FB_PLANE_IN + 4 * u);
+                *(v4i*)(tileA + 16 * u) = fb_obs<0>(d);
+                *(v4i*)(tileA + FB_KIND_A + 16 * u) = fb_obs<2>(d);
             }
-        };
-#pragma unroll
-        for (int k = 0; k < FB_PF; ++k) stage_load_part(obs_of(img), k);
-        // The planner's chunk q of a kernel row is pixels 2q, 2q+1 x channels 0..3.  Lane group g needs channels 2 (g & 1) and
-        // + 1 of pixels 4 (g / 2) .. + 3: dwords (g & 1), 2 + (g & 1) of chunks 2 (g / 2) and + 1, low halves then high halves.
+        }
+    };
+
+    if (wave >= 4) {
+        const int aw = wave - 4;
         v4i wA[8][2];
 #pragma unroll
         for (int st = 0; st < 8; ++st)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const v4i* src = p.wA + (st * 2 + t) * 64 + j + 32 * (g >> 1);
-                const v4i a = src[0], b = src[16];
-                const uint32_t a0 = (uint32_t)(g & 1 ? a[1] : a[0]), a1 = (uint32_t)(g & 1 ? a[3] : a[2]);
-                const uint32_t b0 = (uint32_t)(g & 1 ? b[1] : b[0]), b1 = (uint32_t)(g & 1 ? b[3] : b[2]);
-                wA[st][t] = (v4i){(int)__builtin_amdgcn_perm(a1, a0, 0x05040100u), (int)__builtin_amdgcn_perm(b1, b0, 0x05040100u),
-                                  (int)__builtin_amdgcn_perm(a1, a0, 0x07060302u), (int)__builtin_amdgcn_perm(b1, b0, 0x07060302u)};
-            }
+            for (int t = 0; t < 2; ++t) wA[st][t] = p.wA[(st * 2 + t) * 64 + lane];
         const v4f bi0 = *(const v4f*)(p.biasA + 8 * g), bi1 = *(const v4f*)(p.biasA + 8 * g + 4);
 
         // chain tiles: output row 5 aw + r, column j; then the 4 x 4 tiles aw and (first wavefront only) 4
         const int lane_in = (g >> 1) * 16 + (g & 1) * FB_KIND_A;
         const int rb_chain = (5 * aw) * (4 * FB_ROW_A) + j * 16 + lane_in;
-        const int wb_chain = g * FB_CH_B + (j & 1) * FB_PAR_B + (5 * aw) * FB_ROW_B + (j >> 1) * 16;
-        int rb_blk[2], wb_blk[2];
+        auto at_b = [&](int oy, int ox) { return g * FB_CH_B + (oy & 1) * FB_YPAR_B + (oy >> 1) * FB_ROW_B + (ox & 1) * FB_XPAR_B + (ox >> 1) * 16; };
+        int wb_chain[5], rb_blk[2], wb_blk[2];
+#pragma unroll
+        for (int r = 0; r < 5; ++r) wb_chain[r] = at_b(5 * aw + r, j);
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int b = k == 0 ? aw : 4, oy = 4 * b + (j >> 2), ox = 16 + (j & 3);
             rb_blk[k] = oy * (4 * FB_ROW_A) + ox * 16 + lane_in;
-            wb_blk[k] = g * FB_CH_B + (ox & 1) * FB_PAR_B + oy * FB_ROW_B + (ox >> 1) * 16;
+            wb_blk[k] = at_b(oy, ox);
         }
-        auto frag_a = [&](int r, int st) {
-            const int base = r < 5 ? rb_chain + r * (4 * FB_ROW_A) : rb_blk[r - 5];
-            return *(const v4i*)(tileA + base + st * FB_ROW_A);
-        };
-        auto store_a = [&](char* dstB, int r, v4f a, v4f b) {
-            *(v4i*)(dstB + (r < 5 ? wb_chain + r * FB_ROW_B : wb_blk[r - 5])) = fb_relu_pack(a, b);
-        };
-        // One tile = 16 MFMAs; the fragments of the next tile are requested and the tile before is packed and stored meanwhile,
-        // and the bytes of observation `next` are requested, one unit per tile.
-        auto conv_a = [&](char* dstB, const uint8_t* next) {
-            v4i f[8];
+        // window row i below the lane's first chain pixel (tile r: rows 4r .. 4r + 7), window row i of 4 x 4 tile k
+        auto chain = [&](int i) { return *(const v4i*)(tileA + rb_chain + i * FB_ROW_A); };
+        auto blk = [&](int k, int i) { return *(const v4i*)(tileA + rb_blk[k] + i * FB_ROW_A); };
+        auto store_a = [&](char* dst, v4f a, v4f b) { *(v4i*)dst = fb_relu_pack(a, b); };
+        // Two tiles at a time: four accumulator chains (with two, the matrix core waits for the result of the MFMA before last:
+        // 25 clocks each instead of 16).  Chain tiles (0, 1), (2, 3), then chain tile 4 with the 4 x 4 tile, in the first
+        // wavefront with the fifth 4 x 4 tile too.  Meanwhile the fragments of the next two tiles are requested and the two
+        // tiles before are packed and stored.
+        auto conv_a = [&](char* dstB) {
+            v4i f[12], b[8];
 #pragma unroll
-            for (int st = 0; st < 8; ++st) f[st] = frag_a(0, st);
-            v4f o0 = bi0, o1 = bi1;
+            for (int i = 0; i < 12; ++i) f[i] = chain(i);
+            __builtin_amdgcn_sched_barrier(0);
+            v4f o[4];
 #pragma unroll
-            for (int r = 0; r < 7; ++r) {
-                if (r == 6 && aw != 0) break;            // the fifth 4 x 4 tile
-                v4f n0 = bi0, n1 = bi1;
-                v4i fn[8];
-                stage_load_part(next, r);
+            for (int pr = 0; pr < 2; ++pr) {
+                v4f n[4] = {bi0, bi1, bi0, bi1};
+                v4i fn[12];
 #pragma unroll
                 for (int st = 0; st < 8; ++st) {
-                    n0 = fb_mfma(wA[st][0], f[st], n0);
-                    n1 = fb_mfma(wA[st][1], f[st], n1);
-                    if (r + 1 < 5) fn[st] = st < 4 ? f[st + 4] : frag_a(r + 1, st);
-                    else if (r + 1 < 7) fn[st] = frag_a(r + 1, st);     // (tile 6 is read by every wavefront: one copy of the code)
-                }
-                if (r > 0) store_a(dstB, r - 1, o0, o1);
-                o0 = n0; o1 = n1;
 #pragma unroll
-                for (int st = 0; st < 8; ++st) f[st] = fn[st];
+                    for (int t = 0; t < 4; ++t) n[t] = fb_mfma(wA[st][t & 1], f[st + 4 * (t >> 1)], n[t]);
+                    if (st < 4) fn[st] = f[st + 8];
+                    if (pr == 0 || st < 4) fn[st + 4] = chain(8 * pr + 12 + st);
+                    if (pr == 1) b[st] = blk(0, st);
+                }
+                if (pr > 0) {
+                    store_a(dstB + wb_chain[0], o[0], o[1]);
+                    store_a(dstB + wb_chain[1], o[2], o[3]);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] = n[t];
+#pragma unroll
+                for (int i = 0; i < (pr == 0 ? 12 : 8); ++i) f[i] = fn[i];
+                // the instruction stream in this order (the scheduler alone moves the reads next to their use)
+#pragma unroll
+                for (int st = 0; st < 8; ++st) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    if (pr == 1 && st < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    if (pr > 0) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                }
+                if (pr > 0) __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (aw != 0) stage_load_part(next, 6);
-            store_a(dstB, aw == 0 ? 6 : 5, o0, o1);
+            auto last = [&](auto THIRD) {
+                constexpr bool third = decltype(THIRD)::value;
+                v4f n[6] = {bi0, bi1, bi0, bi1, bi0, bi1};
+                v4i c[8];
+                if constexpr (third) {
+#pragma unroll
+                    for (int st = 0; st < 8; ++st) c[st] = blk(1, st);
+                }
+#pragma unroll
+                for (int st = 0; st < (third ? 12 : 8); ++st) {
+                    if (st < 8) {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) n[t] = fb_mfma(wA[st][t & 1], t < 2 ? f[st] : b[st], n[t]);
+                    }
+                    if (third && st >= 4) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) n[4 + t] = fb_mfma(wA[st - 4][t], c[st - 4], n[4 + t]);
+                    }
+                }
+                store_a(dstB + wb_chain[2], o[0], o[1]);
+                store_a(dstB + wb_chain[3], o[2], o[3]);
+                store_a(dstB + wb_chain[4], n[0], n[1]);
+                store_a(dstB + wb_blk[0], n[2], n[3]);
+                if constexpr (third) store_a(dstB + wb_blk[1], n[4], n[5]);
+            };
+            if (aw == 0) last(std::true_type());
+            else last(std::false_type());
         };
 
-        stage_commit();
+        __syncthreads();                                 // the first observation's bytes are there
+        convert();
         __syncthreads();                                 // observation copy complete
-        conv_a(tilesB, obs_of(img + stride));
-        __syncthreads();                                 // first image complete, observation copy free
-        if (img + stride < p.B) stage_commit();
+        conv_a(tilesB);
+        __syncthreads();                                 // first image complete, observation copy free, next bytes there
+        if (img + stride < p.B) convert();
         __syncthreads();
         for (int n = 0;; ++n, img += stride) {
             if (!(img + stride < p.B)) break;            // the workgroup's observations are done (same test in every wavefront)
-            conv_a(tilesB + ((n + 1) & 1) * FB_TILE_B, obs_of(img + 2 * stride));
+            conv_a(tilesB + ((n + 1) & 1) * FB_TILE_B);
             __syncthreads();
-            if (img + 2 * stride < p.B) stage_commit();
+            if (img + 2 * stride < p.B) convert();
             __syncthreads();
         }
     } else {
+        fetch(img);
         const int h = wave & 1, p0 = (wave >> 1) ? FB_NPIX2 - 48 : 0;
         v4i wB[16][2];
 #pragma unroll
@@ -190,23 +239,30 @@ __global__ __launch_bounds__(FB_THREADS, 2) void conv_front_bf16_kernel(const Fr
         for (int u = 0; u < 3; ++u) {
             const int px = p0 + 16 * u + j;
             const int oy = (px * 7282) >> 16, ox = px - oy * 9;       // px / 9 for px < 81
-            rb[u] = g * FB_CH_B + oy * (2 * FB_ROW_B) + ox * 16;
+            rb[u] = g * FB_CH_B + oy * FB_ROW_B + ox * 16;
         }
         const int oofs = (p0 + j) * FB_PIX2_BYTES + 32 * g + 16 * h;
         auto frag_b = [&](const char* src, int q) {
             const int u = q >> 4, st = q & 15;
-            return *(const v4i*)(src + rb[u] + (st >> 2) * FB_ROW_B + (st & 1) * FB_PAR_B + ((st >> 1) & 1) * 16);
+            return *(const v4i*)(src + rb[u] + ((st >> 2) & 1) * FB_YPAR_B + (st >> 3) * FB_ROW_B + (st & 1) * FB_XPAR_B + ((st >> 1) & 1) * 16);
         };
+        fetched();
         __syncthreads();
+        convert();
         __syncthreads();
+        if (img + stride < p.B) fetch(img + stride);
+        fetched();
+        __syncthreads();
+        if (img + stride < p.B) convert();
         __syncthreads();
         for (int n = 0;; ++n, img += stride) {
+            if (img + 2 * stride < p.B) fetch(img + 2 * stride);
             const char* src = tilesB + (n & 1) * FB_TILE_B;
             char* out = p.out + img * (int64_t)(FB_NPIX2 * FB_PIX2_BYTES);
-            const bool last = !(img + stride < p.B);
             v4i gq[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) gq[q] = frag_b(src, q);
+            __builtin_amdgcn_sched_barrier(0);
             v4f o0 = bi0, o1 = bi1;
 #pragma unroll
             for (int u = 0; u < 3; ++u) {
@@ -220,10 +276,22 @@ __global__ __launch_bounds__(FB_THREADS, 2) void conv_front_bf16_kernel(const Fr
                 }
                 if (u > 0) *(v4i*)(out + oofs + (u - 1) * (16 * FB_PIX2_BYTES)) = fb_relu_pack(o0, o1);
                 o0 = n0; o1 = n1;
-                if (u == 0 && !last) __syncthreads();    // the other wavefronts may replace the observation copy
+                // the instruction stream in this order: two MFMAs, the fragment eight steps ahead (the scheduler alone moves the
+                // reads next to their use, and every MFMA pair waits for LDS)
+#pragma unroll
+                for (int st = 0; st < 16; ++st) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                    if (u * 16 + st + 8 < 48) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    if (u > 0 && st < 8) __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
+                }
+                if (u > 0) __builtin_amdgcn_sched_group_barrier(0x040, 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
             }
             *(v4i*)(out + oofs + 2 * (16 * FB_PIX2_BYTES)) = fb_relu_pack(o0, o1);
-            if (last) break;
+            if (!(img + stride < p.B)) break;
+            fetched();
+            __syncthreads();
+            if (img + 2 * stride < p.B) convert();
             __syncthreads();
         }
     }
