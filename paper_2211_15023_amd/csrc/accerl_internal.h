@@ -146,9 +146,9 @@ hipError_t launch_maxpool(const void* in, void* out, int64_t B, int H, int W, in
                           int k, int s, int pad, Elem el, hipStream_t stream);
 
 // ---------------------------------------------------------------- row gather / scatter (policy mixture)
-hipError_t launch_gather_rows(const void* in, const int32_t* idx, int64_t n, int64_t row_bytes, void* out, hipStream_t s);
-hipError_t launch_gather_f32(const float* in, const int32_t* idx, int64_t n, float* out, hipStream_t s);
-hipError_t launch_scatter_out(const float* logits, const float* value, const int32_t* action, const int32_t* idx, int64_t n, int A,
+hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t row_bytes,
+                             void* out, float* out_uniforms, hipStream_t s);
+hipError_t launch_scatter_mix(const float* logits, const float* value, const int32_t* action, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int A,
                               float* out_logits, float* out_value, int32_t* out_action, hipStream_t s);
 
 // ---------------------------------------------------------------- dense layers (MFMA GEMM)

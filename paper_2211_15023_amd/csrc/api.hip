@@ -1592,18 +1592,14 @@ int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original
     const int64_t o2 = (ns + 3) & ~(int64_t)3;   // keeps every buffer of the second subset 16-byte aligned
     HIP_TRY(hipMemcpyAsync(d_idx, pin, (size_t)B * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(m->mix_ev[slot], st));
-    HIP_TRY(launch_gather_rows(states, d_idx, ns, obs, d_states, st));
-    HIP_TRY(launch_gather_rows(states, d_idx + ns, no, obs, d_states + o2 * obs, st));
-    HIP_TRY(launch_gather_f32(uniforms, d_idx, ns, d_uni, st));
-    HIP_TRY(launch_gather_f32(uniforms, d_idx + ns, no, d_uni + o2, st));
+    HIP_TRY(launch_gather_mix(states, uniforms, d_idx, B, ns, o2, obs, d_states, d_uni, st));
     Call cs{d_states, ns, d_uni, nullptr, nullptr, nullptr, d_logits, d_value, d_action, st};
     rc = run(smaller, cs);
     if (rc) return rc;
     Call co{d_states + o2 * obs, no, d_uni + o2, nullptr, nullptr, nullptr, d_logits + o2 * A, d_value + o2, d_action + o2, st};
     rc = run(original, co);
     if (rc) return rc;
-    HIP_TRY(launch_scatter_out(d_logits, d_value, d_action, d_idx, ns, A, out_logits, out_value, out_action, st));
-    HIP_TRY(launch_scatter_out(d_logits + o2 * A, d_value + o2, d_action + o2, d_idx + ns, no, A, out_logits, out_value, out_action, st));
+    HIP_TRY(launch_scatter_mix(d_logits, d_value, d_action, d_idx, B, ns, o2, A, out_logits, out_value, out_action, st));
     return ACCERL_OK;
 }
 

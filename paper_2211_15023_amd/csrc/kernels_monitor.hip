@@ -136,16 +136,26 @@ __global__ __launch_bounds__(MON_WAVES * 64) void kl_rows_kernel(const float* __
     }
 }
 
-// one wavefront folds the partials in a fixed order: stats = {mean, max, population variance, entropy mean}
-// (monitor) or the mean distillation loss alone (loss_only)
-__global__ __launch_bounds__(64) void kl_stats_kernel(const double* __restrict__ parts, int n_parts, int64_t B, double* __restrict__ stats, int loss_only) {
-    const int lane = threadIdx.x;
+// One workgroup folds the partials in a fixed order: stats = {mean, max, population variance, entropy mean} (monitor) or the
+// mean distillation loss alone (loss_only).  Bound by the latency of its loads: a single wavefront took 32 rounds of them for
+// 2048 records (11 us; now 3.4).
+constexpr int MON_FOLD_WAVES = 16;
+__global__ __launch_bounds__(MON_FOLD_WAVES * 64) void kl_stats_kernel(const double* __restrict__ parts, int n_parts, int64_t B, double* __restrict__ stats, int loss_only) {
+    __shared__ double red[MON_FOLD_WAVES][MON_NSTAT];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double s_kl = 0.0, s_sq = 0.0, s_mx = -1.0, s_h = 0.0, s_loss = 0.0;
-    for (int i = lane; i < n_parts; i += 64) {
+    for (int i = threadIdx.x; i < n_parts; i += MON_FOLD_WAVES * 64) {
         const double* p = parts + MON_NSTAT * i;
         s_kl += p[0]; s_sq += p[1]; s_mx = fmax(s_mx, p[2]); s_h += p[3]; s_loss += p[4];
     }
     s_kl = wave_sum(s_kl); s_sq = wave_sum(s_sq); s_h = wave_sum(s_h); s_mx = wave_max(s_mx); s_loss = wave_sum(s_loss);
+    if (lane == 0) { red[wave][0] = s_kl; red[wave][1] = s_sq; red[wave][2] = s_mx; red[wave][3] = s_h; red[wave][4] = s_loss; }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const bool live = lane < MON_FOLD_WAVES;
+    const double* r = red[live ? lane : 0];
+    s_kl = wave_sum(live ? r[0] : 0.0); s_sq = wave_sum(live ? r[1] : 0.0); s_mx = wave_max(live ? r[2] : -1.0);
+    s_h = wave_sum(live ? r[3] : 0.0); s_loss = wave_sum(live ? r[4] : 0.0);
     if (lane == 0) {
         const double n = (double)B, mean = s_kl / n;
         if (loss_only) {
@@ -191,24 +201,26 @@ __global__ __launch_bounds__(MON_WAVES * 64) void is_ratio_kernel(const float* _
 // ---- backward scan per environment: v_s - V(x_s) = delta_s + gamma_s c_s (v_{s+1} - V(x_{s+1}))
 // A scan with one lane per environment leaves the chip nearly empty (B / 64 wavefronts walking T dependent steps).  The
 // recurrence a_t = delta_t + k_t a_{t+1} (k_t = gamma_t c_t) is linear, so a run of steps [t0, t1) acts on the value
-// entering it as a_t0 = A + M a_t1 with A, M computed from that run alone.  A workgroup takes 64 environments; its
-// wavefronts split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
+// entering it as a_t0 = A + M a_t1 with A, M computed from that run alone.  A workgroup takes VT_ENV environments (a whole
+// 128-byte line of every row; with 64 of them an unroll of 4096 kept 64 compute units busy, 18.3 us for 256 steps against
+// VTNOW); groups of VT_ENV lanes split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
 // backward pass, the pairs meet in LDS, every wavefront folds the pairs of the runs behind it into the value entering
 // its run and walks its registers a second time to write v_s, the clipped weights and the advantages.  Longer unrolls
 // repeat this from the end of the trajectory towards its start, carrying a_t across.  delta_t needs V(x_{t+1}) only,
 // which is an input.  The order of the floating-point operations is fixed by (T, L), not by the launch.
-constexpr int VT_NSEG = 16;
+constexpr int VT_ENV = 32;
+constexpr int VT_NSEG = 16 * 64 / VT_ENV;
 template <int L>
-__global__ __launch_bounds__(VT_NSEG * 64) void vtrace_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ discounts,
+__global__ __launch_bounds__(VT_NSEG * VT_ENV) void vtrace_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ discounts,
                                                                    const float* __restrict__ values, const float* __restrict__ bootstrap,
                                                                    int64_t T, int64_t B, float rho_bar, float c_bar,
                                                                    float* __restrict__ rho /* in: ratio, out: clipped */,
                                                                    float* __restrict__ vs, float* __restrict__ pg_adv) {
-    __shared__ float sA[VT_NSEG][64], sM[VT_NSEG][64];
-    __shared__ float s_carry[64];
-    const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6;
-    const int nseg = blockDim.x >> 6;
-    const int64_t b = (int64_t)blockIdx.x * 64 + lane;
+    __shared__ float sA[VT_NSEG][VT_ENV], sM[VT_NSEG][VT_ENV];
+    __shared__ float s_carry[VT_ENV];
+    const int lane = threadIdx.x % VT_ENV, seg = threadIdx.x / VT_ENV;
+    const int nseg = blockDim.x / VT_ENV;
+    const int64_t b = (int64_t)blockIdx.x * VT_ENV + lane;
     const int64_t bc = b < B ? b : B - 1;                  // lanes past the batch repeat the last environment, store nothing
     if (seg == 0) s_carry[lane] = 0.0f;                    // a_T = v_T - V(x_T) = 0
     for (int64_t hi = T; hi > 0; hi -= (int64_t)nseg * L) {
@@ -355,7 +367,7 @@ static int run_kl(const char* who, const float* logits_original, const float* lo
     kl_rows_kernel<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, B, A, out_kl, out_entropy, parts,
                                                                   v_o, v_s, beta, out_loss);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("kl_rows_kernel", e);
-    kl_stats_kernel<<<dim3(1), dim3(64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
+    kl_stats_kernel<<<dim3(1), dim3(MON_FOLD_WAVES * 64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("kl_stats_kernel", e);
     return ACCERL_OK;
 }
@@ -398,15 +410,14 @@ extern "C" int accerl_vtrace(const float* logits_original, const float* logits_s
     is_ratio_kernel<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, actions, R, A, out_rho);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("is_ratio_kernel", e);
-    // runs of 16 steps for long unrolls, of 4 for short ones; as many wavefronts per workgroup as there are runs (at most 16)
-    const dim3 vgrid((unsigned)((B + 63) / 64));
-    if (T > 32) {
-        const int nseg = (int)((T + 15) / 16 < VT_NSEG ? (T + 15) / 16 : VT_NSEG);
-        vtrace_scan_kernel<16><<<vgrid, dim3(nseg * 64), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
-    } else {
-        const int nseg = (int)((T + 3) / 4);
-        vtrace_scan_kernel<4><<<vgrid, dim3(nseg * 64), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
-    }
+    // runs of 8 steps for long unrolls, of 4 for short ones; as many runs per workgroup as there are (at most VT_NSEG, and an
+    // even number: whole wavefronts)
+    const dim3 vgrid((unsigned)((B + VT_ENV - 1) / VT_ENV));
+    auto runs = [&](int L) { const int64_t n = ((T + L - 1) / L + 1) & ~(int64_t)1; return (unsigned)(n < VT_NSEG ? n : VT_NSEG); };
+    if (T > 32)
+        vtrace_scan_kernel<8><<<vgrid, dim3(runs(8) * VT_ENV), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
+    else
+        vtrace_scan_kernel<4><<<vgrid, dim3(runs(4) * VT_ENV), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("vtrace_scan_kernel", e);
     return ACCERL_OK;
 }
