@@ -296,7 +296,7 @@ hipError_t launch_lstm_pack(const LstmPackParams& p, hipStream_t s) {
 // ------------------------------------------------------------------ row gather / scatter (policy mixture)
 // Compacted row i (of n) is row idx[i] of the batch; the first n0 rows are the first subset, the others start at row `second` of
 // the compacted buffers.  One launch serves both subsets and the uniforms: four launches took 13 us for 1000 rows of 28 KB,
-// most of it start-up (now GNOW).
+// most of it start-up (now 9).
 __global__ __launch_bounds__(256) void gather_mix_kernel(const char* __restrict__ in, const float* __restrict__ uni, const int32_t* __restrict__ idx,
                                                          int64_t n0, int64_t second, int row_units, char* __restrict__ out, float* __restrict__ out_uni) {
     const int64_t i = blockIdx.x, r = idx[i], o = i < n0 ? i : second + (i - n0);
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void gather_mix_kernel(const char* __restrict_
 }
 
 // Results of both compacted forwards back to their rows, a lane per number (a lane per row walked its A logits alone: two
-// launches of 6 us for 1000 rows; now SNOW).
+// launches of 6 us for 1000 rows; now 2.8).
 __global__ __launch_bounds__(256) void scatter_mix_kernel(const float* __restrict__ logits, const float* __restrict__ value, const int32_t* __restrict__ action,
                                                           const int32_t* __restrict__ idx, int64_t n, int64_t n0, int64_t second, int A,
                                                           float* __restrict__ out_logits, float* __restrict__ out_value, int32_t* __restrict__ out_action) {

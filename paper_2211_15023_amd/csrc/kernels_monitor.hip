@@ -87,12 +87,26 @@ __device__ __forceinline__ double wave_max(double v) {
 // ---- KL(original || smaller) and entropy of the smaller policy per state; per-workgroup partial sums.
 // Four wavefronts per workgroup, each walking its own tiles with its own LDS region.
 constexpr int MON_WAVES = 4;
+// the partial sums of a workgroup of the KL pass
+__device__ __forceinline__ void kl_store_parts(double s_kl, double s_sq, double s_mx, double s_h, double s_loss, double* __restrict__ parts) {
+    __shared__ double red[MON_WAVES][MON_NSTAT];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    s_kl = wave_sum(s_kl); s_sq = wave_sum(s_sq); s_h = wave_sum(s_h); s_mx = wave_max(s_mx); s_loss = wave_sum(s_loss);
+    if (lane == 0) { red[wave][0] = s_kl; red[wave][1] = s_sq; red[wave][2] = s_mx; red[wave][3] = s_h; red[wave][4] = s_loss; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double* p = parts + MON_NSTAT * (int64_t)blockIdx.x;
+        double a0 = red[0][0], a1 = red[0][1], a2 = red[0][2], a3 = red[0][3], a4 = red[0][4];
+        for (int w = 1; w < MON_WAVES; ++w) { a0 += red[w][0]; a1 += red[w][1]; a2 = fmax(a2, red[w][2]); a3 += red[w][3]; a4 += red[w][4]; }
+        p[0] = a0; p[1] = a1; p[2] = a2; p[3] = a3; p[4] = a4;
+    }
+}
+
 __global__ __launch_bounds__(MON_WAVES * 64) void kl_rows_kernel(const float* __restrict__ lo, const float* __restrict__ ls, int64_t B, int A,
                                                                  float* __restrict__ out_kl, float* __restrict__ out_ent, double* __restrict__ parts,
                                                                  const float* __restrict__ v_o, const float* __restrict__ v_s, float beta,
                                                                  float* __restrict__ out_loss) {
     extern __shared__ __attribute__((aligned(16))) float mon_sm[];
-    __shared__ double red[MON_WAVES][5];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float* so = mon_sm + wave * 128 * A;
     float* ss = so + 64 * A;
@@ -125,20 +139,131 @@ __global__ __launch_bounds__(MON_WAVES * 64) void kl_rows_kernel(const float* __
         }
         wave_sync_lds();   // rows are read before the next tile overwrites them
     }
-    s_kl = wave_sum(s_kl); s_sq = wave_sum(s_sq); s_h = wave_sum(s_h); s_mx = wave_max(s_mx); s_loss = wave_sum(s_loss);
-    if (lane == 0) { red[wave][0] = s_kl; red[wave][1] = s_sq; red[wave][2] = s_mx; red[wave][3] = s_h; red[wave][4] = s_loss; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double* p = parts + MON_NSTAT * (int64_t)blockIdx.x;
-        double a0 = red[0][0], a1 = red[0][1], a2 = red[0][2], a3 = red[0][3], a4 = red[0][4];
-        for (int w = 1; w < MON_WAVES; ++w) { a0 += red[w][0]; a1 += red[w][1]; a2 = fmax(a2, red[w][2]); a3 += red[w][3]; a4 += red[w][4]; }
-        p[0] = a0; p[1] = a1; p[2] = a2; p[3] = a3; p[4] = a4;
+    kl_store_parts(s_kl, s_sq, s_mx, s_h, s_loss, parts);
+}
+
+// ---- the same two row passes for tables of at most ROW_AMAX actions.  The passes are bound by memory only if a row costs few
+// instructions: with the row walked in LDS at a run-time length they issued about 35 per action (rotation, bounds, addresses)
+// and loaded a tile only after the one before was done.  Here the next tile is in flight while a lane works on its two rows in
+// registers, every access at a fixed offset.  256 x 4096 rows of 18 actions: KL 37 -> 31 us, ratio 34 -> 29 us
+// (151 MB).
+constexpr int ROW_AMAX = 20;
+constexpr int ROW_BLOCKS = 1024;    // four workgroups per compute unit, each wavefront walking its tiles
+struct RowTile { v4f o[ROW_AMAX / 4], s[ROW_AMAX / 4]; float tail_o, tail_s; };   // a lane's share of 64 rows of both tables
+
+__device__ __forceinline__ void rows_load(RowTile& t, const float* __restrict__ lo, const float* __restrict__ ls, int64_t r0, int nrows, int A, int lane) {
+    const int n = nrows * A, n4 = n >> 2;
+    const float* po = lo + r0 * A;
+    const float* ps = ls + r0 * A;
+#pragma unroll
+    for (int q = 0; q < ROW_AMAX / 4; ++q)
+        if (64 * q < n4) {                                   // the same in every lane
+            const int i = min(lane + 64 * q, n4 - 1);
+            t.o[q] = ((const v4f*)po)[i];
+            t.s[q] = ((const v4f*)ps)[i];
+        }
+    const int rest = (n4 << 2) + lane;
+    if (rest < n) { t.tail_o = po[rest]; t.tail_s = ps[rest]; }
+}
+__device__ __forceinline__ void rows_commit(const RowTile& t, float* so, float* ss, int nrows, int A, int lane) {
+    const int n = nrows * A, n4 = n >> 2;
+#pragma unroll
+    for (int q = 0; q < ROW_AMAX / 4; ++q)
+        if (lane + 64 * q < n4) { ((v4f*)so)[lane + 64 * q] = t.o[q]; ((v4f*)ss)[lane + 64 * q] = t.s[q]; }
+    const int rest = (n4 << 2) + lane;
+    if (rest < n) { so[rest] = t.tail_o; ss[rest] = t.tail_s; }
+}
+// one lane's rows and their maxima
+struct RowPair { float o[ROW_AMAX], s[ROW_AMAX], mo, ms; };
+__device__ __forceinline__ void rows_read(RowPair& r, const float* ro, const float* rs, int A) {
+    r.o[0] = r.mo = ro[0];
+    r.s[0] = r.ms = rs[0];
+#pragma unroll
+    for (int a = 1; a < ROW_AMAX; ++a)
+        if (a < A) { r.o[a] = ro[a]; r.s[a] = rs[a]; }
+#pragma unroll
+    for (int a = 1; a < ROW_AMAX; ++a)
+        if (a < A) { r.mo = fmaxf(r.mo, r.o[a]); r.ms = fmaxf(r.ms, r.s[a]); }
+}
+// Walks the tiles of 64 rows of this wavefront and calls body(first row, rows, row pair) in the lanes that have a row.
+template <typename Body>
+__device__ __forceinline__ void for_each_row(const float* __restrict__ lo, const float* __restrict__ ls, int64_t B, int A, float* sm, Body body) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* so = sm + wave * 128 * A;
+    float* ss = so + 64 * A;
+    const int64_t n_tiles = (B + 63) >> 6, step = (int64_t)gridDim.x * MON_WAVES;
+    int64_t tile = (int64_t)blockIdx.x * MON_WAVES + wave;
+    auto rows_of = [&](int64_t t) { return (int)min(B - (t << 6), (int64_t)64); };
+    RowTile reg;
+    if (tile < n_tiles) rows_load(reg, lo, ls, tile << 6, rows_of(tile), A, lane);
+    for (; tile < n_tiles; tile += step) {
+        const int nrows = rows_of(tile);
+        rows_commit(reg, so, ss, nrows, A, lane);
+        wave_sync_lds();
+        RowPair r;
+        rows_read(r, so + min(lane, nrows - 1) * A, ss + min(lane, nrows - 1) * A, A);
+        wave_sync_lds();                                     // rows are read before the next tile overwrites them
+        if (tile + step < n_tiles) rows_load(reg, lo, ls, (tile + step) << 6, rows_of(tile + step), A, lane);
+        if (lane < nrows) body((tile << 6) + lane, r);
     }
+}
+
+__global__ __launch_bounds__(MON_WAVES * 64) void kl_rows_small_kernel(const float* __restrict__ lo, const float* __restrict__ ls, int64_t B, int A,
+                                                                       float* __restrict__ out_kl, float* __restrict__ out_ent, double* __restrict__ parts,
+                                                                       const float* __restrict__ v_o, const float* __restrict__ v_s, float beta,
+                                                                       float* __restrict__ out_loss) {
+    extern __shared__ __attribute__((aligned(16))) float mon_sm[];
+    double s_kl = 0.0, s_sq = 0.0, s_mx = -1.0, s_h = 0.0, s_loss = 0.0;
+    for_each_row(lo, ls, B, A, mon_sm, [&](int64_t row, const RowPair& r) {
+        float zo = 0.0f, zs = 0.0f, so = 0.0f, ss = 0.0f;
+#pragma unroll
+        for (int a = 0; a < ROW_AMAX; ++a)
+            if (a < A) {
+                const float d_o = r.o[a] - r.mo, d_s = r.s[a] - r.ms;
+                const float eo = fast_exp(d_o), es = fast_exp(d_s);
+                zo += eo; zs += es;
+                so += eo * (d_o - d_s);
+                ss += es * d_s;
+            }
+        const float lzo = fast_log(zo), lzs = fast_log(zs);
+        const float kl = so / zo - lzo + lzs, h = lzs - ss / zs;
+        if (out_kl) out_kl[row] = kl;
+        if (out_ent) out_ent[row] = h;
+        s_kl += (double)kl;
+        s_sq += (double)kl * (double)kl;
+        s_mx = fmax(s_mx, (double)kl);
+        s_h += (double)h;
+        if (v_o) {   // distillation loss of the state: KL + (v_original - v_smaller)^2 / 2 - beta H
+            const float dv = v_o[row] - v_s[row];
+            const float loss = kl + 0.5f * (dv * dv) - beta * h;
+            if (out_loss) out_loss[row] = loss;
+            s_loss += (double)loss;
+        }
+    });
+    kl_store_parts(s_kl, s_sq, s_mx, s_h, s_loss, parts);
+}
+
+__global__ __launch_bounds__(MON_WAVES * 64) void is_ratio_small_kernel(const float* __restrict__ lo, const float* __restrict__ ls, const int32_t* __restrict__ act,
+                                                                        int64_t R, int A, float* __restrict__ ratio) {
+    extern __shared__ __attribute__((aligned(16))) float mon_sm[];
+    for_each_row(lo, ls, R, A, mon_sm, [&](int64_t row, const RowPair& r) {
+        const int act_row = min(max(act[row], 0), A - 1);
+        float zo = 0.0f, zs = 0.0f, to = r.o[0], ts = r.s[0];
+#pragma unroll
+        for (int a = 0; a < ROW_AMAX; ++a)
+            if (a < A) {
+                zo += fast_exp(r.o[a] - r.mo);
+                zs += fast_exp(r.s[a] - r.ms);
+                to = a == act_row ? r.o[a] : to;
+                ts = a == act_row ? r.s[a] : ts;
+            }
+        ratio[row] = fast_exp((to - r.mo - fast_log(zo)) - (ts - r.ms - fast_log(zs)));
+    });
 }
 
 // One workgroup folds the partials in a fixed order: stats = {mean, max, population variance, entropy mean} (monitor) or the
 // mean distillation loss alone (loss_only).  Bound by the latency of its loads: a single wavefront took 32 rounds of them for
-// 2048 records (11 us; now 3.4).
+// 2048 records (11 us; now 5.8).
 constexpr int MON_FOLD_WAVES = 16;
 __global__ __launch_bounds__(MON_FOLD_WAVES * 64) void kl_stats_kernel(const double* __restrict__ parts, int n_parts, int64_t B, double* __restrict__ stats, int loss_only) {
     __shared__ double red[MON_FOLD_WAVES][MON_NSTAT];
@@ -203,7 +328,7 @@ __global__ __launch_bounds__(MON_WAVES * 64) void is_ratio_kernel(const float* _
 // recurrence a_t = delta_t + k_t a_{t+1} (k_t = gamma_t c_t) is linear, so a run of steps [t0, t1) acts on the value
 // entering it as a_t0 = A + M a_t1 with A, M computed from that run alone.  A workgroup takes VT_ENV environments (a whole
 // 128-byte line of every row; with 64 of them an unroll of 4096 kept 64 compute units busy, 18.3 us for 256 steps against
-// VTNOW); groups of VT_ENV lanes split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
+// 8.0); groups of VT_ENV lanes split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
 // backward pass, the pairs meet in LDS, every wavefront folds the pairs of the runs behind it into the value entering
 // its run and walks its registers a second time to write v_s, the clipped weights and the advantages.  Longer unrolls
 // repeat this from the end of the trajectory towards its start, carrying a_t across.  delta_t needs V(x_{t+1}) only,
@@ -361,10 +486,13 @@ static int run_kl(const char* who, const float* logits_original, const float* lo
     hipStream_t s = (hipStream_t)hip_stream;
     const int64_t n_tiles = (B + 63) / 64;
     const int64_t want = (n_tiles + MON_WAVES - 1) / MON_WAVES;
-    const int blocks = (int)(want < max_parts ? want : max_parts);
+    const bool small = A <= ROW_AMAX;
+    const int most = small ? (max_parts < ROW_BLOCKS ? max_parts : ROW_BLOCKS) : max_parts;
+    const int blocks = (int)(want < most ? want : most);
     const size_t lds = (size_t)MON_WAVES * 2 * 64 * A * sizeof(float);
-    if (int rc = raise_lds((const void*)kl_rows_kernel, lds)) return rc;
-    kl_rows_kernel<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, B, A, out_kl, out_entropy, parts,
+    const auto rows = small ? kl_rows_small_kernel : kl_rows_kernel;
+    if (int rc = raise_lds((const void*)rows, lds)) return rc;
+    rows<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, B, A, out_kl, out_entropy, parts,
                                                                   v_o, v_s, beta, out_loss);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("kl_rows_kernel", e);
     kl_stats_kernel<<<dim3(1), dim3(MON_FOLD_WAVES * 64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
@@ -404,10 +532,12 @@ extern "C" int accerl_vtrace(const float* logits_original, const float* logits_s
     hipStream_t s = (hipStream_t)hip_stream;
     const int64_t R = T * B, n_tiles = (R + 63) / 64;
     const int64_t want = (n_tiles + MON_WAVES - 1) / MON_WAVES;
-    const int blocks = (int)(want < 2048 ? want : 2048);
+    const int most = A <= ROW_AMAX ? ROW_BLOCKS : 2048;
+    const int blocks = (int)(want < most ? want : most);
     const size_t lds = (size_t)MON_WAVES * 2 * 64 * A * sizeof(float);
-    if (int rc = raise_lds((const void*)is_ratio_kernel, lds)) return rc;
-    is_ratio_kernel<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, actions, R, A, out_rho);
+    const auto rows = A <= ROW_AMAX ? is_ratio_small_kernel : is_ratio_kernel;
+    if (int rc = raise_lds((const void*)rows, lds)) return rc;
+    rows<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, actions, R, A, out_rho);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("is_ratio_kernel", e);
     // runs of 8 steps for long unrolls, of 4 for short ones; as many runs per workgroup as there are (at most VT_NSEG, and an
