@@ -7,6 +7,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "libaccerl.so")
 _lib = None
+torch = None            # set by load_library
 
 INT8, FP32, BF16 = 0, 1, 2
 OBS_U8, OBS_F32 = 0, 1
@@ -33,10 +34,11 @@ class _Arch(C.Structure):
 
 def load_library():
     """Load libaccerl.so (after torch, so that both share one HIP runtime).  No fallback exists."""
-    global _lib
+    global _lib, torch
     if _lib is not None:
         return _lib
-    import torch  # noqa: F401  -- brings in the HIP runtime the library links against
+    import torch as _torch  # brings in the HIP runtime the library links against
+    torch = _torch
     if not os.path.exists(_SO):
         raise ImportError(f"{_SO} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
                           "(or paper_2211_15023_amd/build.py); there is no CPU fallback")
@@ -178,26 +180,26 @@ def accerl_policy_destroy(handle):
     load_library().accerl_policy_destroy(handle)
 
 
+# Marshalling is most of what a small call costs the host (32 states of the 64-unit MLP: 8.8 us between calls with an import
+# statement, a c_void_p and a Stream object per argument, 5.7 without; the kernel takes 2.6): arguments go through as plain
+# integers, which the argtypes convert.
 def _ptr(t, dtype=None):
-    import torch
     if t is None:
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("device tensors must be contiguous CUDA/HIP tensors")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected {dtype}, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def accerl_actor_forward(handle, states, uniforms, out_logits, out_value, out_action, stream=None):
-    import torch
     B = states.shape[0]
     _check(load_library().accerl_actor_forward(handle, _ptr(states), B, _ptr(uniforms, torch.float32),
                                                _ptr(out_logits, torch.float32), _ptr(out_value, torch.float32),
@@ -205,7 +207,6 @@ def accerl_actor_forward(handle, states, uniforms, out_logits, out_value, out_ac
 
 
 def accerl_actor_forward_teacher(handle, states, uniforms, out_logits, out_value, out_action, stream=None):
-    import torch
     B = states.shape[0]
     _check(load_library().accerl_actor_forward_teacher(handle, _ptr(states), B, _ptr(uniforms, torch.float32),
                                                        _ptr(out_logits, torch.float32), _ptr(out_value, torch.float32),
@@ -213,7 +214,6 @@ def accerl_actor_forward_teacher(handle, states, uniforms, out_logits, out_value
 
 
 def accerl_actor_forward_recurrent(handle, states, uniforms, done, h, c, out_logits, out_value, out_action, stream=None):
-    import torch
     B = states.shape[0]
     _check(load_library().accerl_actor_forward_recurrent(
         handle, _ptr(states), B, _ptr(uniforms, torch.float32), _ptr(done, torch.uint8), _ptr(h, torch.float32),
@@ -230,7 +230,6 @@ def accerl_actor_forward_debug(handle, states, layer, tap, out, stream=None):
 def accerl_actor_forward_mixture(smaller, original, states, uniforms, use_smaller, out_logits, out_value, out_action, stream=None):
     """use_smaller: host uint8 array [B] (numpy); the other tensors live on the device."""
     import numpy as np
-    import torch
     B = states.shape[0]
     flags = np.ascontiguousarray(use_smaller, dtype=np.uint8)
     if flags.shape != (B,):
