@@ -855,6 +855,9 @@ int build_plan(Builder& B) {
                 LstmPackParams& lp = pk.lp;
                 lp.x_elem = cur.el; lp.x_scale = cur.scale; lp.x_pitch_bytes = cur.stored * esz; lp.x_relu = cur.relu_pending;
                 lp.In = In; lp.Hd = Hd;
+                // fragment order where the 8-value pieces of both halves are whole and aligned, and the steps come in fours
+                if (In % 8 == 0 && Hd % 8 == 0 && Kx % 128 == 0 && lp.x_pitch_bytes % (cur.el == EL_I8 ? 8 : 16) == 0 && cur.el != EL_F32)
+                    lp.frag_ks = Kx / 32;
                 pk.out_elems = Kx;
                 pol->steps.push_back(pk);
                 const TensorSpec& tih = B.tensor(i, 0);
@@ -876,6 +879,7 @@ int build_plan(Builder& B) {
                 st.o_bias = B.put(bf.data(), bf.size() * 4);
                 GemmParams& gp = st.gp;
                 gp.Kp_bytes = Kx * 2; gp.k_steps = k_steps; gp.N = N; gp.Np = Hd; gp.n_tiles = n_tiles; gp.Hd = Hd;
+                gp.x_frag = lp.frag_ks > 0;
                 st.out_elems = Hd;
                 pol->steps.push_back(st);
                 cur.buf = st.out_buf; cur.el = EL_BF16; cur.shape = P.shapes[i]; cur.relu_pending = false;
