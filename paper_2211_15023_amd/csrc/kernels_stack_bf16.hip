@@ -7,7 +7,7 @@
 // Here a lane is a *column* of the image and walks down it: the fragments of an input row (three reads) serve the output
 // rows above, at and below it, so a row of 16 pixels costs three reads and five (16 channels) or nine (32 channels) MFMAs
 // per 16 output channels.  The three output rows in flight are three independent accumulator chains.  Measured at 1024
-// states: the three stacks 74 / 78 / 40 us where the layer-by-layer kernels took 283 / 163 / 85 us.
+// states: the three stacks 75 / 67 / 32 us where the layer-by-layer kernels took 283 / 163 / 85 us.
 //
 //  * Lanes.  A workgroup of eight wavefronts owns G images.  The lanes of the blocks' tiles are (image, segment of rows,
 //    column) triples: 3 x 42, 3 x 21 and 2 x 2 x 11 of them fill 126 of 128, 63 of 64 and 44 of 48 lanes.  32-channel
@@ -20,6 +20,9 @@
 //    over the two neighbour lanes (DPP).  Rounding to bf16 is monotone, so it follows the maximum.
 //  * The stream is kept un-rectified (the skip connection needs it) and rectified as fragments are read: one packed
 //    16-bit integer maximum per dword, since a negative bf16 is a negative 16-bit integer.
+//  * bf16 inputs go from memory to LDS without passing through registers, a third of the next batch at the start of each of
+//    three phases: loads into registers held their wavefront for 6 000 clocks of 34 000 in a full memory queue and storing
+//    them took another 4 000 (second stack 80 -> 67 us, third 39 -> 32 us at 1024 states).
 //
 // Arithmetic: the planner's weight fragments, the bias in the accumulator and the K steps of every output in the planner's
 // order, so results are bit-identical to the layer-by-layer kernels (conv_kernel.h), which the debug taps still run.  (The
@@ -65,19 +68,19 @@ struct BsShape {
     static constexpr int IPLANE = bs_up(IPB * IROW, 256);
     static constexpr int TILE_IN = U8 ? bs_up((HIN + 3) * IROW, 256) : CI / 8 * IPLANE;
     static constexpr int KS_C = U8 ? 2 : CI == 16 ? 5 : 9, KS_B = C == 16 ? 5 : 9;
-    // staging: 64 units of a wavefront's load are 1 KiB in a row
-    static constexpr int UNITS = U8 ? HIN * HIN / 4 : G * HIN * HIN * CI / 8;
-    static constexpr int PF = (UNITS + THREADS - 1) / THREADS;
+    static constexpr int UNITS = HIN * HIN / 4;                // observations only
+    static constexpr int PF = U8 ? (UNITS + THREADS - 1) / THREADS : 1;
     static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI * 2;
     static constexpr int IMG = H * H * C * 2;
     // conv + pool items: column tiles of seven pooled pixels x row segments x images
     static constexpr int CT = (H + 6) / 7, RP = (H + PSEG - 1) / PSEG, ITEMS = CT * PSEG * G;
     // the inner tensor takes the place of the observation tile, which is dead once it has been pooled
     static constexpr bool OVER = U8;
-    static constexpr int O_IN = G * TILE;
-    static constexpr int O_M = OVER ? O_IN : O_IN + G * TILE_IN;
-    static constexpr int LDS = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);
-    static_assert(C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS <= 160 * 1024, "shape");
+    static constexpr int O_IN = G * TILE, O_M = O_IN;
+    static constexpr int LDS = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);   // dynamic; besides S_IN
+    // bf16 inputs: an LDS array of their own, filled from memory without passing through registers (a load of 64 chunks each)
+    static constexpr int S_IN = OVER ? 16 : G * TILE_IN, NLOAD = (S_IN / 16 + THREADS - 1) / THREADS;
+    static_assert(C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS + S_IN <= 160 * 1024, "shape");
 };
 
 __device__ __forceinline__ v4f bs_mfma(v4i a, v4i b, v4f c) {
@@ -135,7 +138,8 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     constexpr int T = S::THREADS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* tX = smem;                                     // G bordered tiles of the stream
-    char* tin = smem + S::O_IN;                          // G bordered input tiles
+    __shared__ __attribute__((aligned(16))) char s_in[S::S_IN];
+    char* tin = S::OVER ? smem + S::O_IN : s_in;         // G bordered input tiles
     char* tM = smem + S::O_M;                            // G bordered tiles of a block's inner tensor
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -143,71 +147,79 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     const int half = wave % S::NH, tile = wave / S::NH;  // which 16 output channels, which tile
     constexpr int NH = S::NH;
 
-    // ---- staging: unit u of a batch is 16 bytes of bf16 pixels, or one dword of each of the four planes
+    // ---- staging of observations: unit u is one dword of each of the four planes
     v4i pre[S::PF];
-    auto unit_of = [&](int i) -> int {
-        if constexpr (U8) {
-            return tid + i * T;
-        } else {
-            // a wavefront's 64 units in the order (channel block, pixel): its LDS stores then run along a plane
-            constexpr int CB = CI / 8, PX = 64 / CB;
-            return (wave + i * S::NW) * 64 + (lane % PX) * CB + lane / PX;
-        }
-    };
     auto prefetch = [&](int64_t batch) {
-        const int64_t b0 = batch * G;
-        const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
-        const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
-        const int last = (U8 ? S::UNITS : gc * (S::UNITS / G)) - 1;
+        const char* src = (const char*)p.in + batch * (int64_t)S::IMG_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
-            const int u = min(unit_of(i), last);         // a unit that does not exist re-reads the last one
-            if constexpr (U8) {
+            const int u = min(tid + i * T, S::UNITS - 1);    // a unit that does not exist re-reads the last one
 #pragma unroll
-                for (int c = 0; c < 4; ++c) pre[i][c] = *(const int*)(src + (uint32_t)(c * HIN * HIN + 4 * u));
-            } else {
-                pre[i] = *(const v4i*)(src + (uint32_t)u * 16u);
-            }
+            for (int c = 0; c < 4; ++c) pre[i][c] = *(const int*)(src + (uint32_t)(c * HIN * HIN + 4 * u));
         }
     };
     auto commit = [&]() {
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
-            const int u = unit_of(i);
-            if (u >= S::UNITS) continue;                 // (units of an image past the batch: never read by a stored result)
-            if constexpr (U8) {
-                constexpr int RU = HIN / 4;
-                const int row = u / RU, cu = u - row * RU;
-                typedef float v2f __attribute__((ext_vector_type(2)));
-                typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-                const float k255 = 1.0f / 255.0f;        // bf16(v / 255) = bf16(v * (1 / 255)): checked for all 256 values
-                char* d = tin + (row + 1) * S::IROW + (1 + 4 * cu) * 8;
+            const int u = tid + i * T;
+            if (u >= S::UNITS) continue;
+            constexpr int RU = HIN / 4;
+            const int row = u / RU, cu = u - row * RU;
+            typedef float v2f __attribute__((ext_vector_type(2)));
+            typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+            const float k255 = 1.0f / 255.0f;            // bf16(v / 255) = bf16(v * (1 / 255)): checked for all 256 values
+            char* d = tin + (row + 1) * S::IROW + (1 + 4 * cu) * 8;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const v2f lo = {(float)((pre[i][0] >> (8 * e)) & 0xff) * k255, (float)((pre[i][1] >> (8 * e)) & 0xff) * k255};
-                    const v2f hi = {(float)((pre[i][2] >> (8 * e)) & 0xff) * k255, (float)((pre[i][3] >> (8 * e)) & 0xff) * k255};
-                    *(v2i*)(d + 8 * e) = (v2i){__builtin_bit_cast(int, __builtin_convertvector(lo, v2bf)),
-                                               __builtin_bit_cast(int, __builtin_convertvector(hi, v2bf))};
-                }
-            } else {
-                constexpr int CB = CI / 8;
-                const int px = u / CB, cb = u - px * CB;
-                const int img = px / (HIN * HIN), w = px - img * HIN * HIN, row = w / HIN, col = w - row * HIN;
-                *(v4i*)(tin + img * S::TILE_IN + cb * S::IPLANE + (row + 1) * S::IROW + (col + 1) * 16) = pre[i];
+            for (int e = 0; e < 4; ++e) {
+                const v2f lo = {(float)((pre[i][0] >> (8 * e)) & 0xff) * k255, (float)((pre[i][1] >> (8 * e)) & 0xff) * k255};
+                const v2f hi = {(float)((pre[i][2] >> (8 * e)) & 0xff) * k255, (float)((pre[i][3] >> (8 * e)) & 0xff) * k255};
+                *(v2i*)(d + 8 * e) = (v2i){__builtin_bit_cast(int, __builtin_convertvector(lo, v2bf)),
+                                           __builtin_bit_cast(int, __builtin_convertvector(hi, v2bf))};
             }
         }
-        if constexpr (S::OVER) {                         // the border of the observation tile: three rows, two columns
-            for (int i = tid; i < 3 * S::IPB; i += T) {
-                const int rr = i / S::IPB;
-                *(v2i*)(tin + (rr ? HIN + rr : 0) * S::IROW + (i - rr * S::IPB) * 8) = (v2i){0, 0};
+        for (int i = tid; i < 3 * S::IPB; i += T) {      // the border of the observation tile: three rows, two columns
+            const int rr = i / S::IPB;
+            *(v2i*)(tin + (rr ? HIN + rr : 0) * S::IROW + (i - rr * S::IPB) * 8) = (v2i){0, 0};
+        }
+        for (int i = tid; i < 2 * HIN; i += T) *(v2i*)(tin + (1 + (i >> 1)) * S::IROW + (i & 1) * (HIN + 1) * 8) = (v2i){0, 0};
+    };
+    // ---- staging of bf16 inputs: memory to the planes of s_in directly.  Chunk (wave + NW * i) * 64 + l of s_in comes from
+    //      source(i, l) of the batch or, at borders and padding, from nowhere (they stay zero).
+    auto source = [&](int i, int l) -> int {
+        const int q = (wave + i * S::NW) * 64 + l;
+        const int im = q / (S::TILE_IN / 16), r1 = q - im * (S::TILE_IN / 16), cb = r1 / (S::IPLANE / 16), r2 = r1 - cb * (S::IPLANE / 16);
+        const int row = r2 / S::IPB, col = r2 - row * S::IPB;
+        return im < G && row >= 1 && row <= HIN && col >= 1 && col <= HIN ? im * S::IMG_IN + ((row - 1) * HIN + col - 1) * (CI * 2) + cb * 16 : -1;
+    };
+    auto fetch = [&](int64_t batch, int i0, int i1) {
+        if constexpr (!U8) {
+            const int64_t b0 = batch * G;
+            const int lim = (int)min(p.B - b0, (int64_t)G) * S::IMG_IN;      // images past the batch: not fetched, never stored
+            const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
+            int l = lane;
+            asm volatile("" : "+v"(l));                  // worked out anew for every batch: registers are short
+#pragma unroll
+            for (int i = i0; i < i1; ++i) {
+                const int at = i < S::NLOAD ? source(i, l) : -1;
+                if (at >= 0 && at < lim)
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (uint32_t)at),
+                                                     (__attribute__((address_space(3))) void*)(s_in + (wave + i * S::NW) * 1024), 16, 0, 0);
             }
-            for (int i = tid; i < 2 * HIN; i += T) *(v2i*)(tin + (1 + (i >> 1)) * S::IROW + (i & 1) * (HIN + 1) * 8) = (v2i){0, 0};
         }
     };
+    if constexpr (!U8) {
+        for (int i = 0; i < S::NLOAD; ++i) {
+            const int q = (wave + i * S::NW) * 64 + lane;
+            if (source(i, lane) < 0 && q < S::S_IN / 16) ((v4i*)s_in)[q] = (v4i){0, 0, 0, 0};
+        }
+    }
 
     const int64_t n_batch = (p.B + G - 1) / G;
     int64_t batch = blockIdx.x;
-    if (batch < n_batch) prefetch(batch);
+    if (batch < n_batch) {
+        if constexpr (U8) prefetch(batch);
+        else fetch(batch, 0, S::NLOAD);
+    }
 
     // ---- weights of all five convolutions, in registers for the whole kernel
     v4i wC[S::KS_C], wA1[S::KS_B], wB1[S::KS_B], wA2[S::KS_B], wB2[S::KS_B];
@@ -245,7 +257,8 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     __syncthreads();
 
     for (; batch < n_batch; batch += gridDim.x) {
-        commit();
+        if constexpr (U8) commit();
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this wavefront's part of the input is in LDS
         __syncthreads();
         const int64_t b0 = batch * G;
         const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
@@ -385,13 +398,20 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                 else *(v2i*)(tX + own + k * S::ROWB) = bs_pack(y);
             });
         };
+        // the next batch's input, a third of the loads at a time: the memory queue of a compute unit holds a wavefront that
+        // issues into it when it is full
+        const int64_t next = batch + gridDim.x;
+        constexpr int N3 = (S::NLOAD + 2) / 3;
+        if (next < n_batch) fetch(next, 0, N3);
         conv_a(wA1, bias[1]);
         __syncthreads();
+        if (next < n_batch) fetch(next, N3, 2 * N3);
         conv_b(wB1, bias[2], std::false_type{});
         __syncthreads();
+        if (next < n_batch) fetch(next, 2 * N3, S::NLOAD);
         conv_a(wA2, bias[3]);
         __syncthreads();
-        if (batch + gridDim.x < n_batch) prefetch(batch + gridDim.x);
+        if constexpr (U8) { if (next < n_batch) prefetch(next); }
         conv_b(wB2, bias[4], std::true_type{});
         // the observation tile takes the inner tensor's place; otherwise the barrier behind the next commit is enough
         if constexpr (S::OVER) __syncthreads();
