@@ -7,7 +7,7 @@
 // Here a lane is a *column* of the image and walks down it: the fragments of an input row (three reads) serve the output
 // rows above, at and below it, so a row of 16 pixels costs three reads and five (16 channels) or nine (32 channels) MFMAs
 // per 16 output channels.  The three output rows in flight are three independent accumulator chains.  Measured at 1024
-// states: the three stacks 75 / 67 / 32 us where the layer-by-layer kernels took 283 / 163 / 85 us.
+// states: the three stacks 72 / 67 / 32 us where the layer-by-layer kernels took 283 / 163 / 85 us.
 //
 //  * Lanes.  A workgroup of eight wavefronts owns G images.  The lanes of the blocks' tiles are (image, segment of rows,
 //    column) triples: 3 x 42, 3 x 21 and 2 x 2 x 11 of them fill 126 of 128, 63 of 64 and 44 of 48 lanes.  32-channel
@@ -15,7 +15,9 @@
 //    convolutions (4 x 36 registers) for the whole kernel.
 //  * LDS layout.  Planes of eight channels, [channel block][row][column][16 B]: the 16 lanes of a K group read 256
 //    consecutive bytes, and planes a multiple of 256 bytes apart keep the four groups of a read off each other's banks.
-//  * Convolution + pooling.  Lanes are convolution columns 14 t - 1 .. 14 t + 14 (seven pooled pixels); the vertical
+//  * Convolution + pooling.  First stack: lanes are pooled pixels, the even and the odd column under each two sets of
+//    accumulators (74 -> 71 us against seven pooled pixels per tile, which took twice the vector instructions per pixel).
+//    Others: lanes are convolution columns 14 t - 1 .. 14 t + 14 (seven pooled pixels).  The vertical
 //    maximum runs over the rows as they are produced (row 2 py + 1 is kept for the next pooled row), the horizontal one
 //    over the two neighbour lanes (DPP).  Rounding to bf16 is monotone, so it follows the maximum.
 //  * The stream is kept un-rectified (the skip connection needs it) and rectified as fragments are read: one packed
@@ -72,8 +74,8 @@ struct BsShape {
     static constexpr int PF = U8 ? (UNITS + THREADS - 1) / THREADS : 1;
     static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI * 2;
     static constexpr int IMG = H * H * C * 2;
-    // conv + pool items: column tiles of seven pooled pixels x row segments x images
-    static constexpr int CT = (H + 6) / 7, RP = (H + PSEG - 1) / PSEG, ITEMS = CT * PSEG * G;
+    // conv + pool items: column tiles of pooled pixels (14 of observations, else seven) x row segments x images
+    static constexpr int CT = U8 ? (H + 13) / 14 : (H + 6) / 7, RP = (H + PSEG - 1) / PSEG, ITEMS = CT * PSEG * G;
     // the inner tensor takes the place of the observation tile, which is dead once it has been pooled
     static constexpr bool OVER = U8;
     static constexpr int O_IN = G * TILE, O_M = O_IN;
@@ -267,36 +269,54 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
         for (int it = tile; it < S::ITEMS; it += S::TW) {
             const int im = it / (S::CT * PSEG), ps = (it - im * S::CT * PSEG) % PSEG, ct = (it - im * S::CT * PSEG) / PSEG;
             const int p0 = min(ps * S::RP, S::H - S::RP);        // segments may overlap: the same bytes twice
-            const int x = min(max(14 * ct - 1 + j, 0), HIN - 1);  // columns outside repeat the outermost one
-            const int px = 7 * ct + (j >> 1);
-            const bool st_ok = (j & 1) && j < 14 && px < S::H;
-            char* dst = tX + im * S::TILE + (p0 + 1) * S::ROWB + (px + 1) * 16
-                        + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
-            auto store = [&](int k, v4f v) {
-                v4f m;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) m[r] = bs_max_neighbours(v[r]);
-                if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+            auto dst_of = [&](int px) {
+                return tX + im * S::TILE + (p0 + 1) * S::ROWB + (px + 1) * 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
             };
-            v4f carry = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            const v4f none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             if constexpr (U8) {
+                // Lanes are pooled pixels 14 ct - 1 .. 14 ct + 14 with the even and the odd column (E, O) as two sets of
+                // accumulators; the left neighbour's O completes the window, so the first lane only serves its neighbour.
+                // (Columns outside the image repeat one of the same window.)
+                const int px = 14 * ct - 1 + j, pc = min(max(px, 0), S::H - 1);
+                const bool st_ok = j >= 1 && j <= 14 && px < S::H;
+                char* dst = dst_of(px);
                 // window rows y, y + 1 in the two halves of a fragment: F(y) is step 0 of conv row y and step 1 of row y - 2
-                const char* a = tin + (2 * p0 + (g >> 1)) * S::IROW + x * 8 + (g & 1) * 16;
-                v4i f0 = read_chunk<8>(a), f1 = read_chunk<8>(a + S::IROW);
-                if (p0 > 0) carry = bs_mfma(wC[1], f1, bs_mfma(wC[0], read_chunk<8>(a - S::IROW), bias[0]));
+                const char* a = tin + (2 * p0 + (g >> 1)) * S::IROW + 2 * pc * 8 + (g & 1) * 16;
+                auto even = [&](int row) { return *(const v4i*)(a + row * S::IROW); };
+                auto odd = [&](int row) { return read_chunk<8>(a + row * S::IROW + 8); };
+                static_assert(S::IROW % 16 == 0 && HIN % 2 == 0, "whole chunks under even columns");
+                auto conv = [&](v4i lo, v4i hi) { return bs_mfma(wC[1], hi, bs_mfma(wC[0], lo, bias[0])); };
+                v4i e0 = even(0), e1 = even(1), o0 = odd(0), o1 = odd(1);
+                v4f carryE = none, carryO = none;
+                if (p0 > 0) { carryE = conv(even(-1), e1); carryO = conv(odd(-1), o1); }
 #pragma unroll
                 for (int k = 0; k < S::RP; ++k) {
-                    const v4i f2 = read_chunk<8>(a + (2 * k + 2) * S::IROW), f3 = read_chunk<8>(a + (2 * k + 3) * S::IROW);
-                    const v4f c0 = bs_mfma(wC[1], f2, bs_mfma(wC[0], f0, bias[0]));
-                    const v4f c1 = bs_mfma(wC[1], f3, bs_mfma(wC[0], f1, bias[0]));
-                    v4f v;
+                    const v4i e2 = even(2 * k + 2), e3 = even(2 * k + 3), o2 = odd(2 * k + 2), o3 = odd(2 * k + 3);
+                    const v4f cE0 = conv(e0, e2), cO0 = conv(o0, o2), cE1 = conv(e1, e3), cO1 = conv(o1, o3);
+                    v4f m;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = bs_max3(carry[r], c0[r], c1[r]);
-                    carry = c1;
-                    store(k, v);
-                    f0 = f2; f1 = f3;
+                    for (int r = 0; r < 4; ++r) {
+                        const float vO = bs_max3(carryO[r], cO0[r], cO1[r]);
+                        const int i = __float_as_int(vO);
+                        const float left = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false));
+                        m[r] = bs_max3(bs_max3(carryE[r], cE0[r], cE1[r]), vO, left);
+                    }
+                    if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+                    carryE = cE1; carryO = cO1;
+                    e0 = e2; e1 = e3; o0 = o2; o1 = o3;
                 }
             } else {
+                const int x = min(max(14 * ct - 1 + j, 0), HIN - 1);  // columns outside repeat the outermost one
+                const int px = 7 * ct + (j >> 1);
+                const bool st_ok = (j & 1) && j < 14 && px < S::H;
+                char* dst = dst_of(px);
+                auto store = [&](int k, v4f v) {
+                    v4f m;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) m[r] = bs_max_neighbours(v[r]);
+                    if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+                };
+                v4f carry = none;
                 const int base = im * S::TILE_IN + 2 * p0 * S::IROW + x * 16;
                 const char* a = tin + base + (CI == 16 ? (g & 1) * S::IPLANE + (g >> 1) * 16 : g * S::IPLANE);
                 const char* m = tin + base + (g & 1) * S::IPLANE + (g < 2 ? 32 - S::IROW : 0);
@@ -447,7 +467,7 @@ hipError_t bs_go(const BStackParams& p, hipStream_t s) {
 }  // namespace
 
 // (uint8 source, input channels, input size, channels, images per batch, row segments of the blocks' and of the pool's lanes)
-#define ACCERL_BSTACK_SHAPES(X) X(true, 4, 84, 16, 1, 3, 4) X(false, 16, 42, 32, 1, 3, 4) X(false, 32, 21, 32, 2, 2, 1)
+#define ACCERL_BSTACK_SHAPES(X) X(true, 4, 84, 16, 1, 3, 5) X(false, 16, 42, 32, 1, 3, 4) X(false, 32, 21, 32, 2, 2, 1)
 
 bool stack_bf16_supported(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2) {
 #define X(U8, CI, HIN, C, G, SEG, PSEG) if (bs_shape_ok<U8, CI, HIN, C, G, SEG, PSEG>(c, a1, b1, a2, b2)) return true;

@@ -1,0 +1,47 @@
+"""The bf16 kernels of the paper's original network's convolutions (first two in one launch; third with fixed sizes, storing
+the FC's fragment order) against the generic kernels, which run in a child process: the same bits, at the batch sizes where
+the work split changes (one observation, an odd image beside an empty slot, a partly filled tile of 16 states, a second and
+an uneven third round of the resident workgroups)."""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from helpers import policies, teacher_tensors
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+BATCHES = [1, 3, 17, 257, 700]
+
+
+def _forwards(path=None):
+    import paper_2211_15023_amd as A
+    nt, pt, ns, ps, qp = policies(2)
+    pol = A.Policy(nt, "bf16", teacher_tensors(pt))
+    plan = A.accerl_plan_describe(pol.arch, A.pack_weights(teacher_tensors(pt)))
+    x, u = torch.from_numpy(wl.make_frames_u8(max(BATCHES), first=5)).cuda(), torch.from_numpy(wl.make_uniforms(max(BATCHES))).cuda()
+    out = {}
+    for B in BATCHES:
+        print(f"bf16 teacher B={B}", flush=True)
+        out[str(B)] = pol.forward(x[:B], u[:B])[0].cpu().numpy()
+    if path:
+        np.savez(path, fused=int("fuse_next=1" in plan or "out_frag=1" in plan), **out)
+    return plan, out
+
+
+def test_bf16_convolutions_give_the_generic_bits(tmp_path):
+    path = str(tmp_path / "generic.npz")
+    code = f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]; import test_gpu_conv_bf16 as t; t._forwards({path!r})"
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, ACCERL_NO_CONV_FRONT="1", ACCERL_NO_CONV_TAIL="1"),
+                       capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr[-2000:]
+    generic = np.load(path)
+    assert not generic["fused"]
+    plan, got = _forwards()
+    assert plan.count("fuse_next=1 front=1") == 1 and plan.count("tail=1 out_frag=1") == 1
+    for B in BATCHES:
+        assert np.array_equal(got[str(B)], generic[str(B)]), B
