@@ -146,7 +146,8 @@ __global__ __launch_bounds__(MON_WAVES * 64) void kl_rows_kernel(const float* __
 // instructions: with the row walked in LDS at a run-time length they issued about 35 per action (rotation, bounds, addresses)
 // and loaded a tile only after the one before was done.  Here the next tile is in flight while a lane works on its two rows in
 // registers, every access at a fixed offset.  256 x 4096 rows of 18 actions: KL 37 -> 31 us, ratio 34 -> 29 us
-// (151 MB).
+// (151 MB).  Wider tables keep the walk in LDS: two rows of 64 values and the tile in flight do not fit a lane's registers at
+// four wavefronts per SIMD.
 constexpr int ROW_AMAX = 20;
 constexpr int ROW_BLOCKS = 1024;    // four workgroups per compute unit, each wavefront walking its tiles
 struct RowTile { v4f o[ROW_AMAX / 4], s[ROW_AMAX / 4]; float tail_o, tail_s; };   // a lane's share of 64 rows of both tables
