@@ -58,6 +58,7 @@ struct ConvParams {
     const void* bias;        // int32 (int8 path, zero-point correction folded in) or fp32, [NT*16]
     const float* mult;       // [NT*16] (int8 path)
     const uint16_t* lut;     // 256 bf16 values obs/255 (bf16 path with uint8 source)
+    const int32_t* rows;     // bf16 front kernel: observation i is row rows[i] of `in` (NULL = row i)
     int64_t B;
     int H, W;                // input image
     int Cin_real;            // channels present in the source
@@ -146,8 +147,9 @@ hipError_t launch_maxpool(const void* in, void* out, int64_t B, int H, int W, in
                           int k, int s, int pad, Elem el, hipStream_t stream);
 
 // ---------------------------------------------------------------- row gather / scatter (policy mixture)
-hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t row_bytes,
-                             void* out, float* out_uniforms, hipStream_t s);
+// rows [first, last) of the list are copied, the uniforms of all of them
+hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t first, int64_t last,
+                             int64_t row_bytes, void* out, float* out_uniforms, hipStream_t s);
 hipError_t launch_scatter_mix(const float* logits, const float* value, const int32_t* action, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int A,
                               float* out_logits, float* out_value, int32_t* out_action, hipStream_t s);
 

@@ -965,6 +965,7 @@ int ensure_workspace(accerl_policy* p, int64_t n, int layout, hipStream_t stream
 struct Call {
     const void* states; int64_t B; const float* uniforms; const uint8_t* done; float* h; float* c;
     float* logits; float* value; int32_t* action; hipStream_t stream;
+    const int32_t* rows = nullptr;   // state i is row rows[i] of `states` (policies that reads_rows allows only)
     // debug
     bool debug = false; int layer = 0, tap = 0; void* out = nullptr; int64_t out_bytes = 0;
 };
@@ -985,6 +986,12 @@ int find_tap_step(const accerl_policy* p, int layer, int tap, bool& is_acc) {
         found = i;
     }
     return found;
+}
+
+// the first launch reads its observations through a row list: a gathered copy is not needed
+bool reads_rows(const accerl_policy* p) {
+    const Step& s = p->steps[0];
+    return s.kind == ST_CONV && s.el == EL_BF16 && s.fuse_next && !s.resblock && s.in_buf < 0;
 }
 
 int run(accerl_policy* p, const Call& c) {
@@ -1030,7 +1037,7 @@ int run(accerl_policy* p, const Call& c) {
     }
     for (int64_t c0 = 0; c0 < c.B; c0 += chunk) {
         const int64_t n = (c.B - c0 < chunk) ? (c.B - c0) : chunk;
-        const char* states = (const char*)c.states + c0 * p->obs_bytes;
+        const char* states = (const char*)c.states + (c.rows ? 0 : c0 * p->obs_bytes);
         float* logits = c.logits ? c.logits + c0 * A : nullptr;
         float* value = c.value ? c.value + c0 : nullptr;
         int32_t* action = c.action ? c.action + c0 : nullptr;
@@ -1097,6 +1104,7 @@ int run(accerl_policy* p, const Call& c) {
                         const Step& nx = p->steps[si + 1];
                         ConvParams ca = s.cp, cb = nx.cp;
                         ca.in = bufp(s.in_buf); ca.out = nullptr; ca.res = nullptr; ca.tap_acc = nullptr;
+                        ca.rows = c.rows && s.in_buf < 0 ? c.rows + c0 : nullptr;
                         ca.wfrag = p->consts + s.o_w; ca.bias = p->consts + s.o_bias; ca.mult = s.o_mult >= 0 ? (const float*)(p->consts + s.o_mult) : nullptr;
                         ca.B = n;
                         cb.in = nullptr; cb.out = bufp(nx.out_buf); cb.res = nullptr; cb.tap_acc = nullptr;
@@ -1596,11 +1604,16 @@ int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original
     const int64_t o2 = (ns + 3) & ~(int64_t)3;   // keeps every buffer of the second subset 16-byte aligned
     HIP_TRY(hipMemcpyAsync(d_idx, pin, (size_t)B * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(m->mix_ev[slot], st));
-    HIP_TRY(launch_gather_mix(states, uniforms, d_idx, B, ns, o2, obs, d_states, d_uni, st));
-    Call cs{d_states, ns, d_uni, nullptr, nullptr, nullptr, d_logits, d_value, d_action, st};
+    // a policy whose first kernel reads through the row list takes its rows where they are
+    const bool in_place_s = reads_rows(smaller), in_place_o = reads_rows(original);
+    const int64_t first = in_place_s ? ns : 0, last = std::max(first, in_place_o ? ns : B);
+    HIP_TRY(launch_gather_mix(states, uniforms, d_idx, B, ns, o2, first, last, obs, d_states, d_uni, st));
+    Call cs{in_place_s ? states : d_states, ns, d_uni, nullptr, nullptr, nullptr, d_logits, d_value, d_action, st};
+    if (in_place_s) cs.rows = d_idx;
     rc = run(smaller, cs);
     if (rc) return rc;
-    Call co{d_states + o2 * obs, no, d_uni + o2, nullptr, nullptr, nullptr, d_logits + o2 * A, d_value + o2, d_action + o2, st};
+    Call co{in_place_o ? states : d_states + o2 * obs, no, d_uni + o2, nullptr, nullptr, nullptr, d_logits + o2 * A, d_value + o2, d_action + o2, st};
+    if (in_place_o) co.rows = d_idx + ns;
     rc = run(original, co);
     if (rc) return rc;
     HIP_TRY(launch_scatter_mix(d_logits, d_value, d_action, d_idx, B, ns, o2, A, out_logits, out_value, out_action, st));

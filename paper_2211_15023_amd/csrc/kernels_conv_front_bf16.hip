@@ -46,6 +46,7 @@ constexpr int FB_NPIX2 = 81, FB_PIX2_BYTES = 128;
 
 struct FrontBParams {
     const uint8_t* obs;      // [B, 4, 84, 84]
+    const int32_t* rows;     // observation i is row rows[i] of obs (NULL = row i)
     char* out;               // bf16 [B, 9, 9, 64]
     const v4i* wA; const float* biasA;
     const v4i* wB; const float* biasB;
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(FB_THREADS, 2) void conv_front_bf16_kernel(const Fr
     // wavefronts convert their share.
     __shared__ __attribute__((aligned(16))) uint8_t raw[FB_RAW];
     auto fetch = [&](int64_t im) {
-        const uint8_t* src = p.obs + im * (int64_t)(4 * FB_PLANE_IN);
+        const uint8_t* src = p.obs + (p.rows ? (int64_t)p.rows[im] : im) * (int64_t)(4 * FB_PLANE_IN);
 #pragma unroll
         for (int k = 0; k < FB_RAW / 4096; ++k) {
             const uint32_t at = (wave + 4 * k) * 1024;
@@ -317,7 +318,7 @@ hipError_t launch_conv_front_bf16(const ConvParams& a, const ConvParams& b, hipS
         set = true;
     }
     FrontBParams p;
-    p.obs = (const uint8_t*)a.in; p.out = (char*)b.out;
+    p.obs = (const uint8_t*)a.in; p.rows = a.rows; p.out = (char*)b.out;
     p.wA = (const v4i*)a.wfrag; p.biasA = (const float*)a.bias;
     p.wB = (const v4i*)b.wfrag; p.biasB = (const float*)b.bias;
     p.B = a.B;

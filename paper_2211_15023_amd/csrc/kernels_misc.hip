@@ -355,14 +355,21 @@ hipError_t launch_lstm_pack(const LstmPackParams& p, hipStream_t s) {
 // ------------------------------------------------------------------ row gather / scatter (policy mixture)
 // Compacted row i (of n) is row idx[i] of the batch; the first n0 rows are the first subset, the others start at row `second` of
 // the compacted buffers.  One launch serves both subsets and the uniforms: four launches took 13 us for 1000 rows of 28 KB,
-// most of it start-up (now 9).
+// most of it start-up (now 9; 6 when half of them are read in place).  Workgroups past the `last - first` copied rows take
+// 256 uniforms each.
 __global__ __launch_bounds__(256) void gather_mix_kernel(const char* __restrict__ in, const float* __restrict__ uni, const int32_t* __restrict__ idx,
-                                                         int64_t n0, int64_t second, int row_units, char* __restrict__ out, float* __restrict__ out_uni) {
-    const int64_t i = blockIdx.x, r = idx[i], o = i < n0 ? i : second + (i - n0);
-    const v4i* src = (const v4i*)in + r * row_units;
-    v4i* dst = (v4i*)out + o * row_units;
-    for (int u = threadIdx.x; u < row_units; u += 256) dst[u] = src[u];
-    if (threadIdx.x == 0) out_uni[o] = uni[r];
+                                                         int64_t n, int64_t n0, int64_t second, int64_t first, int64_t last, int row_units,
+                                                         char* __restrict__ out, float* __restrict__ out_uni) {
+    auto place = [&](int64_t i) { return i < n0 ? i : second + (i - n0); };
+    if (blockIdx.x < last - first) {
+        const int64_t i = first + blockIdx.x;
+        const v4i* src = (const v4i*)in + (int64_t)idx[i] * row_units;
+        v4i* dst = (v4i*)out + place(i) * row_units;
+        for (int u = threadIdx.x; u < row_units; u += 256) dst[u] = src[u];
+    } else {
+        const int64_t i = (blockIdx.x - (last - first)) * 256 + threadIdx.x;
+        if (i < n) out_uni[place(i)] = uni[idx[i]];
+    }
 }
 
 // Results of both compacted forwards back to their rows, a lane per number (a lane per row walked its A logits alone: two
@@ -380,11 +387,12 @@ __global__ __launch_bounds__(256) void scatter_mix_kernel(const float* __restric
     else out_action[r] = action[o];
 }
 
-hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t row_bytes,
-                             void* out, float* out_uniforms, hipStream_t s) {
+hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t first, int64_t last,
+                             int64_t row_bytes, void* out, float* out_uniforms, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    if (row_bytes % 16) return hipErrorInvalidValue;
-    gather_mix_kernel<<<dim3((unsigned)n), dim3(256), 0, s>>>((const char*)in, uniforms, idx, n0, second, (int)(row_bytes / 16), (char*)out, out_uniforms);
+    if (row_bytes % 16 || first < 0 || last < first || last > n) return hipErrorInvalidValue;
+    gather_mix_kernel<<<dim3((unsigned)(last - first + (n + 255) / 256)), dim3(256), 0, s>>>((const char*)in, uniforms, idx, n, n0, second, first, last,
+                                                                                             (int)(row_bytes / 16), (char*)out, out_uniforms);
     return hipGetLastError();
 }
 hipError_t launch_scatter_mix(const float* logits, const float* value, const int32_t* action, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int A,

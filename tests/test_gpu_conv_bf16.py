@@ -45,3 +45,21 @@ def test_bf16_convolutions_give_the_generic_bits(tmp_path):
     assert plan.count("fuse_next=1 front=1") == 1 and plan.count("tail=1 out_frag=1") == 1
     for B in BATCHES:
         assert np.array_equal(got[str(B)], generic[str(B)]), B
+
+
+@pytest.mark.parametrize("B,alpha", [(5, 0.5), (600, 0.4)])
+def test_mixture_reads_rows_in_place(B, alpha):
+    """Both policies of the mixture are bf16 networks of that shape, so neither's rows are gathered: every row holds what its
+    policy's plain forward computes, bit for bit."""
+    import paper_2211_15023_amd as A
+    nt, pt, ns, ps, qp = policies(2)
+    first = A.Policy(nt, "bf16", teacher_tensors(pt))
+    other = A.Policy(nt, "bf16", teacher_tensors(wl.init_params(nt, wl.STREAM["weights_student"])))
+    x, u = torch.from_numpy(wl.make_frames_u8(B, first=9)).cuda(), torch.from_numpy(wl.make_uniforms(B)).cuda()
+    use = (wl.uniform01(wl.BASE_SEED, 43, 0, B) < np.float32(alpha)).astype(np.uint8)
+    out = first.alloc_outputs(B)
+    print(f"mixture of two bf16 networks, B={B}", flush=True)
+    A.accerl_actor_forward_mixture(first.handle, other.handle, x, u, use, *out)
+    m = torch.from_numpy(use.astype(bool)).cuda()
+    for got, a, b in zip(out, first.forward(x, u), other.forward(x, u)):
+        assert torch.equal(got[m], a[m]) and torch.equal(got[~m], b[~m])
