@@ -11,6 +11,9 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
+// most work-items of one dimension of a launch; what may need more is launched in pieces
+constexpr int64_t MAX_LAUNCH_ITEMS = 0xffffffffll;
+
 enum Elem : int { EL_I8 = 0, EL_BF16 = 1, EL_F32 = 2 };
 
 // records the thread's error message and returns `code`

@@ -13,6 +13,8 @@
 // per product (half that rate at best), read LDS once per eight products and needed four launches: 24-256-256-4 at 8192
 // states 84.5 -> 15.5 us per call (77 TFLOP/s; 7.6 us at the matrix rate, the rest is launch, the first weights and the
 // heads); error against float64 3.0e-7 -> 2.3e-7 (2-norm).
+#include <algorithm>
+
 #include "accerl_internal.h"
 
 namespace accerl {
@@ -169,10 +171,18 @@ __global__ __launch_bounds__(256, 2) void mlp_f32_kernel(const MlpF32Params p) {
     }
 }
 
+// one launch takes 2^29 states less 32 (with 32 of them per workgroup); a larger batch goes out in pieces
 template <int NT, int ST>
-hipError_t go(const MlpF32Params& p, hipStream_t s) {
-    mlp_f32_kernel<NT, ST><<<dim3((unsigned)((p.B + 16 * ST - 1) / (16 * ST))), dim3(256), 0, s>>>(p);
-    return hipGetLastError();
+hipError_t go(MlpF32Params p, hipStream_t s) {
+    constexpr int64_t most = MAX_LAUNCH_ITEMS / 256 * (16 * ST);
+    for (int64_t left = p.B; left > 0; left -= most) {
+        p.B = std::min(left, most);
+        mlp_f32_kernel<NT, ST><<<dim3((unsigned)((p.B + 16 * ST - 1) / (16 * ST))), dim3(256), 0, s>>>(p);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+        p.obs += p.B * p.D; p.uniforms += p.B;
+        p.logits += p.B * p.A; p.value += p.B; p.action += p.B;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

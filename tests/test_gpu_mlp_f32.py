@@ -57,3 +57,24 @@ def test_infinite_observations_stay_in_their_units():
     logits, value, _ = Amd.Policy(net, "fp32", tensors).forward(torch.from_numpy(x).cuda(), torch.zeros(20, device="cuda"))
     logits = logits.cpu().numpy()
     assert np.all(np.isposinf(logits[4])) and np.all(np.delete(logits, 4, 0) == 105.0) and np.isposinf(value[4].item())
+
+
+def test_more_states_than_one_launch_takes():
+    """2^29 + 69 states: workgroups of 256 lanes over 32 states each exceed the work-items of one launch, so the batch goes out
+    in pieces.  The states repeat with a period that divides neither piece: every period must give the bits of the first."""
+    import paper_2211_15023_amd as Amd
+    rng = np.random.default_rng(5)
+    net = SimpleNamespace(name="mlp", obs_dtype="f32", obs_shape=(1,), n_actions=1, layers=[dict(kind="dense", cin=1, cout=8, relu=True)])
+    tensors = [dict(w=rng.uniform(-1, 1, s).astype(np.float32), b=rng.uniform(-1, 1, s[0]).astype(np.float32)) for s in ((8, 1), (2, 8))]
+    pol = Amd.Policy(net, "fp32", tensors)
+    period, B = 5003, (1 << 29) + 69
+    n = B // period
+    base = torch.from_numpy(rng.standard_normal((period, 1)).astype(np.float32)).cuda()
+    x = base.repeat(n + 1, 1)[:B]
+    u = torch.zeros(B, device="cuda")
+    print(f"fp32 mlp B={B}", flush=True)
+    out = pol.forward(x, u)
+    want = pol.forward(base, u[:period])
+    for got, first in zip(out, want):
+        got, first = got.view(-1), first.view(-1)
+        assert bool((got[:n * period].view(n, period) == first).all()) and torch.equal(got[n * period:], first[:B - n * period])
