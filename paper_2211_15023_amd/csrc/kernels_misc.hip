@@ -353,12 +353,12 @@ hipError_t launch_lstm_pack(const LstmPackParams& p, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ row gather / scatter (policy mixture)
-// Compacted row i (of n) is row idx[i] of the batch; the first n0 rows are the first subset, the others start at row `second` of
+// Compacted row i is row idx[i] of the batch; the first n0 rows are the first subset, the others start at row `second` of
 // the compacted buffers.  One launch serves both subsets and the uniforms: four launches took 13 us for 1000 rows of 28 KB,
-// most of it start-up (now 9; 6 when half of them are read in place).  Workgroups past the `last - first` copied rows take
-// 256 uniforms each.
+// most of it start-up (now 9; 6 when half of them are read in place).  Rows [first, last) are copied, a workgroup each; the
+// workgroups past them take 256 of the uniforms [u0, u1) each.
 __global__ __launch_bounds__(256) void gather_mix_kernel(const char* __restrict__ in, const float* __restrict__ uni, const int32_t* __restrict__ idx,
-                                                         int64_t n, int64_t n0, int64_t second, int64_t first, int64_t last, int row_units,
+                                                         int64_t u0, int64_t u1, int64_t n0, int64_t second, int64_t first, int64_t last, int row_units,
                                                          char* __restrict__ out, float* __restrict__ out_uni) {
     auto place = [&](int64_t i) { return i < n0 ? i : second + (i - n0); };
     if (blockIdx.x < last - first) {
@@ -367,39 +367,51 @@ __global__ __launch_bounds__(256) void gather_mix_kernel(const char* __restrict_
         v4i* dst = (v4i*)out + place(i) * row_units;
         for (int u = threadIdx.x; u < row_units; u += 256) dst[u] = src[u];
     } else {
-        const int64_t i = (blockIdx.x - (last - first)) * 256 + threadIdx.x;
-        if (i < n) out_uni[place(i)] = uni[idx[i]];
+        const int64_t i = u0 + (blockIdx.x - (last - first)) * 256 + threadIdx.x;
+        if (i < u1) out_uni[place(i)] = uni[idx[i]];
     }
 }
 
 // Results of both compacted forwards back to their rows, a lane per number (a lane per row walked its A logits alone: two
 // launches of 6 us for 1000 rows; now 2.8).
 __global__ __launch_bounds__(256) void scatter_mix_kernel(const float* __restrict__ logits, const float* __restrict__ value, const int32_t* __restrict__ action,
-                                                          const int32_t* __restrict__ idx, int64_t n, int64_t n0, int64_t second, int A,
+                                                          const int32_t* __restrict__ idx, int64_t i0, int64_t i1, int64_t n0, int64_t second, int A,
                                                           float* __restrict__ out_logits, float* __restrict__ out_value, int32_t* __restrict__ out_action) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t i = t / (A + 2);
-    const int a = (int)(t - i * (A + 2));
-    if (i >= n) return;
+    const int64_t row = t / (A + 2), i = i0 + row;
+    const int a = (int)(t - row * (A + 2));
+    if (i >= i1) return;
     const int64_t r = idx[i], o = i < n0 ? i : second + (i - n0);
     if (a < A) out_logits[r * A + a] = logits[o * A + a];
     else if (a == A) out_value[r] = value[o];
     else out_action[r] = action[o];
 }
 
+// rows per launch: 2^23 workgroups of 256 lanes, or 2^23 rows of up to 66 numbers, stay below MAX_LAUNCH_ITEMS
+constexpr int64_t MIX_ROWS = (int64_t)1 << 23;
+static_assert((MIX_ROWS + MIX_ROWS / 256) * 256 <= MAX_LAUNCH_ITEMS && MIX_ROWS * 66 + 256 <= MAX_LAUNCH_ITEMS, "64 actions, a value and an action");
+
 hipError_t launch_gather_mix(const void* in, const float* uniforms, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int64_t first, int64_t last,
                              int64_t row_bytes, void* out, float* out_uniforms, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
     if (row_bytes % 16 || first < 0 || last < first || last > n) return hipErrorInvalidValue;
-    gather_mix_kernel<<<dim3((unsigned)(last - first + (n + 255) / 256)), dim3(256), 0, s>>>((const char*)in, uniforms, idx, n, n0, second, first, last,
-                                                                                             (int)(row_bytes / 16), (char*)out, out_uniforms);
-    return hipGetLastError();
+    for (int64_t u0 = 0; u0 < n; u0 += MIX_ROWS) {
+        const int64_t u1 = min(n, u0 + MIX_ROWS), f = min(max(first, u0), u1), l = min(max(last, u0), u1);
+        gather_mix_kernel<<<dim3((unsigned)(l - f + (u1 - u0 + 255) / 256)), dim3(256), 0, s>>>((const char*)in, uniforms, idx, u0, u1, n0, second, f, l,
+                                                                                                 (int)(row_bytes / 16), (char*)out, out_uniforms);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 hipError_t launch_scatter_mix(const float* logits, const float* value, const int32_t* action, const int32_t* idx, int64_t n, int64_t n0, int64_t second, int A,
                               float* out_logits, float* out_value, int32_t* out_action, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    scatter_mix_kernel<<<dim3((unsigned)((n * (A + 2) + 255) / 256)), dim3(256), 0, s>>>(logits, value, action, idx, n, n0, second, A, out_logits, out_value, out_action);
-    return hipGetLastError();
+    if (A > 64) return hipErrorInvalidValue;
+    for (int64_t i0 = 0; i0 < n; i0 += MIX_ROWS) {
+        const int64_t i1 = min(n, i0 + MIX_ROWS);
+        scatter_mix_kernel<<<dim3((unsigned)(((i1 - i0) * (A + 2) + 255) / 256)), dim3(256), 0, s>>>(logits, value, action, idx, i0, i1, n0, second, A,
+                                                                                                    out_logits, out_value, out_action);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // ------------------------------------------------------------------ debug conversion

@@ -1,6 +1,8 @@
 """alpha-mixture of the smaller and the original policy (Section 3.2): every row must hold exactly what
 the network chosen for it produces on that row alone — int8 rows bit-exact against the oracle, bf16
 rows within the bf16 tolerance, and equal to the same policy's own forward on the GPU."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -88,3 +90,22 @@ def test_mixture_rejects_mismatched_policies(A):
     with pytest.raises(A.AccerlError):
         A.accerl_actor_forward_mixture(mlp.handle, p3.handle, x, u, np.ones(4, np.uint8), lg, v, a)
     mlp.close(); p3.close()
+
+
+def test_mixture_of_more_rows_than_one_launch_takes(A):
+    """2^24 + 1000 rows of 16 bytes: a workgroup of 256 lanes per copied row exceeds the work-items of one launch, so rows are
+    gathered and scattered in pieces.  Two fp32 MLPs of 4 features; every row against the plain forward of its network."""
+    B, nA = (1 << 24) + 1000, 2
+    net = SimpleNamespace(name="mlp", obs_dtype="f32", obs_shape=(4,), n_actions=nA, layers=[dict(kind="dense", cin=4, cout=8, relu=True)])
+    rng = np.random.default_rng(3)
+    small, orig = (A.Policy(net, "fp32", [dict(w=rng.uniform(-1, 1, s).astype(np.float32), b=rng.uniform(-1, 1, s[0]).astype(np.float32))
+                                          for s in ((8, 4), (nA + 1, 8))]) for _ in range(2))
+    use = (rng.random(B, np.float32) < 0.6).astype(np.uint8)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x, u = torch.randn((B, 4), device="cuda", generator=gen), torch.rand(B, device="cuda", generator=gen)
+    out = small.alloc_outputs(B)
+    print(f"mixture of two MLPs, B={B}", flush=True)
+    A.accerl_actor_forward_mixture(small.handle, orig.handle, x, u, use, *out)
+    m = _dev(use).bool()
+    for got, a, b in zip(out, small.forward(x, u), orig.forward(x, u)):
+        assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
