@@ -155,30 +155,115 @@ hipError_t go(const GemmParams& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The smallest tile that gives at most about one workgroup per compute unit.  Measured on 3136 -> 512 bf16 (us, tile of
-// states x features): 160 states 16x32 7.2, 16x16 8.6, 32x32 9.1; 500 states 32x32 9.7, 16x32 11.1, 32x64 11.5; 1000 states
-// 32x64 11.9, 32x32 14.7, 64x64 15.5; 2048 states 64x64 17.8, 32x64 19.4; 4096 states 128x64 26.8, 64x64 31.5.
+// The same with four wavefronts on 16 states x 64 features of row-major int8: wavefront w takes the steps w, w + 4, ..., every
+// lane fetches its fragment's 16 bytes itself and wavefront t finishes feature tile t.  Shorter than the kernel above (no turn
+// through LDS, half the partial sums), it is the faster one for narrow layers at middle batches: see ksplit_small_i8.
+constexpr int KM_W = 4, KM_NT = 4;
+__global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const GemmParams p) {
+    __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int64_t b = (int64_t)blockIdx.x * 16 + j;
+    const int nt0 = blockIdx.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
+    const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one
+
+    v4i acc[KM_NT];
+#pragma unroll
+    for (int t = 0; t < KM_NT; ++t) acc[t] = (v4i){0, 0, 0, 0};
+    auto load = [&](int st, v4i (&a)[KM_NT], v4i& x) {
+        const int sc = min(st, p.k_steps - 1);                              // past the end: a valid step, not multiplied
+#pragma unroll
+        for (int t = 0; t < KM_NT; ++t) a[t] = ((const v4i*)p.wfrag)[((int64_t)(nt0 + (t < nts ? t : 0)) * p.k_steps + sc) * 64 + lane];
+        x = *(const v4i*)(row + min(sc * 64 + g * 16, (p.Kp_bytes - 16) & ~3));
+    };
+    auto mul = [&](int st, const v4i (&a)[KM_NT], v4i x) {
+        if ((st + 1) * 64 > p.Kp_bytes) {                                   // the end of the row: as in the kernel above
+            const int have = p.Kp_bytes - (st * 64 + g * 16);
+            const int sh = have >= 16 ? 0 : have > 0 ? (16 - have) >> 2 : 4;
+            const v4i v = x;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                int r = 0;
+#pragma unroll
+                for (int k = e; k < 4; ++k) r = k - e == sh ? v[k] : r;
+                x[e] = r;
+            }
+        }
+        if (p.relu_in) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = (int)g_relu_i8x4((uint32_t)x[e]);
+        }
+#pragma unroll
+        for (int t = 0; t < KM_NT; ++t) acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[t], x, acc[t], 0, 0, 0);
+    };
+    v4i a0[KM_NT], a1[KM_NT], x0, x1;
+    load(wave, a0, x0);
+    for (int st = wave; st < p.k_steps; st += 2 * KM_W) {
+        load(st + KM_W, a1, x1);
+        mul(st, a0, x0);
+        load(st + 2 * KM_W, a0, x0);
+        if (st + KM_W < p.k_steps) mul(st + KM_W, a1, x1);
+    }
+#pragma unroll
+    for (int t = 0; t < KM_NT; ++t) s_part[(wave * KM_NT + t) * 64 + lane] = acc[t];
+    __syncthreads();
+    const int n0 = (nt0 + wave) * 16 + 4 * g;
+    if (wave >= nts || b >= p.B || n0 >= p.Np) return;
+    v4i sum = *(const v4i*)((const int*)p.bias + n0);
+#pragma unroll
+    for (int w = 0; w < KM_W; ++w) sum += s_part[(w * KM_NT + wave) * 64 + lane];
+    gemm_finish<EPI_REQUANT>(p, sum, b, n0);
+}
+
+int64_t groups(const GemmParams& p, int rt, int nt) { return ((p.B + 16 * rt - 1) / (16 * rt)) * ((p.n_tiles + nt - 1) / nt); }
+
+// about one workgroup per compute unit
+int64_t most_groups() { return conv_num_cus() * 9 / 8; }
+
+// Row-major int8 layers of at most 256 features between the batches that 16 x 32 tiles cover with one workgroup per compute
+// unit and those with one 64 x 64 workgroup per two.  us, this kernel / the tile that the rule below would take (rocprofv3):
+// 1936 -> 256, ReLU on the input: 600 states 4.9 / 6.0, 1000 5.1 / 5.6, 1500 7.0 / 7.6, 1800 7.0 / 8.0; 1296 -> 128: 1800 states
+// 4.8 / 5.3, 3000 5.7 / 6.2, 3500 5.8 / 6.4.  Smaller batches: 1936 -> 256 at 256 states 4.6 / 4.6, 512 4.6 / 4.2.  Wide layers:
+// 1936 -> 2048 at 160 states 8.6 / 6.9.
+bool ksplit_small_i8(const GemmParams& p) {
+    return !p.x_frag && p.n_tiles <= 16 && groups(p, 1, 2) > most_groups() && 2 * groups(p, 4, 4) < conv_num_cus();
+}
+
+// The smallest tile that gives at most about one workgroup per compute unit.  Measured on 3136 -> 512 (fragment order; us, tile
+// of states x features): bf16, 160 states 16x32 6.5, 16x16 7.2, 32x32 7.3; 500 states 32x32 7.8, 16x64 8.4, 32x64 9.8; 1000
+// states 32x64 9.8, 32x32 11.4, 64x64 12.4; 2048 states 64x64 12.9, 32x64 16.1; 3000 states 128x64 26.9, 64x64 34.2.  int8, 64
+// states 16x16 4.0, 16x32 4.3; 160 states 16x32 4.3, 16x16 4.5; 512 states 32x32 5.7, 16x64 6.2, 16x32 6.6; 1000 states 32x64 7.2,
+// 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.
 template <int EL, int EPI>
 hipError_t pick(const GemmParams& p, hipStream_t s) {
-    const int64_t most = conv_num_cus() * 9 / 8;
-    auto groups = [&](int rt, int nt) { return ((p.B + 16 * rt - 1) / (16 * rt)) * ((p.n_tiles + nt - 1) / nt); };
-    if (groups(1, 1) <= most) return go<EL, EPI, 1, 1>(p, s);
-    if (groups(1, 2) <= most) return go<EL, EPI, 1, 2>(p, s);
-    if (groups(2, 2) <= most) return go<EL, EPI, 2, 2>(p, s);
-    if (groups(2, 4) <= most) return go<EL, EPI, 2, 4>(p, s);
-    if constexpr (EL == EL_BF16) { if (groups(4, 4) > most) return go<EL, EPI, 8, 4>(p, s); }
+    const int64_t most = most_groups();
+    if (groups(p, 1, 1) <= most) return go<EL, EPI, 1, 1>(p, s);
+    if (groups(p, 1, 2) <= most) return go<EL, EPI, 1, 2>(p, s);
+    if constexpr (EL == EL_I8) {
+        if (ksplit_small_i8(p)) {
+            gemm_ksplit_small_i8_kernel<<<dim3((unsigned)((p.B + 15) / 16), (unsigned)((p.n_tiles + KM_NT - 1) / KM_NT)), dim3(64 * KM_W), 0, s>>>(p);
+            return hipGetLastError();
+        }
+    }
+    if (groups(p, 2, 2) <= most) return go<EL, EPI, 2, 2>(p, s);
+    if (groups(p, 2, 4) <= most) return go<EL, EPI, 2, 4>(p, s);
+    if constexpr (EL == EL_BF16) { if (groups(p, 4, 4) > most) return go<EL, EPI, 8, 4>(p, s); }
     return go<EL, EPI, 4, 4>(p, s);
 }
 
 }  // namespace
 
-// Every bf16 layer of eight steps or more.  int8 layers only up to about one 64 x 64 workgroup per compute unit: beyond that
-// the kernels that share the weights through LDS are faster (3136 -> 512 at 4096 states: 12.9 us against 17.4; 1936 -> 256 at
-// 8192: 17 against 20).
+// Every bf16 layer of eight steps or more.  int8 layers only up to one 64 x 64 workgroup per compute unit: beyond that the
+// kernels that share the weights through LDS are faster (us, this / theirs: 3136 -> 2048 at 575 states, 288 workgroups, 21.4 /
+// 18.2; 1936 -> 2048 there 19.3 / 16.3; at 256 workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192
+// states 9.1 / 9.5).  Where the weights exceed the 4 MB of an XCD's second-level cache, the streaming kernel is already the
+// faster one when 32 x 64 tiles no longer fit (3136 -> 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states,
+// 32 x 64 tiles, 8.0 / 10.4).
 bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
     if (p.B <= 0 || p.k_steps < 8) return false;
     if (el == EL_BF16) return epi == EPI_BF16;
-    return epi == EPI_REQUANT && ((p.B + 63) / 64) * ((p.n_tiles + 3) / 4) <= conv_num_cus() * 9 / 8;
+    if (epi != EPI_REQUANT || groups(p, 4, 4) > conv_num_cus()) return false;
+    return (int64_t)p.n_tiles * p.k_steps * 1024 <= 4 << 20 || groups(p, 2, 4) <= most_groups() || !gemm_stream_supported(p);
 }
 
 hipError_t launch_gemm_ksplit(const GemmParams& p, Elem el, hipStream_t s) {
