@@ -4,6 +4,10 @@
 
 namespace accerl {
 
+// bf16 dense layers of this many MFMA steps or more sum K in this many parts: part i is the steps i * k_steps / PARTS up to
+// (i + 1) * k_steps / PARTS in order from zero, and the parts are added to the bias in order
+constexpr int KSPLIT_PARTS = 8;
+
 __device__ __forceinline__ uint32_t g_relu_i8x4(uint32_t x) {
     const uint32_t neg = (x & 0x80808080u) >> 7;
     return x & ~(neg * 0xffu);

@@ -19,8 +19,10 @@ constexpr int GM_WAVES = GM_THREADS / 64;
 constexpr int GM_ROWS = 16 * GM_WAVES * GM_RT;   // states per workgroup
 constexpr int GM_KS = 4;          // MFMA steps per LDS stage (64 bytes of K each); a multiple of 4
 
-template <int EL, int EPI>
-__global__ __launch_bounds__(GM_THREADS, GM_THREADS == 256 ? 2 : 1) void gemm_kernel(const GemmParams p) {
+// PARTS > 1: K is summed in that many parts, which are then added to the bias in order -- the sums of the kernel whose
+// wavefronts split K (kernels_gemm_ksplit.hip), bit for bit, so that a bf16 state's result does not depend on its batch.
+template <int EL, int EPI, int PARTS>
+__global__ __launch_bounds__(GM_THREADS, PARTS > 1 ? 4 : 2) void gemm_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char gm_smem[];
     char* s_w = gm_smem;                              // [GM_NT][GM_KS][64 lanes][16 B]
     const int tid = threadIdx.x, lane = tid & 63;
@@ -42,6 +44,19 @@ __global__ __launch_bounds__(GM_THREADS, GM_THREADS == 256 ? 2 : 1) void gemm_ke
             else acc_f[u][t] = *(const v4f*)((const float*)p.bias + n0);
         }
     }
+    v4f sum[GM_RT][GM_NT];                            // PARTS > 1: the bias and the parts so far
+    int part = 0, part_end = PARTS > 1 ? p.k_steps / PARTS : 0;
+    auto fold = [&]() {
+#pragma unroll
+        for (int u = 0; u < GM_RT; ++u)
+#pragma unroll
+            for (int t = 0; t < GM_NT; ++t) {
+                sum[u][t] = part == 0 ? acc_f[u][t] : sum[u][t] + acc_f[u][t];
+                acc_f[u][t] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+            }
+    };
+    static_assert(PARTS == 1 || EL == EL_BF16, "integer sums do not depend on the order");
+    if constexpr (PARTS > 1) fold();
 
     // Stage s0 of K: the weight fragments [GM_NT tiles][GM_KS steps] go through LDS (all four wavefronts
     // read them); a wavefront's own 16 states need no sharing: lane (j, g) loads state j's 16 bytes of K
@@ -153,6 +168,13 @@ __global__ __launch_bounds__(GM_THREADS, GM_THREADS == 256 ? 2 : 1) void gemm_ke
                 if (st < ns) {
                     if (st + 1 < ns) load_a(fa[(st + 1) & 1], st + 1);
                     mfma(fa[st & 1], st);
+                    if constexpr (PARTS > 1) {
+                        if (s0 + st + 1 == part_end) {
+                            ++part;
+                            part_end = (part + 1) * p.k_steps / PARTS;
+                            fold();
+                        }
+                    }
                 }
             }
         }
@@ -171,15 +193,15 @@ __global__ __launch_bounds__(GM_THREADS, GM_THREADS == 256 ? 2 : 1) void gemm_ke
             // stored activations: rows past N up to the row pitch are written too (zero weights and bias give zeros)
             if (n0 >= ((EPI == EPI_REQUANT || EPI == EPI_BF16) ? p.Np : p.N)) continue;
             if constexpr (EL == EL_I8) gemm_finish<EPI>(p, acc_i[u][t], b, n0);
-            else gemm_finish<EPI>(p, acc_f[u][t], b, n0);
+            else gemm_finish<EPI>(p, PARTS > 1 ? sum[u][t] : acc_f[u][t], b, n0);
         }
     }
 }
 
-template <int EL, int EPI>
+template <int EL, int EPI, int PARTS = 1>
 static hipError_t gemm_go(const GemmParams& p, dim3 grid, hipStream_t s) {
     constexpr size_t lds = GM_NT * GM_KS * 1024;
-    auto kfn = gemm_kernel<EL, EPI>;
+    auto kfn = gemm_kernel<EL, EPI, PARTS>;
     static bool set = false;   // per instantiation: the stage buffers exceed the default dynamic LDS limit
     if (!set) {
         hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -200,7 +222,8 @@ hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s)
         return gemm_go<EL_I8, EPI_REQUANT>(p, grid, s);
     }
     if (el == EL_I8 && epi == EPI_HEADS_I8) return gemm_go<EL_I8, EPI_HEADS_I8>(p, grid, s);
-    if (el == EL_BF16 && epi == EPI_BF16) return gemm_go<EL_BF16, EPI_BF16>(p, grid, s);
+    if (el == EL_BF16 && epi == EPI_BF16)
+        return p.k_steps >= KSPLIT_PARTS ? gemm_go<EL_BF16, EPI_BF16, KSPLIT_PARTS>(p, grid, s) : gemm_go<EL_BF16, EPI_BF16>(p, grid, s);
     if (el == EL_BF16 && epi == EPI_HEADS_F32ACC) return gemm_go<EL_BF16, EPI_HEADS_F32ACC>(p, grid, s);
     if (el == EL_BF16 && epi == EPI_LSTM) return gemm_go<EL_BF16, EPI_LSTM>(p, grid, s);
     return hipErrorInvalidValue;

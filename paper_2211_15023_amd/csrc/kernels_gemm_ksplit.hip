@@ -19,7 +19,7 @@ int conv_num_cus();   // compute units of the current device
 namespace {
 
 constexpr int KS_LDS = 64 * 1024;
-constexpr int KS_W = 8;                                       // wavefronts per workgroup
+constexpr int KS_W = KSPLIT_PARTS;                            // wavefronts per workgroup
 
 template <int EL, int EPI, int RT, int NT, bool RELU, bool FRAG>
 __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams p) {
@@ -253,16 +253,27 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 
 }  // namespace
 
-// Every bf16 layer of eight steps or more.  int8 layers only up to one 64 x 64 workgroup per compute unit: beyond that the
-// kernels that share the weights through LDS are faster (us, this / theirs: 3136 -> 2048 at 575 states, 288 workgroups, 21.4 /
-// 18.2; 1936 -> 2048 there 19.3 / 16.3; at 256 workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192
-// states 9.1 / 9.5).  Where the weights exceed the 4 MB of an XCD's second-level cache, the streaming kernel is already the
-// faster one when 32 x 64 tiles no longer fit (3136 -> 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states,
-// 32 x 64 tiles, 8.0 / 10.4).
+// int8 layers only up to one 64 x 64 workgroup per compute unit: beyond that the kernels that share the weights through LDS are
+// faster (us, this / theirs: 3136 -> 2048 at 575 states, 288 workgroups, 21.4 / 18.2; 1936 -> 2048 there 19.3 / 16.3; at 256
+// workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192 states 9.1 / 9.5).  Where the weights exceed the
+// 4 MB of an XCD's second-level cache, the streaming kernel is already the faster one when 32 x 64 tiles no longer fit (3136 ->
+// 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
+// bf16 layers beyond one 64 x 64 workgroup per compute unit take 128 x 64 tiles while those fill at most one round and the
+// eighth of K that a wavefront walks is at least eight steps (us, this / gemm_kernel: 3136 -> 512 at 3000 states 27 / 34, 4096
+// 28 / 34; 3872 -> 256 at 5000 31 / 49, 8192 40 / 51; but 1296 -> 128 at 10000 20.5 / 17), with a second to fourth round only for
+// row-major states, which gemm_kernel fetches badly, and only if the last round is full (3872 -> 2048: 2000 states, two rounds,
+// 62 / 82, 4096, four, 121 / 151; 6000, six, 313 / 243; 3872 -> 256 at 9300 85 / 61; 3136 -> 512 at 4700 65 / 43, 6000 67 / 47,
+// 12000 110 / 91; 3136 -> 2048 at 2000 53 / 49, 6000 215 / 178).
 bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
-    if (p.B <= 0 || p.k_steps < 8) return false;
-    if (el == EL_BF16) return epi == EPI_BF16;
-    if (epi != EPI_REQUANT || groups(p, 4, 4) > conv_num_cus()) return false;
+    if (p.B <= 0 || p.k_steps < KSPLIT_PARTS) return false;
+    const int64_t cus = conv_num_cus();
+    if (el == EL_BF16) {
+        if (epi != EPI_BF16) return false;
+        if (groups(p, 4, 4) <= most_groups()) return true;
+        const int64_t g = groups(p, 8, 4), rounds = (g + cus - 1) / cus;
+        return p.k_steps >= 8 * KSPLIT_PARTS && (rounds == 1 || (!p.x_frag && rounds <= 4 && 10 * g >= 9 * rounds * cus));
+    }
+    if (epi != EPI_REQUANT || groups(p, 4, 4) > cus) return false;
     return (int64_t)p.n_tiles * p.k_steps * 1024 <= 4 << 20 || groups(p, 2, 4) <= most_groups() || !gemm_stream_supported(p);
 }
 

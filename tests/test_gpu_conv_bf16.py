@@ -1,7 +1,9 @@
 """The bf16 kernels of the paper's original network's convolutions (first two in one launch; third with fixed sizes, storing
 the FC's fragment order) against the generic kernels, which run in a child process: the same bits, at the batch sizes where
-the work split changes (one observation, an odd image beside an empty slot, a partly filled tile of 16 states, a second and
-an uneven third round of the resident workgroups)."""
+the work split changes: one observation, an odd image beside an empty slot, a partly filled tile of 16 states; a second and an
+uneven third round of the front kernel's resident workgroups (257, 700), a third and a fifth of the third convolution's with an
+odd last image (2101, 4133); the FC's 64x64 and 128x64 tiles on fragment-order input (2101, 3001) and, at 4133, the kernel that
+walks K in one wavefront."""
 import os
 import subprocess
 import sys
@@ -15,7 +17,7 @@ from helpers import policies, teacher_tensors
 
 pytestmark = pytest.mark.gpu
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-BATCHES = [1, 3, 17, 257, 700]
+BATCHES = [1, 3, 17, 257, 700, 2101, 3001, 4133]
 
 
 def _forwards(path=None):

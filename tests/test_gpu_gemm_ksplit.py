@@ -1,8 +1,8 @@
 """The dense kernels whose wavefronts split K, at every tile they can take: the batch picks the tile (layers of about 512
-features: 1, 100 states 16x16; 160 16x32; 500 32x32; 900 32x64; 2000 64x64; 2400 128x64 for bf16; int8 layers of at most 256
-features: 16x64 from 577 or, of 128, from 1153 states on), the layer's rows end inside a 16-byte chunk or inside an MFMA step, with
-and without a ReLU on the input, with a partly filled last feature tile.  int8: the oracle's bits.  bf16: the oracle's tolerance,
-and a state's result does not depend on the tile (the split of K and the order of its sums are fixed)."""
+features: 1, 100 states 16x16; 160 16x32; 500 32x32; 900 32x64; 2000 64x64; bf16 at 2400 128x64 or, with fewer than 64 steps, the
+kernel that walks K in one wavefront; int8 layers of at most 256 features: 16x64 from 577 or, of 128, from 1153 states on), the
+layer's rows end inside a 16-byte chunk or inside an MFMA step, with and without a ReLU on the input, with a
+partly filled last feature tile.  int8: the oracle's bits.  bf16: the oracle's tolerance, and a state's result does not depend on the tile or the kernel (the split of K and the order of its sums are fixed)."""
 import numpy as np
 import pytest
 import torch
@@ -19,8 +19,9 @@ BATCHES = [1, 100, 160, 500, 900, 2000, 2400]
 
 def _net(cout, act, width, side=15):
     # 15 x 15 pixels of cout channels: int8 900 bytes (14.06 steps, the last chunk holds 4 bytes), 16 channels: whole chunks;
-    # bf16 3600 bytes (8 channels, the last chunk whole), 1800 bytes (4 channels, the last chunk holds 8 bytes).  11 x 11 pixels
-    # of 16 channels are the 1936 inputs behind the IMPALA student's stacks
+    # bf16 3600 bytes (8 channels, 56.25 steps, the last chunk whole), 1800 bytes (4 channels, 28.1 steps, the last chunk holds
+    # 8 bytes), 7200 bytes (16 channels, 112.5 steps).  11 x 11
+    # pixels of 16 channels are the 1936 inputs behind the IMPALA student's stacks
     return Net("ksplit", "u8", (4, side + 1, side + 1), 5,
                [conv(4, cout, 2, 1, 0, False)] + ([relu()] if act else []) + [flatten(), dense(cout * side * side, width, True)])
 
@@ -41,7 +42,7 @@ def test_int8_all_tiles(cout, act, width, side):
         assert np.array_equal(value.cpu().numpy(), ref["value"][:B])
 
 
-@pytest.mark.parametrize("cout,act,width", [(4, True, 512), (8, False, 500)])
+@pytest.mark.parametrize("cout,act,width", [(4, True, 512), (8, False, 500), (16, True, 500)])
 def test_bf16_all_tiles(cout, act, width):
     import paper_2211_15023_amd as A
     net = _net(cout, act, width)
