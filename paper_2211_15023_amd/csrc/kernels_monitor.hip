@@ -331,26 +331,25 @@ __global__ __launch_bounds__(MON_WAVES * 64) void is_ratio_kernel(const float* _
 // ---- backward scan per environment: v_s - V(x_s) = delta_s + gamma_s c_s (v_{s+1} - V(x_{s+1}))
 // A scan with one lane per environment leaves the chip nearly empty (B / 64 wavefronts walking T dependent steps).  The
 // recurrence a_t = delta_t + k_t a_{t+1} (k_t = gamma_t c_t) is linear, so a run of steps [t0, t1) acts on the value
-// entering it as a_t0 = A + M a_t1 with A, M computed from that run alone.  A workgroup takes VT_ENV environments (a whole
-// 128-byte line of every row; with 64 of them an unroll of 4096 kept 64 compute units busy, 18.3 us for 256 steps against
-// 8.0); groups of VT_ENV lanes split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
+// entering it as a_t0 = A + M a_t1 with A, M computed from that run alone.  A workgroup takes ENV environments; groups of ENV
+// lanes split the last (up to) NSEG * L steps into runs of L steps held in registers: each forms its (A, M) with one
 // backward pass, the pairs meet in LDS, every wavefront folds the pairs of the runs behind it into the value entering
 // its run and walks its registers a second time to write v_s, the clipped weights and the advantages.  Longer unrolls
 // repeat this from the end of the trajectory towards its start, carrying a_t across.  delta_t needs V(x_{t+1}) only,
 // which is an input.  The order of the floating-point operations is fixed by (T, L), not by the launch.
-constexpr int VT_ENV = 32;
-constexpr int VT_NSEG = 16 * 64 / VT_ENV;
-template <int L>
-__global__ __launch_bounds__(VT_NSEG * VT_ENV) void vtrace_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ discounts,
-                                                                   const float* __restrict__ values, const float* __restrict__ bootstrap,
-                                                                   int64_t T, int64_t B, float rho_bar, float c_bar,
-                                                                   float* __restrict__ rho /* in: ratio, out: clipped */,
-                                                                   float* __restrict__ vs, float* __restrict__ pg_adv) {
-    __shared__ float sA[VT_NSEG][VT_ENV], sM[VT_NSEG][VT_ENV];
-    __shared__ float s_carry[VT_ENV];
-    const int lane = threadIdx.x % VT_ENV, seg = threadIdx.x / VT_ENV;
-    const int nseg = blockDim.x / VT_ENV;
-    const int64_t b = (int64_t)blockIdx.x * VT_ENV + lane;
+constexpr int VT_LANES = 1024;
+template <int L, int ENV>
+__global__ __launch_bounds__(VT_LANES) void vtrace_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ discounts,
+                                                               const float* __restrict__ values, const float* __restrict__ bootstrap,
+                                                               int64_t T, int64_t B, float rho_bar, float c_bar,
+                                                               float* __restrict__ rho /* in: ratio, out: clipped */,
+                                                               float* __restrict__ vs, float* __restrict__ pg_adv) {
+    constexpr int NSEG = VT_LANES / ENV;
+    __shared__ float sA[NSEG][ENV], sM[NSEG][ENV];
+    __shared__ float s_carry[ENV];
+    const int lane = threadIdx.x % ENV, seg = threadIdx.x / ENV;
+    const int nseg = blockDim.x / ENV;
+    const int64_t b = (int64_t)blockIdx.x * ENV + lane;
     const int64_t bc = b < B ? b : B - 1;                  // lanes past the batch repeat the last environment, store nothing
     if (seg == 0) s_carry[lane] = 0.0f;                    // a_T = v_T - V(x_T) = 0
     for (int64_t hi = T; hi > 0; hi -= (int64_t)nseg * L) {
@@ -546,14 +545,18 @@ extern "C" int accerl_vtrace(const float* logits_original, const float* logits_s
     rows<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, actions, R, A, out_rho);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail("is_ratio_kernel", e);
-    // runs of 8 steps for long unrolls, of 4 for short ones; as many runs per workgroup as there are (at most VT_NSEG, and an
-    // even number: whole wavefronts)
-    const dim3 vgrid((unsigned)((B + VT_ENV - 1) / VT_ENV));
-    auto runs = [&](int L) { const int64_t n = ((T + L - 1) / L + 1) & ~(int64_t)1; return (unsigned)(n < VT_NSEG ? n : VT_NSEG); };
-    if (T > 32)
-        vtrace_scan_kernel<8><<<vgrid, dim3(runs(8) * VT_ENV), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
-    else
-        vtrace_scan_kernel<4><<<vgrid, dim3(runs(4) * VT_ENV), 0, s>>>(rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
+    // Runs of 8 steps for long unrolls, of 4 for short ones; as many runs per workgroup as there are, in whole wavefronts and at
+    // most VT_LANES.  A long unroll takes 32 environments per workgroup, a whole 128-byte line of every row: with 64 an unroll of
+    // 4096 kept 64 compute units busy (256 steps 17.6 us, now 8.0; 64 x 1000 7.8, now 4.3).  Up to 32 steps the smaller workgroups
+    // gain nothing (16 x 4096 3.2 us both) and half wavefronts cost (us, 64 / 32 environments: 5 x 37 2.0 / 2.5, 16 x 256 2.6 /
+    // 3.1, 32 x 256 3.0 / 3.3).
+    auto scan = [&](auto kernel, int L, int env) {
+        const int64_t runs = (T + L - 1) / L, per_wave = 64 / env, up = (runs + per_wave - 1) / per_wave * per_wave * env;
+        kernel<<<dim3((unsigned)((B + env - 1) / env)), dim3((unsigned)(up < VT_LANES ? up : VT_LANES)), 0, s>>>(
+            rewards, discounts, values, bootstrap, T, B, rho_bar, c_bar, out_rho, out_vs, out_pg_adv);
+    };
+    if (T > 32) scan(vtrace_scan_kernel<8, 32>, 8, 32);
+    else scan(vtrace_scan_kernel<4, 64>, 4, 64);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("vtrace_scan_kernel", e);
     return ACCERL_OK;
 }
