@@ -674,31 +674,32 @@ int build_plan(Builder& B) {
             m.nt = widest <= 64 ? 1 : widest <= 128 ? 2 : 4;
             m.kb0 = (int)up((a->obs_c + 15) / 16, 2);
             const int ut = 4 * m.nt;
-            // fragments of 16 units x 16 inputs: lane holds inputs 4 * (lane / 16) .. + 3 of unit lane % 16
-            auto put_tile = [&](float* dst, const TensorSpec& t, int tile, int block) {
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int e = 0; e < 4; ++e) {
-                        const int64_t n = 16 * tile + (lane & 15), k = 16 * block + 4 * (lane >> 4) + e;
-                        if (n < t.rows && k < t.cols) dst[4 * lane + e] = B.wf(t)[n * t.cols + k];
-                    }
+            // fragments of 16 units x 16 inputs: lane holds inputs 4 * (lane / 16) .. + 3 of unit lane % 16.  They are laid out in
+            // the constants' own memory, zeroed by put
+            auto put_tile = [&](int64_t at, const TensorSpec& t, int tile, int block) {
+                char* dst = B.cst.data() + at;
+                const float* src = B.wf(t);
+                for (int lane = 0; lane < 64; ++lane) {
+                    const int64_t n = 16 * tile + (lane & 15), k = 16 * block + 4 * (lane >> 4);
+                    if (n < t.rows && k < t.cols) memcpy(dst + 16 * lane, src + n * t.cols + k, 4 * std::min<int64_t>(t.cols - k, 4));
+                }
             };
-            std::vector<float> w((size_t)(m.kb0 + (m.n_hidden - 1) * ut + 4) * ut * 256, 0.f), b((size_t)m.n_hidden * 16 * ut, 0.f);
-            size_t at = 0;
+            const int ht = (a->n_actions + 16) / 16;
+            B.cst.reserve(B.cst.size() + 1024 * (int64_t)ut * (m.kb0 + (m.n_hidden - 1) * ut + 4 + ht) + 64 * (int64_t)ut * m.n_hidden + 4096);
+            st.o_wall = B.put(nullptr, 1024 * (int64_t)ut * (m.kb0 + (m.n_hidden - 1) * ut + 4));
+            st.o_ball = B.put(nullptr, 64 * (int64_t)ut * m.n_hidden);
+            int64_t at = st.o_wall;
             for (int l = 0; l < m.n_hidden; ++l) {
                 const TensorSpec& t = B.tensor(l, 0);
                 m.N[l] = (int)t.rows; m.relu[l] = a->layers[l].relu;
                 for (int block = 0; block < (l ? ut : m.kb0); ++block)
-                    for (int tile = 0; tile < ut; ++tile, at += 256) put_tile(&w[at], t, tile, block);
-                for (int n = 0; n < m.N[l]; ++n) b[(size_t)l * 16 * ut + n] = B.bias(t)[n];
+                    for (int tile = 0; tile < ut; ++tile, at += 1024) put_tile(at, t, tile, block);
+                memcpy(B.cst.data() + st.o_ball + 64 * (int64_t)ut * l, B.bias(t), 4 * t.rows);
             }
             const TensorSpec& th = B.tensor(a->n_layers, 0);
-            const int ht = (a->n_actions + 16) / 16;
-            std::vector<float> wh((size_t)ht * ut * 256, 0.f);
+            st.o_whead = at = B.put(nullptr, 1024 * (int64_t)ut * ht);
             for (int h = 0; h < ht; ++h)
-                for (int block = 0; block < ut; ++block) put_tile(&wh[(size_t)(h * ut + block) * 256], th, h, block);
-            st.o_wall = B.put(w.data(), (int64_t)w.size() * 4);
-            st.o_ball = B.put(b.data(), (int64_t)b.size() * 4);
-            st.o_whead = B.put(wh.data(), (int64_t)wh.size() * 4);
+                for (int block = 0; block < ut; ++block, at += 1024) put_tile(at, th, h, block);
             st.o_bhead = B.put(B.bias(th), th.rows * 4);
         }
         return ACCERL_OK;
