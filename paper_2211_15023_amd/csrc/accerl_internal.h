@@ -238,6 +238,7 @@ hipError_t launch_mlp_f32(const MlpF32Params& p, hipStream_t s);
 struct LstmPackParams {
     const void* x; int x_elem; float x_scale; int x_pitch_bytes; int x_relu; int In;
     const uint8_t* done; float* h; float* c; uint16_t* xh; int Hd; int64_t B;
+    int pitch;               // elements of a row of xh, In + Hd and zeros (a multiple of 8)
     int frag_ks;             // > 0: xh in the fragment order of the product's frag_ks MFMA steps (GemmParams::x_frag)
 };
 hipError_t launch_lstm_pack(const LstmPackParams& p, hipStream_t s);

@@ -848,18 +848,18 @@ int build_plan(Builder& B) {
                 if (Hd % 4) return fail(ACCERL_EUNSUPPORTED, "lstm hidden size must be a multiple of 4");
                 for (int k = 0; k < In; ++k) if (cur.perm[k] != k) return fail(ACCERL_EUNSUPPORTED, "lstm input must be a plain vector");
                 pol->lstm_hidden = Hd;
-                const int Kx = In + Hd;
+                const int Kx = In + Hd, Kp = (int)up(Kx, 8);      // rows of whole 16-byte chunks, zeros behind the inputs
                 Step pk;
                 pk.kind = ST_LSTM_PACK; pk.layer = i; pk.sub = 0;
                 pk.in_buf = cur.buf;
-                pk.out_buf = B.new_buf((int64_t)Kx * 2);
+                pk.out_buf = B.new_buf((int64_t)Kp * 2);
                 LstmPackParams& lp = pk.lp;
                 lp.x_elem = cur.el; lp.x_scale = cur.scale; lp.x_pitch_bytes = cur.stored * esz; lp.x_relu = cur.relu_pending;
-                lp.In = In; lp.Hd = Hd;
+                lp.In = In; lp.Hd = Hd; lp.pitch = Kp;
                 // fragment order where the 8-value pieces of both halves are whole and aligned, and the steps come in fours
                 if (In % 8 == 0 && Hd % 8 == 0 && Kx % 128 == 0 && lp.x_pitch_bytes % (cur.el == EL_I8 ? 8 : 16) == 0 && cur.el != EL_F32)
                     lp.frag_ks = Kx / 32;
-                pk.out_elems = Kx;
+                pk.out_elems = Kp;
                 pol->steps.push_back(pk);
                 const TensorSpec& tih = B.tensor(i, 0);
                 const TensorSpec& thh = B.tensor(i, 1);
@@ -879,7 +879,7 @@ int build_plan(Builder& B) {
                 for (int n = 0; n < N; ++n) bf[n] = B.bias(tih)[rowmap[n]];
                 st.o_bias = B.put(bf.data(), bf.size() * 4);
                 GemmParams& gp = st.gp;
-                gp.Kp_bytes = Kx * 2; gp.k_steps = k_steps; gp.N = N; gp.Np = Hd; gp.n_tiles = n_tiles; gp.Hd = Hd;
+                gp.Kp_bytes = Kp * 2; gp.k_steps = k_steps; gp.N = N; gp.Np = Hd; gp.n_tiles = n_tiles; gp.Hd = Hd;
                 gp.x_frag = lp.frag_ks > 0;
                 st.out_elems = Hd;
                 pol->steps.push_back(st);

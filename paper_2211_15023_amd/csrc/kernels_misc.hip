@@ -253,14 +253,15 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float x) {
 }
 
 __global__ __launch_bounds__(256) void lstm_pack_kernel(LstmPackParams p) {
-    const int K = p.In + p.Hd;
     const int f = blockIdx.x * 256 + threadIdx.x;      // one grid row per state: no division
-    if (f >= K) return;
+    if (f >= p.pitch) return;
     const int64_t b = blockIdx.y;
-    const int64_t i = b * K + f;
+    const int64_t i = b * p.pitch + f;
     const bool dn = p.done && p.done[b] != 0;
-    float v;
-    if (f < p.In) {
+    float v = 0.0f;
+    if (f >= p.In + p.Hd) {
+        // the row's end: the product reads whole chunks
+    } else if (f < p.In) {
         const char* row = (const char*)p.x + b * p.x_pitch_bytes;
         if (p.x_elem == EL_I8) {
             int q = ((const int8_t*)row)[f];
@@ -348,7 +349,7 @@ hipError_t launch_lstm_pack(const LstmPackParams& p, hipStream_t s) {
         return hipGetLastError();
     }
     if (p.B > 65535) return hipErrorInvalidValue;
-    lstm_pack_kernel<<<dim3((unsigned)((p.In + p.Hd + 255) / 256), (unsigned)p.B), dim3(256), 0, s>>>(p);
+    lstm_pack_kernel<<<dim3((unsigned)((p.pitch + 255) / 256), (unsigned)p.B), dim3(256), 0, s>>>(p);
     return hipGetLastError();
 }
 

@@ -199,3 +199,45 @@ def test_bf16_teacher_layer_by_layer(A, ci):
     print(f"  cfg{ci} heads on the HIP path's own features: logits {el:.2e}", flush=True)
     assert el <= 2e-3
     pol.close()
+
+
+@pytest.mark.parametrize("role,In,Hd,act", [("student", 48, 20, False), ("teacher", 48, 20, False), ("student", 17, 12, True), ("teacher", 40, 12, True),
+                                            ("student", 24, 104, False), ("teacher", 24, 104, False), ("student", 200, 56, True), ("teacher", 200, 56, True)])
+def test_lstm_operand_orders(A, role, In, Hd, act):
+    """The LSTM's operand in both orders it is packed in: rows (no whole MFMA steps, rows that end inside a 16-byte chunk, an odd
+    number of inputs) and the product's fragments (128 and 256 inputs, where the state's half begins inside a step of 32), with a
+    ReLU in front or not, 37 rows (two tiles of 16 and a cut one), every third episode done.  The cell is fed the HIP path's own dense output, so
+    that only the order of fp32 sums in front of the gates separates the two sides; bounds as in the layer-by-layer test above."""
+    layers = [wl.nets.conv(4, 4, 2, 1, 0, False), wl.nets.flatten(), wl.nets.dense(900, In, not act)] + ([wl.nets.relu()] if act else []) + [wl.nets.lstm(In, Hd)]
+    net = wl.Net("lstm_orders", "u8", (4, 16, 16), 5, layers)
+    params = wl.init_params(net, 3)
+    B = 37
+    x, u = make_states(net, B, wl.STREAM["states"]), wl.make_uniforms(B)
+    h0, c0 = wl.make_hc(B, Hd)
+    done = (np.arange(B) % 3 == 1).astype(np.uint8)
+    dh, dc = dev(h0), dev(c0)
+    if role == "student":
+        qp = oracle.quantize_policy(net, params, make_states(net, 16, wl.STREAM["calibration"]))
+        pol = A.Policy(net, "int8", qp.tensors, qp.act_scales)
+        plan = A.accerl_plan_describe(pol.arch, A.pack_weights(qp.tensors), A.pack_scales(qp.act_scales, qp.tensors))
+    else:
+        pol = A.Policy(net, "bf16", teacher_tensors(params))
+        plan = A.accerl_plan_describe(pol.arch, A.pack_weights(teacher_tensors(params)))
+    assert ("x_frag=1" in plan) == ((In + Hd) % 128 == 0)
+    print(f"lstm {In} + {Hd} {role}", flush=True)
+    logits, value, action = pol.forward(dev(x), dev(u), done=dev(done), h=dh, c=dc)
+    if role == "student":                                   # the int8 layers are exact
+        ref = oracle.forward_int8(net, qp, x, u, h=h0.copy(), c=c0.copy(), done=done)
+        h1, c1, out, want_value = ref["h"], ref["c"], ref["logits"], ref["value"]
+    else:
+        feat = pol.tap(dev(x), 2, A.TAP_ACT, (B, In), torch.float32).cpu().numpy()
+        P = {n: (w, b) for n, w, b in params}
+        at = len(layers) - 1
+        h1, c1 = L.lstm_step(np.maximum(feat, 0) if act else feat, h0.copy(), c0.copy(), done, P[f"l{at}.lstm_ih"][0], P[f"l{at}.lstm_hh"][0], P[f"l{at}.lstm_ih"][1], True)
+        both = L.dense_f(h1, *P["heads"], False, True)
+        out, want_value = both[:, :5], both[:, 5]
+    eh, ec = float(np.abs(dh.cpu().numpy() - h1).max()), float(np.abs(dc.cpu().numpy() - c1).max())
+    el, ev = float(rel_err_rows(logits.cpu().numpy(), out).max()), float(rel_err_rows(value.cpu().numpy(), want_value).max())
+    print(f"  |dh| {eh:.1e} |dc| {ec:.1e} logits {el:.1e} value {ev:.1e}", flush=True)
+    assert eh <= 1e-4 and ec <= 1e-4 and el <= 2e-3 and ev <= 1e-2
+    check_sampler_self_consistency(action.cpu().numpy(), logits.cpu().numpy(), u)
