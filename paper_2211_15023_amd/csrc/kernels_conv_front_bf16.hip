@@ -61,7 +61,8 @@ __device__ __forceinline__ int fb_pack2(float a, float b) {
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(int, __builtin_convertvector((v2f){a, b}, v2bf));
 }
-// ReLU of eight accumulators (consecutive channels) as bf16: a negative bf16 is a negative 16-bit integer
+// ReLU of eight accumulators (consecutive channels) as bf16: a negative bf16 is a negative 16-bit integer, and so is the only NaN
+// that the matrix cores produce (0xffc0), which becomes 0 as in fmaxf
 __device__ __forceinline__ v4i fb_relu_pack(v4f a, v4f b) {
     typedef short v8s __attribute__((ext_vector_type(8)));
     const v8s z = {0, 0, 0, 0, 0, 0, 0, 0};

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(TB_THREADS, 2) void conv_tail_bf16_kernel(const Tai
         const int u = q / 18, st = q - 18 * u, tap = st >> 1;
         return *(const v4i*)(src + rb[u] + (st & 1) * (4 * TB_PLANE) + ((tap / 3) * 9 + (tap % 3)) * 16);
     };
-    auto store = [&](char* outp, int u, v4f a, v4f b) {   // ReLU on the rounded values: a negative bf16 is a negative 16-bit integer
+    auto store = [&](char* outp, int u, v4f a, v4f b) {   // ReLU on the rounded values: see fb_relu_pack
         typedef float v2f __attribute__((ext_vector_type(2)));
         typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
         typedef short v8s __attribute__((ext_vector_type(8)));

@@ -21,7 +21,8 @@
 //    maximum runs over the rows as they are produced (row 2 py + 1 is kept for the next pooled row), the horizontal one
 //    over the two neighbour lanes (DPP).  Rounding to bf16 is monotone, so it follows the maximum.
 //  * The stream is kept un-rectified (the skip connection needs it) and rectified as fragments are read: one packed
-//    16-bit integer maximum per dword, since a negative bf16 is a negative 16-bit integer.
+//    16-bit integer maximum per dword, since a negative bf16 is a negative 16-bit integer (the NaN that the matrix cores
+//    produce, 0xffc0, is one too and becomes 0 as in fmaxf).
 //  * bf16 inputs go from memory to LDS without passing through registers, a third of the next batch at the start of each of
 //    three phases: loads into registers held their wavefront for 6 000 clocks of 34 000 in a full memory queue and storing
 //    them took another 4 000 (second stack 80 -> 67 us, third 39 -> 32 us at 1024 states).

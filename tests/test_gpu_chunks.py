@@ -1,6 +1,6 @@
 """Batches larger than one pass of the workspace: the forward then runs in chunks of whole 64-state tiles.
 
-The bf16 IMPALA teacher needs about 165 KB of workspace per state, so its configured batch of 16384 runs as three
+The bf16 IMPALA teacher needs about 85 KB of workspace per state, so its configured batch of 16384 runs as two
 passes; a child process repeats a student forward with the pass size forced down to 1024 states (override 1040,
 rounded down to whole tiles) at B = 4133, which must give the bits of the single-pass run."""
 import os
@@ -96,3 +96,14 @@ def test_student_in_small_passes_is_bit_identical(tmp_path, ci, B):
     ref = oracle.forward_int8(ns, qp, x[rows], u[rows])
     assert np.array_equal(got["logits"][rows], ref["logits"]) and np.array_equal(got["value"][rows], ref["value"])
     check_actions(got["action"][rows], ref["action"], ref["logits"], u[rows], 1e-5)
+
+
+def test_mixture_rows_in_place_across_passes():
+    """The mixture of two bf16 networks that read their rows through the row list, in passes of 128 states (600 rows: both
+    subsets take several): the child repeats the comparison with the plain forwards."""
+    code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]; import test_gpu_conv_bf16 as t, paper_2211_15023_amd as A; "
+            "nt, pt, *_ = t.policies(2); w = t.teacher_tensors(pt); "
+            "assert 'chunk=128' in A.accerl_plan_describe(A.make_arch(nt, 'bf16'), A.pack_weights(w)).splitlines()[0]; "
+            "t.test_mixture_reads_rows_in_place(600, 0.4)")
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, ACCERL_CHUNK="128"), capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr[-2000:]

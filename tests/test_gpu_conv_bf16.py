@@ -65,3 +65,26 @@ def test_mixture_reads_rows_in_place(B, alpha):
     m = torch.from_numpy(use.astype(bool)).cuda()
     for got, a, b in zip(out, first.forward(x, u), other.forward(x, u)):
         assert torch.equal(got[m], a[m]) and torch.equal(got[~m], b[~m])
+
+
+NAN = [np.uint32(0x7fc00000), np.uint32(0xffc00000)]          # of either sign
+
+
+@pytest.mark.parametrize("bad_bits", NAN)
+@pytest.mark.parametrize("layer", [0, 1, 2])
+def test_relu_turns_nan_sums_into_zero(layer, bad_bits):
+    """A filter with a NaN weight sums to NaN everywhere; the ReLU behind it gives zeros (max(NaN, 0) = 0, as in the oracle), so the
+    network computes the bits it computes with that filter set to zero."""
+    import paper_2211_15023_amd as A
+    nt, pt, ns, ps, qp = policies(2)
+    x, u = torch.from_numpy(wl.make_frames_u8(19, first=5)).cuda(), torch.from_numpy(wl.make_uniforms(19)).cuda()
+    out = []
+    for bad in (bad_bits.view(np.float32), np.float32(0)):
+        params = [(n, w.copy(), b.copy()) for n, w, b in pt]
+        params[layer][1][5] = 0
+        params[layer][1][5, 0, 0, 0] = bad
+        params[layer][2][5] = 0
+        out.append([t.cpu().numpy() for t in A.Policy(nt, "bf16", teacher_tensors(params)).forward(x, u)])
+    assert np.isfinite(out[0][0]).all()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)

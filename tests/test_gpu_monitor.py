@@ -24,7 +24,8 @@ def _dev(x):
     return torch.from_numpy(np.ascontiguousarray(x)).cuda()
 
 
-@pytest.mark.parametrize("B,nA", [(1, 2), (63, 18), (64, 18), (4096 + 17, 18), (1000, 64), (777, 7), (300, 32)])
+@pytest.mark.parametrize("B,nA", [(1, 2), (63, 18), (64, 18), (4096 + 17, 18), (1000, 64), (777, 7), (300, 32), (1, 1), (65, 1),
+                                  (1001, 20), (1001, 21), (300017, 20)])
 def test_kl_monitor_matches_oracle(A, B, nA):
     lo, ls = wl.make_logits_pair(B, nA, gap=0.5)
     kl_o, ent_o, st_o = L.kl_monitor(lo, ls)
@@ -68,11 +69,14 @@ def test_kl_monitor_large_batch_stats(A):
     assert np.allclose(st.cpu().numpy(), st_o, rtol=2e-4, atol=1e-6)
 
 
-# the scan splits a trajectory into runs of 4 steps (T <= 32) or 16 steps handled by different wavefronts, and walks
-# unrolls of more than 256 steps in several rounds: 40 and 257 steps end in a cut run, 300 and 257 need a second round
+# the scan splits a trajectory into runs of 4 steps (T <= 32) or 8 steps handled by different lanes of a workgroup, and walks
+# unrolls of more than 256 steps in several rounds: 20, 33 and 257 steps end in a cut run, 300 and 257 need a second round.  The
+# ratios of up to 20 actions are computed in registers (20), wider rows in LDS (21); above 262144 rows (70 x 4096) a wavefront
+# has a second tile, which it loads while it works on the first
 @pytest.mark.parametrize("T,B,nA,rb,cb", [(1, 1, 2, 1.0, 1.0), (16, 300, 18, 1.0, 1.0), (20, 257, 6, 1.5, 0.8),
                                          (5, 4096, 18, 1.0, 1.0), (64, 33, 64, 2.0, 1.0), (40, 65, 4, 1.0, 0.9),
-                                         (257, 64, 3, 1.0, 1.0), (300, 70, 5, 1.2, 1.0), (32, 64, 18, 1.0, 1.0), (33, 5, 18, 1.0, 1.0)])
+                                         (257, 64, 3, 1.0, 1.0), (300, 70, 5, 1.2, 1.0), (32, 64, 18, 1.0, 1.0), (33, 5, 18, 1.0, 1.0),
+                                         (9, 150, 20, 1.0, 1.0), (9, 150, 21, 1.0, 1.0), (70, 4096, 5, 1.0, 1.0), (66, 4001, 20, 1.0, 1.0)])
 def test_vtrace_matches_oracle(A, T, B, nA, rb, cb):
     tr = wl.make_trajectory(T, B, nA, p_done=0.05)
     vs_o, adv_o, rho_o = L.vtrace(**tr, rho_bar=rb, c_bar=cb)

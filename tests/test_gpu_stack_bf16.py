@@ -34,3 +34,25 @@ def test_bf16_stacks_give_the_layerwise_bits(monkeypatch, B):
     ref = oracle.forward_float(nt, pt, x[rows], u[rows], "bf16")
     assert rel_err_rows(out[0][0][rows], ref["logits"]).max() <= 2e-2     # the bf16 bound of the parity tests
     check_actions(out[0][2][rows], ref["action"], ref["logits"], u[rows], 2e-2)
+
+
+@pytest.mark.parametrize("bad_bits", [np.uint32(0x7fc00000), np.uint32(0xffc00000)])
+@pytest.mark.parametrize("stack,block", [(0, 0), (1, 1), (2, 0)])
+def test_relu_inside_a_block_turns_nan_sums_into_zero(stack, block, bad_bits):
+    """As in the oracle, max(NaN, 0) = 0: a filter of a block's first convolution with a NaN weight computes the bits of a
+    filter of zeros."""
+    import paper_2211_15023_amd as A
+    nt, pt, ns, ps, qp = policies(3)
+    x, u = torch.from_numpy(wl.make_frames_u8(5, first=11)).cuda(), torch.from_numpy(wl.make_uniforms(5)).cuda()
+    at = 5 * stack + 1 + 2 * block                                 # stack convolution, then two blocks of two
+    out = []
+    for bad in (bad_bits.view(np.float32), np.float32(0)):
+        params = [(n, w.copy(), b.copy()) for n, w, b in pt]
+        assert params[at][0].endswith("convA")
+        params[at][1][7] = 0
+        params[at][1][7, 0, 0, 0] = bad
+        params[at][2][7] = 0
+        out.append([t.cpu().numpy() for t in A.Policy(nt, "bf16", teacher_tensors(params)).forward(x, u)])
+    assert np.isfinite(out[0][0]).all()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
