@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, 2) void mlp_f32_kernel(const MlpF32Params p) {
     }
 }
 
-// one launch takes 2^29 states less 32 (with 32 of them per workgroup); a larger batch goes out in pieces
+// one launch takes 2^28 or 2^29 states less a workgroup's; a larger batch goes out in pieces
 template <int NT, int ST>
 hipError_t go(MlpF32Params p, hipStream_t s) {
     constexpr int64_t most = MAX_LAUNCH_ITEMS / 256 * (16 * ST);
@@ -190,14 +190,14 @@ hipError_t go(MlpF32Params p, hipStream_t s) {
 hipError_t launch_mlp_f32(const MlpF32Params& p, hipStream_t s) {
     if (p.B <= 0) return hipSuccess;
     if (p.n_hidden < 1 || p.n_hidden > MLP_F32_MAX_LAYERS || p.kb0 < 2 || (p.kb0 & 1) || p.kb0 > 4 * p.nt) return hipErrorInvalidValue;
-    // 32 states per workgroup halve the weight traffic, but up to 4096 states they leave compute units empty (24-256-256-4:
-    // 10.6 us with 16 states per workgroup against 15.4 at any batch up to 4096; 16.2 against 15.4 at 8192, 102 against 90
-    // at 65536).
-    const bool two = p.B > 4096;
+    // 32 states per workgroup halve the weight traffic, but leave compute units empty or with one workgroup where 16 would give
+    // each of them more.  us with 16 / 32: 24-256-256-4 at 4096 states 11.4 / 15.6, 4100 15.8 / 15.5, 8192 17.0 / 16.0, 65536
+    // 104 / 90; two layers of 128 at 8192 8.4 / 8.8, four of them 13.8 / 14.3, 16384 12.4 / 12.2 and 22.8 / 21.8, 65536 37.4 / 35.1
+    // and 76.8 / 69.6; two layers of 64 at 8192 6.0 / 6.4, 16384 7.7 / 7.6, 65536 18.2 / 19.3.
     switch (p.nt) {
-        case 1: return two ? go<1, 2>(p, s) : go<1, 1>(p, s);
-        case 2: return two ? go<2, 2>(p, s) : go<2, 1>(p, s);
-        case 4: return two ? go<4, 2>(p, s) : go<4, 1>(p, s);
+        case 1: return go<1, 1>(p, s);
+        case 2: return p.B > 8192 ? go<2, 2>(p, s) : go<2, 1>(p, s);
+        case 4: return p.B > 4096 ? go<4, 2>(p, s) : go<4, 1>(p, s);
     }
     return hipErrorInvalidValue;
 }

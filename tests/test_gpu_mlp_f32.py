@@ -1,7 +1,8 @@
 """The whole-network fp32 MLP kernel at the edges of its tiles: widths around 64 / 128 / 256, ragged observations and
-batches, one to three hidden layers, one to four head tiles, both state-tile counts (16 up to 4096 states, 32 above) and a
-width that stays on the layer-by-layer path.  The bound is the forward error bound of the sums themselves: a dot product
-of K terms in any order is within (K + 2) eps of sum |w||x| + |b|, and |W| carries the error of the layer before."""
+batches, one to three hidden layers, one to four head tiles, both state-tile counts (32 states per workgroup above 4096 states of
+256 units or 8192 of 128, else 16) and a width that stays on the layer-by-layer path.  The bound is the forward error bound of the
+sums themselves: a dot product of K terms in any order is within (K + 2) eps of sum |w||x| + |b|, and |W| carries the error of the
+layer before."""
 from types import SimpleNamespace
 
 import numpy as np
@@ -17,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (4, [64, 64], 2, True, 1), (4, [64, 64], 2, True, 33), (24, [256, 256], 4, True, 4096), (24, [256, 256], 4, True, 4113),
     (1, [1], 1, True, 17), (65, [63, 127, 128], 18, True, 50), (200, [255], 63, False, 31), (256, [256, 3, 129], 15, False, 16),
     (17, [33, 65], 16, True, 5000), (8, [257], 3, True, 40),
+    (17, [33, 65], 16, True, 8209), (9, [64, 30], 5, True, 8209),
 ])
 def test_whole_network_kernel(D, hidden, A, relu, B):
     import paper_2211_15023_amd as Amd
@@ -60,8 +62,8 @@ def test_infinite_observations_stay_in_their_units():
 
 
 def test_more_states_than_one_launch_takes():
-    """2^29 + 69 states: workgroups of 256 lanes over 32 states each exceed the work-items of one launch, so the batch goes out
-    in pieces.  The states repeat with a period that divides neither piece: every period must give the bits of the first."""
+    """2^29 + 69 states: workgroups of 256 lanes over 16 or 32 states each exceed the work-items of one launch, so the batch goes
+    out in pieces.  The states repeat with a period that divides neither piece: every period must give the bits of the first."""
     import paper_2211_15023_amd as Amd
     rng = np.random.default_rng(5)
     net = SimpleNamespace(name="mlp", obs_dtype="f32", obs_shape=(1,), n_actions=1, layers=[dict(kind="dense", cin=1, cout=8, relu=True)])
