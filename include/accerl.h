@@ -167,8 +167,10 @@ typedef enum {
 } accerl_tap;
 
 /*
- * Debug forward for parity tests: runs the same kernels as the forward calls up to and
- * including layer `layer` and copies one intermediate tensor to `out` (DEVICE, `out_bytes`
+ * Debug forward for parity tests: runs the network layer by layer up to and including layer
+ * `layer` (kernels that the forward calls fuse run one by one: the same bits, except that an
+ * ACCERL_FP32 policy's whole-network kernel adds in another order) and copies one intermediate
+ * tensor to `out` (DEVICE, `out_bytes`
  * must equal the tensor's size).  Image tensors are written channels-last, [B, H, W, Cs] with
  * Cs = C rounded up to a multiple of 4 (padding channels are zero); flat tensors [B, N].  Accumulator taps are student-only and include the integer bias and are
  * zero-point free (uint8 observations count as 0..255).  Recurrent policies: layers before the
@@ -248,8 +250,9 @@ int accerl_monitor_kl(const float* logits_original, const float* logits_smaller,
  * message and enqueues nothing (split the batch).  Every call on a GPU uses that GPU's one array: calls that
  * overlap in time on one GPU (different streams or threads) race and must be serialised by the caller; calls
  * in sequence need no clearing in between, since a pass overwrites every record that its fold reads.
- * With more than 1024 x 256 rows the row pass runs over 1024 workgroups where accerl_monitor_kl uses up to
- * 2048, so the fp64 sums may differ from it in their last bits; out_kl and out_entropy are identical.
+ * With more than 20 actions and more than 1024 x 256 rows the row pass runs over 1024 workgroups where
+ * accerl_monitor_kl uses up to 2048, so the fp64 sums may differ from it in their last bits; out_kl and
+ * out_entropy are identical.
  */
 int accerl_monitor_kl_noalloc(const float* logits_original, const float* logits_smaller, int64_t B, int A,
                               float* out_kl, float* out_entropy, double* out_stats, void* hip_stream);

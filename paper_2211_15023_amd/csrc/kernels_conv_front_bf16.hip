@@ -23,8 +23,8 @@
 //  * The second layer's 81 pixels are the tiles 0..47 and 33..80; the overlap is stored twice with the same bytes.
 //
 // What bounds it (clocks per observation inside the kernel): the two layers 3 900, 3 330 of them at the matrix cores' rate; the
-// conversion 1 400 to 1 600, at the vector ALUs' rate, with the matrix cores idle.  4096 states: 56 us (the generic kernels
-// 82 + 98 us).  Without effect on the time: bank conflicts of the fragment reads (six million clocks of 15 removed), the
+// conversion 1 400 to 1 600, at the vector ALUs' rate, with the matrix cores idle.  4096 states: 59 us (the generic kernels
+// 79 + 97 us; medians of kernel traces).  Without effect on the time: bank conflicts of the fragment reads (six million clocks of 15 removed), the
 // order of the loads, two accumulator chains or four in the first layer.
 #include <type_traits>
 

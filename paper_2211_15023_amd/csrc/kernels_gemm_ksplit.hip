@@ -6,8 +6,8 @@
 // What bounds it: bytes in flight.  A compute unit pulls about 25 bytes per clock out of the second-level cache and the
 // memory behind it however many loads its wavefronts keep open, so the tile is the smallest that still gives every unit one
 // workgroup: more units pull, and none of them twice.  The kernel this replaces walked K alone in each 64 x 64 workgroup
-// (64 workgroups on 256 units for 1024 states of a 3872 -> 256 layer): 42 -> 10.6 us there; 3136 -> 512 at 500 states
-// 28 -> 9.7 us, at 4096 states 35 -> 27 us (rocprofv3 / HIP events less the event cost).
+// (64 workgroups on 256 units for 1024 states of a 3872 -> 256 layer): 41 -> 10.2 us there; 3136 -> 512 at 500 states
+// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us (medians of kernel traces).
 #include <type_traits>
 
 #include "gemm_epilogue.h"

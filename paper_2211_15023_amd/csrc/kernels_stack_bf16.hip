@@ -7,7 +7,7 @@
 // Here a lane is a *column* of the image and walks down it: the fragments of an input row (three reads) serve the output
 // rows above, at and below it, so a row of 16 pixels costs three reads and five (16 channels) or nine (32 channels) MFMAs
 // per 16 output channels.  The three output rows in flight are three independent accumulator chains.  Measured at 1024
-// states: the three stacks 72 / 67 / 32 us where the layer-by-layer kernels took 283 / 163 / 85 us.
+// states: the three stacks 66 / 63 / 31 us (72 / 68 / 33 on another card) where the layer-by-layer kernels took 283 / 163 / 85 us.
 //
 //  * Lanes.  A workgroup of eight wavefronts owns G images.  The lanes of the blocks' tiles are (image, segment of rows,
 //    column) triples: 3 x 42, 3 x 21 and 2 x 2 x 11 of them fill 126 of 128, 63 of 64 and 44 of 48 lanes.  32-channel
