@@ -266,18 +266,21 @@ __global__ __launch_bounds__(MON_WAVES * 64) void is_ratio_small_kernel(const fl
 // mean distillation loss alone (loss_only).  Bound by the latency of its loads: a single wavefront took 32 rounds of them for
 // 2048 records (11 us; now 5.8 with sixteen of them, at most one per 64 records).  Up to 512 records one wavefront is the
 // faster one, without a barrier and a second round of exchanges (us, one / several: 1 record 1.7 / 4.4, 83 records 2.2 / 3.0,
-// 256 2.6 / 3.3, 384 3.2 / 3.6, 512 3.8 / 3.9, 640 4.2 / 4.1, 768 4.9 / 4.4, 1024 5.9 / 5.0).
+// 256 2.6 / 3.3, 384 3.2 / 3.6, 512 3.8 / 3.9, 640 4.2 / 4.1, 768 4.9 / 4.4, 1024 5.9 / 5.0), and as a kernel of its own it is
+// also cheaper to launch than one that may have 1024 lanes and has LDS (a call of 100 rows 12.2 us between calls against 12.5).
 constexpr int MON_FOLD_WAVES = 16;
-__global__ __launch_bounds__(MON_FOLD_WAVES * 64) void kl_stats_kernel(const double* __restrict__ parts, int n_parts, int64_t B, double* __restrict__ stats, int loss_only) {
-    __shared__ double red[MON_FOLD_WAVES][MON_NSTAT];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+template <int MOST>
+__global__ __launch_bounds__(MOST * 64) void kl_stats_kernel(const double* __restrict__ parts, int n_parts, int64_t B, double* __restrict__ stats, int loss_only) {
+    const int lane = threadIdx.x & 63;
     double s_kl = 0.0, s_sq = 0.0, s_mx = -1.0, s_h = 0.0, s_loss = 0.0;
-    for (int i = threadIdx.x; i < n_parts; i += blockDim.x) {
+    for (int i = threadIdx.x; i < n_parts; i += MOST > 1 ? blockDim.x : 64) {
         const double* p = parts + MON_NSTAT * i;
         s_kl += p[0]; s_sq += p[1]; s_mx = fmax(s_mx, p[2]); s_h += p[3]; s_loss += p[4];
     }
     s_kl = wave_sum(s_kl); s_sq = wave_sum(s_sq); s_h = wave_sum(s_h); s_mx = wave_max(s_mx); s_loss = wave_sum(s_loss);
-    if (waves > 1) {
+    if constexpr (MOST > 1) {
+        __shared__ double red[MOST][MON_NSTAT];
+        const int wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
         if (lane == 0) { red[wave][0] = s_kl; red[wave][1] = s_sq; red[wave][2] = s_mx; red[wave][3] = s_h; red[wave][4] = s_loss; }
         __syncthreads();
         if (threadIdx.x >= 64) return;
@@ -499,8 +502,12 @@ static int run_kl(const char* who, const float* logits_original, const float* lo
     rows<<<dim3(blocks), dim3(MON_WAVES * 64), lds, s>>>(logits_original, logits_smaller, B, A, out_kl, out_entropy, parts,
                                                                   v_o, v_s, beta, out_loss);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("kl_rows_kernel", e);
-    const int fold_waves = blocks <= 512 ? 1 : (blocks + 63) / 64 < MON_FOLD_WAVES ? (blocks + 63) / 64 : MON_FOLD_WAVES;
-    kl_stats_kernel<<<dim3(1), dim3(fold_waves * 64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
+    if (blocks <= 512) {
+        kl_stats_kernel<1><<<dim3(1), dim3(64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
+    } else {
+        const int waves = (blocks + 63) / 64 < MON_FOLD_WAVES ? (blocks + 63) / 64 : MON_FOLD_WAVES;
+        kl_stats_kernel<MON_FOLD_WAVES><<<dim3(1), dim3(waves * 64), 0, s>>>(parts, blocks, B, out_stats, loss_only);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail("kl_stats_kernel", e);
     return ACCERL_OK;
 }
