@@ -44,19 +44,16 @@ __global__ __launch_bounds__(GM_THREADS, PARTS > 1 ? 4 : 2) void gemm_kernel(con
             else acc_f[u][t] = *(const v4f*)((const float*)p.bias + n0);
         }
     }
-    v4f sum[GM_RT][GM_NT];                            // PARTS > 1: the bias and the parts so far
-    int part = 0, part_end = PARTS > 1 ? p.k_steps / PARTS : 0;
-    auto fold = [&]() {
+    // PARTS > 1: the bias and the parts so far
+    static_assert(PARTS == 1 || EL == EL_BF16, "integer sums do not depend on the order");
+    v4f sum[GM_RT][GM_NT];
+    int part = 0, part_end = p.k_steps / PARTS;
+    if constexpr (PARTS > 1) {
 #pragma unroll
         for (int u = 0; u < GM_RT; ++u)
 #pragma unroll
-            for (int t = 0; t < GM_NT; ++t) {
-                sum[u][t] = part == 0 ? acc_f[u][t] : sum[u][t] + acc_f[u][t];
-                acc_f[u][t] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-            }
-    };
-    static_assert(PARTS == 1 || EL == EL_BF16, "integer sums do not depend on the order");
-    if constexpr (PARTS > 1) fold();
+            for (int t = 0; t < GM_NT; ++t) { sum[u][t] = acc_f[u][t]; acc_f[u][t] = (v4f){0.0f, 0.0f, 0.0f, 0.0f}; }
+    }
 
     // Stage s0 of K: the weight fragments [GM_NT tiles][GM_KS steps] go through LDS (all four wavefronts
     // read them); a wavefront's own 16 states need no sharing: lane (j, g) loads state j's 16 bytes of K
@@ -172,7 +169,10 @@ __global__ __launch_bounds__(GM_THREADS, PARTS > 1 ? 4 : 2) void gemm_kernel(con
                         if (s0 + st + 1 == part_end) {
                             ++part;
                             part_end = (part + 1) * p.k_steps / PARTS;
-                            fold();
+#pragma unroll
+                            for (int u = 0; u < GM_RT; ++u)
+#pragma unroll
+                                for (int t = 0; t < GM_NT; ++t) { sum[u][t] += acc_f[u][t]; acc_f[u][t] = (v4f){0.0f, 0.0f, 0.0f, 0.0f}; }
                         }
                     }
                 }
@@ -182,14 +182,20 @@ __global__ __launch_bounds__(GM_THREADS, PARTS > 1 ? 4 : 2) void gemm_kernel(con
     }
 
     // ---- epilogue: lane holds features n0 .. n0+3 of state b
+    int ln = lane;
+    if constexpr (PARTS > 1) {                               // counted anew: a register kept for it through the loop is one too many
+        uint32_t zero = 0;
+        asm volatile("" : "+v"(zero));
+        ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+    }
 #pragma unroll
     for (int u = 0; u < GM_RT; ++u) {
-        const int64_t b = b0 + (wave * GM_RT + u) * 16 + j;
+        const int64_t b = b0 + (wave * GM_RT + u) * 16 + (ln & 15);
         if (b >= p.B) continue;
 #pragma unroll
         for (int t = 0; t < GM_NT; ++t) {
             if (t >= nts) continue;
-            const int n0 = (nt0 + t) * 16 + 4 * g;
+            const int n0 = (nt0 + t) * 16 + 4 * (ln >> 4);
             // stored activations: rows past N up to the row pitch are written too (zero weights and bias give zeros)
             if (n0 >= ((EPI == EPI_REQUANT || EPI == EPI_BF16) ? p.Np : p.N)) continue;
             if constexpr (EL == EL_I8) gemm_finish<EPI>(p, acc_i[u][t], b, n0);
