@@ -260,10 +260,10 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 // 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
 // bf16 layers beyond one 64 x 64 workgroup per compute unit take 128 x 64 tiles while those fill at most one round and the
 // eighth of K that a wavefront walks is at least eight steps (us, this / gemm_kernel: 3136 -> 512 at 3000 states 27 / 34, 4096
-// 28 / 34; 3872 -> 256 at 5000 31 / 49, 8192 40 / 51; but 1296 -> 128 at 10000 20.5 / 17), with a second to fourth round only for
+// 28 / 34; 3872 -> 256 at 5000 31 / 49, 8192 40 / 51; but 1296 -> 128 at 10000 20.5 / 16.5), with a second to fourth round only for
 // row-major states, which gemm_kernel fetches badly, and only if the last round is full (3872 -> 2048: 2000 states, two rounds,
-// 62 / 82, 4096, four, 121 / 151; 6000, six, 313 / 243; 3872 -> 256 at 9300 85 / 61; 3136 -> 512 at 4700 65 / 43, 6000 67 / 47,
-// 12000 110 / 91; 3136 -> 2048 at 2000 53 / 49, 6000 215 / 178).
+// 62 / 82, 4096, four, 121 / 151; 6000, six, 313 / 243; 3872 -> 256 at 9300 85 / 60; 3136 -> 512 at 4700 65 / 43, 6000 67 / 45,
+// 12000 110 / 89; 3136 -> 2048 at 2000 53 / 48, 6000 215 / 178).
 bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
     if (p.B <= 0 || p.k_steps < KSPLIT_PARTS) return false;
     const int64_t cus = conv_num_cus();
