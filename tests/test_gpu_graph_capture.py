@@ -8,17 +8,20 @@ import pytest
 import torch
 
 import workloads as wl
-from helpers import policies, student_tensors
+from helpers import policies, student_tensors, teacher_tensors
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("ci,B", [(2, 160), (1, 1024), (3, 21)])
-def test_forward_replays_from_a_graph(ci, B):
+@pytest.mark.parametrize("ci,B,role", [(2, 160, "student"), (1, 1024, "student"), (3, 21, "student"), (2, 160, "teacher"), (1, 1024, "teacher"), (3, 21, "teacher")])
+def test_forward_replays_from_a_graph(ci, B, role):
     import paper_2211_15023_amd as A
     A.load_library()
     nt, pt, ns, ps, qp = policies(ci)
-    pol = A.Policy(ns, "int8", student_tensors(qp), qp.act_scales)
+    if role == "student":
+        pol = A.Policy(ns, "int8", student_tensors(qp), qp.act_scales)
+    else:
+        pol = A.Policy(nt, "fp32" if ns.obs_dtype == "f32" else "bf16", teacher_tensors(pt))
 
     def states(first):
         if ns.obs_dtype == "u8":
@@ -34,7 +37,7 @@ def test_forward_replays_from_a_graph(ci, B):
         pol.forward(x, u, outputs=outs, stream=s)          # first call at this batch size: workspace, kernel attributes
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
-        print(f"capture cfg{ci} B={B}", flush=True)
+        print(f"capture cfg{ci} B={B} {role}", flush=True)
         with torch.cuda.graph(g, stream=s):
             pol.forward(x, u, outputs=outs, stream=s)
     torch.cuda.synchronize()
@@ -49,5 +52,5 @@ def test_forward_replays_from_a_graph(ci, B):
         pol.forward(x, u, outputs=eager_outs)               # eager work between the replays
         torch.cuda.synchronize()
         for a, b in zip(outs, eager_outs):
-            assert torch.equal(a, b), (ci, B, rep)
+            assert torch.equal(a, b), (ci, B, role, rep)
     pol.close()
