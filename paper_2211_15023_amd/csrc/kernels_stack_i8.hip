@@ -4,35 +4,43 @@
 // is read once and the stack's output written once, and every tensor in between lives in LDS or in registers.
 //
 // What bounds these layers is not the matrix cores but the vector instructions around them (requantization, pooling,
-// addressing): counters of the layer-by-layer kernels show 70-80 % of all issue slots taken by vector instructions.
-// The kernel is therefore organised to issue few of them:
+// addressing), four clocks of a SIMD each.  The kernel is therefore organised to issue few of them:
 //
-//  * conv + pool without storing the convolution.  Requantization is monotone per channel, so pooling the int32
-//    accumulators first and requantizing the maxima gives the same bytes with a quarter of the requantizations.  A
-//    pooled pixel (py, px) needs the conv outputs of rows 2py-1..2py+1 and columns 2px-1..2px+1.  MFMA columns are
-//    pooled pixels; per conv row the kernel multiplies the columns x = 2px (E) and x = 2px+1 (O): the vertical maximum
-//    over the three rows is an in-lane v_max3, the horizontal one max(E, O, O of the pixel to the left), the last term
-//    fetched with one DPP row shift.  Lane 0 of a tile only serves as left neighbour (tiles advance by 15 pixels), and
-//    a pooled row starts with a dummy that repeats the first pixel's windows, so that a maximum never picks up a
-//    value from outside its window.  Rows and columns outside the image are replaced by their nearest neighbour
-//    inside, which is part of the same window, so no -infinity is needed.
-//    16-channel layers: columns are "slots", the pooled pixels of the batch in raster order with the dummy in front
-//    of every row; one 8-byte table entry per slot gives the window addresses.  E and O are separate MFMAs on the
-//    same LDS reads: their windows together are the bordered pixels 2px .. 2px+3, whole aligned 16-byte chunks, which
-//    are multiplied with the planner's weight fragments (E) and with the same fragments shifted by one pixel (O).
-//    8-channel layers put E and O into the two halves of the 16 MFMA rows (the pixel packing of the layer-by-layer
-//    kernel: same weight fragments): E then sits in lanes 0-31 and O in lanes 32-63.  A tile is 15 pixels of one
-//    pooled row; two vertically adjacent pooled rows are processed together (they share a conv row: five MFMAs for
-//    the two tiles) and one v_permlane32_swap per register brings E and O of the upper row into the lower lanes and
-//    of the lower row into the upper lanes.  All addresses of a tile are a per-lane constant plus a wave-uniform row
-//    offset.
-//  * the pooled stream is written twice into LDS: max(x, 0) into a zero-bordered tile (the first block's conv A reads
-//    it) and x itself into a plain image (the skip connection).  The blocks run as in the single-block kernel, from
-//    LDS to LDS; the first block's output replaces the plain image in place, the second block's goes to memory.
+//  * Lanes are columns of the image and walk down it: a fragment read from LDS serves every output row whose window holds
+//    it, and a row's address is a per-lane constant plus an immediate.  (Tiles of 16 pixels in raster order read every
+//    window anew and looked each one up in a table: 9 instead of 2 further instructions beside the 12 of a requantized
+//    ReLU row of four channels, and two to three times the LDS reads.)  The lanes of a workgroup's wavefronts are (image,
+//    segment of rows, column) triples: 6 x 21 of 128 (a column is two pixels of 8 channels), 3 x 21 of 64, 5 x 11 of 64.
+//    Where the columns do not fill the lanes, the last ones repeat a column of the same wavefront: no predicates.
+//  * Block convolutions, 16 channels: a K step is one window row (three pixels; the fourth lane group reads the zeros of
+//    the left border), so the fragment of an input row is multiplied with the weights of its three places in a window.
+//    8 channels (two adjacent pixels fill the 16 MFMA rows): a fragment is two rows of four pixels, and two fragments are
+//    the four rows that two output rows need, multiplied with the weights of the upper and of the lower one: one read
+//    and four MFMAs per two rows.
+//  * Convolution + pooling without storing the convolution.  Requantization is monotone per channel, so pooling the int32
+//    accumulators first and requantizing the maxima gives the same bytes with a quarter of the requantizations.  A lane is
+//    a pooled pixel; the four rows of four pixels under it give both conv rows 2py, 2py+1 of its even and odd columns (E =
+//    2px, O = 2px+1).  The vertical maximum takes the lower conv row of the pooled row above, the horizontal one is
+//    max(E, O, O of the pixel to the left), the last term one DPP row shift; a tile's first lane only serves its neighbour
+//    (tiles advance by 15 pixels).  The first column needs no left neighbour: 16-channel layers, whose tiles hold several
+//    runs of columns, put a dummy in front of each run.  Rows and columns outside the image are replaced by their nearest
+//    neighbour inside, which is part of the same window, so no -infinity is needed.  8-channel layers: the MFMA rows are
+//    ordered so that a lane holds E and O of two channels (E and O in the two halves of a wavefront took a swap and two
+//    more maxima per register: 340 -> 320 us for the first stack).
+//  * The pooled stream goes to LDS twice: max(x, 0) where the first block's conv A reads it, and x itself where the inner
+//    tensor will be; the lanes that own its pixels take it into registers (a dword per row) before they write the inner
+//    tensor there.  From then on the skip connection stays in registers.  max(x, 0) of four packed bytes costs two
+//    instructions: v_perm_b32 spreads the signs of the 16-bit halves the bytes are packed from.
+//  * The weights of the block convolutions are read from LDS at the start of each phase (all of them in registers held
+//    the wavefronts at 188, two to a SIMD: 435 -> 345 us for the first stack at 128), a few stay in registers where LDS
+//    is what limits the workgroups.
 //  * the next batch's input bytes are requested at the start of the current batch's last phase and land while it runs.
 //
-// Arithmetic, fragments and constants are those of the layer-by-layer kernels (conv_kernel.h), so results are
-// bit-identical; the debug taps still run that path.  Network: the benchmark's IMPALA configuration (three such stacks).
+// Measured at 16384 states (kernel traces): 429 / 270 / 95 -> 325 / 182 / 72 us.  Vector issue 80 / 69 / 56 % of the clocks,
+// LDS pipe 56 / 42 / 36 %, matrix cores 27 / 39 / 35 %.
+//
+// Arithmetic and constants are those of the layer-by-layer kernels (conv_kernel.h), so results are bit-identical; the debug
+// taps still run that path.  Network: the benchmark's IMPALA configuration (three such stacks).
 #include <stdlib.h>
 
 #include <type_traits>
@@ -55,141 +63,157 @@ struct StackParams {
 
 constexpr int st_up16(int v) { return (v + 15) / 16 * 16; }
 
-template <bool U8, int CI, int HIN, int C, int G_, int NW_>
+template <bool U8, int CI, int HIN, int C, int G_, int SEG_, int PSEG_, int NW_, int WL_>
 struct StShape {
-    static constexpr int G = G_;
-    static constexpr int NW = NW_;                            // wavefronts per workgroup
-    static constexpr int ST_THREADS = NW * 64;
-    static constexpr int TU = (NW >= 8 || C == 16) ? 1 : 2;   // block column tiles per wavefront and step (two only where registers allow)
+    static constexpr int G = G_, SEG = SEG_, PSEG = PSEG_, WL = WL_;
+    static constexpr int NW = NW_, THREADS = NW * 64;         // wavefronts per workgroup
     static constexpr int P = 16 / C;                          // output pixels per MFMA column (2 for 8 channels)
     // input tile: one pixel of border on every side
     static constexpr int PITCH_IN = st_up16((HIN + 2) * CI);
     static constexpr int TILE_IN = (HIN + 2) * PITCH_IN;
-    static constexpr int CPR_C = ((3 + P - 1) * CI + 15) / 16;  // 16-byte chunks per kernel row
-    static constexpr int KS_C = (3 * CPR_C + 3) / 4;
     static constexpr int UPR_IN = U8 ? HIN / 4 : HIN * CI / 16; // staging units per image row
     static constexpr int UNITS_IN = HIN * UPR_IN;
     static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI;
-    static constexpr int PF = (G * UNITS_IN + ST_THREADS - 1) / ST_THREADS;
-    static constexpr int RD_E = ((2 * CI) % 16 == 0) ? 16 : 8;  // alignment of the E windows (byte offset 2 px CI)
-    // 16-channel layers: E (x = 2px) and O (x = 2px+1) windows together span the bordered pixels 2px .. 2px+3, which are
-    // whole aligned 16-byte chunks; the kernel reads CPRK chunks per kernel row once and multiplies them with two
-    // weight sets, the planner's (E) and the same shifted by one pixel (O): no second, misaligned read for O
-    static constexpr int CPRK = 4 * CI / 16;                    // chunks per kernel row as read (2 or 4)
-    static constexpr int KSK = (3 * CPRK + 3) / 4;              // MFMA steps over those chunks
+    static constexpr int PF = (G * UNITS_IN + THREADS - 1) / THREADS;
+    static constexpr int CPR_C = ((3 + P - 1) * CI + 15) / 16;  // 16-byte chunks per kernel row of the planner's fragments
+    static constexpr int KS_C = (3 * CPR_C + 3) / 4;
     // pooled stream
     static constexpr int H = (HIN - 1) / 2 + 1;
-    static constexpr int SLOTS = H * (H + 1);                  // per image: a dummy slot in front of every pooled row
+    static constexpr int RP = (H + PSEG - 1) / PSEG;            // pooled rows a lane walks
+    static constexpr int SLOTS = G * PSEG * (H + 1) - 1;        // a dummy slot in front of every column run but the first
+    static constexpr int NT1 = SLOTS <= 16 ? 1 : 1 + (SLOTS - 16 + 14) / 15;
     // residual blocks
     static constexpr int WP = H / P;                           // columns per image row
-    static constexpr int NPX = H * WP;                         // columns = 16-byte units per image
+    static constexpr int R = (H + SEG - 1) / SEG;              // rows a lane walks
+    static constexpr int NCOL = G * SEG * WP;                  // lanes
     static constexpr int IMG = H * H * C;
-    static constexpr int PITCH_B = st_up16((H + 2) * C);
-    static constexpr int TILE_B = (H + 2) * PITCH_B;
-    static constexpr int COLS = G * NPX;
-    static constexpr int TILES = (COLS + 15) / 16;
+    static constexpr int PITCH_B = st_up16((H + 3) * C);       // the pixel behind the border takes what the pooling's spare lanes write
+    // rows behind the border are read (and meet zero weights, or belong to a row that is not stored): the second of a pair
+    static constexpr int TILE_B = (H + 2 + (P == 2 || SEG * R > H ? 1 : 0)) * PITCH_B;
     static constexpr int CPR_B = ((3 + P - 1) * C + 15) / 16;
     static constexpr int KS_B = (3 * CPR_B + 3) / 4;
-    // conv + pool work items
-    static constexpr int NS = (H + 14) / 15;                   // 8-channel layers: tiles (strips of 15 pixels) per pooled row
-    static constexpr int NT1 = (G * SLOTS - 1 + 14) / 15;      // 16-channel layers: slot tiles per full batch
-    static constexpr int T1_BYTES = (P == 2) ? NS * 64 * 16 : st_up16(G * SLOTS * 8);
-    // LDS layout (bytes); 64 bytes of slack behind the input tiles: the last window of the last row reaches past it
+    static constexpr int NWB = P == 2 ? 4 : 3;                 // fragments of a block convolution
+    static constexpr int WB = P == 2 ? 4096 : 9 * 256;         // their bytes in LDS (three lane groups of 16-channel layers)
+    static constexpr int NWP = P == 2 ? 2 : CI == 8 ? 8 : 6;   // fragments of the stack convolution
+    // LDS layout (bytes)
     static constexpr int O_TX = st_up16(G * TILE_IN + 64);
     static constexpr int O_TM = O_TX + G * TILE_B;
-    static constexpr int O_RAW = O_TM + G * TILE_B;
-    static constexpr int O_T1 = O_RAW + G * IMG;
-    static constexpr int O_TABB = O_T1 + T1_BYTES;
-    static constexpr int O_CST = O_TABB + st_up16((TILES + 3 * NW * TU) * 16 * 2);   // the block loops read their table two steps ahead
+    static constexpr int O_W = O_TM + G * TILE_B;              // weight fragments of the first WL block convolutions
+    static constexpr int O_CST = O_W + WL * WB;
     static constexpr int LDS = O_CST + 5 * 2 * 16 * 4;
-    static_assert(H % P == 0 && IMG == NPX * 16 && (U8 ? (HIN % 4 == 0 && CI == 4) : (HIN * CI) % 16 == 0), "shape");
-    static_assert(G * TILE_IN + 64 < 65536 && G * TILE_B < 32768 && G * SLOTS < (1 << 20) && COLS < (1 << 20), "offsets");
-    static_assert(P == 1 || (G == 1 && KS_C == 1 && H % 2 == 0 && HIN % 2 == 0), "8-channel layers: one image, one MFMA step, even sizes");
-    static_assert(P == 2 || (KSK == KS_C && (CI == 8 || CI == 16)), "16-channel layers: 8 or 16 stored input channels");
+    static_assert(H % P == 0 && (U8 ? (HIN % 4 == 0 && CI == 4 && G == 1) : (HIN * CI) % 16 == 0), "shape");
+    static_assert(NCOL <= NW * 16 && NT1 <= NW * (P == 2 ? 99 : 1), "one tile of columns per wavefront");
+    static_assert(P == 1 || (G == 1 && KS_C == 1 && KS_B == 2 && H % 2 == 0 && HIN % 2 == 0), "8-channel layers: one image, even sizes");
+    static_assert(P == 2 || (KS_B == 3 && (CI == 8 || CI == 16) && (CI == 16 || HIN % 2 == 0)), "16-channel layers");
+    static_assert(LDS <= 160 * 1024 && SEG * R - H <= 1 && WL <= 4, "LDS, rows");
 };
 
-// max(v, v of the lane to its left in the same 16-lane row) for the lanes of rows `ROWS` (a 4-bit mask over the four
-// rows); lane 0 of a row, and the rows not selected, keep v.  One DPP instruction: lanes without a source are not
-// written and keep the destination's old value, which is v.  (The two idle cycles a DPP read needs after the vector
+// v[r] = max(v[r], v[r] of the lane to its left in the same 16-lane row); lane 0 of a row keeps its value: a DPP lane without
+// a source is not written and keeps the destination's old value.  (The two idle cycles a DPP read needs after the vector
 // instruction that wrote its source are spelled out: the compiler does not look inside the statement.)
-template <int ROWS>
-__device__ __forceinline__ int max_with_left(int v) {
-    int d = v;
-    if constexpr (ROWS == 0xC) asm("s_nop 1\n\tv_max_i32_dpp %0, %1, %1 row_shr:1 row_mask:0xc bank_mask:0xf" : "+v"(d) : "v"(v));
-    else asm("s_nop 1\n\tv_max_i32_dpp %0, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(v));
-    return d;
+__device__ __forceinline__ void max_with_left(int (&v)[4]) {
+    asm("s_nop 1\n\tv_max_i32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\tv_max_i32_dpp %1, %1, %1 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_max_i32_dpp %2, %2, %2 row_shr:1 row_mask:0xf bank_mask:0xf\n\tv_max_i32_dpp %3, %3, %3 row_shr:1 row_mask:0xf bank_mask:0xf"
+        : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+
+__device__ __forceinline__ v4i st_mfma(v4i a, v4i b, v4i c) { return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0); }
+
+// Four clamped results (rne_clamp127: the low 16 bits are the value as int16) -> their bytes, and max(., 0) of the bytes:
+// the two halves as 16-bit pairs, whose sign bits v_perm_b32 spreads over a byte each.
+struct StBytes { uint32_t raw, pos; };
+__device__ __forceinline__ StBytes st_pack(const int (&q)[4]) {
+    const uint32_t lo = __builtin_amdgcn_perm((uint32_t)q[1], (uint32_t)q[0], 0x05040100u);
+    const uint32_t hi = __builtin_amdgcn_perm((uint32_t)q[3], (uint32_t)q[2], 0x05040100u);
+    const uint32_t raw = __builtin_amdgcn_perm(hi, lo, 0x06040200u);
+    const uint32_t neg = __builtin_amdgcn_perm(hi, lo, 0x0b0a0908u);
+    return {raw, raw & ~neg};
 }
 
 // P23: the first convolution of both blocks keeps its accumulators below 2^23 (see requant_relu4_p23)
-template <bool U8, int CI, int HIN, int C, int G, int NW, int MINB, bool P23>
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool P23>
 __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams p) {
-    typedef StShape<U8, CI, HIN, C, G, NW> S;
-    constexpr int ST_THREADS = S::ST_THREADS, TU = S::TU;
+    typedef StShape<U8, CI, HIN, C, G, SEG, PSEG, NW, WL> S;
+    constexpr int T = S::THREADS;
     typedef int v2i __attribute__((ext_vector_type(2)));
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* tin = smem;                                    // G bordered input tiles
     char* tX = smem + S::O_TX;                           // G bordered tiles of max(stream, 0)
-    char* tM = smem + S::O_TM;                           // G bordered tiles of a block's inner tensor
-    char* xraw = smem + S::O_RAW;                        // G plain images of the stream (skip connection)
-    char* tab1 = smem + S::O_T1;                         // conv + pool: per (strip, lane) or per slot, see below
-    uint16_t* tabB = (uint16_t*)(smem + S::O_TABB);      // block column -> offset of its window in a bordered tile set
+    char* tM = smem + S::O_TM;                           // G bordered tiles of the pooled stream, then of a block's inner tensor
     int* cst = (int*)(smem + S::O_CST);                  // [conv][bias 16 | mult 16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
 
-    // ---- weights of all five convolutions and the chunk offsets of this lane
-    v4i wC[S::KS_C], wO[S::P == 1 ? S::KS_C : 1], wA1[S::KS_B], wB1[S::KS_B], wA2[S::KS_B], wB2[S::KS_B];
-    int koffC[S::KS_C], koffB[S::KS_B];
-    if constexpr (S::P == 2) {
+    // ---- weights of all five convolutions, in registers for the whole kernel
+    v4i wP[S::NWP], wR[4 - S::WL + 1][S::NWB];
+    {
+        // chunk (ky, cx) of the planner's fragments (cpr chunks per kernel row), zero outside the kernel
+        auto chunk = [&](int cv, int cpr, int ky, int cx, int mrow) -> v4i {
+            const bool in = ky >= 0 && ky < 3 && cx >= 0 && cx < cpr;
+            const int q = in ? ky * cpr + cx : 0;
+            const v4i v = p.w[cv][(q >> 2) * 64 + 16 * (q & 3) + mrow];
+            return in ? v : (v4i){0, 0, 0, 0};
+        };
+        if constexpr (S::P == 2) {
+            // a window is four input rows of four pixels, a row per lane group: the upper and the lower conv row under it.
+            // MFMA rows 4 g .. 4 g + 3: the even column of channels 2 g, 2 g + 1, then the odd one (the planner's rows are
+            // the eight channels of the even column, then of the odd one)
+            const int jr = 8 * ((j >> 1) & 1) + 2 * (j >> 2) + (j & 1);
+            wP[0] = chunk(0, S::CPR_C, g, 0, jr);
+            wP[1] = chunk(0, S::CPR_C, g - 1, 0, jr);
+        } else if constexpr (CI == 8) {
+            // four input rows of four pixels in two steps of two rows: [E | O][upper | lower][step]
 #pragma unroll
-        for (int st = 0; st < S::KS_C; ++st) {
-            const int q = 4 * st + g, ky = q / S::CPR_C, cx = q - ky * S::CPR_C;
-            koffC[st] = (ky < 3) ? ky * S::PITCH_IN + cx * 16 : 0;
-            wC[st] = p.w[0][st * 64 + lane];
+            for (int e = 0; e < 8; ++e) {
+                const int ky = 2 * (e & 1) + (g >> 1) - ((e >> 1) & 1), cx = g & 1;
+                const v4i own = chunk(0, S::CPR_C, ky, cx, j), prev = chunk(0, S::CPR_C, ky, cx - 1, j);   // a chunk is two pixels
+                wP[e] = e < 4 ? own : (v4i){prev[2], prev[3], own[0], own[1]};
+            }
+        } else {
+            // an input row of four pixels per step: [E | O][ky]
+#pragma unroll
+            for (int e = 0; e < 6; ++e) wP[e] = chunk(0, S::CPR_C, e % 3, e < 3 ? g : g - 1, j);        // a pixel is a whole chunk
         }
-    } else {
-        // chunk (ky, cx) of the planner's fragments (CPR_C chunks per kernel row), zero outside the kernel
-        auto host_chunk = [&](int ky, int cx) -> v4i {
-            if (ky >= 3 || cx < 0 || cx >= S::CPR_C) return (v4i){0, 0, 0, 0};
-            const int qh = ky * S::CPR_C + cx;
-            return p.w[0][(qh >> 2) * 64 + 16 * (qh & 3) + (lane & 15)];
+        auto block = [&](v4i (&w)[S::NWB], int cv) {
+            if constexpr (S::P == 2) {
+                // four rows of four pixels in two steps of two rows serve two output rows: [upper | lower][step]
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = chunk(cv, S::CPR_B, 2 * (e & 1) + (g >> 1) - (e >> 1), g & 1, j);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e) w[e] = chunk(cv, S::CPR_B, e, g, j);                        // a row of three pixels per step
+            }
         };
 #pragma unroll
-        for (int st = 0; st < S::KS_C; ++st) {
-            const int q = 4 * st + g, ky = q / S::CPRK, cx = q - ky * S::CPRK;
-            koffC[st] = (ky < 3) ? ky * S::PITCH_IN + cx * 16 : 0;
-            wC[st] = host_chunk(ky, cx);
-            if constexpr (CI == 16) {
-                wO[st] = host_chunk(ky, cx - 1);                 // a pixel is a whole chunk
-            } else {
-                const v4i prev = host_chunk(ky, cx - 1), own = host_chunk(ky, cx);   // a chunk is two pixels
-                wO[st] = (v4i){prev[2], prev[3], own[0], own[1]};
-            }
+        for (int cv = S::WL; cv < 4; ++cv) block(wR[cv - S::WL], cv + 1);
+        for (int cv = wave; cv < S::WL; cv += NW) {
+            v4i w[S::NWB];
+            block(w, cv + 1);
+#pragma unroll
+            for (int e = 0; e < S::NWB; ++e)
+                if (S::P == 2 || g < 3) *(v4i*)(smem + S::O_W + cv * S::WB + e * (S::WB / S::NWB) + lane * 16) = w[e];
         }
     }
+    const int woff = S::O_W + (S::P == 2 ? lane : 16 * min(g, 2) + j) * 16;
+    auto weights = [&](auto conv, v4i (&w)[S::NWB]) {    // fragments of block convolution 0 .. 3
+        constexpr int cv = decltype(conv)::value;
 #pragma unroll
-    for (int st = 0; st < S::KS_B; ++st) {
-        const int q = 4 * st + g, ky = q / S::CPR_B, cx = q - ky * S::CPR_B;
-        koffB[st] = (ky < 3) ? ky * S::PITCH_B + cx * 16 : 0;
-        wA1[st] = p.w[1][st * 64 + lane];
-        wB1[st] = p.w[2][st * 64 + lane];
-        wA2[st] = p.w[3][st * 64 + lane];
-        wB2[st] = p.w[4][st * 64 + lane];
-    }
+        for (int e = 0; e < S::NWB; ++e)
+            if constexpr (cv >= S::WL) w[e] = wR[cv - S::WL][e];
+            else w[e] = *(const v4i*)(smem + woff + cv * S::WB + e * (S::WB / S::NWB));
+    };
     // the weights are in their registers before any other load is issued: the waits the compiler places in the batch
     // loop then only ever concern the loads of the next batch, not these
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
 
-    // ---- staging: which bytes a lane requests, and where they land in the input tiles, is the same for every batch
+    // ---- staging: unit u of the batch is one dword of each of the four planes, or 16 bytes of the images
     v4i pre[S::PF];
-    uint32_t soff[S::PF];
     int doff[S::PF];
 #pragma unroll
     for (int i = 0; i < S::PF; ++i) {
-        const int u = min(tid + i * ST_THREADS, G * S::UNITS_IN - 1);
+        const int u = min(tid + i * T, G * S::UNITS_IN - 1);
         const int img = u / S::UNITS_IN, w = u - img * S::UNITS_IN, row = w / S::UPR_IN, cu = w - row * S::UPR_IN;
-        soff[i] = U8 ? (uint32_t)(img * S::IMG_IN + row * HIN + 4 * cu) : (uint32_t)(img * S::IMG_IN + w * 16);
         doff[i] = img * S::TILE_IN + (row + 1) * S::PITCH_IN + CI + cu * 16;
     }
     const int64_t n_batch = (p.B + G - 1) / G;
@@ -200,14 +224,14 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
-            const uint32_t so = (tid + i * ST_THREADS <= last) ? soff[i] : 0u;     // a unit that does not exist re-reads unit 0
+            const uint32_t u = (uint32_t)min(tid + i * T, last);        // a unit that does not exist re-reads the last one
             if constexpr (U8) {
                 v4i v;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(c * HIN * HIN) + so);
+                for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(c * HIN * HIN) + 4u * u);
                 pre[i] = v;
             } else {
-                pre[i] = *(const v4i*)(src + so);
+                pre[i] = *(const v4i*)(src + 16u * u);
             }
         }
     };
@@ -216,7 +240,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         const int total = (int)((p.B - b0 < G) ? (p.B - b0) : G) * S::UNITS_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
-            if (tid + i * ST_THREADS >= total) break;
+            if (tid + i * T >= total) break;
             const v4i v = pre[i];
             if constexpr (U8) {
                 // one dword (4 pixels) of each plane -> four channels-last pixels, stored as obs - 128
@@ -240,49 +264,41 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     int64_t batch = blockIdx.x;
     if (batch < n_batch) prefetch(batch);
 
-    // ---- once per workgroup: borders, tables, constants
+    // ---- once per workgroup: borders (only interiors are written later), constants
     {
         const int padv = U8 ? (int)0x80808080u : 0;       // a padding pixel is the observation value 0
-        for (int i = tid; i < S::O_TX / 4; i += ST_THREADS) ((int*)tin)[i] = padv;
-        for (int i = tid; i < (S::O_RAW - S::O_TX) / 4; i += ST_THREADS) ((int*)tX)[i] = 0;
-        if constexpr (S::P == 2) {
-            // per (strip, lane): window offset in an input row (chunk offset included), offsets of the lane's four
-            // output bytes in the bordered tile and in the plain image (lanes 32-63 end up with the lower pooled row),
-            // and whether the lane's pixel exists.  Pixel of lane j of strip s: 15 s + j - 1.
-            for (int i = tid; i < S::NS * 64; i += ST_THREADS) {
-                const int st = i >> 6, l = i & 63, jj = l & 15, gg = l >> 4;
-                const int px = 15 * st + jj - 1, pc = min(max(px, 0), S::H - 1);
-                const int ky = gg / S::CPR_C, cx = gg - ky * S::CPR_C;
-                const int kf = (ky < 3) ? ky * S::PITCH_IN + cx * 16 : 0;
-                ((v4i*)tab1)[i] = (v4i){2 * pc * CI + kf, (pc + 1) * C + 4 * (gg & 1) + (gg >> 1) * S::PITCH_B,
-                                        pc * C + 4 * (gg & 1) + (gg >> 1) * S::H * C, (jj >= 1 && px < S::H) ? 1 : 0};
-            }
-        } else {
-            // per slot (image, pooled row, dummy | pixel): offsets of the E window in the first and in the middle input
-            // row (odd sizes: bit 0 of the first = no row below, of the second = no column to the right), offsets of the
-            // pixel's output in the bordered tile and in the plain image (bit 15 = the slot is a dummy)
-            for (int sidx = tid; sidx < G * S::SLOTS; sidx += ST_THREADS) {
-                const int img = sidx / S::SLOTS, si = sidx - img * S::SLOTS, py = si / (S::H + 1), ps = si - py * (S::H + 1);
-                const int px = max(ps - 1, 0);
-                const int r0 = max(2 * py - 1, 0), r1 = 2 * py;
-                const int xe = 2 * px * CI + img * S::TILE_IN;
-                const int nb = (2 * py + 1 > HIN - 1) ? 1 : 0, nr = (ps > 0 && 2 * px + 1 > HIN - 1) ? 1 : 0;
-                const uint32_t a0 = (uint32_t)(r0 * S::PITCH_IN + xe) | (uint32_t)nb, a1 = (uint32_t)(r1 * S::PITCH_IN + xe) | (uint32_t)nr;
-                const uint32_t ox = (uint32_t)(img * S::TILE_B + (py + 1) * S::PITCH_B + (px + 1) * C) | (ps == 0 ? 0x8000u : 0u);
-                const uint32_t orr = (uint32_t)(img * S::IMG + (py * S::H + px) * C);
-                ((v2i*)tab1)[sidx] = (v2i){(int)(a0 | (a1 << 16)), (int)(ox | (orr << 16))};
-            }
-        }
-        for (int c = tid; c < (S::TILES + 3 * NW * TU) * 16; c += ST_THREADS) {
-            const int cc = min(c, S::COLS - 1);            // columns past the end repeat the last one (never stored)
-            const int img = cc / S::NPX, w = cc - img * S::NPX, y = w / S::WP, xp = w - y * S::WP;
-            tabB[c] = (uint16_t)(img * S::TILE_B + y * S::PITCH_B + xp * 16);
-        }
-        for (int i = tid; i < 5 * 16; i += ST_THREADS) {
+        for (int i = tid; i < S::O_TX / 4; i += T) ((int*)tin)[i] = padv;
+        for (int i = tid; i < (S::O_W - S::O_TX) / 4; i += T) ((int*)tX)[i] = 0;
+        for (int i = tid; i < 5 * 16; i += T) {
             const int cv = i >> 4, n = i & 15;
             cst[cv * 32 + n] = p.bias[cv][n];
             ((float*)cst)[cv * 32 + 16 + n] = p.mult[cv][n];
         }
+    }
+
+    // ---- this lane's column of the blocks; lanes past the last column repeat it (the same bytes written twice)
+    const int n = wave * 16 + j, nc = min(n, S::NCOL - 1);
+    const int bimg = nc / (SEG * S::WP), bseg = (nc - bimg * SEG * S::WP) / S::WP, bcol = nc - (bimg * SEG + bseg) * S::WP;
+    const int row0 = bseg * S::R;
+    const bool lastrow = SEG * S::R == S::H || row0 + S::R <= S::H;   // the last row a lane walks is inside the image
+    const int bpos = bimg * S::TILE_B + row0 * S::PITCH_B + bcol * 16;
+    // (16-channel layers have no fourth chunk: its lanes read the zeros of the left border)
+    const int boff = S::P == 2 ? bpos + (g >> 1) * S::PITCH_B + (g & 1) * 16 : g < 3 ? bpos + g * 16 : bpos - bcol * 16;
+    const int bown = bpos + S::PITCH_B + C + 4 * g;       // the column's own pixel(s) sit one row and one pixel inside its window
+    const int brel = (row0 * S::WP + bcol) * 16 + 4 * g;  // in a plain image
+    // ---- this lane's column of the pooling (16-channel layers): slots are the column runs (image, segment), each behind a
+    //      dummy that repeats its first pixel; a tile's first lane repeats the last slot of the tile before it
+    int ppos = 0, pout = 0, pfirst = 0, plast = 0;
+    if constexpr (S::P == 1) {
+        const int s = min(15 * wave + j, S::SLOTS - 1) + 1, run = s / (S::H + 1), at = s - run * (S::H + 1);
+        const int px = max(at - 1, 0), img = run / PSEG, p0 = min((run - img * PSEG) * S::RP, S::H - S::RP);
+        const bool st = at > 0 && 15 * wave + j < S::SLOTS && (wave == 0 || j > 0);
+        // (odd sizes: the last pooled pixel's columns are the last two, its window starts a pixel earlier)
+        const int wx = 2 * px - ((HIN & 1) && px == S::H - 1 ? 1 : 0);
+        ppos = img * S::TILE_IN + 2 * p0 * S::PITCH_IN + wx * CI + (CI == 8 ? (g >> 1) * S::PITCH_IN + (g & 1) * 16 : g * 16);
+        pfirst = p0 > 0 ? -2 * S::PITCH_IN : 0;            // the window above, for the conv row shared with it
+        pout = img * S::TILE_B + (p0 + 1) * S::PITCH_B + (st ? px + 1 : S::H + 2) * C + 4 * g;
+        if ((HIN & 1) && p0 + S::RP == S::H) plast = -S::PITCH_IN;   // no conv row below the last: the one above once more
     }
     __syncthreads();
 
@@ -292,218 +308,207 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         const int64_t b0 = batch * G;
         const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
 
-        // ---- stack convolution + max-pool, in registers -> the bordered tile of max(x, 0) and the plain image
+        // ---- stack convolution + max-pool, in registers -> bordered tiles of max(x, 0) and of x itself
         {
-            const v4i biC = *(const v4i*)(cst + 4 * g);
-            const v4f mlC = *(const v4f*)(cst + 16 + 4 * g);
-            auto finish = [&](const v4i& pooled, int ox, int orw, bool ok) {
+            v4i biC = *(const v4i*)(cst + 4 * g);
+            v4f mlC = *(const v4f*)(cst + 16 + 4 * g);
+            if constexpr (S::P == 2) {                   // channels 2 g, 2 g + 1 twice
+                const int b0 = cst[2 * g], b1 = cst[2 * g + 1];
+                const float m0 = ((const float*)cst)[16 + 2 * g], m1 = ((const float*)cst)[16 + 2 * g + 1];
+                biC = (v4i){b0, b1, b0, b1};
+                mlC = (v4f){m0, m1, m0, m1};
+            }
+            auto requant = [&](const int (&pooled)[4]) {
                 int q[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) q[r] = rne_clamp127((float)pooled[r] * mlC[r]);
-                const uint32_t w = pack_low_bytes(q);
-                if (ok) {
-                    *(uint32_t*)(tX + ox) = relu_i8x4(w);
-                    *(uint32_t*)(xraw + orw) = w;
-                }
+                return st_pack(q);
             };
             if constexpr (S::P == 2) {
-                // work item: (pair of pooled rows rp, strip): conv rows 4rp-1 .. 4rp+3, the middle one shared.  The five
-                // window reads of the next item are issued before the current item's maxima are formed and requantized.
-                constexpr int N_IT = (S::H / 2) * S::NS;
-                auto issue = [&](int it, v4i (&o)[5], v4i& e, int& rp) {
-                    it = min(it, N_IT - 1);                  // past the end: a valid item, read and dropped
-                    rp = it / S::NS;
-                    e = ((const v4i*)tab1)[(it - rp * S::NS) * 64 + lane];
-                    const char* a0 = tin + e[0] + max(4 * rp - 1, 0) * S::PITCH_IN;
-                    const char* a1 = tin + e[0] + 4 * rp * S::PITCH_IN;
-                    o[0] = read_chunk<S::RD_E>(a0);
+                // work item: (pair of pooled rows rp, strip of pixels 15 s .. 15 s + 15): the windows of both rows and of the
+                // row above, whose lower conv row they share
+                constexpr int NS = (S::H - 1 + 14) / 15, N_IT = S::H / 2 * NS;
+                const char* a = tin + j * 2 * CI + g * S::PITCH_IN;
+                char* d = tX + 2 * g + S::PITCH_B;
+                const uint64_t m_mid = __ballot(j > 0), m_last = __ballot(j > 0 && 15 * (NS - 1) + j < S::H);
+#pragma unroll 2
+                for (int i = 0; i < (N_IT + NW - 1) / NW; ++i) {
+                    const int it = min(wave + i * NW, N_IT - 1);      // past the end: the last one's bytes once more
+                    const int rp = it / NS, s = it - rp * NS;
+                    const char* w0 = a + s * 30 * CI + 4 * rp * S::PITCH_IN;
+                    const v4i fm = read_chunk<8>(a + s * 30 * CI + max(4 * rp - 2, 0) * S::PITCH_IN);
+                    const v4i f0 = read_chunk<8>(w0), f1 = read_chunk<8>(w0 + 2 * S::PITCH_IN);
+                    const v4i c0 = st_mfma(wP[1], fm, biC), c1 = st_mfma(wP[0], f0, biC), c2 = st_mfma(wP[1], f0, biC);
+                    const v4i c3 = st_mfma(wP[0], f1, biC), c4 = st_mfma(wP[1], f1, biC);
+                    // a lane holds two channels of both columns: upper pooled row in pooled[0], [1], lower in [2], [3]
+                    int vo[4] = {max(max(c0[2], c1[2]), c2[2]), max(max(c0[3], c1[3]), c2[3]), max(max(c2[2], c3[2]), c4[2]), max(max(c2[3], c3[3]), c4[3])};
+                    max_with_left(vo);
+                    const int pooled[4] = {max(max(max(c0[0], c1[0]), c2[0]), vo[0]), max(max(max(c0[1], c1[1]), c2[1]), vo[1]),
+                                           max(max(max(c2[0], c3[0]), c4[0]), vo[2]), max(max(max(c2[1], c3[1]), c4[1]), vo[3])};
+                    const StBytes w = requant(pooled);
+                    const bool ok = __builtin_amdgcn_inverse_ballot_w64(s == 0 ? ~0ull : s == NS - 1 ? m_last : m_mid);
+                    char* o = d + 2 * rp * S::PITCH_B + (ok ? (s * 15 + 1) * C + j * C : (S::H + 2) * C);
+                    *(uint16_t*)o = (uint16_t)w.pos;
+                    *(uint16_t*)(o + S::PITCH_B) = (uint16_t)(w.pos >> 16);
+                    *(uint16_t*)(o + S::O_TM - S::O_TX) = (uint16_t)w.raw;
+                    *(uint16_t*)(o + S::O_TM - S::O_TX + S::PITCH_B) = (uint16_t)(w.raw >> 16);
+                }
+            } else if (wave < S::NT1) {
+                auto out = [&](int k, v4i e, v4i o) {
+                    int vo[4] = {o[0], o[1], o[2], o[3]}, pooled[4];
+                    max_with_left(vo);
 #pragma unroll
-                    for (int k = 1; k < 5; ++k) o[k] = read_chunk<S::RD_E>(a1 + (k - 1) * S::PITCH_IN);
+                    for (int r = 0; r < 4; ++r) pooled[r] = max(e[r], vo[r]);
+                    const StBytes w = requant(pooled);
+                    *(uint32_t*)(tX + pout + k * S::PITCH_B) = w.pos;
+                    *(uint32_t*)(tM + pout + k * S::PITCH_B) = w.raw;
                 };
-                v4i oA[5], oB[5], eA, eB;
-                int rpA, rpB;
-                // E in lanes 0-31, O in lanes 32-63 of each row's tile: O takes its left neighbour in, then one swap per
-                // register puts E and O of the upper row into the lower lanes and of the lower row into the upper
-                auto pool_store = [&](const v4i (&c)[5], const v4i& e, int rp) {
-                    v4i pooled;
+                auto max3 = [](v4i x, v4i y, v4i z) {
+                    v4i m;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int x0 = max_with_left<0xC>(max(max(c[0][r], c[1][r]), c[2][r]));
-                        const int x1 = max_with_left<0xC>(max(max(c[2][r], c[3][r]), c[4][r]));
-                        const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)x0, (unsigned)x1, false, false);
-                        pooled[r] = max((int)sw[0], (int)sw[1]);
+                    for (int r = 0; r < 4; ++r) m[r] = max(max(x[r], y[r]), z[r]);
+                    return m;
+                };
+                const char* a = tin + ppos;
+                if constexpr (CI == 8) {
+                    auto conv = [&](const v4i* w, v4i lo, v4i hi) { return st_mfma(w[1], hi, st_mfma(w[0], lo, biC)); };
+                    v4i f0 = *(const v4i*)a;
+                    // the lower conv row of the window above (for the first pooled row: of its own window)
+                    v4i cE, cO;
+                    {
+                        const v4i m0 = *(const v4i*)(a + pfirst), m1 = *(const v4i*)(a + pfirst + 2 * S::PITCH_IN);
+                        cE = conv(wP + 2, m0, m1);
+                        cO = conv(wP + 6, m0, m1);
                     }
-                    finish(pooled, e[1] + (2 * rp + 1) * S::PITCH_B, e[2] + 2 * rp * S::H * C, e[3] != 0);
-                };
-                if constexpr (NW >= 8) {
-                    // four wavefronts per SIMD hide the read latency by themselves: one item at a time, fewer registers
-                    for (int it = wave; it < N_IT; it += NW) {
-                        issue(it, oA, eA, rpA);
-                        v4i c[5];
 #pragma unroll
-                        for (int k = 0; k < 5; ++k) c[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wC[0], oA[k], biC, 0, 0, 0);
-                        pool_store(c, eA, rpA);
+                    for (int k = 0; k < S::RP; ++k) {
+                        const v4i f1 = *(const v4i*)(a + (2 * k + 2) * S::PITCH_IN);
+                        const v4i e0 = conv(wP, f0, f1), e1 = conv(wP + 2, f0, f1), o0 = conv(wP + 4, f0, f1), o1 = conv(wP + 6, f0, f1);
+                        out(k, max3(cE, e0, e1), max3(cO, o0, o1));
+                        cE = e1; cO = o1; f0 = f1;
                     }
                 } else {
-                issue(wave, oA, eA, rpA);
-                for (int it = wave; it < N_IT; it += 2 * NW) {
-                    v4i c[5];
+                    auto conv = [&](const v4i* w, v4i r0, v4i r1, v4i r2) { return st_mfma(w[2], r2, st_mfma(w[1], r1, st_mfma(w[0], r0, biC))); };
+                    auto row = [&](int y) { return *(const v4i*)(a + y * S::PITCH_IN); };
+                    v4i f0 = row(0), f1 = row(1), cE, cO;
+                    {
+                        const char* m = a + pfirst;
+                        const v4i m1 = *(const v4i*)(m + S::PITCH_IN), m2 = *(const v4i*)(m + 2 * S::PITCH_IN), m3 = *(const v4i*)(m + 3 * S::PITCH_IN);
+                        cE = conv(wP, m1, m2, m3);
+                        cO = conv(wP + 3, m1, m2, m3);
+                    }
 #pragma unroll
-                    for (int k = 0; k < 5; ++k) c[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wC[0], oA[k], biC, 0, 0, 0);
-                    issue(it + NW, oB, eB, rpB);
-                    pool_store(c, eA, rpA);
-                    if (it + NW >= N_IT) break;
-#pragma unroll
-                    for (int k = 0; k < 5; ++k) c[k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wC[0], oB[k], biC, 0, 0, 0);
-                    issue(it + 2 * NW, oA, eA, rpA);
-                    pool_store(c, eB, rpB);
-                }
-                }
-            } else {
-                constexpr bool ODD = (HIN & 1) != 0;
-                const int n_slots = gc * S::SLOTS;
-                const int n_tiles = (n_slots - 1 + 14) / 15;
-                for (int t = wave; t < n_tiles; t += NW) {
-                    const int s = 15 * t + j;
-                    const v2i e = ((const v2i*)tab1)[min(s, n_slots - 1)];
-                    const uint32_t ex = (uint32_t)e[0], ey = (uint32_t)e[1];
-                    const int a0 = (int)(ex & (ODD ? 0xfffeu : 0xffffu)), a1 = (int)((ex >> 16) & (ODD ? 0xfffeu : 0xffffu));
-                    const int d2 = (ODD && (ex & 1u)) ? 0 : S::PITCH_IN;            // no row below: repeat the middle one
-                    const bool no_right = ODD && ((ex >> 16) & 1u);                 // no column to the right: O repeats E
-                    v4i acc[2][3];
-#pragma unroll
-                    for (int eo = 0; eo < 2; ++eo)
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) acc[eo][k] = biC;
-#pragma unroll
-                    for (int st = 0; st < S::KS_C; ++st) {
-                        const char* w0 = tin + a0 + koffC[st];
-                        const char* w1 = tin + a1 + koffC[st];
-                        const char* wr[3] = {w0, w1, w1 + d2};
-#pragma unroll
-                        for (int k = 0; k < 3; ++k) {
-                            const v4i b = *(const v4i*)wr[k];      // one aligned read serves the E and the O window
-                            acc[0][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wC[st], b, acc[0][k], 0, 0, 0);
-                            acc[1][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wO[st], b, acc[1][k], 0, 0, 0);
+                    for (int k = 0; k < S::RP; ++k) {
+                        const v4i f2 = row(2 * k + 2);
+                        const v4i e0 = conv(wP, f0, f1, f2), o0 = conv(wP + 3, f0, f1, f2);
+                        v4i e1 = e0, o1 = o0, f3 = f2;
+                        if (!(HIN & 1) || k + 1 < S::RP) {
+                            f3 = row(2 * k + 3);
+                            e1 = conv(wP, f1, f2, f3);
+                            o1 = conv(wP + 3, f1, f2, f3);
+                        } else if (PSEG > 1) {
+                            const char* m = a + plast + (2 * k + 1) * S::PITCH_IN;
+                            const v4i m1 = *(const v4i*)m, m2 = *(const v4i*)(m + S::PITCH_IN), m3 = *(const v4i*)(m + 2 * S::PITCH_IN);
+                            e1 = conv(wP, m1, m2, m3);
+                            o1 = conv(wP + 3, m1, m2, m3);
                         }
+                        out(k, max3(cE, e0, e1), max3(cO, o0, o1));
+                        cE = e1; cO = o1; f0 = f2; f1 = f3;
                     }
-                    v4i pooled;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int ve = max(max(acc[0][0][r], acc[0][1][r]), acc[0][2][r]);
-                        int vo = max(max(acc[1][0][r], acc[1][1][r]), acc[1][2][r]);
-                        if (no_right) vo = ve;
-                        pooled[r] = max(ve, max_with_left<0xF>(vo));
-                    }
-                    finish(pooled, (int)(ey & 0x7fffu) + 4 * g, (int)(ey >> 16) + 4 * g, s < n_slots && j >= 1 && !(ey & 0x8000u));
                 }
             }
         }
         __syncthreads();
 
-        const int total = gc * S::NPX;
-        const int n_tiles = (total + 15) >> 4;
-        // Block convolutions: TU column tiles per wavefront and step (tiles t, t + NW, ...); the window reads of the next
-        // step are issued before the current step's epilogue, and the table entries two steps ahead of their use.
-        constexpr int STEP = NW * TU;
-        auto load_ops = [&](const char* src, const int (&b)[TU], v4i (&o)[TU][S::KS_B]) {
+        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k
+        auto walk = [&](const char* src, const v4i (&w)[S::NWB], v4i b, auto&& done) {
+            const char* a = src + boff;
+            if constexpr (S::P == 2) {
+                v4i f0 = *(const v4i*)a;
 #pragma unroll
-            for (int st = 0; st < S::KS_B; ++st)
+                for (int k = 0; k < S::R; k += 2) {
+                    const v4i f1 = *(const v4i*)(a + (k + 2) * S::PITCH_B);
+                    const v4i u = st_mfma(w[1], f1, st_mfma(w[0], f0, b));
+                    if (k + 1 < S::R) {
+                        const v4i l = st_mfma(w[3], f1, st_mfma(w[2], f0, b));
+                        done(k, u);
+                        done(k + 1, l);
+                    } else {
+                        done(k, u);
+                    }
+                    f0 = f1;
+                }
+            } else {
+                auto row = [&](int y) { return *(const v4i*)(a + y * S::PITCH_B); };
+                v4i f0 = row(0), f1 = row(1);
 #pragma unroll
-                for (int u = 0; u < TU; ++u) o[u][st] = *(const v4i*)(src + b[u] + koffB[st]);
+                for (int k = 0; k < S::R; ++k) {
+                    const v4i f2 = row(k + 2);
+                    done(k, st_mfma(w[2], f2, st_mfma(w[1], f1, st_mfma(w[0], f0, b))));
+                    f0 = f1; f1 = f2;
+                }
+            }
         };
         // ---- a block's first convolution: max(x, 0) -> inner tensor, requantized with the fused ReLU
-        auto conv_a = [&](const v4i (&wA)[S::KS_B], int cv) {
-            const v4i biA = *(const v4i*)(cst + cv * 32 + 4 * g) + (P23 ? P23_MAGIC : 0);
-            const v4f mlA = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
-            const v4f cA = mlA * -8388608.0f;
-            int bN[TU], bNN[TU];
-#pragma unroll
-            for (int u = 0; u < TU; ++u) { bN[u] = tabB[(wave + NW * u) * 16 + j]; bNN[u] = tabB[(wave + STEP + NW * u) * 16 + j]; }
-            v4i ops[TU][S::KS_B];
-            load_ops(tX, bN, ops);
-            for (int t = wave; t < n_tiles; t += STEP) {
-                int base[TU];
-                v4i acc[TU];
-#pragma unroll
-                for (int u = 0; u < TU; ++u) { base[u] = bN[u]; acc[u] = biA; }
-#pragma unroll
-                for (int st = 0; st < S::KS_B; ++st)
-#pragma unroll
-                    for (int u = 0; u < TU; ++u) acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wA[st], ops[u][st], acc[u], 0, 0, 0);
-#pragma unroll
-                for (int u = 0; u < TU; ++u) { bN[u] = bNN[u]; bNN[u] = tabB[(t + 2 * STEP + NW * u) * 16 + j]; }
-                load_ops(tX, bN, ops);
-#pragma unroll
-                for (int u = 0; u < TU; ++u) {
-                    const uint32_t w = requant_relu4_p23<P23>(acc[u], mlA, cA);
-                    // the column's own pixel(s) sit one row and one pixel inside its window
-                    if ((t + NW * u) * 16 + j < total) *(uint32_t*)(tM + base[u] + S::PITCH_B + C + 4 * g) = w;
-                }
-            }
+        auto conv_a = [&](const v4i (&w)[S::NWB], int cv) {
+            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (P23 ? P23_MAGIC : 0);
+            const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
+            const v4f cc = ml * -8388608.0f;
+            walk(tX, w, bi, [&](int k, v4i acc) {
+                const uint32_t y = requant_relu4_p23<P23>(acc, ml, cc);
+                if (k + 1 < S::R || lastrow) *(uint32_t*)(tM + bown + k * S::PITCH_B) = y;
+            });
         };
-        // ---- a block's second convolution, joined with the block's input; LAST: to memory, else back into LDS
-        auto conv_b = [&](const v4i (&wB)[S::KS_B], int cv, float rr, auto last) {
+        uint32_t x[S::R];                                 // the stream under this lane, four channels per row
+        // ---- a block's second convolution, joined with the block's input; LAST: to memory, else back into registers and LDS
+        auto conv_b = [&](const v4i (&w)[S::NWB], int cv, float rr, auto last) {
             constexpr bool LAST = decltype(last)::value;
-            const v4i biB = *(const v4i*)(cst + cv * 32 + 4 * g);
-            const v4f mlB = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
-            int8_t* outp = p.out + b0 * (int64_t)S::IMG;
-            int bN[TU], bNN[TU];
-            uint32_t xn[TU];
+            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g);
+            const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
+            char* outp = (char*)p.out + b0 * (int64_t)S::IMG + (uint32_t)(bimg * S::IMG + brel);
+            walk(tM, w, bi, [&](int k, v4i acc) {
+                int q[4];
 #pragma unroll
-            for (int u = 0; u < TU; ++u) {
-                bN[u] = tabB[(wave + NW * u) * 16 + j];
-                bNN[u] = tabB[(wave + STEP + NW * u) * 16 + j];
-                xn[u] = *(const uint32_t*)(xraw + (uint32_t)min((wave + NW * u) * 16 + j, total - 1) * 16u + 4 * g);
-            }
-            v4i ops[TU][S::KS_B];
-            load_ops(tM, bN, ops);
-            for (int t = wave; t < n_tiles; t += STEP) {
-                int base[TU];
-                uint32_t xr[TU];
-                v4i acc[TU];
-#pragma unroll
-                for (int u = 0; u < TU; ++u) { base[u] = bN[u]; xr[u] = xn[u]; acc[u] = biB; }
-#pragma unroll
-                for (int st = 0; st < S::KS_B; ++st)
-#pragma unroll
-                    for (int u = 0; u < TU; ++u) acc[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wB[st], ops[u][st], acc[u], 0, 0, 0);
-#pragma unroll
-                for (int u = 0; u < TU; ++u) { bN[u] = bNN[u]; bNN[u] = tabB[(t + 2 * STEP + NW * u) * 16 + j]; }
-                load_ops(tM, bN, ops);
-#pragma unroll
-                for (int u = 0; u < TU; ++u) xn[u] = *(const uint32_t*)(xraw + (uint32_t)min((t + STEP + NW * u) * 16 + j, total - 1) * 16u + 4 * g);
-#pragma unroll
-                for (int u = 0; u < TU; ++u) {
-                    const int col = (t + NW * u) * 16 + j;
-                    int q[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float tr = (float)(int)(int8_t)(xr[u] >> (8 * r)) * rr;
-                        q[r] = rne_clamp127(fmaf((float)acc[u][r], mlB[r], tr));
-                    }
-                    const uint32_t w = pack_low_bytes(q);
-                    if (col < total) {
-                        if constexpr (LAST) {
-                            *(uint32_t*)(outp + (uint32_t)col * 16u + 4 * g) = w;
-                        } else {
-                            *(uint32_t*)(xraw + (uint32_t)col * 16u + 4 * g) = w;
-                            *(uint32_t*)(tX + base[u] + S::PITCH_B + C + 4 * g) = relu_i8x4(w);
-                        }
-                    }
+                for (int r = 0; r < 4; ++r) {
+                    const float tr = (float)(int)(int8_t)(x[k] >> (8 * r)) * rr;
+                    q[r] = rne_clamp127(fmaf((float)acc[r], ml[r], tr));
                 }
-            }
+                const StBytes y = st_pack(q);
+                const bool ok = k + 1 < S::R || lastrow;
+                if constexpr (LAST) {
+                    if (ok) *(uint32_t*)(outp + k * S::WP * 16) = y.raw;
+                } else {
+                    x[k] = y.raw;
+                    if (ok) *(uint32_t*)(tX + bown + k * S::PITCH_B) = y.pos;
+                }
+            });
         };
-        conv_a(wA1, 1);
+        // The pooled stream waits where the inner tensor will be: its pixels' owners take it into registers before they
+        // write there, and it stays in registers from then on.
+        const bool work = S::NCOL > NW * 16 - 16 || wave * 16 < S::NCOL;            // (a wavefront that owns no column must not touch another's)
+        v4i wA[S::NWB], wB[S::NWB];
+        if (work) {
+#pragma unroll
+            for (int k = 0; k < S::R; ++k) x[k] = *(const uint32_t*)(tM + bown + k * S::PITCH_B);
+            weights(std::integral_constant<int, 0>{}, wA);
+            conv_a(wA, 1);
+            weights(std::integral_constant<int, 1>{}, wB);
+        }
         __syncthreads();
-        conv_b(wB1, 2, p.r1, std::false_type{});
+        if (work) {
+            conv_b(wB, 2, p.r1, std::false_type{});
+            weights(std::integral_constant<int, 2>{}, wA);
+        }
         __syncthreads();
-        conv_a(wA2, 3);
+        if (work) {
+            conv_a(wA, 3);
+            weights(std::integral_constant<int, 3>{}, wB);
+        }
         __syncthreads();
         // the next batch's bytes are requested here, not earlier: their registers are then free during the phases above
         // (where the kernel needs the most), and the last phase is long enough for the loads to land
         if (batch + gridDim.x < n_batch) prefetch(batch + gridDim.x);
-        conv_b(wB2, 4, p.r2, std::true_type{});
+        if (work && (G == 1 || bimg < gc)) conv_b(wB, 4, p.r2, std::true_type{});
         // no barrier here: the next commit writes the input tiles only, and the barrier behind it comes before the
         // next batch writes anything that the last phase reads
     }
@@ -511,9 +516,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
 
 // the five convolutions of a stack as the planner laid them out: c = stack convolution (with its fused pool),
 // a1 / b1 and a2 / b2 = the two blocks
-template <bool U8, int CI, int HIN, int C, int G, int NW>
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL>
 bool st_shape_ok(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2) {
-    typedef StShape<U8, CI, HIN, C, G, NW> S;
+    typedef StShape<U8, CI, HIN, C, G, SEG, PSEG, NW, WL> S;
     if (c.H != HIN || c.W != HIN || c.Cs_in != CI || c.Cin_real != CI || c.Ho != HIN || c.Wo != HIN / S::P || c.Cs_out != 16) return false;
     if (c.k != 3 || c.s != 1 || c.pad != 1 || c.sx != S::P || c.cpr != S::CPR_C || c.k_steps != S::KS_C) return false;
     if ((c.src_u8 != 0) != U8 || !c.pool || c.PH != S::H || c.PW != S::H || c.relu || c.relu_in || c.out_frag) return false;
@@ -525,16 +530,16 @@ bool st_shape_ok(const ConvParams& c, const ConvParams& a1, const ConvParams& b1
     return a1.relu_in && a1.relu && !b1.relu_in && !b1.relu && a2.relu_in && a2.relu && !b2.relu_in && !b2.relu;
 }
 
-template <bool U8, int CI, int HIN, int C, int G, int NW, int MINB, bool P23>
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool P23>
 hipError_t st_go(const StackParams& p, hipStream_t s) {
-    typedef StShape<U8, CI, HIN, C, G, NW> S;
-    auto kfn = stack_kernel<U8, CI, HIN, C, G, NW, MINB, P23>;
+    typedef StShape<U8, CI, HIN, C, G, SEG, PSEG, NW, WL> S;
+    auto kfn = stack_kernel<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, P23>;
     static int occ = 0;
     if (!occ) {
         hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
         if (e != hipSuccess) return e;
         int o = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, (const void*)kfn, S::ST_THREADS, S::LDS);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, (const void*)kfn, S::THREADS, S::LDS);
         if (e != hipSuccess) return e;
         occ = o < 1 ? 1 : o;
     }
@@ -543,21 +548,22 @@ hipError_t st_go(const StackParams& p, hipStream_t s) {
     const int64_t cap = (int64_t)occ * conv_num_cus();
     const int64_t rounds = (batches + cap - 1) / cap;
     dim3 grid((unsigned)((batches + rounds - 1) / rounds));
-    kfn<<<grid, dim3(S::ST_THREADS), S::LDS, s>>>(p);
+    kfn<<<grid, dim3(S::THREADS), S::LDS, s>>>(p);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// (uint8 source, stored input channels, input size, channels, images per batch, wavefronts per workgroup, wavefronts per
-// SIMD the register budget is set for).  Stack 1 is held to two workgroups per CU by its LDS: eight wavefronts per
-// workgroup at 128 registers give its SIMDs four wavefronts each (504 -> 453 us at 16384 states); stacks 2 and 3, bound by
-// LDS traffic rather than by issue, gain nothing from that and keep four-wavefront workgroups, three to a CU.
-#define ACCERL_STACK_SHAPES(X) X(true, 4, 84, 8, 1, 8, 4) X(false, 8, 42, 16, 1, 4, 3) X(false, 16, 21, 16, 2, 4, 3)
+// (uint8 source, stored input channels, input size, channels, images per batch, row segments of the blocks' and of the pool's
+// lanes, wavefronts per workgroup, block convolutions whose weights live in LDS, wavefronts per SIMD the register budget is
+// set for).  Measured at 16384 states: the second stack as two images in eight wavefronts 212 us (its barriers hold twice as
+// many), with 16 wavefronts per unit instead of 12 182 for 196; the third with five images in four wavefronts 72 us (55 of 64
+// lanes and 59 of 61 pooling slots in use), four images 79, four in eight wavefronts of two segments 88, two 94.
+#define ACCERL_STACK_SHAPES(X) X(true, 4, 84, 8, 1, 6, 1, 8, 4, 4) X(false, 8, 42, 16, 1, 3, 2, 4, 3, 4) X(false, 16, 21, 16, 5, 1, 1, 4, 4, 2)
 
 bool stack_supported(const ConvParams& c, int NTC, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2) {
     if (NTC != 1) return false;
-#define X(U8, CI, HIN, C, G, NW, MINB) if (st_shape_ok<U8, CI, HIN, C, G, NW>(c, a1, b1, a2, b2)) return true;
+#define X(U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB) if (st_shape_ok<U8, CI, HIN, C, G, SEG, PSEG, NW, WL>(c, a1, b1, a2, b2)) return true;
     ACCERL_STACK_SHAPES(X)
 #undef X
     return false;
@@ -572,9 +578,9 @@ hipError_t launch_stack(const ConvParams& c, const ConvParams& a1, const ConvPar
     p.r1 = b1.r; p.r2 = b2.r; p.B = c.B;
     static const bool no_p23 = getenv("ACCERL_NO_P23") != nullptr;
     const bool p23 = a1.pos23 && a2.pos23 && !no_p23;
-#define X(U8, CI, HIN, C, G, NW, MINB)                                                              \
-    if (st_shape_ok<U8, CI, HIN, C, G, NW>(c, a1, b1, a2, b2))                                      \
-        return p23 ? st_go<U8, CI, HIN, C, G, NW, MINB, true>(p, s) : st_go<U8, CI, HIN, C, G, NW, MINB, false>(p, s);
+#define X(U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB)                                                              \
+    if (st_shape_ok<U8, CI, HIN, C, G, SEG, PSEG, NW, WL>(c, a1, b1, a2, b2))                                      \
+        return p23 ? st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, true>(p, s) : st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, false>(p, s);
     ACCERL_STACK_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
