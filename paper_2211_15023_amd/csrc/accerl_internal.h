@@ -61,7 +61,7 @@ struct ConvParams {
     const void* bias;        // int32 (int8 path, zero-point correction folded in) or fp32, [NT*16]
     const float* mult;       // [NT*16] (int8 path)
     const uint16_t* lut;     // 256 bf16 values obs/255 (bf16 path with uint8 source)
-    const int32_t* rows;     // bf16 front kernel: observation i is row rows[i] of `in` (NULL = row i)
+    const int32_t* rows;     // first layers: observation i is row rows[i] of `in` (NULL = row i)
     int64_t B;
     int H, W;                // input image
     int Cin_real;            // channels present in the source
@@ -203,6 +203,7 @@ struct HeadsParams {
     const float* uniforms;
     float* logits; float* value; int32_t* action;
     int32_t* tap_acc;        // int32 [B, A+1] (NULL = off)
+    const int32_t* rows;     // state i draws from and is written to row rows[i] of uniforms, logits, value, action (NULL = row i)
     int64_t B;
     int Kp_bytes, k_steps, A, relu_in;
 };

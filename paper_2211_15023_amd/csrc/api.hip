@@ -215,7 +215,7 @@ struct accerl_policy {
     // policy mixture (owned by the smaller policy of a pair): compacted inputs and results of both subsets,
     // and a ring of pinned host buffers for the row lists
     char* mix_dev = nullptr;
-    int64_t mix_rows = 0;
+    int64_t mix_bytes = 0;
     int32_t* mix_pin[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t mix_ev[4] = {nullptr, nullptr, nullptr, nullptr};
     int64_t mix_pin_rows = 0;
@@ -966,7 +966,10 @@ int ensure_workspace(accerl_policy* p, int64_t n, int layout, hipStream_t stream
 struct Call {
     const void* states; int64_t B; const float* uniforms; const uint8_t* done; float* h; float* c;
     float* logits; float* value; int32_t* action; hipStream_t stream;
-    const int32_t* rows = nullptr;   // state i is row rows[i] of `states` (policies that reads_rows allows only)
+    // state i is row rows[i]: of `states` if in_rows, of the uniforms and the outputs if out_rows (policies that reads_rows
+    // and writes_rows allow only)
+    const int32_t* rows = nullptr;
+    bool in_rows = false, out_rows = false;
     // debug
     bool debug = false; int layer = 0, tap = 0; void* out = nullptr; int64_t out_bytes = 0;
 };
@@ -989,11 +992,10 @@ int find_tap_step(const accerl_policy* p, int layer, int tap, bool& is_acc) {
     return found;
 }
 
-// the first launch reads its observations through a row list: a gathered copy is not needed
-bool reads_rows(const accerl_policy* p) {
-    const Step& s = p->steps[0];
-    return s.kind == ST_CONV && s.el == EL_BF16 && s.fuse_next && !s.resblock && s.in_buf < 0;
-}
+// image policies: every kernel that may be the first launch reads its observations through a row list, and the heads
+// kernel writes through one, so neither a gathered copy nor a scattered one is needed
+bool reads_rows(const accerl_policy* p) { return p->steps[0].kind == ST_CONV && p->steps[0].in_buf < 0; }
+bool writes_rows(const accerl_policy* p) { return p->steps.back().kind == ST_HEADS; }
 
 int run(accerl_policy* p, const Call& c) {
     if (c.B == 0) return ACCERL_OK;
@@ -1038,11 +1040,13 @@ int run(accerl_policy* p, const Call& c) {
     }
     for (int64_t c0 = 0; c0 < c.B; c0 += chunk) {
         const int64_t n = (c.B - c0 < chunk) ? (c.B - c0) : chunk;
-        const char* states = (const char*)c.states + (c.rows ? 0 : c0 * p->obs_bytes);
-        float* logits = c.logits ? c.logits + c0 * A : nullptr;
-        float* value = c.value ? c.value + c0 : nullptr;
-        int32_t* action = c.action ? c.action + c0 : nullptr;
-        const float* uni = c.uniforms ? c.uniforms + c0 : nullptr;
+        const int32_t* in_rows = c.in_rows ? c.rows + c0 : nullptr;
+        const int64_t o0 = c.out_rows ? 0 : c0;
+        const char* states = (const char*)c.states + (c.in_rows ? 0 : c0 * p->obs_bytes);
+        float* logits = c.logits ? c.logits + o0 * A : nullptr;
+        float* value = c.value ? c.value + o0 : nullptr;
+        int32_t* action = c.action ? c.action + o0 : nullptr;
+        const float* uni = c.uniforms ? c.uniforms + o0 : nullptr;
         char* tap_out = c.debug ? (char*)c.out + c0 * tap_elems * tap_esz : nullptr;
         auto bufp = [&](int b) -> char* { return b < 0 ? const_cast<char*>(states) : p->ws + p->bufs[b].off; };
         bool pooled = false;   // the last conv step also did the max-pool that follows it
@@ -1093,6 +1097,7 @@ int run(accerl_policy* p, const Call& c) {
                             cv[k].B = n;
                         }
                         cv[0].in = bufp(s.in_buf);
+                        cv[0].rows = s.in_buf < 0 ? in_rows : nullptr;
                         cv[4].out = bufp(p->steps[si + 5].out_buf);
                         e = s.el == EL_I8 ? launch_stack(cv[0], cv[1], cv[2], cv[3], cv[4], c.stream)
                                           : launch_stack_bf16(cv[0], cv[1], cv[2], cv[3], cv[4], c.stream);
@@ -1105,7 +1110,7 @@ int run(accerl_policy* p, const Call& c) {
                         const Step& nx = p->steps[si + 1];
                         ConvParams ca = s.cp, cb = nx.cp;
                         ca.in = bufp(s.in_buf); ca.out = nullptr; ca.res = nullptr; ca.tap_acc = nullptr;
-                        ca.rows = c.rows && s.in_buf < 0 ? c.rows + c0 : nullptr;
+                        ca.rows = s.in_buf < 0 ? in_rows : nullptr;
                         ca.wfrag = p->consts + s.o_w; ca.bias = p->consts + s.o_bias; ca.mult = s.o_mult >= 0 ? (const float*)(p->consts + s.o_mult) : nullptr;
                         ca.B = n;
                         cb.in = nullptr; cb.out = bufp(nx.out_buf); cb.res = nullptr; cb.tap_acc = nullptr;
@@ -1118,6 +1123,7 @@ int run(accerl_policy* p, const Call& c) {
                     }
                     ConvParams cp = s.cp;
                     cp.in = bufp(s.in_buf); cp.out = bufp(s.out_buf);
+                    cp.rows = s.in_buf < 0 ? in_rows : nullptr;
                     cp.res = s.res_buf >= 0 ? bufp(s.res_buf) : nullptr;
                     cp.tap_acc = (tap_here && tap_acc) ? (int32_t*)tap_out : nullptr;
                     cp.wfrag = p->consts + s.o_w;
@@ -1192,6 +1198,7 @@ int run(accerl_policy* p, const Call& c) {
                     hp.bias = p->consts + s.o_bias;
                     hp.mult = s.o_mult >= 0 ? (const float*)(p->consts + s.o_mult) : nullptr;
                     hp.uniforms = uni; hp.logits = logits; hp.value = value; hp.action = action;
+                    hp.rows = c.out_rows ? c.rows + c0 : nullptr;
                     hp.tap_acc = (tap_here && tap_acc) ? (int32_t*)tap_out : nullptr;
                     hp.B = n; hp.Kp_bytes = s.gp.Kp_bytes; hp.k_steps = s.gp.k_steps; hp.A = A; hp.relu_in = s.gp.relu_in;
                     e = launch_heads(hp, s.el, c.stream);
@@ -1577,14 +1584,21 @@ int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original
         }
         m->mix_pin_rows = B;
     }
+    // Image policies take their rows where they are and write their results there; others work on gathered copies, and
+    // unless both write through the row list the results are scattered back from compacted ones.
+    const bool in_place_s = reads_rows(smaller), in_place_o = reads_rows(original);
+    const bool direct = writes_rows(smaller) && writes_rows(original), gathered = !(direct && in_place_s && in_place_o);
     auto rup = [](int64_t v) { return (v + 255) / 256 * 256; };
-    const int64_t per_row = obs + 4 + 4 * (int64_t)A + 4 + 4;
-    if (m->mix_rows < B) {
+    // the row list; behind it states, uniforms, logits, values and actions of both subsets (the second starts at a row count
+    // rounded up to 4)
+    const int64_t copies = rup((B + 4) * obs) + rup((B + 4) * 4 * (int64_t)A) + 3 * rup((B + 4) * 4);
+    const int64_t need = rup(B * 4) + (gathered ? copies : 0);
+    if (m->mix_bytes < need) {
         HIP_TRY(hipStreamSynchronize(st));
-        if (m->mix_dev) { HIP_TRY(hipFree(m->mix_dev)); m->mix_dev = nullptr; m->mix_rows = 0; }
-        hipError_t e = hipMalloc((void**)&m->mix_dev, (size_t)(rup((B + 4) * 4) + rup((B + 4) * obs) + 4 * rup((B + 4) * 4 * (int64_t)(A > 1 ? A : 1)) + 4096));
-        if (e != hipSuccess) { (void)hipGetLastError(); return fail(ACCERL_ENOMEM, "mixture workspace of %lld rows x %lld bytes", (long long)B, (long long)per_row); }
-        m->mix_rows = B;
+        if (m->mix_dev) { HIP_TRY(hipFree(m->mix_dev)); m->mix_dev = nullptr; m->mix_bytes = 0; }
+        hipError_t e = hipMalloc((void**)&m->mix_dev, (size_t)need);
+        if (e != hipSuccess) { (void)hipGetLastError(); return fail(ACCERL_ENOMEM, "mixture workspace of %lld rows, %lld bytes", (long long)B, (long long)need); }
+        m->mix_bytes = need;
     }
     const int slot = m->mix_slot;
     m->mix_slot = (slot + 1) & 3;
@@ -1594,30 +1608,31 @@ int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original
         int64_t is = 0, io = ns;
         for (int64_t b = 0; b < B; ++b) { if (use_smaller[b]) pin[is++] = (int32_t)b; else pin[io++] = (int32_t)b; }
     }
-    const int64_t cap = m->mix_rows + 4;         // the second subset starts at a row count rounded up to 4
     char* d = m->mix_dev;
-    int32_t* d_idx = (int32_t*)d;               d += rup(cap * 4);
-    char* d_states = d;                          d += rup(cap * obs);
-    float* d_uni = (float*)d;                    d += rup(cap * 4);
-    float* d_logits = (float*)d;                 d += rup(cap * 4 * (int64_t)A);
-    float* d_value = (float*)d;                  d += rup(cap * 4);
+    int32_t* d_idx = (int32_t*)d;                d += rup(B * 4);
+    char* d_states = d;                          d += rup((B + 4) * obs);
+    float* d_uni = (float*)d;                    d += rup((B + 4) * 4);
+    float* d_logits = (float*)d;                 d += rup((B + 4) * 4 * (int64_t)A);
+    float* d_value = (float*)d;                  d += rup((B + 4) * 4);
     int32_t* d_action = (int32_t*)d;
     const int64_t o2 = (ns + 3) & ~(int64_t)3;   // keeps every buffer of the second subset 16-byte aligned
     HIP_TRY(hipMemcpyAsync(d_idx, pin, (size_t)B * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(m->mix_ev[slot], st));
-    // a policy whose first kernel reads through the row list takes its rows where they are
-    const bool in_place_s = reads_rows(smaller), in_place_o = reads_rows(original);
-    const int64_t first = in_place_s ? ns : 0, last = std::max(first, in_place_o ? ns : B);
-    HIP_TRY(launch_gather_mix(states, uniforms, d_idx, B, ns, o2, first, last, obs, d_states, d_uni, st));
-    Call cs{in_place_s ? states : d_states, ns, d_uni, nullptr, nullptr, nullptr, d_logits, d_value, d_action, st};
-    if (in_place_s) cs.rows = d_idx;
-    rc = run(smaller, cs);
+    if (gathered) {
+        const int64_t first = in_place_s ? ns : 0, last = std::max(first, in_place_o ? ns : B);
+        HIP_TRY(launch_gather_mix(states, uniforms, d_idx, B, ns, o2, first, last, obs, d_states, d_uni, st));
+    }
+    auto call = [&](bool in_place, int64_t i0, int64_t at, int64_t n) {      // rows i0 .. i0 + n of the list, place `at` of the copies
+        Call c{in_place ? states : d_states + at * obs, n, uniforms, nullptr, nullptr, nullptr, out_logits, out_value, out_action, st};
+        c.rows = d_idx + i0; c.in_rows = in_place; c.out_rows = direct;
+        if (!direct) { c.uniforms = d_uni + at; c.logits = d_logits + at * A; c.value = d_value + at; c.action = d_action + at; }
+        return c;
+    };
+    rc = run(smaller, call(in_place_s, 0, 0, ns));
     if (rc) return rc;
-    Call co{in_place_o ? states : d_states + o2 * obs, no, d_uni + o2, nullptr, nullptr, nullptr, d_logits + o2 * A, d_value + o2, d_action + o2, st};
-    if (in_place_o) co.rows = d_idx + ns;
-    rc = run(original, co);
+    rc = run(original, call(in_place_o, ns, o2, no));
     if (rc) return rc;
-    HIP_TRY(launch_scatter_mix(d_logits, d_value, d_action, d_idx, B, ns, o2, A, out_logits, out_value, out_action, st));
+    if (!direct) HIP_TRY(launch_scatter_mix(d_logits, d_value, d_action, d_idx, B, ns, o2, A, out_logits, out_value, out_action, st));
     return ACCERL_OK;
 }
 

@@ -323,7 +323,8 @@ __global__ __launch_bounds__(NW * 64, conv_min_blocks(NT, KS, PF, PT, NW, MODE))
                 pre[i] = v;
             }
         } else {   // CM_U8T: one dword (4 pixels) from each channel plane
-            const uint8_t* src = (const uint8_t*)p.in + b0 * (int64_t)p.Cin_real * p.H * p.W;
+            // (through a row list a batch is one image: see conv_go)
+            const uint8_t* src = (const uint8_t*)p.in + (p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)p.Cin_real * p.H * p.W;
             const int plane = p.H * p.W;
 #pragma unroll
             for (int i = 0; i < PF; ++i) {
@@ -735,6 +736,7 @@ hipError_t conv_go(const ConvParams& p, dim3 grid, size_t lds, hipStream_t s) {
         const int64_t g = (q.B + slots - 1) / slots;
         q.G = (int)(g < 1 ? 1 : g < q.G ? g : q.G);
     }
+    if (q.rows) q.G = 1;                                             // images that are not neighbours in memory
     const int64_t n_batch = (q.B + q.G - 1) / q.G;
     const int64_t items = WP ? (n_batch + NW - 1) / NW : n_batch;     // batches a workgroup takes per round
     const int64_t rounds = (items + cap - 1) / cap;

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256, 2) void conv_fused_kernel(const ConvParams a, 
     }
     const int plane = a.H * a.W;
     auto prefetch = [&](int64_t img) {
-        const uint8_t* src = (const uint8_t*)a.in + img * (int64_t)a.Cin_real * plane;
+        const uint8_t* src = (const uint8_t*)a.in + (a.rows ? (int64_t)a.rows[img] : img) * (int64_t)a.Cin_real * plane;
 #pragma unroll
         for (int i = 0; i < FUSED_PF; ++i) {
             v4i v;

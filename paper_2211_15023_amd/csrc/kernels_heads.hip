@@ -28,7 +28,8 @@ __global__ __launch_bounds__(HD_WAVES * 64) void heads_kernel(const HeadsParams 
     const bool live = row < p.B;
     if (!live) row = p.B - 1;
 
-    const float u_row = p.uniforms ? p.uniforms[row] : 0.0f;      // requested first: the sampler at the end needs it
+    const int64_t orow = p.rows ? (int64_t)p.rows[row] : row;     // where the state's draw and results are
+    const float u_row = p.uniforms ? p.uniforms[orow] : 0.0f;     // requested first: the sampler at the end needs it
     // this lane's K chunks of its state: unconditional loads, the tail chunk rebuilt below
     v4i xb[KM];
     const char* xrow = (const char*)p.x + row * p.Kp_bytes;
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(HD_WAVES * 64) void heads_kernel(const HeadsParams 
             // rows of A floats: 16- or 8-byte stores where the row pitch allows (neighbouring states fill the lines)
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                float* dst = p.logits + row * A + 16 * t + 4 * g;
+                float* dst = p.logits + orow * A + 16 * t + 4 * g;
                 if ((A & 3) == 0) {
                     if (is_logit[t][3]) *(v4f*)dst = (v4f){o[t][0], o[t][1], o[t][2], o[t][3]};
                 } else if ((A & 1) == 0) {
@@ -167,12 +168,12 @@ __global__ __launch_bounds__(HD_WAVES * 64) void heads_kernel(const HeadsParams 
             const auto c32 = pair32((unsigned)cnt);
             cnt = (int)(c32[0] + c32[1]);
             if (live) {
-                if (g == 0) p.action[row] = min(cnt, A - 1);
+                if (g == 0) p.action[orow] = min(cnt, A - 1);
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (16 * t + 4 * g + r == A) p.value[row] = o[t][r];
+                        if (16 * t + 4 * g + r == A) p.value[orow] = o[t][r];
             }
         }
         return;
@@ -204,10 +205,10 @@ __global__ __launch_bounds__(HD_WAVES * 64) void heads_kernel(const HeadsParams 
     if (p.logits) {
         const int rows = (int)((p.B - row0 < 16) ? (p.B - row0) : 16);
         const float inv_A = 1.0f / (float)A;
-        float* dst = p.logits + row0 * A;
         for (int i = lane; i < rows * A; i += 64) {
             const int rr = (int)(((float)i + 0.5f) * inv_A), a = i - rr * A;   // i < 1024: the float quotient is exact
-            dst[i] = stage[rr * HD_PITCH + a];
+            const int64_t to = p.rows ? (int64_t)p.rows[row0 + rr] : row0 + rr;
+            p.logits[to * A + a] = stage[rr * HD_PITCH + a];
         }
     }
     if (p.action) {
@@ -221,17 +222,17 @@ __global__ __launch_bounds__(HD_WAVES * 64) void heads_kernel(const HeadsParams 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (g == 0 && live) {   // one lane per state: normaliser and scan in index order
             const float* ex = stage_e + j * HD_PITCH;
-            p.value[row] = lg[A];
+            p.value[orow] = lg[A];
             float Z = 0.0f;
             for (int a = 0; a < A; ++a) Z += ex[a];
-            const float thr = p.uniforms[row] * Z;
+            const float thr = u_row * Z;
             float cum = 0.0f;
             int act = A - 1;
             for (int a = 0; a < A; ++a) {
                 cum += ex[a];
                 if (cum > thr) { act = a; break; }
             }
-            p.action[row] = act;
+            p.action[orow] = act;
         }
     }
 }

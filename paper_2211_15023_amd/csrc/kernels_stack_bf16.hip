@@ -45,6 +45,7 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 
 struct BStackParams {
     const void* in;          // uint8 planes [B, 4, HIN, HIN] or bf16 [B, HIN, HIN, CI]
+    const int32_t* rows;     // observation i is row rows[i] of in (NULL = row i)
     char* out;               // bf16 [B, H, H, C]
     const v4i* w[5];         // 0: stack convolution, 1 / 2: first block's conv A / B, 3 / 4: second block's
     const float* bias[5];
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     // ---- staging of observations: unit u is one dword of each of the four planes
     v4i pre[S::PF];
     auto prefetch = [&](int64_t batch) {
-        const char* src = (const char*)p.in + batch * (int64_t)S::IMG_IN;
+        const char* src = (const char*)p.in + (p.rows ? (int64_t)p.rows[batch] : batch) * (int64_t)S::IMG_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
             const int u = min(tid + i * T, S::UNITS - 1);    // a unit that does not exist re-reads the last one
@@ -480,7 +481,7 @@ bool stack_bf16_supported(const ConvParams& c, const ConvParams& a1, const ConvP
 hipError_t launch_stack_bf16(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2, hipStream_t s) {
     if (c.B <= 0) return hipSuccess;
     BStackParams p;
-    p.in = c.in; p.out = (char*)b2.out;
+    p.in = c.in; p.rows = c.rows; p.out = (char*)b2.out;
     const ConvParams* cv[5] = {&c, &a1, &b1, &a2, &b2};
     for (int i = 0; i < 5; ++i) { p.w[i] = (const v4i*)cv[i]->wfrag; p.bias[i] = (const float*)cv[i]->bias; }
     p.B = c.B;

@@ -53,6 +53,7 @@ namespace {
 
 struct StackParams {
     const void* in;          // uint8 planes [B, 4, HIN, HIN] or int8 [B, HIN, HIN, CI]
+    const int32_t* rows;     // observation i is row rows[i] of in (NULL = row i)
     int8_t* out;             // [B, H, H, C]
     const v4i* w[5];         // 0: stack convolution, 1 / 2: first block's conv A / B, 3 / 4: second block's
     const int* bias[5];
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         const int64_t b0 = batch * G;
         const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
         const int last = gc * S::UNITS_IN - 1;
-        const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
+        const char* src = (const char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
             const uint32_t u = (uint32_t)min(tid + i * T, last);        // a unit that does not exist re-reads the last one
@@ -572,7 +573,7 @@ bool stack_supported(const ConvParams& c, int NTC, const ConvParams& a1, const C
 hipError_t launch_stack(const ConvParams& c, const ConvParams& a1, const ConvParams& b1, const ConvParams& a2, const ConvParams& b2, hipStream_t s) {
     if (c.B <= 0) return hipSuccess;
     StackParams p;
-    p.in = c.in; p.out = (int8_t*)b2.out;
+    p.in = c.in; p.rows = c.rows; p.out = (int8_t*)b2.out;
     const ConvParams* cv[5] = {&c, &a1, &b1, &a2, &b2};
     for (int i = 0; i < 5; ++i) { p.w[i] = (const v4i*)cv[i]->wfrag; p.bias[i] = (const int*)cv[i]->bias; p.mult[i] = cv[i]->mult; }
     p.r1 = b1.r; p.r2 = b2.r; p.B = c.B;

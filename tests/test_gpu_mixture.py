@@ -109,3 +109,53 @@ def test_mixture_of_more_rows_than_one_launch_takes(A):
     m = _dev(use).bool()
     for got, a, b in zip(out, small.forward(x, u), orig.forward(x, u)):
         assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
+
+
+def _wide_head_net(cout):
+    return SimpleNamespace(name="wide", obs_dtype="u8", obs_shape=(4, 84, 84), n_actions=40,
+                           layers=[dict(kind="conv", cin=4, cout=cout, k=8, stride=4, pad=0, relu=True),
+                                   dict(kind="conv", cin=cout, cout=8, k=4, stride=2, pad=0, relu=True),
+                                   dict(kind="flatten"), dict(kind="dense", cin=8 * 81, cout=64, relu=True)])
+
+
+@pytest.mark.parametrize("passes", [False, True])
+@pytest.mark.parametrize("pair", ["nature", "impala", "net1", "net2", "wide heads", "odd size"])
+def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes):
+    """Every kernel that can be the first of an image policy reads through the row list, and both forms of the heads kernel
+    write through it: bit for bit what the policies compute on those rows alone, also when a policy runs in several passes."""
+    if passes:
+        monkeypatch.setenv("ACCERL_CHUNK", "64")                  # read when the policy is created
+    rng = np.random.default_rng(5)
+
+    def float_policy(net, prec="bf16"):
+        return A.Policy(net, prec, teacher_tensors(wl.init_params(net, wl.STREAM["weights_teacher"])))
+
+    def int8_policy(net):
+        params = wl.init_params(net, wl.STREAM["weights_student"])
+        qp = oracle.quantize_policy(net, params, make_states(net, 16, wl.STREAM["calibration"]))
+        return A.Policy(net, "int8", qp.tensors, qp.act_scales)
+
+    if pair in ("nature", "impala"):
+        nt, pt, ns, ps, qp = policies(2 if pair == "nature" else 3)
+        net, small, orig = ns, A.Policy(ns, "int8", student_tensors(qp), qp.act_scales), A.Policy(nt, "bf16", teacher_tensors(pt))
+    elif pair == "wide heads":
+        net = _wide_head_net(8)
+        small, orig = int8_policy(net), float_policy(_wide_head_net(20))
+    elif pair == "odd size":                                      # several images per batch in the generic first kernel
+        net = SimpleNamespace(name="odd", obs_dtype="u8", obs_shape=(3, 12, 16), n_actions=3,
+                              layers=[dict(kind="conv", cin=3, cout=12, k=3, stride=1, pad=1, relu=True),
+                                      dict(kind="flatten"), dict(kind="dense", cin=12 * 192, cout=24, relu=True)])
+        small, orig = int8_policy(net), float_policy(net)
+    else:
+        net = wl.configs.PAPER_STUDENTS[pair]
+        small, orig = int8_policy(net), float_policy(net)
+    B = 150
+    x = make_states(net, B, wl.STREAM["states"])
+    dx, du = _dev(x), _dev(wl.make_uniforms(B))
+    use = (rng.random(B) < 0.55).astype(np.uint8)
+    out = small.alloc_outputs(B)
+    print(f"mixture in place: {pair}, B={B}, {'passes of 64' if passes else 'one pass'}", flush=True)
+    A.accerl_actor_forward_mixture(small.handle, orig.handle, dx, du, use, *out)
+    m = _dev(use).bool()
+    for got, a, b in zip(out, small.forward(dx, du), orig.forward(dx, du)):
+        assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
