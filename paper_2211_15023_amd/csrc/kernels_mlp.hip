@@ -371,6 +371,163 @@ __global__ __launch_bounds__(MLP_WAVES * 64, NH <= 2 ? 3 : 2) void mlp_i8_kernel
     }
 }
 
+// The same network for many states, at most 32 features and at most four actions: a wavefront takes four tiles, 64
+// consecutive states, at a time.
+//  * What binds the one-tile kernel is not vector issue but what LDS returns: the layers' biases and multipliers, 24 reads of
+//    16 bytes per lane and tile, are 192 clocks of a compute unit's LDS per tile, 22 us for a million states.  Here a read
+//    serves four tiles, whose MFMAs and requantizations are four independent chains.
+//  * At most four actions: a state's logits lie in its first lane alone.  The head weights sit in rows 4t .. 4t+3 of the MFMA
+//    for tile t (zeros elsewhere) and all four tiles are added up in one accumulator, so lane 16t + j ends up with the logits
+//    of state j of tile t, which is state number `lane`: heads, sampler and (coalesced) stores run once per 64 states.
+//  * Rows are addressed by a wave-uniform base and a constant lane offset; the next round's observations are in flight.
+// One million states of 24-64-64: 34.3 -> 29.1 us (floor at the rate of a copy 24); with 4 features 30.9 -> 25.5; at 131072
+// states 7.8 -> 6.6.  Three wavefronts per SIMD: with four (128 registers) 30.8.
+template <int NH>
+__global__ __launch_bounds__(MLP_WAVES * 64, NH <= 2 ? 3 : 2) void mlp_i8_quad_kernel(MlpParams p) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    constexpr int FPL = 8, NGR = FPL / 4;                      // features and groups of four per lane: the K = 32 MFMA
+    const int D = p.D, A = p.A;
+    const int64_t n_quads = (p.B + 63) / 64, n_waves = (int64_t)gridDim.x * MLP_WAVES;
+    int64_t quad = (int64_t)blockIdx.x * MLP_WAVES + wave;
+
+    float keep[NGR];
+    uint32_t off[NGR];
+#pragma unroll
+    for (int q = 0; q < NGR; ++q) {
+        const int f0 = FPL * g + 4 * q;
+        keep[q] = f0 < D ? p.inv_s0 : 0.0f;                    // the quantizer's multiplier, or 0 for padding
+        off[q] = 4u * (uint32_t)(j * D + min(f0, D - 4));
+    }
+    v4f raw[4][NGR];                                           // the next round's observations are in flight during a round
+    auto load_obs = [&](int64_t qd) {
+        const int64_t row0 = 64 * qd;
+        const char* src = (const char*)(p.obs + row0 * D);
+        if (row0 + 64 <= p.B) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < NGR; ++q) raw[t][q] = *(const v4f*)(src + (int64_t)t * (64 * D) + off[q]);
+        } else {                                               // rows past the batch repeat its last one
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int64_t at = row0 + 16 * t + j, back = 4 * (min(at, p.B - 1) - at) * D;
+#pragma unroll
+                for (int q = 0; q < NGR; ++q) raw[t][q] = *(const v4f*)(src + (int64_t)t * (64 * D) + back + (int64_t)off[q]);
+            }
+        }
+    };
+    if (quad < n_quads) load_obs(quad);
+
+    __shared__ __attribute__((aligned(16))) int s_bs[NH][64];
+    __shared__ __attribute__((aligned(16))) float s_ml[NH][64], s_cf[NH][64];
+    for (int i = threadIdx.x; i < NH * 64; i += MLP_WAVES * 64) {
+        (&s_bs[0][0])[i] = p.bias[i] + 0x4B000000;
+        (&s_ml[0][0])[i] = p.mult[i];
+        (&s_cf[0][0])[i] = p.cfma[i];
+    }
+    v4i wf[NH][4];
+#pragma unroll
+    for (int l = 0; l < NH; ++l)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wf[l][t] = p.wfrag[(l * 4 + t) * 64 + lane];
+    const v4i* hf = p.wfrag + NH * 4 * 64 + (lane & 48);
+    const v4i rows = hf[j & 3], row_v = hf[A], none = {0, 0, 0, 0};
+    __shared__ v4i s_hl[4][64], s_hv[4][64];                   // logits to lane group t; value to its first register
+    if (wave == 0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            s_hl[t][lane] = (j >> 2) == t ? rows : none;
+            s_hv[t][lane] = j == 4 * t ? row_v : none;
+        }
+    }
+    const v4i bl = *(const v4i*)(p.bias + NH * 64);
+    const v4f dl = *(const v4f*)(p.mult + NH * 64);
+    const int bv = p.bias[NH * 64 + A];
+    const float dv = p.mult[NH * 64 + A];
+    __syncthreads();
+
+    for (; quad < n_quads; quad += n_waves) {
+        const int64_t row = 64 * quad + lane;
+        const float u = p.uniforms[min(row, p.B - 1)];
+        // the layer constants are read from LDS again in every round (96 registers if kept): nothing is hoisted past here
+        asm volatile("" ::: "memory");
+        v4i x[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            x[t] = (v4i){0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < NGR; ++q) {
+                float y[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = raw[t][q][e] * keep[q];
+                x[t][q] = (int)requant4(y, false);
+            }
+        }
+        load_obs(min(quad + n_waves, n_quads - 1));            // (past the end: the last one, not used)
+#pragma unroll
+        for (int l = 0; l < NH; ++l) {
+            v4i nx[4];
+#pragma unroll
+            for (int ft = 0; ft < 4; ++ft) {
+                const v4i bs = *(const v4i*)&s_bs[l][16 * ft + 4 * g];
+                const v4f mq = *(const v4f*)&s_ml[l][16 * ft + 4 * g], cq = *(const v4f*)&s_cf[l][16 * ft + 4 * g];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    v4i acc;
+                    if (l == 0) {
+                        const long a8 = ((long)(uint32_t)wf[l][ft][0]) | ((long)wf[l][ft][1] << 32);
+                        const long b8 = ((long)(uint32_t)x[t][0]) | ((long)x[t][1] << 32);
+                        acc = __builtin_amdgcn_mfma_i32_16x16x32_i8(a8, b8, bs, 0, 0, 0);
+                    } else {
+                        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[l][ft], x[t], bs, 0, 0, 0);
+                    }
+                    float y[4];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) y[r] = __builtin_fmaf(__int_as_float(acc[r]), mq[r], cq[r]);
+                    nx[t][ft] = (int)requant4(y, true);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = nx[t];
+        }
+        v4i al = bl, av = {bv, bv, bv, bv};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            al = __builtin_amdgcn_mfma_i32_16x16x64_i8(s_hl[t][lane], x[t], al, 0, 0, 0);
+            av = __builtin_amdgcn_mfma_i32_16x16x64_i8(s_hv[t][lane], x[t], av, 0, 0, 0);
+        }
+        // heads and sampler of state `lane`: the arithmetic of the one-tile kernel's first lanes
+        float o[4], cum[4], run = 0.0f, m = -3.0e38f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            o[r] = (float)al[r] * dl[r];
+            m = fmaxf(m, r < A ? o[r] : -3.0e38f);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            run += (r < A) ? __builtin_amdgcn_exp2f((o[r] - m) * 1.44269504088896341f) : 0.0f;
+            cum[r] = run;
+        }
+        if (row < p.B) {
+            float* dst = p.logits + row * A;
+            if (A == 4) *(v4f*)dst = (v4f){o[0], o[1], o[2], o[3]};
+            else {
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+                    if (r < A) dst[r] = o[r];
+            }
+            const float thr = u * run;
+            int cnt = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) cnt += (r < A && !(cum[r] > thr)) ? 1 : 0;
+            p.action[row] = min(cnt, A - 1);
+            p.value[row] = (float)av[0] * dv;
+        }
+    }
+}
+
 template <int NH, bool TAPS, bool RELU, bool P23, int KM>
 static hipError_t launch_nh(const MlpParams& p, int ht, int blocks, hipStream_t s) {
     dim3 grid(blocks), block(MLP_WAVES * 64);
@@ -380,6 +537,26 @@ static hipError_t launch_nh(const MlpParams& p, int ht, int blocks, hipStream_t 
         case 3: mlp_i8_kernel<NH, 3, TAPS, RELU, P23, KM><<<grid, block, 0, s>>>(p); break;
         default: mlp_i8_kernel<NH, 4, TAPS, RELU, P23, KM><<<grid, block, 0, s>>>(p); break;
     }
+    return hipGetLastError();
+}
+
+// two wavefronts of 64 states per SIMD; below, more and smaller shares finish earlier (65537 states 6.0 us, by fours 6.2)
+constexpr int64_t QUAD_MIN_B = 1 << 17;
+int conv_num_cus();
+
+template <int NH>
+static hipError_t launch_quad(const MlpParams& p, hipStream_t s) {
+    static int occ = 0;
+    if (!occ) {
+        int o = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, (const void*)mlp_i8_quad_kernel<NH>, MLP_WAVES * 64, 0);
+        if (e != hipSuccess) return e;
+        occ = o < 1 ? 1 : o;
+    }
+    // resident workgroups, their wavefronts striding over groups of 64 states.  All of them, also when the last round is
+    // nearly empty: fewer wavefronts in even rounds would leave some SIMDs with two and others with three
+    const int64_t quads = (p.B + 63) / 64, waves = min(quads, (int64_t)occ * conv_num_cus() * MLP_WAVES);
+    mlp_i8_quad_kernel<NH><<<dim3((unsigned)((waves + MLP_WAVES - 1) / MLP_WAVES)), dim3(MLP_WAVES * 64), 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -395,10 +572,12 @@ hipError_t launch_mlp_i8(const MlpParams& p, hipStream_t s) {
     for (int l = 0; l < p.n_hidden; ++l) relu = relu && p.lo[l] == 0;
     const bool p23 = relu && p.p23 != 0 && p.cfma != nullptr;
     const bool k32 = p.k32 != 0;
+    const bool quad = p23 && !taps && k32 && p.A <= 4 && (p.D & 3) == 0 && p.B >= QUAD_MIN_B;
 #define GO(N)                                                                                                 \
     case N:                                                                                                   \
         if (taps) return launch_nh<N, true, false, false, 2>(p, ht, (int)blocks, s);                          \
         if (!relu) return launch_nh<N, false, false, false, 2>(p, ht, (int)blocks, s);                        \
+        if (quad) return launch_quad<N>(p, s);                                                                \
         if (p23) return k32 ? launch_nh<N, false, true, true, 1>(p, ht, (int)blocks, s)                       \
                             : launch_nh<N, false, true, true, 0>(p, ht, (int)blocks, s);                      \
         return k32 ? launch_nh<N, false, true, false, 1>(p, ht, (int)blocks, s)                               \
