@@ -109,6 +109,7 @@ struct ConvParams {
     // weights when the plan is built): a kernel may then start its accumulators at bias + 0x4B000000, read the result's
     // bits as the float 2^23 + acc and requantize with one fused multiply-add (see requant_relu4_p23)
     int pos23;
+    int mag22;               // the accumulators stay within +-2^22 whatever the input: read as a float, bits 0x4B400000 + acc are 1.5 * 2^23 + acc
 };
 // KS > 0: weights in registers, that many MFMA steps unrolled; KS = 0: weights in LDS, runtime loop.
 // RD: alignment (16 / 8 / 4) of a chunk read in LDS.  PF: staging units per lane the kernel holds.

@@ -478,7 +478,7 @@ int plan_conv(Builder& B, int layer, int sub, const TensorSpec& t, Elem el, bool
     if (el == EL_I8) {
         std::vector<int32_t> bq(NT * 16, 0);
         std::vector<float> ml(NT * 16, 0.f);
-        bool pos23 = relu;
+        bool pos23 = relu, mag22 = true;
         for (int n = 0; n < CoutK; ++n) {
             const int ch = n % Cs_img;
             if (ch >= Cout) continue;
@@ -486,6 +486,8 @@ int plan_conv(Builder& B, int layer, int sub, const TensorSpec& t, Elem el, bool
             // the largest accumulator any input can produce: observations are 0 .. 255, activations -127 .. 127
             const int64_t top = b + (src_u8 ? 255 * wpos[n] : 127 * wabs[n]);
             if (top >= (1 << 23) || b <= -(1 << 30)) pos23 = false;
+            const int64_t bottom = b - (src_u8 ? 255 * (wabs[n] - wpos[n]) : 127 * wabs[n]);
+            if (top >= (1 << 22) || bottom <= -(1 << 22)) mag22 = false;
             if (src_u8) b += 128 * wsum[n];          // observations are staged as obs - 128
             bq[n] = (int32_t)b;
             ml[n] = Builder::mult(s_in, B.sw(t)[ch], s_out);
@@ -494,6 +496,7 @@ int plan_conv(Builder& B, int layer, int sub, const TensorSpec& t, Elem el, bool
         st.o_mult = B.put(ml.data(), ml.size() * 4);
         c.r = res_buf >= 0 ? (float)((double)s_res / (double)s_out) : 0.f;
         c.pos23 = pos23 ? 1 : 0;
+        c.mag22 = mag22 ? 1 : 0;
     } else {
         std::vector<float> bf(NT * 16, 0.f);
         for (int n = 0; n < CoutK; ++n) if (n % Cs_img < Cout) bf[n] = B.bias(t)[n % Cs_img];

@@ -4,7 +4,9 @@
 // is read once and the stack's output written once, and every tensor in between lives in LDS or in registers.
 //
 // What bounds these layers is not the matrix cores but the vector instructions around them (requantization, pooling,
-// addressing), four clocks of a SIMD each.  The kernel is therefore organised to issue few of them:
+// addressing), two clocks of a SIMD each (32-bit additions, subtractions, products and logic on vector registers) or four
+// (conversions, minima and maxima, shifts, byte permutes, anything with a scalar register).  The kernel is therefore
+// organised to issue few of them:
 //
 //  * Lanes are columns of the image and walk down it: a fragment read from LDS serves every output row whose window holds
 //    it, and a row's address is a per-lane constant plus an immediate.  (Tiles of 16 pixels in raster order read every
@@ -36,7 +38,8 @@
 //    is what limits the workgroups.
 //  * the next batch's input bytes are requested at the start of the current batch's last phase and land while it runs.
 //
-// Measured at 16384 states (kernel traces): 429 / 270 / 95 -> 325 / 182 / 72 us.  Vector issue 80 / 69 / 56 % of the clocks,
+// Measured at 16384 states (kernel traces): 429 / 270 / 95 -> 325 / 182 / 72 us (320 / 180 / 71 without conversions, see
+// BITS).  Vector issue 80 / 69 / 56 % of the clocks,
 // LDS pipe 56 / 42 / 36 %, matrix cores 27 / 39 / 35 %.
 //
 // Arithmetic and constants are those of the layer-by-layer kernels (conv_kernel.h), so results are bit-identical; the debug
@@ -131,8 +134,15 @@ __device__ __forceinline__ StBytes st_pack(const int (&q)[4]) {
     return {raw, raw & ~neg};
 }
 
-// P23: the first convolution of both blocks keeps its accumulators below 2^23 (see requant_relu4_p23)
-template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool P23>
+// BITS: the sums are small enough to be read as floats without a conversion (half the clocks of a subtraction): those of the
+// blocks' first convolutions start at bias + 0x4B000000 (see requant_relu4_p23), the others at bias + 0x4B400000, which is
+// 1.5 * 2^23 + sum as a float.  Three stacks at 16384 states, in turn on one card: 583, 592, 594 -> 576, 581, 585 us.  A
+// bias can take a layer out of these ranges (no weights of these sizes can); such a network converts.
+constexpr int ST_MAGIC = 0x4B400000;
+template <bool BITS>
+__device__ __forceinline__ float st_float(int acc) { return BITS ? __int_as_float(acc) - 12582912.0f : (float)acc; }
+
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool BITS>
 __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams p) {
     typedef StShape<U8, CI, HIN, C, G, SEG, PSEG, NW, WL> S;
     constexpr int T = S::THREADS;
@@ -311,10 +321,10 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
 
         // ---- stack convolution + max-pool, in registers -> bordered tiles of max(x, 0) and of x itself
         {
-            v4i biC = *(const v4i*)(cst + 4 * g);
+            v4i biC = *(const v4i*)(cst + 4 * g) + (BITS ? ST_MAGIC : 0);
             v4f mlC = *(const v4f*)(cst + 16 + 4 * g);
             if constexpr (S::P == 2) {                   // channels 2 g, 2 g + 1 twice
-                const int b0 = cst[2 * g], b1 = cst[2 * g + 1];
+                const int b0 = cst[2 * g] + (BITS ? ST_MAGIC : 0), b1 = cst[2 * g + 1] + (BITS ? ST_MAGIC : 0);
                 const float m0 = ((const float*)cst)[16 + 2 * g], m1 = ((const float*)cst)[16 + 2 * g + 1];
                 biC = (v4i){b0, b1, b0, b1};
                 mlC = (v4f){m0, m1, m0, m1};
@@ -322,7 +332,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             auto requant = [&](const int (&pooled)[4]) {
                 int q[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) q[r] = rne_clamp127((float)pooled[r] * mlC[r]);
+                for (int r = 0; r < 4; ++r) q[r] = rne_clamp127(st_float<BITS>(pooled[r]) * mlC[r]);
                 return st_pack(q);
             };
             if constexpr (S::P == 2) {
@@ -452,11 +462,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         };
         // ---- a block's first convolution: max(x, 0) -> inner tensor, requantized with the fused ReLU
         auto conv_a = [&](const v4i (&w)[S::NWB], int cv) {
-            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (P23 ? P23_MAGIC : 0);
+            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (BITS ? P23_MAGIC : 0);
             const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
             const v4f cc = ml * -8388608.0f;
             walk(tX, w, bi, [&](int k, v4i acc) {
-                const uint32_t y = requant_relu4_p23<P23>(acc, ml, cc);
+                const uint32_t y = requant_relu4_p23<BITS>(acc, ml, cc);
                 if (k + 1 < S::R || lastrow) *(uint32_t*)(tM + bown + k * S::PITCH_B) = y;
             });
         };
@@ -464,15 +474,16 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         // ---- a block's second convolution, joined with the block's input; LAST: to memory, else back into registers and LDS
         auto conv_b = [&](const v4i (&w)[S::NWB], int cv, float rr, auto last) {
             constexpr bool LAST = decltype(last)::value;
-            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g);
+            const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (BITS ? ST_MAGIC : 0);
             const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
+            asm("" : "+v"(rr));                           // a vector register: a multiplication by a scalar one takes twice as long
             char* outp = (char*)p.out + b0 * (int64_t)S::IMG + (uint32_t)(bimg * S::IMG + brel);
             walk(tM, w, bi, [&](int k, v4i acc) {
                 int q[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float tr = (float)(int)(int8_t)(x[k] >> (8 * r)) * rr;
-                    q[r] = rne_clamp127(fmaf((float)acc[r], ml[r], tr));
+                    q[r] = rne_clamp127(fmaf(st_float<BITS>(acc[r]), ml[r], tr));
                 }
                 const StBytes y = st_pack(q);
                 const bool ok = k + 1 < S::R || lastrow;
@@ -531,10 +542,10 @@ bool st_shape_ok(const ConvParams& c, const ConvParams& a1, const ConvParams& b1
     return a1.relu_in && a1.relu && !b1.relu_in && !b1.relu && a2.relu_in && a2.relu && !b2.relu_in && !b2.relu;
 }
 
-template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool P23>
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, int NW, int WL, int MINB, bool BITS>
 hipError_t st_go(const StackParams& p, hipStream_t s) {
     typedef StShape<U8, CI, HIN, C, G, SEG, PSEG, NW, WL> S;
-    auto kfn = stack_kernel<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, P23>;
+    auto kfn = stack_kernel<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, BITS>;
     static int occ = 0;
     if (!occ) {
         hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
@@ -578,10 +589,10 @@ hipError_t launch_stack(const ConvParams& c, const ConvParams& a1, const ConvPar
     for (int i = 0; i < 5; ++i) { p.w[i] = (const v4i*)cv[i]->wfrag; p.bias[i] = (const int*)cv[i]->bias; p.mult[i] = cv[i]->mult; }
     p.r1 = b1.r; p.r2 = b2.r; p.B = c.B;
     static const bool no_p23 = getenv("ACCERL_NO_P23") != nullptr;
-    const bool p23 = a1.pos23 && a2.pos23 && !no_p23;
+    const bool bits = a1.pos23 && a2.pos23 && c.mag22 && b1.mag22 && b2.mag22 && !no_p23;
 #define X(U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB)                                                              \
     if (st_shape_ok<U8, CI, HIN, C, G, SEG, PSEG, NW, WL>(c, a1, b1, a2, b2))                                      \
-        return p23 ? st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, true>(p, s) : st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, false>(p, s);
+        return bits ? st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, true>(p, s) : st_go<U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB, false>(p, s);
     ACCERL_STACK_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
