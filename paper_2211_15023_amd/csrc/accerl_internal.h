@@ -185,6 +185,13 @@ struct GemmParams {
     // so that a wavefront's fragment load is one contiguous KiB (a row-major x makes every lane of a quarter
     // wavefront touch a different row).  Needs Kp_bytes == 64 * k_steps and storage for whole tiles of 16 states.
     int x_frag;
+    // xh != NULL (kernels whose wavefronts split K only): the layer in front of an LSTM writes its results, and the state h
+    // beside them, straight into the operand of the LSTM's product (LstmPackParams with frag_ks > 0) instead of out
+    uint16_t* xh;
+    const uint8_t* done;
+    float xh_scale;
+    int xh_relu;
+    int xh_ks;
 };
 hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s);
 // int8 + requantizing epilogue for large batches whose rows are whole MFMA steps (launch_gemm picks it)

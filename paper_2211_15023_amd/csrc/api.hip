@@ -166,6 +166,7 @@ struct Step {
     bool fused_prev = false;    // conv: normally done by the conv step before it
     bool resblock = false;      // conv with fuse_next: the pair is a residual block (skip connection from this step's input)
     bool stack_head = false;    // conv: normally runs together with its max-pool and the two residual blocks behind it (steps +1 .. +5)
+    bool packs_next = false;    // dense: the step behind it packs an LSTM's operand, which the kernels that split K write themselves
     bool mlp_head = false;      // fp32 dense: normally runs the whole network (all steps behind it are then skipped)
     bool stack_member = false;  // max-pool / conv: normally done by the stack kernel of an earlier step
     ConvParams cp{};
@@ -863,6 +864,10 @@ int build_plan(Builder& B) {
                 if (In % 8 == 0 && Hd % 8 == 0 && Kx % 128 == 0 && lp.x_pitch_bytes % (cur.el == EL_I8 ? 8 : 16) == 0 && cur.el != EL_F32)
                     lp.frag_ks = Kx / 32;
                 pk.out_elems = Kp;
+                if (lp.frag_ks > 0 && !pol->steps.empty() && !getenv("ACCERL_NO_LSTM_FUSE")) {
+                    Step& fc = pol->steps.back();
+                    fc.packs_next = fc.kind == ST_GEMM && fc.out_buf == pk.in_buf && fc.gp.N == In && fc.gp.Np == In;
+                }
                 pol->steps.push_back(pk);
                 const TensorSpec& tih = B.tensor(i, 0);
                 const TensorSpec& thh = B.tensor(i, 1);
@@ -1054,6 +1059,7 @@ int run(accerl_policy* p, const Call& c) {
         auto bufp = [&](int b) -> char* { return b < 0 ? const_cast<char*>(states) : p->ws + p->bufs[b].off; };
         bool pooled = false;   // the last conv step also did the max-pool that follows it
         bool conv_pair_done = false;   // the last conv step also did the conv that follows it
+        bool packed = false;           // the last dense step also packed the LSTM's operand
         int stack_skip = 0;            // conv steps still to pass over: a stack kernel has done them
         hipEvent_t prof_prev = nullptr;
         for (int si = 0; si <= last_step; ++si) {
@@ -1158,6 +1164,13 @@ int run(accerl_policy* p, const Call& c) {
                     gp.c = c.c ? c.c + c0 * p->lstm_hidden : nullptr;
                     gp.B = n;
                     if (c.debug) gp.x_frag = 0;
+                    if (s.packs_next && !c.debug && gemm_ksplit_supported(gp, s.el, s.epi)) {
+                        const Step& pk = p->steps[si + 1];
+                        gp.xh = (uint16_t*)bufp(pk.out_buf);
+                        gp.done = c.done ? c.done + c0 : nullptr;
+                        gp.Hd = pk.lp.Hd; gp.xh_scale = pk.lp.x_scale; gp.xh_relu = pk.lp.x_relu; gp.xh_ks = pk.lp.frag_ks;
+                        packed = true;
+                    }
                     e = launch_gemm(gp, s.el, s.epi, c.stream);
                     break;
                 }
@@ -1182,6 +1195,7 @@ int run(accerl_policy* p, const Call& c) {
                     break;
                 }
                 case ST_LSTM_PACK: {
+                    if (packed) { packed = false; launched = false; break; }   // done by the dense step before
                     LstmPackParams lp = s.lp;
                     lp.x = bufp(s.in_buf);
                     lp.done = c.done ? c.done + c0 : nullptr;
@@ -1275,6 +1289,7 @@ static void assign_slots(accerl_policy* pol, int layout) {
         if (layout == 0 && st.kind == ST_CONV && st.pool_buf >= 0 && !st.stack_head) touched[2] = st.pool_buf;   // writes the pooled image only
         if (layout == 1 && st.kind == ST_CONV) touched[3] = st.pool_buf;                       // may run either way
         if (layout == 0 && pol->steps[0].mlp_head) continue;                                    // the whole network is one launch
+        if (layout == 0 && st.packs_next) touched[3] = pol->steps[si + 1].out_buf;              // may write the LSTM's operand
         if (layout == 0 && st.stack_member) continue;                                           // done by the stack kernel
         if (layout == 0 && st.stack_head) touched[2] = pol->steps[si + 5].out_buf;              // reads its input, writes the stack's output
         if (layout == 0 && st.kind == ST_MAXPOOL && st.fused) continue;                         // never launched

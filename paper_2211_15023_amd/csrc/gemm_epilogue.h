@@ -25,8 +25,18 @@ __device__ __forceinline__ uint32_t g_f2bf(float x) {
 __device__ __forceinline__ float g_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 
+// 16-byte piece of inputs k .. k + 7 (k a multiple of 8) of state b in the LSTM operand's fragment order
+__device__ __forceinline__ char* lstm_piece(const GemmParams& p, int64_t b, int k) {
+    return (char*)p.xh + ((((b >> 4) * p.xh_ks + (k >> 5)) << 6) + ((k >> 3) & 3) * 16 + (b & 15)) * 16;
+}
+typedef int v2i __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ v2i lstm_pack4(const float (&v)[4]) {
+    return (v2i){(int)(g_f2bf(v[0]) | (g_f2bf(v[1]) << 16)), (int)(g_f2bf(v[2]) | (g_f2bf(v[3]) << 16))};
+}
+
 // Results of features n0 .. n0 + 3 of state b (sums with the bias): requantized int8, bf16, head outputs or the LSTM cell.
-template <int EPI, typename ACC>
+// XH: to the LSTM's operand instead (the values lstm_pack_frag_kernel makes of the stored ones).
+template <int EPI, bool XH = false, typename ACC>
 __device__ __forceinline__ void gemm_finish(const GemmParams& p, const ACC& acc, int64_t b, int n0) {
     if constexpr (EPI == EPI_REQUANT) {
         const v4f ml = *(const v4f*)(p.mult + n0);
@@ -42,7 +52,17 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, const ACC& acc,
                 pk |= ((uint32_t)(int)y & 0xffu) << (8 * r);
             }
         }
-        *(uint32_t*)((int8_t*)p.out + b * p.Np + n0) = pk;
+        if constexpr (XH) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int q = (int)(int8_t)(pk >> (8 * r));
+                v[r] = (float)(p.xh_relu ? max(q, 0) : q) * p.xh_scale;
+            }
+            *(v2i*)(lstm_piece(p, b, n0) + 2 * (n0 & 4)) = lstm_pack4(v);
+        } else {
+            *(uint32_t*)((int8_t*)p.out + b * p.Np + n0) = pk;
+        }
     } else if constexpr (EPI == EPI_HEADS_I8) {
         const v4f ml = *(const v4f*)(p.mult + n0);
 #pragma unroll
@@ -60,6 +80,14 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, const ACC& acc,
         for (int r = 0; r < 4; ++r) {
             v[r] = acc[r];
             if (p.relu) v[r] = fmaxf(v[r], 0.0f);
+        }
+        if constexpr (XH) {
+            if (p.xh_relu) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(__uint_as_float(g_f2bf(v[r]) << 16), 0.0f);
+            }
+            *(v2i*)(lstm_piece(p, b, n0) + 2 * (n0 & 4)) = lstm_pack4(v);
+            return;
         }
         uint32_t* d = (uint32_t*)((uint16_t*)p.out + b * p.Np + n0);
         d[0] = g_f2bf(v[0]) | (g_f2bf(v[1]) << 16);

@@ -21,7 +21,54 @@ namespace {
 constexpr int KS_LDS = 64 * 1024;
 constexpr int KS_W = KSPLIT_PARTS;                            // wavefronts per workgroup
 
-template <int EL, int EPI, int RT, int NT, bool RELU, bool FRAG>
+// The state's half of an LSTM operand (GemmParams::xh): thread tid of T packs 8-value pieces of ROWS states, those of the
+// workgroup's share (y of ny) of h; as lstm_pack_frag_kernel.  The first piece is requested when the kernel starts and
+// stored when it ends (one piece a thread is all there is for 64 x 64 tiles and as many units as inputs).  4096 states, 1936 -> 256
+// in front of 256 units: 10.7 us and 5.2 for the packing kernel -> 12.2; bf16 3872 -> 256 at 999 states 10.5 + 3.8 -> 11.2.  Kernels of
+// their own: carried by the plain ones as a test of p.xh, this cost every dense layer about a microsecond.
+template <bool XH, int T, int ROWS>
+struct LstmState {
+    const GemmParams& p;
+    int64_t b0, b;
+    int tid, q0, np, items, q;
+    v4f h0, h1;
+    bool dn;
+    __device__ __forceinline__ LstmState(const GemmParams& p_, int64_t b0_, int tid_) : p(p_), b0(b0_), tid(tid_), items(0) {
+        if (!XH) return;
+        const int Q = p.Hd >> 3;
+        q0 = blockIdx.y * Q / gridDim.y;
+        np = (blockIdx.y + 1) * Q / gridDim.y - q0;
+        items = ROWS * np;
+        if (tid < items) load(tid);
+    }
+    __device__ __forceinline__ void load(int i) {
+        const int t = i >> 4, u = t / np;
+        b = b0 + 16 * u + (i & 15);
+        q = q0 + t - u * np;
+        if (b >= p.B) return;
+        const v4f* h = (const v4f*)(p.h + b * p.Hd + 8 * q);
+        h0 = h[0]; h1 = h[1];
+        dn = p.done && p.done[b] != 0;
+    }
+    __device__ __forceinline__ void store() {
+        if (!XH) return;
+        for (int i = tid; i < items; i += T) {
+            if (i != tid) load(i);
+            if (b >= p.B) continue;                        // (the product does not store these states)
+            if (dn) {
+                const v4f z = {0.0f, 0.0f, 0.0f, 0.0f};
+                v4f *h = (v4f*)(p.h + b * p.Hd + 8 * q), *c = (v4f*)(p.c + b * p.Hd + 8 * q);
+                h[0] = h0 = z; h[1] = h1 = z;
+                c[0] = z; c[1] = z;
+            }
+            const float lo[4] = {h0[0], h0[1], h0[2], h0[3]}, hi[4] = {h1[0], h1[1], h1[2], h1[3]};
+            const v2i l = lstm_pack4(lo), u = lstm_pack4(hi);
+            *(v4i*)lstm_piece(p, b, p.N + 8 * q) = (v4i){l[0], l[1], u[0], u[1]};
+        }
+    }
+};
+
+template <int EL, int EPI, int RT, int NT, bool RELU, bool FRAG, bool XH>
 __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams p) {
     typedef typename std::conditional<EL == EL_I8, v4i, v4f>::type Acc;
     constexpr int W = KS_W, D = 2;                          // D steps in flight per wavefront
@@ -35,6 +82,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     const int nt0 = blockIdx.y * NT;
     const int ks = p.k_steps;
     const int s0 = wave * ks / W, s1 = (wave + 1) * ks / W;   // this wavefront's steps
+    LstmState<XH, 64 * W, 16 * RT> lstm(p, b0, tid);
 
     // Row-major states: a lane fetches 16 bytes of row lane / 4 (four lanes read 64 consecutive bytes; the fragment's own order
     // would touch 16 rows per quarter wavefront), and the wavefront turns them into fragments through its own LDS region.
@@ -140,17 +188,20 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
             Acc sum = *(const Acc*)((const char*)p.bias + 4 * n0);
 #pragma unroll
             for (int w = 0; w < W; ++w) sum += s_part[((w * RH + u) * NT + t) * 64 + lane];
-            gemm_finish<EPI>(p, sum, b, n0);
+            gemm_finish<EPI, XH>(p, sum, b, n0);
         }
     }
+    lstm.store();
 }
 
 template <int EL, int EPI, int RT, int NT>
 hipError_t go(const GemmParams& p, hipStream_t s) {
     const dim3 grid((unsigned)((p.B + 16 * RT - 1) / (16 * RT)), (unsigned)((p.n_tiles + NT - 1) / NT));
-#define GO(RELU, FRAG) gemm_ksplit_kernel<EL, EPI, RT, NT, RELU, FRAG><<<grid, dim3(64 * KS_W), 0, s>>>(p)
-    if (p.relu_in) { if (p.x_frag) GO(true, true); else GO(true, false); }
-    else { if (p.x_frag) GO(false, true); else GO(false, false); }
+#define GO(RELU, FRAG, XH) gemm_ksplit_kernel<EL, EPI, RT, NT, RELU, FRAG, XH><<<grid, dim3(64 * KS_W), 0, s>>>(p)
+#define GO2(RELU, FRAG) do { if (p.xh) GO(RELU, FRAG, true); else GO(RELU, FRAG, false); } while (0)
+    if (p.relu_in) { if (p.x_frag) GO2(true, true); else GO2(true, false); }
+    else { if (p.x_frag) GO2(false, true); else GO2(false, false); }
+#undef GO2
 #undef GO
     return hipGetLastError();
 }
@@ -159,6 +210,7 @@ hipError_t go(const GemmParams& p, hipStream_t s) {
 // lane fetches its fragment's 16 bytes itself and wavefront t finishes feature tile t.  Shorter than the kernel above (no turn
 // through LDS, half the partial sums), it is the faster one for narrow layers at middle batches: see ksplit_small_i8.
 constexpr int KM_W = 4, KM_NT = 4;
+template <bool XH>
 __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const GemmParams p) {
     __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -166,6 +218,7 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
     const int64_t b = (int64_t)blockIdx.x * 16 + j;
     const int nt0 = blockIdx.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
     const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one
+    LstmState<XH, 64 * KM_W, 16> lstm(p, (int64_t)blockIdx.x * 16, tid);
 
     v4i acc[KM_NT];
 #pragma unroll
@@ -207,12 +260,13 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
 #pragma unroll
     for (int t = 0; t < KM_NT; ++t) s_part[(wave * KM_NT + t) * 64 + lane] = acc[t];
     __syncthreads();
+    lstm.store();
     const int n0 = (nt0 + wave) * 16 + 4 * g;
     if (wave >= nts || b >= p.B || n0 >= p.Np) return;
     v4i sum = *(const v4i*)((const int*)p.bias + n0);
 #pragma unroll
     for (int w = 0; w < KM_W; ++w) sum += s_part[(w * KM_NT + wave) * 64 + lane];
-    gemm_finish<EPI_REQUANT>(p, sum, b, n0);
+    gemm_finish<EPI_REQUANT, XH>(p, sum, b, n0);
 }
 
 int64_t groups(const GemmParams& p, int rt, int nt) { return ((p.B + 16 * rt - 1) / (16 * rt)) * ((p.n_tiles + nt - 1) / nt); }
@@ -241,7 +295,9 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
     if (groups(p, 1, 2) <= most) return go<EL, EPI, 1, 2>(p, s);
     if constexpr (EL == EL_I8) {
         if (ksplit_small_i8(p)) {
-            gemm_ksplit_small_i8_kernel<<<dim3((unsigned)((p.B + 15) / 16), (unsigned)((p.n_tiles + KM_NT - 1) / KM_NT)), dim3(64 * KM_W), 0, s>>>(p);
+            const dim3 grid((unsigned)((p.B + 15) / 16), (unsigned)((p.n_tiles + KM_NT - 1) / KM_NT));
+            if (p.xh) gemm_ksplit_small_i8_kernel<true><<<grid, dim3(64 * KM_W), 0, s>>>(p);
+            else gemm_ksplit_small_i8_kernel<false><<<grid, dim3(64 * KM_W), 0, s>>>(p);
             return hipGetLastError();
         }
     }

@@ -287,7 +287,8 @@ __global__ __launch_bounds__(256) void lstm_pack_kernel(LstmPackParams p) {
     p.xh[i] = f32_to_bf16_rne(v);
 }
 
-// The same operand in the fragment order of the matrix product (GemmParams::x_frag): a wavefront packs 16 states x 32 inputs,
+// The same operand in the fragment order of the matrix product (GemmParams::x_frag), behind dense kernels that do not write it
+// themselves (GemmParams::xh: those whose wavefronts split K do): a wavefront packs 16 states x 32 inputs,
 // lane (state j, block g) the eight values of its 16 bytes, and stores one contiguous KiB.  The product then reads whole KiB
 // too instead of 16 rows per quarter wavefront.  4096 states, 256 + 256 inputs: pack 7.6 -> 5.2 us (two bytes a lane before), product
 // 19.6 -> 16.2 us.
