@@ -196,6 +196,7 @@ struct GemmParams {
 hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s);
 // int8 + requantizing epilogue for large batches whose rows are whole MFMA steps (launch_gemm picks it)
 bool gemm_stream_supported(const GemmParams& p);
+bool gemm_stream_rows_supported(const GemmParams& p);   // the same for row-major states with a ReLU, or whose rows end inside a step
 hipError_t launch_gemm_stream(const GemmParams& p, hipStream_t s);
 
 // the wavefronts of a workgroup split K (launch_gemm picks it)

@@ -224,7 +224,7 @@ hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s)
     if (gemm_ksplit_supported(p, el, epi)) return launch_gemm_ksplit(p, el, s);
     if (el == EL_I8 && epi == EPI_REQUANT) {
         static const bool no_stream = getenv("ACCERL_NO_GEMM_STREAM") != nullptr;
-        if (!no_stream && gemm_stream_supported(p)) return launch_gemm_stream(p, s);
+        if (!no_stream && (gemm_stream_supported(p) || gemm_stream_rows_supported(p))) return launch_gemm_stream(p, s);
         return gemm_go<EL_I8, EPI_REQUANT>(p, grid, s);
     }
     if (el == EL_I8 && epi == EPI_HEADS_I8) return gemm_go<EL_I8, EPI_HEADS_I8>(p, grid, s);

@@ -10,10 +10,10 @@
 //   * the loads are spread between the MFMAs of the stage, two after every four MFMAs, instead of one burst;
 //   * LDS holds two stages of weight fragments, so one barrier per stage suffices.
 // Rows are whole MFMA steps here (Kp_bytes == 64 * k_steps, no ReLU on the input), which leaves no fix-ups in
-// the loop; other shapes stay with gemm_kernel.  Integer accumulation: results are bit-identical.
+// the loop, or at large batches whole 16-byte chunks; other shapes stay with gemm_kernel.  Integer accumulation: results are bit-identical.
 #include <type_traits>
 
-#include "accerl_internal.h"
+#include "gemm_epilogue.h"
 
 namespace accerl {
 
@@ -27,7 +27,9 @@ constexpr int SG_LDS = 2 * SG_BUF;
 
 // WAVES wavefronts of 16 states each: eight when that still gives every compute unit a workgroup (the weight
 // fragments are then fetched and written to LDS once per 128 states), else four
-template <int WAVES>
+// RELU: of the input.  TAIL: rows of whole 16-byte chunks that end inside a step: the chunks behind the row re-read its last one
+// (their weights are zero).
+template <int WAVES, bool RELU, bool TAIL>
 __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const GemmParams p) {
     constexpr int SG_ROWS = 16 * WAVES;
     constexpr int SG_WF = SG_NT * SG_KS / WAVES;    // weight fragments a wavefront fetches per stage
@@ -57,7 +59,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
     for (int t = 0; t < SG_NT; ++t) acc[t] = *(const v4i*)((const int*)p.bias + (nt0 + t) * 16 + 4 * g);
 
     // steps past the end of K load the last step again (never multiplied)
-    auto load_x = [&](v4i& d, int step) { d = *(const v4i*)(xb + (int64_t)min(step, ks - 1) * xstep); };
+    const int xlast = p.Kp_bytes - 16 - g * 16;
+    auto load_x = [&](v4i& d, int step) {
+        if constexpr (TAIL) d = *(const v4i*)(xb + min(step * 64, xlast));
+        else d = *(const v4i*)(xb + (int64_t)min(step, ks - 1) * xstep);
+    };
     auto load_w = [&](v4i& d, int step) { d = *(const v4i*)(wb + (int64_t)min(step + wstep0, ks - 1) * 1024); };
     auto commit = [&](const v4i (&w)[SG_WF], int buf) {
 #pragma unroll
@@ -99,10 +105,15 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
 #pragma unroll
                 for (int t = 0; t < SG_NT; ++t) fa[(st + 1) & 1][t] = *(const v4i*)(src + (t * SG_KS + st + 1) * 1024);
             }
+            v4i x = xs[cur][st];
+            if constexpr (RELU) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = (int)g_relu_i8x4((uint32_t)x[e]);
+            }
             if (full || s * SG_KS + st < ks) {
 #pragma unroll
                 for (int t = 0; t < SG_NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[st & 1][t], xs[cur][st], acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[st & 1][t], x, acc[t], 0, 0, 0);
             }
             if (full) {
                 load_x(xs[cur][st], (s + 2) * SG_KS + st);
@@ -160,20 +171,36 @@ bool gemm_stream_supported(const GemmParams& p) {
     return p.B > 0 && !p.relu_in && p.k_steps >= 2 * SG_KS && p.Kp_bytes == 64 * p.k_steps && p.n_tiles % SG_NT == 0;
 }
 
-hipError_t launch_gemm_stream(const GemmParams& p, hipStream_t s) {
+template <int WAVES>
+static int64_t stream_groups(const GemmParams& p) { return (p.B + 16 * WAVES - 1) / (16 * WAVES) * (p.n_tiles / SG_NT); }
+
+// Rows with a ReLU or an end inside a step take this kernel where eight wavefronts are used: 1936 -> 256 behind the int8
+// stacks, 16384 states, 26.3 -> 22.0 us (kernel traces); whole forwards through a small convolution: 1936 -> 256 at 8192 states
+// 36.1 -> 32.2 us, 3600 -> 500 at 4096 39.7 -> 36.6, 784 -> 512 at 16384 45.6 -> 41.5.  With four it is not always the faster one
+// (3600 -> 500 at 2100 states 35.9 -> 38.4, 1936 -> 256 at 4200 34.8 -> 32.5).
+bool gemm_stream_rows_supported(const GemmParams& p) {
+    return p.B > 0 && !p.x_frag && p.k_steps >= 2 * SG_KS && p.Kp_bytes % 16 == 0 && p.n_tiles % SG_NT == 0 &&
+           stream_groups<8>(p) >= conv_num_cus();
+}
+
+template <int WAVES, bool RELU, bool TAIL>
+static hipError_t stream_go(const GemmParams& p, hipStream_t s) {
     static bool set = false;
     if (!set) {
-        hipError_t e = hipFuncSetAttribute((const void*)gemm_stream_i8_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, SG_LDS);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void*)gemm_stream_i8_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, SG_LDS);
+        hipError_t e = hipFuncSetAttribute((const void*)gemm_stream_i8_kernel<WAVES, RELU, TAIL>, hipFuncAttributeMaxDynamicSharedMemorySize, SG_LDS);
         if (e != hipSuccess) return e;
         set = true;
     }
-    const unsigned gy = (unsigned)(p.n_tiles / SG_NT);
-    const int64_t g8 = (p.B + 127) / 128, g4 = (p.B + 63) / 64;
-    if (g8 * gy >= conv_num_cus()) gemm_stream_i8_kernel<8><<<dim3((unsigned)g8, gy), dim3(512), SG_LDS, s>>>(p);
-    else gemm_stream_i8_kernel<4><<<dim3((unsigned)g4, gy), dim3(256), SG_LDS, s>>>(p);
+    const dim3 grid((unsigned)((p.B + 16 * WAVES - 1) / (16 * WAVES)), (unsigned)(p.n_tiles / SG_NT));
+    gemm_stream_i8_kernel<WAVES, RELU, TAIL><<<grid, dim3(64 * WAVES), SG_LDS, s>>>(p);
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_stream(const GemmParams& p, hipStream_t s) {
+    if (gemm_stream_supported(p))
+        return stream_groups<8>(p) >= conv_num_cus() ? stream_go<8, false, false>(p, s) : stream_go<4, false, false>(p, s);
+    if (p.Kp_bytes == 64 * p.k_steps) return stream_go<8, true, false>(p, s);
+    return p.relu_in ? stream_go<8, true, true>(p, s) : stream_go<8, false, true>(p, s);
 }
 
 }  // namespace accerl
