@@ -7,7 +7,8 @@
 // memory behind it however many loads its wavefronts keep open, so the tile is the smallest that still gives every unit one
 // workgroup: more units pull, and none of them twice.  The kernel this replaces walked K alone in each 64 x 64 workgroup
 // (64 workgroups on 256 units for 1024 states of a 3872 -> 256 layer): 41 -> 10.2 us there; 3136 -> 512 at 500 states
-// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us (medians of kernel traces).
+// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us, then 25 with two 64 x 64 tiles per
+// unit (medians of kernel traces).
 #include <type_traits>
 
 #include "gemm_epilogue.h"
@@ -21,6 +22,20 @@ namespace {
 constexpr int KS_LDS = 64 * 1024;
 constexpr int KS_W = KSPLIT_PARTS;                            // wavefronts per workgroup
 
+// The tile of a workgroup: x of the states, y of the features.  Workgroup n runs on XCD n mod 8; every XCD takes consecutive tiles, all
+// features of one group of states before the next group, so that a group's states come into one second-level cache.  (In the grid's own
+// order they do only if the groups of states are a multiple of eight; else each is fetched by up to eight.  Whole forwards around
+// 3136 -> 512, us: bf16 200 states 24.7 -> 22.6, 400 30.2 -> 27.8, 500 28.5 -> 28.6 (16 groups), 3600 111 -> 100; int8 400 states
+// 21.7 -> 19.8, 513 27.4 -> 24.9, 900 28.7 -> 26.6.  All states of one group of features before the next, whose weights are then
+// fetched once: no faster than the grid's order at the small batches where weights are the larger part, 160 states 16.6 -> 17.1.)
+struct KsTile { unsigned x, y; };
+__device__ __forceinline__ KsTile ks_tile() {
+    const unsigned n = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7;
+    const unsigned t = xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);     // the first n mod 8 XCDs have one tile more
+    const unsigned x = t / gridDim.y;
+    return {x, t - x * gridDim.y};
+}
+
 // The state's half of an LSTM operand (GemmParams::xh): thread tid of T packs 8-value pieces of ROWS states, those of the
 // workgroup's share (y of ny) of h; as lstm_pack_frag_kernel.  The first piece is requested when the kernel starts and
 // stored when it ends (one piece a thread is all there is for 64 x 64 tiles and as many units as inputs).  4096 states, 1936 -> 256
@@ -33,11 +48,11 @@ struct LstmState {
     int tid, q0, np, items, q;
     v4f h0, h1;
     bool dn;
-    __device__ __forceinline__ LstmState(const GemmParams& p_, int64_t b0_, int tid_) : p(p_), b0(b0_), tid(tid_), items(0) {
+    __device__ __forceinline__ LstmState(const GemmParams& p_, int64_t b0_, unsigned y, int tid_) : p(p_), b0(b0_), tid(tid_), items(0) {
         if (!XH) return;
         const int Q = p.Hd >> 3;
-        q0 = blockIdx.y * Q / gridDim.y;
-        np = (blockIdx.y + 1) * Q / gridDim.y - q0;
+        q0 = y * Q / gridDim.y;
+        np = (y + 1) * Q / gridDim.y - q0;
         items = ROWS * np;
         if (tid < items) load(tid);
     }
@@ -78,11 +93,12 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const int64_t b0 = (int64_t)blockIdx.x * (16 * RT);
-    const int nt0 = blockIdx.y * NT;
+    const KsTile tile = ks_tile();
+    const int64_t b0 = (int64_t)tile.x * (16 * RT);
+    const int nt0 = tile.y * NT;
     const int ks = p.k_steps;
     const int s0 = wave * ks / W, s1 = (wave + 1) * ks / W;   // this wavefront's steps
-    LstmState<XH, 64 * W, 16 * RT> lstm(p, b0, tid);
+    LstmState<XH, 64 * W, 16 * RT> lstm(p, b0, tile.y, tid);
 
     // Row-major states: a lane fetches 16 bytes of row lane / 4 (four lanes read 64 consecutive bytes; the fragment's own order
     // would touch 16 rows per quarter wavefront), and the wavefront turns them into fragments through its own LDS region.
@@ -199,8 +215,12 @@ hipError_t go(const GemmParams& p, hipStream_t s) {
     const dim3 grid((unsigned)((p.B + 16 * RT - 1) / (16 * RT)), (unsigned)((p.n_tiles + NT - 1) / NT));
 #define GO(RELU, FRAG, XH) gemm_ksplit_kernel<EL, EPI, RT, NT, RELU, FRAG, XH><<<grid, dim3(64 * KS_W), 0, s>>>(p)
 #define GO2(RELU, FRAG) do { if (p.xh) GO(RELU, FRAG, true); else GO(RELU, FRAG, false); } while (0)
-    if (p.relu_in) { if (p.x_frag) GO2(true, true); else GO2(true, false); }
-    else { if (p.x_frag) GO2(false, true); else GO2(false, false); }
+    if (RT == 8 && p.x_frag) return hipErrorInvalidValue;     // (128 x 64 tiles are for row-major states, see pick)
+    if constexpr (RT < 8) {
+        if (p.x_frag) { if (p.relu_in) GO2(true, true); else GO2(false, true); return hipGetLastError(); }
+    }
+    if (p.relu_in) GO2(true, false);
+    else GO2(false, false);
 #undef GO2
 #undef GO
     return hipGetLastError();
@@ -215,10 +235,11 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
     __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const int64_t b = (int64_t)blockIdx.x * 16 + j;
-    const int nt0 = blockIdx.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
+    const KsTile tile = ks_tile();
+    const int64_t b = (int64_t)tile.x * 16 + j;
+    const int nt0 = tile.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
     const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one
-    LstmState<XH, 64 * KM_W, 16> lstm(p, (int64_t)blockIdx.x * 16, tid);
+    LstmState<XH, 64 * KM_W, 16> lstm(p, (int64_t)tile.x * 16, tile.y, tid);
 
     v4i acc[KM_NT];
 #pragma unroll
@@ -285,9 +306,11 @@ bool ksplit_small_i8(const GemmParams& p) {
 
 // The smallest tile that gives at most about one workgroup per compute unit.  Measured on 3136 -> 512 (fragment order; us, tile
 // of states x features): bf16, 160 states 16x32 6.5, 16x16 7.2, 32x32 7.3; 500 states 32x32 7.8, 16x64 8.4, 32x64 9.8; 1000
-// states 32x64 9.8, 32x32 11.4, 64x64 12.4; 2048 states 64x64 12.9, 32x64 16.1; 3000 states 128x64 26.9, 64x64 34.2.  int8, 64
+// states 32x64 9.8, 32x32 11.4, 64x64 12.4; 2048 states 64x64 12.9, 32x64 16.1.  int8, 64
 // states 16x16 4.0, 16x32 4.3; 160 states 16x32 4.3, 16x16 4.5; 512 states 32x32 5.7, 16x64 6.2, 16x32 6.6; 1000 states 32x64 7.2,
-// 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.
+// 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.  bf16 beyond one 64x64 workgroup per unit: two of them in fragment order, 128x64 for
+// row-major states (whole forwards, 64x64 / 128x64: 3136 -> 512 in fragment order at 2310 states 77.2 / 81.0, 3000 85.8 / 88.7,
+// 3600 96.9 / 100.4, 4096 103.5 / 106.2; 3872 -> 256 row-major at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
 template <int EL, int EPI>
 hipError_t pick(const GemmParams& p, hipStream_t s) {
     const int64_t most = most_groups();
@@ -303,7 +326,7 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
     }
     if (groups(p, 2, 2) <= most) return go<EL, EPI, 2, 2>(p, s);
     if (groups(p, 2, 4) <= most) return go<EL, EPI, 2, 4>(p, s);
-    if constexpr (EL == EL_BF16) { if (groups(p, 4, 4) > most) return go<EL, EPI, 8, 4>(p, s); }
+    if constexpr (EL == EL_BF16) { if (groups(p, 4, 4) > most && !p.x_frag) return go<EL, EPI, 8, 4>(p, s); }
     return go<EL, EPI, 4, 4>(p, s);
 }
 
@@ -314,7 +337,7 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 // workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192 states 9.1 / 9.5).  Where the weights exceed the
 // 4 MB of an XCD's second-level cache, the streaming kernel is already the faster one when 32 x 64 tiles no longer fit (3136 ->
 // 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
-// bf16 layers beyond one 64 x 64 workgroup per compute unit take 128 x 64 tiles while those fill at most one round and the
+// bf16 layers beyond one 64 x 64 workgroup per compute unit stay here while 128 x 64 tiles (or twice as many of 64 x 64) fill at most one round and the
 // eighth of K that a wavefront walks is at least eight steps (us, this / gemm_kernel: 3136 -> 512 at 3000 states 27 / 34, 4096
 // 28 / 34; 3872 -> 256 at 5000 31 / 49, 8192 40 / 51; but 1296 -> 128 at 10000 20.5 / 16.5), with a second to fourth round only for
 // row-major states, which gemm_kernel fetches badly, and only if the last round is full (3872 -> 2048: 2000 states, two rounds,
