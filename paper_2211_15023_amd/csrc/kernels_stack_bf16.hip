@@ -45,7 +45,7 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 
 struct BStackParams {
     const void* in;          // uint8 planes [B, 4, HIN, HIN] or bf16 [B, HIN, HIN, CI]
-    const int32_t* rows;     // observation i is row rows[i] of in (NULL = row i)
+    const int32_t* rows;     // ROWS: observation i is row rows[i] of in
     char* out;               // bf16 [B, H, H, C]
     const v4i* w[5];         // 0: stack convolution, 1 / 2: first block's conv A / B, 3 / 4: second block's
     const float* bias[5];
@@ -136,7 +136,8 @@ __device__ __forceinline__ v4f bs_bottom(const v4i* w, const BsRow& r, v4f acc) 
     else return bs_mfma(w[8], r.f[2], bs_mfma(w[7], r.f[1], bs_mfma(w[6], r.f[0], acc)));
 }
 
-template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG>
+// ROWS: observations through the row list (as a test in the kernel it cost the others 0.5 us of 169 at 1024 states)
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, bool ROWS>
 __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p) {
     typedef BsShape<U8, CI, HIN, C, G, SEG, PSEG> S;
     constexpr int T = S::THREADS;
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     // ---- staging of observations: unit u is one dword of each of the four planes
     v4i pre[S::PF];
     auto prefetch = [&](int64_t batch) {
-        const char* src = (const char*)p.in + (p.rows ? (int64_t)p.rows[batch] : batch) * (int64_t)S::IMG_IN;
+        const char* src = (const char*)p.in + (ROWS ? (int64_t)p.rows[batch] : batch) * (int64_t)S::IMG_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
             const int u = min(tid + i * T, S::UNITS - 1);    // a unit that does not exist re-reads the last one
@@ -453,10 +454,11 @@ bool bs_shape_ok(const ConvParams& c, const ConvParams& a1, const ConvParams& b1
     return a1.relu_in && a1.relu && !b1.relu_in && !b1.relu && a2.relu_in && a2.relu && !b2.relu_in && !b2.relu;
 }
 
-template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG>
+template <bool U8, int CI, int HIN, int C, int G, int SEG, int PSEG, bool ROWS = false>
 hipError_t bs_go(const BStackParams& p, hipStream_t s) {
+    if constexpr (U8 && !ROWS) { if (p.rows) return bs_go<U8, CI, HIN, C, G, SEG, PSEG, true>(p, s); }
     typedef BsShape<U8, CI, HIN, C, G, SEG, PSEG> S;
-    auto kfn = stack_bf16_kernel<U8, CI, HIN, C, G, SEG, PSEG>;
+    auto kfn = stack_bf16_kernel<U8, CI, HIN, C, G, SEG, PSEG, ROWS>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS);
     if (attr != hipSuccess) return attr;
     // one workgroup per compute unit (LDS and registers), striding over the batches in even rounds
