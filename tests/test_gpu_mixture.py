@@ -119,7 +119,7 @@ def _wide_head_net(cout):
 
 
 @pytest.mark.parametrize("passes", [False, True])
-@pytest.mark.parametrize("pair", ["nature", "impala", "net1", "net2", "wide heads", "odd size"])
+@pytest.mark.parametrize("pair", ["nature", "impala", "net1", "net2", "wide heads", "odd size", "two convolutions"])
 def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes):
     """Every kernel that can be the first of an image policy reads through the row list, and both forms of the heads kernel
     write through it: bit for bit what the policies compute on those rows alone, also when a policy runs in several passes."""
@@ -145,6 +145,12 @@ def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes
         net = SimpleNamespace(name="odd", obs_dtype="u8", obs_shape=(3, 12, 16), n_actions=3,
                               layers=[dict(kind="conv", cin=3, cout=12, k=3, stride=1, pad=1, relu=True),
                                       dict(kind="flatten"), dict(kind="dense", cin=12 * 192, cout=24, relu=True)])
+        small, orig = int8_policy(net), float_policy(net)
+    elif pair == "two convolutions":                              # the generic kernel of the first two layers
+        net = SimpleNamespace(name="two", obs_dtype="u8", obs_shape=(4, 60, 60), n_actions=6,
+                              layers=[dict(kind="conv", cin=4, cout=16, k=8, stride=4, pad=0, relu=True),
+                                      dict(kind="conv", cin=16, cout=64, k=4, stride=2, pad=0, relu=True),
+                                      dict(kind="flatten"), dict(kind="dense", cin=64 * 36, cout=24, relu=False)])
         small, orig = int8_policy(net), float_policy(net)
     else:
         net = wl.configs.PAPER_STUDENTS[pair]
