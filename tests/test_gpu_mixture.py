@@ -165,3 +165,32 @@ def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes
     m = _dev(use).bool()
     for got, a, b in zip(out, small.forward(dx, du), orig.forward(dx, du)):
         assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
+
+
+@pytest.mark.parametrize("B", [6001, 30011])
+@pytest.mark.parametrize("shape,convs", [((3, 12, 16), [(12, 3, 1, 1)]), ((4, 20, 20), [(16, 4, 2, 0)]), ((4, 40, 40), [(16, 8, 4, 0), (32, 4, 2, 0)])])
+def test_mixture_of_small_images_in_batches(A, shape, convs, B):
+    """Small images are staged several at a time, neighbours or not: batches with fewer images than planned and with all of them
+    (the larger call), a last batch that is not full, a second pass of the larger policy."""
+    layers, c, hw = [], shape[0], shape[1:]
+    for cout, k, stride, pad in convs:
+        layers.append(dict(kind="conv", cin=c, cout=cout, k=k, stride=stride, pad=pad, relu=True))
+        c, hw = cout, [(v + 2 * pad - k) // stride + 1 for v in hw]
+    layers += [dict(kind="flatten"), dict(kind="dense", cin=c * hw[0] * hw[1], cout=24, relu=True)]
+    net = SimpleNamespace(name="small", obs_dtype="u8", obs_shape=shape, n_actions=3, layers=layers)
+    params = wl.init_params(net, wl.STREAM["weights_student"])
+    qp = oracle.quantize_policy(net, params, make_states(net, 16, wl.STREAM["calibration"]))
+    small, orig = A.Policy(net, "int8", qp.tensors, qp.act_scales), A.Policy(net, "bf16", teacher_tensors(params))
+    for prec, tensors, scales in (("int8", qp.tensors, A.pack_scales(qp.act_scales, qp.tensors)), ("bf16", teacher_tensors(params), None)):
+        plan = A.accerl_plan_describe(A.make_arch(net, prec), A.pack_weights(tensors), scales).splitlines()[1]
+        assert int(plan.split(" G=")[1].split()[0]) > 1 and "fuse_next=0" in plan
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randint(0, 256, (B, *shape), dtype=torch.uint8, device="cuda", generator=gen)
+    u = torch.rand(B, device="cuda", generator=gen)
+    use = (np.random.default_rng(B).random(B) < 0.55).astype(np.uint8)
+    out = small.alloc_outputs(B)
+    print(f"mixture of {shape}, B={B}, smaller rows={int(use.sum())}", flush=True)
+    A.accerl_actor_forward_mixture(small.handle, orig.handle, x, u, use, *out)
+    m = _dev(use).bool()
+    for got, a, b in zip(out, small.forward(x, u), orig.forward(x, u)):
+        assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
