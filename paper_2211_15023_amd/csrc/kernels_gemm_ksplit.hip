@@ -22,14 +22,12 @@ namespace {
 constexpr int KS_LDS = 64 * 1024;
 constexpr int KS_W = KSPLIT_PARTS;                            // wavefronts per workgroup
 
-// The tile of a workgroup: x of the states, y of the features.  Workgroup n runs on XCD n mod 8; every XCD takes consecutive tiles, all
-// features of one group of states before the next group, so that a group's states come into one second-level cache.  (In the grid's own
-// order they do only if the groups of states are a multiple of eight; else each is fetched by up to eight.  Whole forwards around
-// 3136 -> 512, us: bf16 200 states 24.7 -> 22.6, 400 30.2 -> 27.8, 500 28.5 -> 28.6 (16 groups), 3600 111 -> 100; int8 400 states
-// 21.7 -> 19.8, 513 27.4 -> 24.9, 900 28.7 -> 26.6.  All states of one group of features before the next, whose weights are then
-// fetched once: no faster than the grid's order at the small batches where weights are the larger part, 160 states 16.6 -> 17.1.)
+// The tile of a workgroup: x of the states, y of the features.  Workgroup n runs on XCD n mod 8.  by_xcd: every XCD takes consecutive
+// tiles, all features of one group of states before the next group, so that a group's states come into one second-level cache
+// (see by_xcd below for when).
 struct KsTile { unsigned x, y; };
-__device__ __forceinline__ KsTile ks_tile() {
+__device__ __forceinline__ KsTile ks_tile(int by_xcd) {
+    if (!by_xcd) return {blockIdx.x, blockIdx.y};
     const unsigned n = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7;
     const unsigned t = xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);     // the first n mod 8 XCDs have one tile more
     const unsigned x = t / gridDim.y;
@@ -93,7 +91,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const KsTile tile = ks_tile();
+    const KsTile tile = ks_tile(p.by_xcd);
     const int64_t b0 = (int64_t)tile.x * (16 * RT);
     const int nt0 = tile.y * NT;
     const int ks = p.k_steps;
@@ -210,9 +208,28 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     lstm.store();
 }
 
+// about one workgroup per compute unit
+int64_t most_groups() { return conv_num_cus() * 9 / 8; }
+
+// Whether ks_tile orders by XCD.  In the grid's own order the workgroups of one group of states meet on an XCD only if the groups are a
+// multiple of eight; else each is fetched by up to eight (whole forwards, us, grid / XCD: 3136 -> 512 bf16 200 states 25.8 / 23.9, 400
+// 31.3 / 28.8, 3600 110 / 97, int8 400 22.5 / 20.7, 900 29.5 / 27.4; 3600 -> 500 bf16 3900 83.2 / 60.6).  With a multiple of eight, or one
+// workgroup over all features, nothing is gained in the product, and the convolution in front of it takes longer (2304 -> 256 bf16 at 4096
+// states 20.2 / 22.9, whole forwards 35.0 / 37.0, at 2048 24.6 / 25.9; -> 24 at 3000, 188 groups, 23.7 / 26.3) -- except beyond one round,
+// where a group's first and last features no longer run together, as long as the weights then stay in the 4 MB of an XCD's second-level
+// cache (3600 -> 500 at 16384 states 186 / 173, 2304 -> 512 124 / 116; 3600 -> 2048 at 4096 161 / 169, -> 1500 126 / 130).
+// All states of one group of features before the next, whose weights are then fetched once: no faster than the grid's order at the
+// small batches where weights are the larger part, 160 states 16.6 -> 17.1.
+bool by_xcd(const GemmParams& p, dim3 grid) {
+    const bool l2 = (int64_t)p.n_tiles * p.k_steps * 1024 <= 4 << 20;
+    return grid.y > 1 && ((grid.x & 7) != 0 || (l2 && (int64_t)grid.x * grid.y > most_groups()));
+}
+
 template <int EL, int EPI, int RT, int NT>
-hipError_t go(const GemmParams& p, hipStream_t s) {
+hipError_t go(const GemmParams& q, hipStream_t s) {
+    GemmParams p = q;
     const dim3 grid((unsigned)((p.B + 16 * RT - 1) / (16 * RT)), (unsigned)((p.n_tiles + NT - 1) / NT));
+    p.by_xcd = by_xcd(q, grid);
 #define GO(RELU, FRAG, XH) gemm_ksplit_kernel<EL, EPI, RT, NT, RELU, FRAG, XH><<<grid, dim3(64 * KS_W), 0, s>>>(p)
 #define GO2(RELU, FRAG) do { if (p.xh) GO(RELU, FRAG, true); else GO(RELU, FRAG, false); } while (0)
     if (RT == 8 && p.x_frag) return hipErrorInvalidValue;     // (128 x 64 tiles are for row-major states, see pick)
@@ -235,7 +252,7 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
     __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const KsTile tile = ks_tile();
+    const KsTile tile = ks_tile(p.by_xcd);
     const int64_t b = (int64_t)tile.x * 16 + j;
     const int nt0 = tile.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
     const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one
@@ -292,9 +309,6 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
 
 int64_t groups(const GemmParams& p, int rt, int nt) { return ((p.B + 16 * rt - 1) / (16 * rt)) * ((p.n_tiles + nt - 1) / nt); }
 
-// about one workgroup per compute unit
-int64_t most_groups() { return conv_num_cus() * 9 / 8; }
-
 // Row-major int8 layers of at most 256 features between the batches that 16 x 32 tiles cover with one workgroup per compute
 // unit and those with one 64 x 64 workgroup per two.  us, this kernel / the tile that the rule below would take (rocprofv3):
 // 1936 -> 256, ReLU on the input: 600 states 4.9 / 6.0, 1000 5.1 / 5.6, 1500 7.0 / 7.6, 1800 7.0 / 8.0; 1296 -> 128: 1800 states
@@ -319,8 +333,10 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
     if constexpr (EL == EL_I8) {
         if (ksplit_small_i8(p)) {
             const dim3 grid((unsigned)((p.B + 15) / 16), (unsigned)((p.n_tiles + KM_NT - 1) / KM_NT));
-            if (p.xh) gemm_ksplit_small_i8_kernel<true><<<grid, dim3(64 * KM_W), 0, s>>>(p);
-            else gemm_ksplit_small_i8_kernel<false><<<grid, dim3(64 * KM_W), 0, s>>>(p);
+            GemmParams q = p;
+            q.by_xcd = by_xcd(p, grid);
+            if (p.xh) gemm_ksplit_small_i8_kernel<true><<<grid, dim3(64 * KM_W), 0, s>>>(q);
+            else gemm_ksplit_small_i8_kernel<false><<<grid, dim3(64 * KM_W), 0, s>>>(q);
             return hipGetLastError();
         }
     }
