@@ -192,7 +192,7 @@ struct GemmParams {
     float xh_scale;
     int xh_relu;
     int xh_ks;
-    int by_xcd;              // kernels whose wavefronts split K: the order of their tiles (ks_tile)
+    int by_xcd;              // order of the workgroups' tiles (gemm_tile)
 };
 hipError_t launch_gemm(const GemmParams& p, Elem el, GemmEpi epi, hipStream_t s);
 // int8 + requantizing epilogue for large batches whose rows are whole MFMA steps (launch_gemm picks it)

@@ -25,6 +25,18 @@ __device__ __forceinline__ uint32_t g_f2bf(float x) {
 __device__ __forceinline__ float g_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 
+// The tile of a workgroup: x of the states, y of the features.  Workgroup n runs on XCD n mod 8.  by_xcd: every XCD takes consecutive
+// tiles, all features of one group of states before the next group, so that a group's states come into one second-level cache
+// (the kernels' launch functions say when).
+struct GemmTile { unsigned x, y; };
+__device__ __forceinline__ GemmTile gemm_tile(int by_xcd) {
+    if (!by_xcd) return {blockIdx.x, blockIdx.y};
+    const unsigned n = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7;
+    const unsigned t = xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);     // the first n mod 8 XCDs have one tile more
+    const unsigned x = t / gridDim.y;
+    return {x, t - x * gridDim.y};
+}
+
 // 16-byte piece of inputs k .. k + 7 (k a multiple of 8) of state b in the LSTM operand's fragment order
 __device__ __forceinline__ char* lstm_piece(const GemmParams& p, int64_t b, int k) {
     return (char*)p.xh + ((((b >> 4) * p.xh_ks + (k >> 5)) << 6) + ((k >> 3) & 3) * 16 + (b & 15)) * 16;

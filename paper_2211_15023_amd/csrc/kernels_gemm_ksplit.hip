@@ -22,18 +22,6 @@ namespace {
 constexpr int KS_LDS = 64 * 1024;
 constexpr int KS_W = KSPLIT_PARTS;                            // wavefronts per workgroup
 
-// The tile of a workgroup: x of the states, y of the features.  Workgroup n runs on XCD n mod 8.  by_xcd: every XCD takes consecutive
-// tiles, all features of one group of states before the next group, so that a group's states come into one second-level cache
-// (see by_xcd below for when).
-struct KsTile { unsigned x, y; };
-__device__ __forceinline__ KsTile ks_tile(int by_xcd) {
-    if (!by_xcd) return {blockIdx.x, blockIdx.y};
-    const unsigned n = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7;
-    const unsigned t = xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);     // the first n mod 8 XCDs have one tile more
-    const unsigned x = t / gridDim.y;
-    return {x, t - x * gridDim.y};
-}
-
 // The state's half of an LSTM operand (GemmParams::xh): thread tid of T packs 8-value pieces of ROWS states, those of the
 // workgroup's share (y of ny) of h; as lstm_pack_frag_kernel.  The first piece is requested when the kernel starts and
 // stored when it ends (one piece a thread is all there is for 64 x 64 tiles and as many units as inputs).  4096 states, 1936 -> 256
@@ -91,7 +79,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const KsTile tile = ks_tile(p.by_xcd);
+    const GemmTile tile = gemm_tile(p.by_xcd);
     const int64_t b0 = (int64_t)tile.x * (16 * RT);
     const int nt0 = tile.y * NT;
     const int ks = p.k_steps;
@@ -211,7 +199,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
 // about one workgroup per compute unit
 int64_t most_groups() { return conv_num_cus() * 9 / 8; }
 
-// Whether ks_tile orders by XCD.  In the grid's own order the workgroups of one group of states meet on an XCD only if the groups are a
+// Whether gemm_tile orders by XCD.  In the grid's own order the workgroups of one group of states meet on an XCD only if the groups are a
 // multiple of eight; else each is fetched by up to eight (whole forwards, us, grid / XCD: 3136 -> 512 bf16 200 states 25.8 / 23.9, 400
 // 31.3 / 28.8, 3600 110 / 97, int8 400 22.5 / 20.7, 900 29.5 / 27.4; 3600 -> 500 bf16 3900 83.2 / 60.6).  With a multiple of eight, or one
 // workgroup over all features, nothing is gained in the product, and the convolution in front of it takes longer (2304 -> 256 bf16 at 4096
@@ -252,7 +240,7 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
     __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const KsTile tile = ks_tile(p.by_xcd);
+    const GemmTile tile = gemm_tile(p.by_xcd);
     const int64_t b = (int64_t)tile.x * 16 + j;
     const int nt0 = tile.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
     const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one

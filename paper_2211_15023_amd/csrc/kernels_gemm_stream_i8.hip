@@ -37,8 +37,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const int64_t b0 = (int64_t)blockIdx.x * SG_ROWS;
-    const int nt0 = blockIdx.y * SG_NT;
+    const GemmTile tile = gemm_tile((RELU || TAIL) && p.by_xcd);
+    const int64_t b0 = (int64_t)tile.x * SG_ROWS;
+    const int nt0 = tile.y * SG_NT;
     const int ks = p.k_steps;
 
     // a state past the batch re-reads the last one; its results are not stored
@@ -177,10 +178,17 @@ static int64_t stream_groups(const GemmParams& p) { return (p.B + 16 * WAVES - 1
 // Rows with a ReLU or an end inside a step take this kernel where eight wavefronts are used: 1936 -> 256 behind the int8
 // stacks, 16384 states, 26.3 -> 22.0 us (kernel traces); whole forwards through a small convolution: 1936 -> 256 at 8192 states
 // 36.1 -> 32.2 us, 3600 -> 500 at 4096 39.7 -> 36.6, 784 -> 512 at 16384 45.6 -> 41.5.  With four it is not always the faster one
-// (3600 -> 500 at 2100 states 35.9 -> 38.4, 1936 -> 256 at 4200 34.8 -> 32.5).
+// (3600 -> 500 at 2100 states 35.9 -> 38.4, 1936 -> 256 at 4200 34.8 -> 32.5), nor with up to one and a half workgroups per compute
+// unit, or little more than two, if gemm_kernel's groups of 64 states are a multiple of eight (see below) or its workgroups, half the
+// size, need no round more (gemm_kernel / this: 3600 -> 768 at 4096 46.7 / 48.6, -> 1024 at 2500 43.5 / 44.9, -> 1536 at 1300 42.3 / 50.4,
+// 2048 50.8 / 52.5, -> 3000 at 1300 65.7 / 70.0; else 3600 -> 512 at 5000 55.5 / 49.8, -> 1024 at 3000 50.3 / 46.5, -> 1536 at 1700
+// 54.5 / 51.9, 3000 79.5 / 68.4, 1936 -> 512 at 6000 38.6 / 38.4).
 bool gemm_stream_rows_supported(const GemmParams& p) {
-    return p.B > 0 && !p.x_frag && p.k_steps >= 2 * SG_KS && p.Kp_bytes % 16 == 0 && p.n_tiles % SG_NT == 0 &&
-           stream_groups<8>(p) >= conv_num_cus();
+    if (p.B <= 0 || p.x_frag || p.k_steps < 2 * SG_KS || p.Kp_bytes % 16 != 0 || p.n_tiles % SG_NT != 0) return false;
+    const int64_t cus = conv_num_cus(), g = stream_groups<8>(p), x4 = (p.B + 63) / 64;
+    if (g <= cus) return g == cus;
+    const bool thin_round = 2 * g <= 3 * cus || (g > 2 * cus && 4 * g <= 9 * cus);
+    return !thin_round || (x4 % 8 != 0 && stream_groups<4>(p) > 2 * cus * (g / cus));
 }
 
 template <int WAVES, bool RELU, bool TAIL>
@@ -192,7 +200,14 @@ static hipError_t stream_go(const GemmParams& p, hipStream_t s) {
         set = true;
     }
     const dim3 grid((unsigned)((p.B + 16 * WAVES - 1) / (16 * WAVES)), (unsigned)(p.n_tiles / SG_NT));
-    gemm_stream_i8_kernel<WAVES, RELU, TAIL><<<grid, dim3(64 * WAVES), SG_LDS, s>>>(p);
+    // Rows: the workgroups of a group of states that do not meet on an XCD by themselves are brought together; fetched by up to eight
+    // of them, rows made this kernel slower than gemm_kernel (whole forwards, us, gemm_kernel / not / brought together: 3600 -> 512 at 6000
+    // states 53.2 / 60.0 / 50.0, 3600 -> 1024 at 4200 70.8 / 78.5 / 62.7, 3600 -> 2048 at 4200 117 / 128 / 101, 1936 -> 256 at 10000
+    // 42.3 / 44.9 / 42.0).  Groups that are a multiple of eight do meet: in the grid's order / by XCD 3600 -> 512 at
+    // 4096 36.0 / 37.5, 16384 95.8 / 92.4, 3600 -> 2048 at 4096 84.5 / 86.3.
+    GemmParams q = p;
+    q.by_xcd = (RELU || TAIL) && grid.y > 1 && (grid.x & 7) != 0;
+    gemm_stream_i8_kernel<WAVES, RELU, TAIL><<<grid, dim3(64 * WAVES), SG_LDS, s>>>(q);
     return hipGetLastError();
 }
 
