@@ -109,7 +109,7 @@ struct StShape {
     static_assert(NCOL <= NW * 16 && NT1 <= NW * (P == 2 ? 99 : 1), "one tile of columns per wavefront");
     static_assert(P == 1 || (G == 1 && KS_C == 1 && KS_B == 2 && H % 2 == 0 && HIN % 2 == 0), "8-channel layers: one image, even sizes");
     static_assert(P == 2 || (KS_B == 3 && (CI == 8 || CI == 16) && (CI == 16 || HIN % 2 == 0)), "16-channel layers");
-    static_assert(LDS <= 160 * 1024 && SEG * R - H <= 1 && WL <= 4, "LDS, rows");
+    static_assert(LDS <= 160 * 1024 && SEG * R - H <= (G > 1 ? 0 : 1) && WL <= 4, "LDS, rows");
 };
 
 // v[r] = max(v[r], v[r] of the lane to its left in the same 16-lane row); lane 0 of a row keeps its value: a DPP lane without
@@ -477,7 +477,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (BITS ? ST_MAGIC : 0);
             const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
             asm("" : "+v"(rr));                           // a vector register: a multiplication by a scalar one takes twice as long
-            char* outp = (char*)p.out + b0 * (int64_t)S::IMG + (uint32_t)(bimg * S::IMG + brel);
+            char* outp = (char*)p.out + b0 * (int64_t)S::IMG;
+            const int at = bimg * S::IMG + brel;
+            // (a short last batch: the buffer ends with its last image, and what lanes of missing ones store behind it is dropped.  A
+            // branch around the phase would leave the matrix instructions with some of a wavefront's lanes only)
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(outp, 0, gc * S::IMG, 0x00027000);
             walk(tM, w, bi, [&](int k, v4i acc) {
                 int q[4];
 #pragma unroll
@@ -488,7 +492,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                 const StBytes y = st_pack(q);
                 const bool ok = k + 1 < S::R || lastrow;
                 if constexpr (LAST) {
-                    if (ok) *(uint32_t*)(outp + k * S::WP * 16) = y.raw;
+                    if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, at + k * S::WP * 16, 0, 0);
+                    else if (ok) *(uint32_t*)(outp + at + k * S::WP * 16) = y.raw;
                 } else {
                     x[k] = y.raw;
                     if (ok) *(uint32_t*)(tX + bown + k * S::PITCH_B) = y.pos;
@@ -520,7 +525,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         // the next batch's bytes are requested here, not earlier: their registers are then free during the phases above
         // (where the kernel needs the most), and the last phase is long enough for the loads to land
         if (batch + gridDim.x < n_batch) prefetch(batch + gridDim.x);
-        if (work && (G == 1 || bimg < gc)) conv_b(wB, 4, p.r2, std::true_type{});
+        if (work && (G == 1 || __builtin_amdgcn_ballot_w64(bimg < gc))) conv_b(wB, 4, p.r2, std::true_type{});
         // no barrier here: the next commit writes the input tiles only, and the barrier behind it comes before the
         // next batch writes anything that the last phase reads
     }
