@@ -84,10 +84,10 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
     // LDS: observation tile of slot 0, of slot 1, then the output tiles [slot][buffer]
     char* tilesB = smem + 2 * FR_TILE_A;
 
-    // pair n of this workgroup: observations 2 * (blockIdx.x + n * gridDim.x) + {0, 1}
+    // tick n of this workgroup: observations per * (blockIdx.x + n * gridDim.x) + {0, .., per - 1} ("pair" below, also where it is one)
     const int64_t stride = p.per * (int64_t)gridDim.x;
     const int64_t second = p.per == 2 ? 1 : p.B;        // one observation per workgroup: the second slot's lies past the batch
-    int64_t img = p.per * (int64_t)blockIdx.x;              // first observation of the pair whose second convolution runs this tick
+    int64_t img = p.per * (int64_t)blockIdx.x;          // first observation of the pair whose second convolution runs this tick
     if (img >= p.B) return;
 
     if (wave >= 4) {
@@ -349,7 +349,8 @@ static hipError_t front_go(const FrontParams& q, hipStream_t s) {
         occ = o < 1 ? 1 : o;
     }
     // resident workgroups striding over the pairs of observations, in even rounds; single observations where the chip has a
-    // workgroup for each (160 states: 7.2 -> 6.0 us; in two rounds of single observations a pair would wait for its second)
+    // workgroup for each (160 states: 7.2 -> 6.0 us; whole forwards, pairs / single, us: 8 states 16.9 / 15.9, 64 17.5 / 16.4, 100
+    // 17.8 / 16.6, 256 18.5 / 17.7; in two rounds of single observations a pair waits for its second: 300 19.6 / 20.2, 512 20.8 / 21.3)
     const int64_t cap = (int64_t)occ * conv_num_cus();
     FrontParams p = q;
     p.per = p.B <= cap ? 1 : 2;

@@ -312,7 +312,7 @@ bool ksplit_small_i8(const GemmParams& p) {
 // states 16x16 4.0, 16x32 4.3; 160 states 16x32 4.3, 16x16 4.5; 512 states 32x32 5.7, 16x64 6.2, 16x32 6.6; 1000 states 32x64 7.2,
 // 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.  bf16 beyond one 64x64 workgroup per unit: two of them in fragment order, 128x64 for
 // row-major states (whole forwards, 64x64 / 128x64: 3136 -> 512 in fragment order at 2310 states 77.2 / 81.0, 3000 85.8 / 88.7,
-// 3600 96.9 / 100.4, 4096 103.5 / 106.2; 3872 -> 256 row-major at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
+// 3600 96.9 / 100.4, 4096 102.3 / 105.3, both with the tiles by XCD; 3872 -> 256 row-major at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
 template <int EL, int EPI>
 hipError_t pick(const GemmParams& p, hipStream_t s) {
     const int64_t most = most_groups();

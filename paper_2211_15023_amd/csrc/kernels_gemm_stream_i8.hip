@@ -143,13 +143,13 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
         stage(s, even(), false_type());
     }
 
-    // ---- epilogue: lane holds features n0 .. n0+3 of state b
+    // ---- epilogue: lane holds features n0 .. n0+3 of state b; int8 rows are whole tiles of features (Np == 16 * n_tiles; padding features
+    //      have zero weights and bias and are stored as zeros)
     const int64_t b = b0 + wave * 16 + j;
     if (b >= p.B) return;
 #pragma unroll
     for (int t = 0; t < SG_NT; ++t) {
         const int n0 = (nt0 + t) * 16 + 4 * g;
-        if (n0 >= p.Np) continue;      // stored rows reach the row pitch (zero weights and bias give zeros)
         const v4f ml = *(const v4f*)(p.mult + n0);
         uint32_t pk = 0;
 #pragma unroll
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
 }  // namespace
 
 bool gemm_stream_supported(const GemmParams& p) {
-    return p.B > 0 && !p.relu_in && p.k_steps >= 2 * SG_KS && p.Kp_bytes == 64 * p.k_steps && p.n_tiles % SG_NT == 0;
+    return p.B > 0 && p.Np == 16 * p.n_tiles && !p.relu_in && p.k_steps >= 2 * SG_KS && p.Kp_bytes == 64 * p.k_steps && p.n_tiles % SG_NT == 0;
 }
 
 template <int WAVES>
@@ -184,7 +184,7 @@ static int64_t stream_groups(const GemmParams& p) { return (p.B + 16 * WAVES - 1
 // 2048 50.8 / 52.5, -> 3000 at 1300 65.7 / 70.0; else 3600 -> 512 at 5000 55.5 / 49.8, -> 1024 at 3000 50.3 / 46.5, -> 1536 at 1700
 // 54.5 / 51.9, 3000 79.5 / 68.4, 1936 -> 512 at 6000 38.6 / 38.4).
 bool gemm_stream_rows_supported(const GemmParams& p) {
-    if (p.B <= 0 || p.x_frag || p.k_steps < 2 * SG_KS || p.Kp_bytes % 16 != 0 || p.n_tiles % SG_NT != 0) return false;
+    if (p.B <= 0 || p.Np != 16 * p.n_tiles || p.x_frag || p.k_steps < 2 * SG_KS || p.Kp_bytes % 16 != 0 || p.n_tiles % SG_NT != 0) return false;
     const int64_t cus = conv_num_cus(), g = stream_groups<8>(p), x4 = (p.B + 63) / 64;
     if (g <= cus) return g == cus;
     const bool thin_round = 2 * g <= 3 * cus || (g > 2 * cus && 4 * g <= 9 * cus);

@@ -540,7 +540,9 @@ static hipError_t launch_nh(const MlpParams& p, int ht, int blocks, hipStream_t 
     return hipGetLastError();
 }
 
-// two wavefronts of 64 states per SIMD; below, more and smaller shares finish earlier (65537 states 6.0 us, by fours 6.2)
+// two wavefronts of 64 states per SIMD; well below, more and smaller shares finish earlier (one tile / four per wavefront, whole calls,
+// us: 24 features 80000 states 5.6 / 5.9, 98304 6.1 / 6.0, 131072 7.2 / 6.3, 196608 9.2 / 7.6; 4 features 5.6 / 5.7, 6.0 / 5.8, 7.1 / 6.0,
+// 8.8 / 7.2)
 constexpr int64_t QUAD_MIN_B = 1 << 17;
 int conv_num_cus();
 

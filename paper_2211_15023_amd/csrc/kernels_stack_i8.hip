@@ -88,12 +88,12 @@ struct StShape {
     static constexpr int NT1 = SLOTS <= 16 ? 1 : 1 + (SLOTS - 16 + 14) / 15;
     // residual blocks
     static constexpr int WP = H / P;                           // columns per image row
-    static constexpr int R = (H + SEG - 1) / SEG;              // rows a lane walks
+    static constexpr int R = H / SEG;                          // rows a lane walks
     static constexpr int NCOL = G * SEG * WP;                  // lanes
     static constexpr int IMG = H * H * C;
     static constexpr int PITCH_B = st_up16((H + 3) * C);       // the pixel behind the border takes what the pooling's spare lanes write
-    // rows behind the border are read (and meet zero weights, or belong to a row that is not stored): the second of a pair
-    static constexpr int TILE_B = (H + 2 + (P == 2 || SEG * R > H ? 1 : 0)) * PITCH_B;
+    // a row behind the border is read (and meets zero weights): the second of a pair
+    static constexpr int TILE_B = (H + 2 + (P == 2 ? 1 : 0)) * PITCH_B;
     static constexpr int CPR_B = ((3 + P - 1) * C + 15) / 16;
     static constexpr int KS_B = (3 * CPR_B + 3) / 4;
     static constexpr int NWB = P == 2 ? 4 : 3;                 // fragments of a block convolution
@@ -109,7 +109,8 @@ struct StShape {
     static_assert(NCOL <= NW * 16 && NT1 <= NW * (P == 2 ? 99 : 1), "one tile of columns per wavefront");
     static_assert(P == 1 || (G == 1 && KS_C == 1 && KS_B == 2 && H % 2 == 0 && HIN % 2 == 0), "8-channel layers: one image, even sizes");
     static_assert(P == 2 || (KS_B == 3 && (CI == 8 || CI == 16) && (CI == 16 || HIN % 2 == 0)), "16-channel layers");
-    static_assert(LDS <= 160 * 1024 && SEG * R - H <= (G > 1 ? 0 : 1) && WL <= 4, "LDS, rows");
+    static_assert(LDS <= 160 * 1024 && WL <= 4 && SEG * R == H && (HIN % 2 == 0 || PSEG == 1), "LDS, rows");
+    static_assert(NCOL > NW * 16 - 16, "every wavefront owns a column");
 };
 
 // v[r] = max(v[r], v[r] of the lane to its left in the same 16-lane row); lane 0 of a row keeps its value: a DPP lane without
@@ -156,8 +157,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
 
-    // ---- weights of all five convolutions, in registers for the whole kernel
-    v4i wP[S::NWP], wR[4 - S::WL + 1][S::NWB];
+    // ---- weights: those of the stack convolution and of the block convolutions WL .. 3 stay in registers, the others go to LDS
+    v4i wP[S::NWP], wR[S::WL < 4 ? 4 - S::WL : 1][S::NWB];
     {
         // chunk (ky, cx) of the planner's fragments (cpr chunks per kernel row), zero outside the kernel
         auto chunk = [&](int cv, int cpr, int ky, int cx, int mrow) -> v4i {
@@ -291,7 +292,6 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     const int n = wave * 16 + j, nc = min(n, S::NCOL - 1);
     const int bimg = nc / (SEG * S::WP), bseg = (nc - bimg * SEG * S::WP) / S::WP, bcol = nc - (bimg * SEG + bseg) * S::WP;
     const int row0 = bseg * S::R;
-    const bool lastrow = SEG * S::R == S::H || row0 + S::R <= S::H;   // the last row a lane walks is inside the image
     const int bpos = bimg * S::TILE_B + row0 * S::PITCH_B + bcol * 16;
     // (16-channel layers have no fourth chunk: its lanes read the zeros of the left border)
     const int boff = S::P == 2 ? bpos + (g >> 1) * S::PITCH_B + (g & 1) * 16 : g < 3 ? bpos + g * 16 : bpos - bcol * 16;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     const int brel = (row0 * S::WP + bcol) * 16 + 4 * g;  // in a plain image
     // ---- this lane's column of the pooling (16-channel layers): slots are the column runs (image, segment), each behind a
     //      dummy that repeats its first pixel; a tile's first lane repeats the last slot of the tile before it
-    int ppos = 0, pout = 0, pfirst = 0, plast = 0;
+    int ppos = 0, pout = 0, pfirst = 0;
     if constexpr (S::P == 1) {
         const int s = min(15 * wave + j, S::SLOTS - 1) + 1, run = s / (S::H + 1), at = s - run * (S::H + 1);
         const int px = max(at - 1, 0), img = run / PSEG, p0 = min((run - img * PSEG) * S::RP, S::H - S::RP);
@@ -309,7 +309,6 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         ppos = img * S::TILE_IN + 2 * p0 * S::PITCH_IN + wx * CI + (CI == 8 ? (g >> 1) * S::PITCH_IN + (g & 1) * 16 : g * 16);
         pfirst = p0 > 0 ? -2 * S::PITCH_IN : 0;            // the window above, for the conv row shared with it
         pout = img * S::TILE_B + (p0 + 1) * S::PITCH_B + (st ? px + 1 : S::H + 2) * C + 4 * g;
-        if ((HIN & 1) && p0 + S::RP == S::H) plast = -S::PITCH_IN;   // no conv row below the last: the one above once more
     }
     __syncthreads();
 
@@ -417,12 +416,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                             f3 = row(2 * k + 3);
                             e1 = conv(wP, f1, f2, f3);
                             o1 = conv(wP + 3, f1, f2, f3);
-                        } else if (PSEG > 1) {
-                            const char* m = a + plast + (2 * k + 1) * S::PITCH_IN;
-                            const v4i m1 = *(const v4i*)m, m2 = *(const v4i*)(m + S::PITCH_IN), m3 = *(const v4i*)(m + 2 * S::PITCH_IN);
-                            e1 = conv(wP, m1, m2, m3);
-                            o1 = conv(wP + 3, m1, m2, m3);
-                        }
+                        }                                            // (odd sizes: no conv row below the last)
                         out(k, max3(cE, e0, e1), max3(cO, o0, o1));
                         cE = e1; cO = o1; f0 = f2; f1 = f3;
                     }
@@ -467,7 +461,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             const v4f cc = ml * -8388608.0f;
             walk(tX, w, bi, [&](int k, v4i acc) {
                 const uint32_t y = requant_relu4_p23<BITS>(acc, ml, cc);
-                if (k + 1 < S::R || lastrow) *(uint32_t*)(tM + bown + k * S::PITCH_B) = y;
+                *(uint32_t*)(tM + bown + k * S::PITCH_B) = y;
             });
         };
         uint32_t x[S::R];                                 // the stream under this lane, four channels per row
@@ -490,42 +484,34 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                     q[r] = rne_clamp127(fmaf(st_float<BITS>(acc[r]), ml[r], tr));
                 }
                 const StBytes y = st_pack(q);
-                const bool ok = k + 1 < S::R || lastrow;
                 if constexpr (LAST) {
                     if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, at + k * S::WP * 16, 0, 0);
-                    else if (ok) *(uint32_t*)(outp + at + k * S::WP * 16) = y.raw;
+                    else *(uint32_t*)(outp + at + k * S::WP * 16) = y.raw;
                 } else {
                     x[k] = y.raw;
-                    if (ok) *(uint32_t*)(tX + bown + k * S::PITCH_B) = y.pos;
+                    *(uint32_t*)(tX + bown + k * S::PITCH_B) = y.pos;
                 }
             });
         };
         // The pooled stream waits where the inner tensor will be: its pixels' owners take it into registers before they
         // write there, and it stays in registers from then on.
-        const bool work = S::NCOL > NW * 16 - 16 || wave * 16 < S::NCOL;            // (a wavefront that owns no column must not touch another's)
         v4i wA[S::NWB], wB[S::NWB];
-        if (work) {
 #pragma unroll
-            for (int k = 0; k < S::R; ++k) x[k] = *(const uint32_t*)(tM + bown + k * S::PITCH_B);
-            weights(std::integral_constant<int, 0>{}, wA);
-            conv_a(wA, 1);
-            weights(std::integral_constant<int, 1>{}, wB);
-        }
+        for (int k = 0; k < S::R; ++k) x[k] = *(const uint32_t*)(tM + bown + k * S::PITCH_B);
+        weights(std::integral_constant<int, 0>{}, wA);
+        conv_a(wA, 1);
+        weights(std::integral_constant<int, 1>{}, wB);
         __syncthreads();
-        if (work) {
-            conv_b(wB, 2, p.r1, std::false_type{});
-            weights(std::integral_constant<int, 2>{}, wA);
-        }
+        conv_b(wB, 2, p.r1, std::false_type{});
+        weights(std::integral_constant<int, 2>{}, wA);
         __syncthreads();
-        if (work) {
-            conv_a(wA, 3);
-            weights(std::integral_constant<int, 3>{}, wB);
-        }
+        conv_a(wA, 3);
+        weights(std::integral_constant<int, 3>{}, wB);
         __syncthreads();
         // the next batch's bytes are requested here, not earlier: their registers are then free during the phases above
         // (where the kernel needs the most), and the last phase is long enough for the loads to land
         if (batch + gridDim.x < n_batch) prefetch(batch + gridDim.x);
-        if (work && (G == 1 || __builtin_amdgcn_ballot_w64(bimg < gc))) conv_b(wB, 4, p.r2, std::true_type{});
+        if (G == 1 || __builtin_amdgcn_ballot_w64(bimg < gc)) conv_b(wB, 4, p.r2, std::true_type{});
         // no barrier here: the next commit writes the input tiles only, and the barrier behind it comes before the
         // next batch writes anything that the last phase reads
     }
