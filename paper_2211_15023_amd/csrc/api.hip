@@ -1514,8 +1514,8 @@ int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t w
                      (int)(!s.fused_prev && (s.el == EL_I8 ? conv_tail_supported(c, s.NT) : conv_tail_bf16_supported(c, s.NT))), c.out_frag, (int)s.resblock, c.pos23,
                      s.el != EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0, s.el == EL_I8 ? 0 : s.stack_head ? 1 : s.stack_member ? 2 : 0);
         } else if (s.kind == ST_GEMM) {
-            snprintf(line, sizeof line, "step %zu gemm layer=%d el=%d epi=%d N=%d Np=%d Kp_bytes=%d k_steps=%d n_tiles=%d relu_in=%d relu=%d x_frag=%d\n",
-                     i, s.layer, (int)s.el, (int)s.epi, s.gp.N, s.gp.Np, s.gp.Kp_bytes, s.gp.k_steps, s.gp.n_tiles, s.gp.relu_in, s.gp.relu, s.gp.x_frag);
+            snprintf(line, sizeof line, "step %zu gemm layer=%d el=%d epi=%d N=%d Np=%d Kp_bytes=%d k_steps=%d n_tiles=%d relu_in=%d relu=%d x_frag=%d packs_next=%d\n",
+                     i, s.layer, (int)s.el, (int)s.epi, s.gp.N, s.gp.Np, s.gp.Kp_bytes, s.gp.k_steps, s.gp.n_tiles, s.gp.relu_in, s.gp.relu, s.gp.x_frag, (int)s.packs_next);
         } else {
             snprintf(line, sizeof line, "step %zu %s layer=%d%s\n", i, kinds[s.kind], s.layer, s.mlp_head ? " whole_network=1" : "");
         }

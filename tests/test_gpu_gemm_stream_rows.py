@@ -20,7 +20,7 @@ def _behind_conv(cout, act, width, side):
 
 NETS = {
     "relu, 30.25 steps": (_behind_conv(16, True, 256, 11), [8065, 8192, 8321]),
-    "56.25 steps, Np < 16 n_tiles": (_behind_conv(16, False, 500, 15), [4001, 4100]),
+    "56.25 steps, 500 of 512 features": (_behind_conv(16, False, 500, 15), [4001, 4100]),
     "relu, 8 whole steps": (Net("rows", "u8", (4, 8, 8), 5, [conv(4, 16, 2, 1, 0, False), flatten(), dense(784, 512, False), relu(), dense(512, 512, True)]), [4001, 4100]),
     "12.25 steps": (_behind_conv(16, False, 512, 7), [4001]),
 }

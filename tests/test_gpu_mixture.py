@@ -122,7 +122,8 @@ def _wide_head_net(cout):
 @pytest.mark.parametrize("pair", ["nature", "impala", "net1", "net2", "wide heads", "odd size", "two convolutions"])
 def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes):
     """Every kernel that can be the first of an image policy reads through the row list, and both forms of the heads kernel
-    write through it: bit for bit what the policies compute on those rows alone, also when a policy runs in several passes."""
+    write through it: bit for bit what the policies compute on those rows alone, also when a policy runs in several passes.  (Calls
+    of one round: the next test has several.)"""
     if passes:
         monkeypatch.setenv("ACCERL_CHUNK", "64")                  # read when the policy is created
     rng = np.random.default_rng(5)
@@ -141,7 +142,7 @@ def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes
     elif pair == "wide heads":
         net = _wide_head_net(8)
         small, orig = int8_policy(net), float_policy(_wide_head_net(20))
-    elif pair == "odd size":                                      # several images per batch in the generic first kernel
+    elif pair == "odd size":                                      # the generic first kernel, one image at a time in calls of this size
         net = SimpleNamespace(name="odd", obs_dtype="u8", obs_shape=(3, 12, 16), n_actions=3,
                               layers=[dict(kind="conv", cin=3, cout=12, k=3, stride=1, pad=1, relu=True),
                                       dict(kind="flatten"), dict(kind="dense", cin=12 * 192, cout=24, relu=True)])
@@ -164,6 +165,28 @@ def test_mixture_rows_are_read_and_written_in_place(A, monkeypatch, pair, passes
     A.accerl_actor_forward_mixture(small.handle, orig.handle, dx, du, use, *out)
     m = _dev(use).bool()
     for got, a, b in zip(out, small.forward(dx, du), orig.forward(dx, du)):
+        assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
+
+
+@pytest.mark.parametrize("pair", ["nature", "impala"])
+def test_mixture_rows_beyond_one_round(A, pair):
+    """An odd number of rows for each policy, more than its first kernel takes in a round: the second observation of a workgroup, the
+    one requested ahead and the last, single one are looked up in the list too."""
+    ci = 2 if pair == "nature" else 3
+    nt, pt, ns, ps, qp = policies(ci)
+    small, orig = A.Policy(ns, "int8", student_tensors(qp), qp.act_scales), A.Policy(nt, "bf16", teacher_tensors(pt))
+    n = 4 * torch.cuda.get_device_properties(0).multi_processor_count + 3
+    B = 2 * n
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randint(0, 256, (B, 4, 84, 84), dtype=torch.uint8, device="cuda", generator=gen)
+    u = torch.rand(B, device="cuda", generator=gen)
+    use = np.zeros(B, np.uint8)
+    use[np.random.default_rng(7).permutation(B)[:n]] = 1
+    out = small.alloc_outputs(B)
+    print(f"mixture beyond one round: {pair}, {n} rows each", flush=True)
+    A.accerl_actor_forward_mixture(small.handle, orig.handle, x, u, use, *out)
+    m = _dev(use).bool()
+    for got, a, b in zip(out, small.forward(x, u), orig.forward(x, u)):
         assert torch.equal(got, torch.where(m.view(-1, *[1] * (got.dim() - 1)), a, b))
 
 
