@@ -474,7 +474,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             char* outp = (char*)p.out + b0 * (int64_t)S::IMG;
             const int at = bimg * S::IMG + brel;
             // (a short last batch: the buffer ends with its last image, and what lanes of missing ones store behind it is dropped.  A
-            // branch around the phase would leave the matrix instructions with some of a wavefront's lanes only)
+            // branch around the phase would leave the matrix instructions with some of a wavefront's lanes only.  Rows by the scalar
+            // offset: added to the lanes' they took a register and an instruction each)
             const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(outp, 0, gc * S::IMG, 0x00027000);
             walk(tM, w, bi, [&](int k, v4i acc) {
                 int q[4];
@@ -485,7 +486,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                 }
                 const StBytes y = st_pack(q);
                 if constexpr (LAST) {
-                    if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, at + k * S::WP * 16, 0, 0);
+                    if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, at, k * S::WP * 16, 0);
                     else *(uint32_t*)(outp + at + k * S::WP * 16) = y.raw;
                 } else {
                     x[k] = y.raw;
