@@ -471,12 +471,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (BITS ? ST_MAGIC : 0);
             const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
             asm("" : "+v"(rr));                           // a vector register: a multiplication by a scalar one takes twice as long
-            char* outp = (char*)p.out + b0 * (int64_t)S::IMG;
-            const int at = bimg * S::IMG + brel;
+            char* outp = (char*)p.out + b0 * (int64_t)S::IMG + (uint32_t)(bimg * S::IMG + brel);
             // (a short last batch: the buffer ends with its last image, and what lanes of missing ones store behind it is dropped.  A
             // branch around the phase would leave the matrix instructions with some of a wavefront's lanes only.  Rows by the scalar
             // offset: added to the lanes' they took a register and an instruction each)
-            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(outp, 0, gc * S::IMG, 0x00027000);
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((char*)p.out + b0 * (int64_t)S::IMG, 0, gc * S::IMG, 0x00027000);
             walk(tM, w, bi, [&](int k, v4i acc) {
                 int q[4];
 #pragma unroll
@@ -486,8 +485,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                 }
                 const StBytes y = st_pack(q);
                 if constexpr (LAST) {
-                    if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, at, k * S::WP * 16, 0);
-                    else *(uint32_t*)(outp + at + k * S::WP * 16) = y.raw;
+                    if constexpr (G > 1) __builtin_amdgcn_raw_buffer_store_b32(y.raw, rsrc, bimg * S::IMG + brel, k * S::WP * 16, 0);
+                    else *(uint32_t*)(outp + k * S::WP * 16) = y.raw;
                 } else {
                     x[k] = y.raw;
                     *(uint32_t*)(tX + bown + k * S::PITCH_B) = y.pos;
