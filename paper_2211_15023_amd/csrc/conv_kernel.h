@@ -155,8 +155,9 @@ constexpr int conv_min_blocks(int NT, int KS, int PF, int PT, int NW, int MODE, 
 
 // EX: residual join and fused max-pooling compiled in (kernels for layers that need neither do without their registers).
 // ROWS: observations through the row list, 1 = a batch is one image, 2 = any number, every unit looks its image up.  As a test in the
-// kernel the list cost the others up to 0.8 us (20x20x4, 4096 states, 12.3 -> 13.1 us); the two in one instance take registers that
-// leave two workgroups per compute unit for three (mixture with a two-convolution 84x84 student, 4096 rows, 101 -> 112 us).
+// kernel the list cost those with their weights in registers up to 0.8 us (20x20x4, 4096 states, 12.3 -> 13.1 us); in the others
+// (KS = 0) it costs nothing and is one (net2's first layer at 160 states 12.3 us without, 11.8 with it).  Both forms of the list in one
+// instance take registers that leave two workgroups per compute unit for three (mixture with net2, 4096 rows, 101 -> 112 us).
 template <int EL, int NT, int KS, int RD, int MODE, int PF, int PT, int NW, bool WP, bool EX, int ROWS>
 __global__ __launch_bounds__(NW * 64, conv_min_blocks(NT, KS, PF, PT, NW, MODE, ROWS)) void conv_kernel(const ConvParams p) {
     constexpr int CONV_THREADS = NW * 64;
@@ -328,25 +329,30 @@ __global__ __launch_bounds__(NW * 64, conv_min_blocks(NT, KS, PF, PT, NW, MODE, 
             }
         } else {   // CM_U8T: one dword (4 pixels) from each channel plane
             const int plane = p.H * p.W;
-            const int64_t img_bytes = (int64_t)p.Cin_real * plane;
-            auto load = [&](int i, const uint8_t* src, uint32_t so) {
-                v4i v;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(min(c, p.Cin_real - 1) * plane) + so);
-                pre[i] = v;
-            };
             if constexpr (ROWS == 2) {
                 // the batch's images are no neighbours in memory, and soff counts from the first one
+                const int64_t img_bytes = (int64_t)p.Cin_real * plane;
 #pragma unroll
                 for (int i = 0; i < PF; ++i) {
                     const bool there = stid + i * SN <= last;
                     const int img = there ? (int)fdiv((uint32_t)(stid + i * SN), p.magic_units) : 0;
-                    load(i, (const uint8_t*)p.in + ((int64_t)p.rows[b0 + img] - img) * img_bytes, there ? soff[i] : 0u);
+                    const uint8_t* src = (const uint8_t*)p.in + ((int64_t)p.rows[b0 + img] - img) * img_bytes;
+                    const uint32_t so = there ? soff[i] : 0u;
+                    v4i v;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(min(c, p.Cin_real - 1) * plane) + so);
+                    pre[i] = v;
                 }
             } else {
-                const uint8_t* src = (const uint8_t*)p.in + (ROWS ? (int64_t)p.rows[b0] : b0) * img_bytes;
+                const uint8_t* src = (const uint8_t*)p.in + ((KS > 0 ? ROWS == 1 : p.rows != nullptr) ? (int64_t)p.rows[b0] : b0) * (int64_t)p.Cin_real * p.H * p.W;
 #pragma unroll
-                for (int i = 0; i < PF; ++i) load(i, src, (stid + i * SN <= last) ? soff[i] : 0u);
+                for (int i = 0; i < PF; ++i) {
+                    const uint32_t so = (stid + i * SN <= last) ? soff[i] : 0u;
+                    v4i v;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(min(c, p.Cin_real - 1) * plane) + so);
+                    pre[i] = v;
+                }
             }
         }
     };
@@ -721,9 +727,10 @@ hipError_t conv_go(const ConvParams& p, dim3 grid, size_t lds, hipStream_t s) {
     // Through a row list too a batch has the planned number of images: mixtures of 12x16x3 images, gathered rows / one image per batch /
     // this, us: 4096 rows 50.6 / 48.8 / 45.4, 16384 92.2 / 105.0 / 85.9; 20x20x4 48.8 / 45.8 / 43.4, 89.8 / 102.2 / 83.2; 40x40x4
     // 81.7 / 76.5 / 76.4, 160.8 / 148.1 / 140.9
+    constexpr int ONE = KS > 0 ? 1 : 0;                              // the instance for batches of one image
     if constexpr (MODE == CM_U8T && ROWS == 0) {
-        if (p.rows) return p.G > 1 ? conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, 2>(p, grid, lds, s)
-                                   : conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, 1>(p, grid, lds, s);
+        if (p.rows && p.G > 1) return conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, 2>(p, grid, lds, s);
+        if constexpr (ONE != 0) { if (p.rows) return conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, ONE>(p, grid, lds, s); }
     }
     auto kfn = conv_kernel<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, ROWS>;
     static size_t set_lds = 0;   // per instantiation: raise the dynamic LDS limit when needed
@@ -756,7 +763,7 @@ hipError_t conv_go(const ConvParams& p, dim3 grid, size_t lds, hipStream_t s) {
     if ((q.B + q.G - 1) / q.G < slots) {
         const int64_t g = (q.B + slots - 1) / slots;
         q.G = (int)(g < 1 ? 1 : g < q.G ? g : q.G);
-        if constexpr (ROWS == 2) { if (q.G == 1) return conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, 1>(q, grid, lds, s); }
+        if constexpr (ROWS == 2) { if (q.G == 1) return conv_go<EL, NT, KS, RD, MODE, PF, PT, NW, WP, EX, ONE>(q, grid, lds, s); }
     }
     const int64_t n_batch = (q.B + q.G - 1) / q.G;
     const int64_t items = WP ? (n_batch + NW - 1) / NW : n_batch;     // batches a workgroup takes per round
