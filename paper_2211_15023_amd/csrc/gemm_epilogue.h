@@ -29,12 +29,15 @@ __device__ __forceinline__ float g_sigmoid(float x) { return 1.0f / (1.0f + expf
 // tiles, all features of one group of states before the next group, so that a group's states come into one second-level cache
 // (the kernels' launch functions say when).
 struct GemmTile { unsigned x, y; };
+// BRANCH: a branch around the division (kernels that divide by the grid's height anyway share its reciprocal instead: with the branch they
+// waited for two scalar loads and two reciprocals in a row, 0.25 us).
+template <bool BRANCH>
 __device__ __forceinline__ GemmTile gemm_tile(int by_xcd) {
-    if (!by_xcd) return {blockIdx.x, blockIdx.y};
+    if (BRANCH && !by_xcd) return {blockIdx.x, blockIdx.y};
     const unsigned n = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x, xcd = id & 7;
     const unsigned t = xcd * (n >> 3) + min(xcd, n & 7) + (id >> 3);     // the first n mod 8 XCDs have one tile more
-    const unsigned x = t / gridDim.y;
-    return {x, t - x * gridDim.y};
+    const unsigned x = t / gridDim.y, y = t - x * gridDim.y;
+    return {by_xcd ? x : blockIdx.x, by_xcd ? y : blockIdx.y};
 }
 
 // 16-byte piece of inputs k .. k + 7 (k a multiple of 8) of state b in the LSTM operand's fragment order

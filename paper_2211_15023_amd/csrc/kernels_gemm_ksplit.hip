@@ -79,7 +79,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const GemmTile tile = gemm_tile(p.by_xcd);
+    const GemmTile tile = gemm_tile<!XH>(p.by_xcd);
     const int64_t b0 = (int64_t)tile.x * (16 * RT);
     const int nt0 = tile.y * NT;
     const int ks = p.k_steps;
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * KM_W) void gemm_ksplit_small_i8_kernel(const G
     __shared__ __attribute__((aligned(16))) v4i s_part[KM_W * KM_NT * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const GemmTile tile = gemm_tile(p.by_xcd);
+    const GemmTile tile = gemm_tile<!XH>(p.by_xcd);
     const int64_t b = (int64_t)tile.x * 16 + j;
     const int nt0 = tile.y * KM_NT, nts = min(p.n_tiles - nt0, KM_NT);
     const char* row = (const char*)p.x + min(b, p.B - 1) * p.Kp_bytes;      // states past the batch re-read the last one

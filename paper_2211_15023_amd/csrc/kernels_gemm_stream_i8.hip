@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void gemm_stream_i8_kernel(const Gem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
-    const GemmTile tile = gemm_tile((RELU || TAIL) && p.by_xcd);
+    const GemmTile tile = gemm_tile<true>((RELU || TAIL) && p.by_xcd);
     const int64_t b0 = (int64_t)tile.x * SG_ROWS;
     const int nt0 = tile.y * SG_NT;
     const int ks = p.k_steps;
