@@ -3,12 +3,12 @@
 // meet in LDS, where every wavefront finishes its share of the tiles.  The split of K and the order of the partial sums do
 // not depend on the tile, so a state's result does not depend on the batch it is in.
 //
-// What bounds it: bytes in flight.  A compute unit pulls about 25 bytes per clock out of the second-level cache and the
-// memory behind it however many loads its wavefronts keep open, so the tile is the smallest that still gives every unit one
-// workgroup: more units pull, and none of them twice.  The kernel this replaces walked K alone in each 64 x 64 workgroup
+// What bounds it: the fetches.  A compute unit pulls 25 to 45 bytes per clock out of the second-level cache and the memory behind it
+// however many loads its wavefronts keep open, so the tile is the smallest that still gives every unit one workgroup: more units
+// pull, and none of them twice; beyond that the largest, whose operands are fetched least often.  The kernel this replaces walked K alone in each 64 x 64 workgroup
 // (64 workgroups on 256 units for 1024 states of a 3872 -> 256 layer): 41 -> 10.2 us there; 3136 -> 512 at 500 states
-// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us, then 25 with two 64 x 64 tiles per
-// unit (medians of kernel traces).
+// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us, 25 with two 64 x 64 tiles per
+// unit, 20 with one of 128 x 64 (13 of it the fetches, 3 the partial sums in LDS).
 #include <type_traits>
 
 #include "gemm_epilogue.h"
@@ -161,7 +161,40 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
                 else acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[t]), __builtin_bit_cast(v8bf, x[u]), acc[u][t], 0, 0, 0);
             }
     };
-    {
+    if constexpr (RT == 8 && FRAG) {
+        // One step in flight: a state fragment is requested again as soon as its products are issued, the weights a step ahead.  Two whole
+        // steps a wavefront (192 KB a unit) fetch 31 bytes a clock and unit where one fetches 43 (the loads alone, 3136 -> 512 at 4096 states).
+        v4i a[2][NT], x[RT];
+        auto load_a = [&](int step, v4i (&v)[NT]) {
+            const uint32_t st = (uint32_t)min(step, ks - 1) << 10;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v[t] = *(const v4i*)(wb + (wo[t] + st));
+        };
+        auto load_x = [&](int step, int u) { x[u] = *(const v4i*)(xb + (xo[u] + ((uint32_t)min(step, ks - 1) << 10))); };
+        load_a(s0, a[0]);
+#pragma unroll
+        for (int u = 0; u < RT; ++u) load_x(s0, u);
+        for (int st = s0; st < s1; st += 2) {
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                load_a(st + d + 1, a[d ^ 1]);
+                if (d && st + d >= s1) break;
+#pragma unroll
+                for (int u = 0; u < RT; ++u) {
+                    if (RELU) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[u][e] = (int)g_relu_bf16x2((uint32_t)x[u][e]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[d][t]), __builtin_bit_cast(v8bf, x[u]), acc[u][t], 0, 0, 0);
+                    load_x(st + d + 1, u);
+                    __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
+            }
+        }
+    } else {
         v4i a[D][NT], x[D][RT];
 #pragma unroll
         for (int d = 0; d < D; ++d) load(s0 + d, a[d], x[d]);
@@ -220,10 +253,7 @@ hipError_t go(const GemmParams& q, hipStream_t s) {
     p.by_xcd = by_xcd(q, grid);
 #define GO(RELU, FRAG, XH) gemm_ksplit_kernel<EL, EPI, RT, NT, RELU, FRAG, XH><<<grid, dim3(64 * KS_W), 0, s>>>(p)
 #define GO2(RELU, FRAG) do { if (p.xh) GO(RELU, FRAG, true); else GO(RELU, FRAG, false); } while (0)
-    if (RT == 8 && p.x_frag) return hipErrorInvalidValue;     // (128 x 64 tiles are for row-major states, see pick)
-    if constexpr (RT < 8) {
-        if (p.x_frag) { if (p.relu_in) GO2(true, true); else GO2(false, true); return hipGetLastError(); }
-    }
+    if (p.x_frag) { if (p.relu_in) GO2(true, true); else GO2(false, true); return hipGetLastError(); }
     if (p.relu_in) GO2(true, false);
     else GO2(false, false);
 #undef GO2
@@ -310,9 +340,9 @@ bool ksplit_small_i8(const GemmParams& p) {
 // of states x features): bf16, 160 states 16x32 6.5, 16x16 7.2, 32x32 7.3; 500 states 32x32 7.8, 16x64 8.4, 32x64 9.8; 1000
 // states 32x64 9.8, 32x32 11.4, 64x64 12.4; 2048 states 64x64 12.9, 32x64 16.1.  int8, 64
 // states 16x16 4.0, 16x32 4.3; 160 states 16x32 4.3, 16x16 4.5; 512 states 32x32 5.7, 16x64 6.2, 16x32 6.6; 1000 states 32x64 7.2,
-// 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.  bf16 beyond one 64x64 workgroup per unit: two of them in fragment order, 128x64 for
-// row-major states (whole forwards, 64x64 / 128x64: 3136 -> 512 in fragment order at 2310 states 77.2 / 81.0, 3000 85.8 / 88.7,
-// 3600 96.9 / 100.4, 4096 102.3 / 105.3, both with the tiles by XCD; 3872 -> 256 row-major at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
+// 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.  bf16 beyond one 64x64 workgroup per unit: 128x64, half the fetches of the weights (3136 -> 512
+// in fragment order, this kernel alone, 64x64 / 128x64: 2100 states 23.0 / 18.7, 3000 23.6 / 18.1, 4096 23.7 / 18.7, 8192 45.6 / 35.2;
+// whole forwards with row-major states, 3872 -> 256 at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
 template <int EL, int EPI>
 hipError_t pick(const GemmParams& p, hipStream_t s) {
     const int64_t most = most_groups();
@@ -330,7 +360,7 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
     }
     if (groups(p, 2, 2) <= most) return go<EL, EPI, 2, 2>(p, s);
     if (groups(p, 2, 4) <= most) return go<EL, EPI, 2, 4>(p, s);
-    if constexpr (EL == EL_BF16) { if (groups(p, 4, 4) > most && !p.x_frag) return go<EL, EPI, 8, 4>(p, s); }
+    if constexpr (EL == EL_BF16) { if (groups(p, 4, 4) > most) return go<EL, EPI, 8, 4>(p, s); }
     return go<EL, EPI, 4, 4>(p, s);
 }
 
@@ -341,12 +371,13 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 // workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192 states 9.1 / 9.5).  Where the weights exceed the
 // 4 MB of an XCD's second-level cache, the streaming kernel is already the faster one when 32 x 64 tiles no longer fit (3136 ->
 // 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
-// bf16 layers beyond one 64 x 64 workgroup per compute unit stay here while 128 x 64 tiles (or twice as many of 64 x 64) fill at most one round and the
-// eighth of K that a wavefront walks is at least eight steps (us, this / gemm_kernel: 3136 -> 512 at 3000 states 27 / 34, 4096
-// 28 / 34; 3872 -> 256 at 5000 31 / 49, 8192 40 / 51; but 1296 -> 128 at 10000 20.5 / 16.5), with a second to fourth round only for
-// row-major states, which gemm_kernel fetches badly, and only if the last round is full (3872 -> 2048: 2000 states, two rounds,
-// 62 / 82, 4096, four, 121 / 151; 6000, six, 313 / 243; 3872 -> 256 at 9300 85 / 60; 3136 -> 512 at 4700 65 / 43, 6000 67 / 45,
-// 12000 110 / 89; 3136 -> 2048 at 2000 53 / 48, 6000 215 / 178).
+// bf16 layers beyond one 64 x 64 workgroup per compute unit (128 x 64 tiles) stay here while the eighth of K that a wavefront walks is at
+// least eight steps (1296 -> 128 at 10000 20.5 / 16.5) and the rounds of workgroups are full enough.  States in fragment order: one round, or
+// weights of at most 8 MB (us, this / gemm_kernel: 3136 -> 512 at 3000 states 18.1 / 28.3, 4096 18.7 / 27.1, 4500, two rounds, 33.9 / 42.5, 6000
+// 35.2 / 38.9, 12000 52.6 / 77.0; 2304 -> 512 at 4500 27.8 / 31.7, 6000 28.9 / 28.3; 3136 -> 1024 at 2100 34.5 / 34.6, 4096 36.0 / 42.7), or 85 %
+// of the rounds (3136 -> 2048 at 1050, 56 %, 37.9 / 35.3, 3300, 81 %, 79.1 / 71.5, 2600 60.7 / 82.0, 4096 69.2 / 80.1).  Row-major states:
+// up to four rounds, the last one full (3872 -> 256 at 5000 31 / 49, 8192 40 / 51, 9300 85 / 60; 3872 -> 2048 at 2000, two rounds, 62 / 82,
+// 4096, four, 121 / 151; 6000, six, 313 / 243).
 bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
     if (p.B <= 0 || p.k_steps < KSPLIT_PARTS) return false;
     const int64_t cus = conv_num_cus();
@@ -354,7 +385,10 @@ bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
         if (epi != EPI_BF16) return false;
         if (groups(p, 4, 4) <= most_groups()) return true;
         const int64_t g = groups(p, 8, 4), rounds = (g + cus - 1) / cus;
-        return p.k_steps >= 8 * KSPLIT_PARTS && (rounds == 1 || (!p.x_frag && rounds <= 4 && 10 * g >= 9 * rounds * cus));
+        if (p.k_steps < 8 * KSPLIT_PARTS) return false;
+        if (rounds == 1) return true;
+        if (!p.x_frag) return rounds <= 4 && 10 * g >= 9 * rounds * cus;
+        return (int64_t)p.n_tiles * p.k_steps * 1024 <= 8 << 20 || 20 * g >= 17 * rounds * cus;
     }
     if (epi != EPI_REQUANT || groups(p, 4, 4) > cus) return false;
     return (int64_t)p.n_tiles * p.k_steps * 1024 <= 4 << 20 || groups(p, 2, 4) <= most_groups() || !gemm_stream_supported(p);
