@@ -1,4 +1,4 @@
-"""ctypes binding of include/accerl.h: same names, argument marshalling only."""
+"""Binding of include/accerl.h (ctypes; the calls made every step through the compiled accerl_args): same names, argument marshalling only."""
 import ctypes as C
 import os
 
@@ -8,6 +8,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "libaccerl.so")
 _lib = None
 torch = None            # set by load_library
+_args = None            # accerl_args, set by load_library
 
 INT8, FP32, BF16 = 0, 1, 2
 OBS_U8, OBS_F32 = 0, 1
@@ -34,7 +35,7 @@ class _Arch(C.Structure):
 
 def load_library():
     """Load libaccerl.so (after torch, so that both share one HIP runtime).  No fallback exists."""
-    global _lib, torch
+    global _lib, torch, _args
     if _lib is not None:
         return _lib
     import torch as _torch  # brings in the HIP runtime the library links against
@@ -80,8 +81,16 @@ def load_library():
               "accerl_actor_forward_recurrent", "accerl_actor_forward_debug", "accerl_profile_begin",
               "accerl_profile_end"):
         getattr(lib, f).restype = C.c_int
+    from . import accerl_args                # links against torch and the library loaded above
+    accerl_args.init(C.c_void_p)
+    _args = accerl_args
     _lib = lib
     return lib
+
+
+def _loaded():
+    load_library()
+    return _args
 
 
 def accerl_last_error():
@@ -180,9 +189,9 @@ def accerl_policy_destroy(handle):
     load_library().accerl_policy_destroy(handle)
 
 
-# Marshalling is most of what a small call costs the host (32 states of the 64-unit MLP: 8.8 us between calls with an import
-# statement, a c_void_p and a Stream object per argument, 5.7 without; the kernel takes 2.6): arguments go through as plain
-# integers, which the argtypes convert.
+# Marshalling is most of what a small call costs the host (32 states of the 64-unit MLP, time between calls: 5.8 us through ctypes from
+# the code below, 3.6 through accerl_args; the kernel takes 2.5).  The calls made every step go through accerl_args and come here
+# where it returns None, because an argument is not a plain tensor: an error to raise, a subclass of torch.Tensor, a stream object.
 def _ptr(t, dtype=None):
     if t is None:
         return None
@@ -200,6 +209,11 @@ def _stream(stream):
 
 
 def accerl_actor_forward(handle, states, uniforms, out_logits, out_value, out_action, stream=None):
+    rc = (_args or _loaded()).forward(handle, states, uniforms, out_logits, out_value, out_action, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     B = states.shape[0]
     _check(load_library().accerl_actor_forward(handle, _ptr(states), B, _ptr(uniforms, torch.float32),
                                                _ptr(out_logits, torch.float32), _ptr(out_value, torch.float32),
@@ -207,6 +221,11 @@ def accerl_actor_forward(handle, states, uniforms, out_logits, out_value, out_ac
 
 
 def accerl_actor_forward_teacher(handle, states, uniforms, out_logits, out_value, out_action, stream=None):
+    rc = (_args or _loaded()).forward_teacher(handle, states, uniforms, out_logits, out_value, out_action, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     B = states.shape[0]
     _check(load_library().accerl_actor_forward_teacher(handle, _ptr(states), B, _ptr(uniforms, torch.float32),
                                                        _ptr(out_logits, torch.float32), _ptr(out_value, torch.float32),
@@ -214,6 +233,11 @@ def accerl_actor_forward_teacher(handle, states, uniforms, out_logits, out_value
 
 
 def accerl_actor_forward_recurrent(handle, states, uniforms, done, h, c, out_logits, out_value, out_action, stream=None):
+    rc = (_args or _loaded()).forward_recurrent(handle, states, uniforms, done, h, c, out_logits, out_value, out_action, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     B = states.shape[0]
     _check(load_library().accerl_actor_forward_recurrent(
         handle, _ptr(states), B, _ptr(uniforms, torch.float32), _ptr(done, torch.uint8), _ptr(h, torch.float32),
@@ -260,6 +284,11 @@ def accerl_probe_empty(stream=None):
 
 def accerl_monitor_kl(logits_original, logits_smaller, out_kl, out_entropy, out_stats, stream=None):
     """out_stats: float64 device tensor [4] = KL mean, KL max, KL variance, entropy mean."""
+    rc = (_args or _loaded()).monitor_kl(logits_original, logits_smaller, out_kl, out_entropy, out_stats, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     import torch
     B, A = logits_original.shape
     if tuple(logits_smaller.shape) != (B, A):
@@ -271,6 +300,11 @@ def accerl_monitor_kl(logits_original, logits_smaller, out_kl, out_entropy, out_
 
 def accerl_monitor_kl_noalloc(logits_original, logits_smaller, out_kl, out_entropy, out_stats, stream=None):
     """accerl_monitor_kl on the library's fixed partial-sum array: no device allocation, at most 2^24 rows."""
+    rc = (_args or _loaded()).monitor_kl_noalloc(logits_original, logits_smaller, out_kl, out_entropy, out_stats, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     import torch
     B, A = logits_original.shape
     if tuple(logits_smaller.shape) != (B, A):
@@ -293,6 +327,11 @@ def accerl_distill_loss(logits_original, logits_smaller, value_original, value_s
 
 def accerl_vtrace(logits_original, logits_smaller, actions, rewards, discounts, values, bootstrap,
                   rho_bar, c_bar, out_vs, out_pg_adv, out_rho, stream=None):
+    rc = (_args or _loaded()).vtrace(logits_original, logits_smaller, actions, rewards, discounts, values, bootstrap, rho_bar, c_bar, out_vs, out_pg_adv, out_rho, stream)
+    if rc is not None:
+        if rc:
+            _check(rc)
+        return
     import torch
     T, B, A = logits_original.shape
     if tuple(logits_smaller.shape) != (T, B, A):

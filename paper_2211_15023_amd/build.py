@@ -1,13 +1,16 @@
-"""Compile the HIP library in-tree: csrc/*.hip -> libaccerl.so (gfx950 only)."""
+"""Compile in-tree: csrc/*.hip -> libaccerl.so (gfx950 only), csrc/arguments.cpp -> accerl_args.so (the binding's marshalling)."""
 import glob
+import importlib.util
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 SO = os.path.join(HERE, "libaccerl.so")
+ARGS_SO = os.path.join(HERE, "accerl_args.so")
 OBJ = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -39,7 +42,23 @@ def build(verbose=False):
                        capture_output=True, text=True)
     if r.returncode:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _build_args(verbose)
     return SO
+
+
+def _build_args(verbose):
+    """The CPython module that takes torch tensors to pointers: host code, against torch's headers and libaccerl.so beside it."""
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
+    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE,
+                        *(a for d in (f"{torch}/include", f"{torch}/include/torch/csrc/api/include", f"{rocm}/include",
+                                      sysconfig.get_path("include")) for a in ("-isystem", d)),
+                        os.path.join(CSRC, "arguments.cpp"), "-o", ARGS_SO, "-L", HERE, "-l:libaccerl.so", "-L", f"{torch}/lib",
+                        "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
+    if r.returncode:
+        raise RuntimeError("arguments.cpp failed:\n" + r.stderr)
+    if verbose and r.stderr.strip():
+        print(r.stderr)
 
 
 if __name__ == "__main__":
