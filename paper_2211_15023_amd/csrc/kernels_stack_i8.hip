@@ -22,7 +22,9 @@
 //  * Convolution + pooling without storing the convolution.  Requantization is monotone per channel, so pooling the int32
 //    accumulators first and requantizing the maxima gives the same bytes with a quarter of the requantizations.  A lane is
 //    a pooled pixel; the four rows of four pixels under it give both conv rows 2py, 2py+1 of its even and odd columns (E =
-//    2px, O = 2px+1).  The vertical maximum takes the lower conv row of the pooled row above, the horizontal one is
+//    2px, O = 2px+1).  The vertical maximum takes the lower conv row of the pooled row above (8-channel layers walk down
+//    strips for it, with the next windows read before the results are stored: two reads and four MFMAs per pair of rows in place of
+//    three and five, 340 -> 328 us for the first stack with the observations by buffer loads), the horizontal one is
 //    max(E, O, O of the pixel to the left), the last term one DPP row shift; a tile's first lane only serves its neighbour
 //    (tiles advance by 15 pixels).  The first column needs no left neighbour: 16-channel layers, whose tiles hold several
 //    runs of columns, put a dummy in front of each run.  Rows and columns outside the image are replaced by their nearest
@@ -232,24 +234,24 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     auto prefetch = [&](int64_t batch) {
         const int64_t b0 = batch * G;
         const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
-        const int last = gc * S::UNITS_IN - 1;
-        const char* src = (const char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN;
+        // (buffer loads: the plane is their scalar offset, and a unit that does not exist is out of the buffer's range and reads 0)
+        const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN, 0,
+                                                           gc * S::IMG_IN, 0x00027000);
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
-            const uint32_t u = (uint32_t)min(tid + i * T, last);        // a unit that does not exist re-reads the last one
             if constexpr (U8) {
                 v4i v;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = *(const int*)(src + (uint32_t)(c * HIN * HIN) + 4u * u);
+                for (int c = 0; c < 4; ++c) v[c] = (int)__builtin_amdgcn_raw_buffer_load_b32(src, 4 * (tid + i * T), c * HIN * HIN, 0);
                 pre[i] = v;
             } else {
-                pre[i] = *(const v4i*)(src + 16u * u);
+                pre[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(src, 16 * (tid + i * T), 0, 0));
             }
         }
     };
     auto commit = [&](int64_t batch) {
         const int64_t b0 = batch * G;
-        const int total = (int)((p.B - b0 < G) ? (p.B - b0) : G) * S::UNITS_IN;
+        const int total = (G == 1 || p.B - b0 >= G ? G : (int)(p.B - b0)) * S::UNITS_IN;
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
             if (tid + i * T >= total) break;
@@ -335,33 +337,60 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                 return st_pack(q);
             };
             if constexpr (S::P == 2) {
-                // work item: (pair of pooled rows rp, strip of pixels 15 s .. 15 s + 15): the windows of both rows and of the
-                // row above, whose lower conv row they share
-                constexpr int NS = (S::H - 1 + 14) / 15, N_IT = S::H / 2 * NS;
-                const char* a = tin + j * 2 * CI + g * S::PITCH_IN;
-                char* d = tX + 2 * g + S::PITCH_B;
-                const uint64_t m_mid = __ballot(j > 0), m_last = __ballot(j > 0 && 15 * (NS - 1) + j < S::H);
-#pragma unroll 2
-                for (int i = 0; i < (N_IT + NW - 1) / NW; ++i) {
-                    const int it = min(wave + i * NW, N_IT - 1);      // past the end: the last one's bytes once more
-                    const int rp = it / NS, s = it - rp * NS;
-                    const char* w0 = a + s * 30 * CI + 4 * rp * S::PITCH_IN;
-                    const v4i fm = read_chunk<8>(a + s * 30 * CI + max(4 * rp - 2, 0) * S::PITCH_IN);
-                    const v4i f0 = read_chunk<8>(w0), f1 = read_chunk<8>(w0 + 2 * S::PITCH_IN);
-                    const v4i c0 = st_mfma(wP[1], fm, biC), c1 = st_mfma(wP[0], f0, biC), c2 = st_mfma(wP[1], f0, biC);
-                    const v4i c3 = st_mfma(wP[0], f1, biC), c4 = st_mfma(wP[1], f1, biC);
+                // work item: (pair of pooled rows, strip of 15 pixels behind the one that only serves its neighbour).  A wavefront
+                // walks down runs of them: an item's windows are two fragments, and the lower conv row of the row above is the
+                // last product of the item before.  Runs that cross into the next strip do so at few places of the unrolled walk.
+                constexpr int NS = (S::H - 1 + 14) / 15, RPS = S::H / 2, N_IT = RPS * NS, PER = (N_IT + NW - 1) / NW;
+                static_assert((NW - 1) * PER < N_IT && PER <= RPS && N_IT > NW * PER - PER, "runs");
+                constexpr auto crosses = [](int i) {
+                    for (int w = 0; w < NW; ++w) if (i > 0 && (w * PER + i) % RPS == 0) return true;
+                    return false;
+                };
+                const int it0 = wave * PER;
+                int s = it0 / RPS, left = RPS - (it0 - s * RPS);      // (the strip, its items that are left)
+                const char* a;
+                char* o;
+                auto strip = [&](int rp) {                            // at row pair rp of strip s
+                    a = tin + j * 2 * CI + g * S::PITCH_IN + s * 30 * CI + 4 * rp * S::PITCH_IN;
+                    const bool ok = (s == 0 || j > 0) && (s < NS - 1 || 15 * (NS - 1) + j < S::H);
+                    o = tX + 2 * g + (2 * rp + 1) * S::PITCH_B + (ok ? (s * 15 + 1 + j) * C : (S::H + 2) * C);
+                };
+                strip(RPS - left);
+                v4i c0 = st_mfma(wP[1], read_chunk<8>(a - (left < RPS ? 2 * S::PITCH_IN : 0)), biC);
+                int at = 0;                                           // the item that a and o belong to
+                auto window = [&](int i) { return read_chunk<8>(a + i * 2 * S::PITCH_IN); };
+                v4i f0 = window(0), f1 = window(1);
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    if (crosses(i)) {
+                        if (left == i) {                              // the first row's window has no row above it: its own upper one again
+                            ++s;
+                            strip(0);
+                            f0 = window(0);
+                            f1 = window(1);
+                            c0 = st_mfma(wP[1], f0, biC);
+                        } else {
+                            a += 4 * (i - at) * S::PITCH_IN;
+                            o += 2 * (i - at) * S::PITCH_B;
+                        }
+                        at = i;
+                    }
+                    if (N_IT % PER && i == PER - 1 && it0 + i >= N_IT) break;
+                    const v4i c1 = st_mfma(wP[0], f0, biC), c2 = st_mfma(wP[1], f0, biC), c3 = st_mfma(wP[0], f1, biC), c4 = st_mfma(wP[1], f1, biC);
+                    // the next item's, before this one's results are stored (past the strip's end: something, and not used)
+                    if (i + 1 < PER) { f0 = window(2 * (i + 1 - at)); f1 = window(2 * (i + 1 - at) + 1); }
                     // a lane holds two channels of both columns: upper pooled row in pooled[0], [1], lower in [2], [3]
                     int vo[4] = {max(max(c0[2], c1[2]), c2[2]), max(max(c0[3], c1[3]), c2[3]), max(max(c2[2], c3[2]), c4[2]), max(max(c2[3], c3[3]), c4[3])};
                     max_with_left(vo);
                     const int pooled[4] = {max(max(max(c0[0], c1[0]), c2[0]), vo[0]), max(max(max(c0[1], c1[1]), c2[1]), vo[1]),
                                            max(max(max(c2[0], c3[0]), c4[0]), vo[2]), max(max(max(c2[1], c3[1]), c4[1]), vo[3])};
+                    c0 = c4;
                     const StBytes w = requant(pooled);
-                    const bool ok = __builtin_amdgcn_inverse_ballot_w64(s == 0 ? ~0ull : s == NS - 1 ? m_last : m_mid);
-                    char* o = d + 2 * rp * S::PITCH_B + (ok ? (s * 15 + 1) * C + j * C : (S::H + 2) * C);
-                    *(uint16_t*)o = (uint16_t)w.pos;
-                    *(uint16_t*)(o + S::PITCH_B) = (uint16_t)(w.pos >> 16);
-                    *(uint16_t*)(o + S::O_TM - S::O_TX) = (uint16_t)w.raw;
-                    *(uint16_t*)(o + S::O_TM - S::O_TX + S::PITCH_B) = (uint16_t)(w.raw >> 16);
+                    char* d = o + 2 * (i - at) * S::PITCH_B;
+                    *(uint16_t*)d = (uint16_t)w.pos;
+                    *(uint16_t*)(d + S::PITCH_B) = (uint16_t)(w.pos >> 16);
+                    *(uint16_t*)(d + S::O_TM - S::O_TX) = (uint16_t)w.raw;
+                    *(uint16_t*)(d + S::O_TM - S::O_TX + S::PITCH_B) = (uint16_t)(w.raw >> 16);
                 }
             } else if (wave < S::NT1) {
                 auto out = [&](int k, v4i e, v4i o) {
