@@ -65,6 +65,7 @@ struct StackParams {
     const float* mult[5];
     float r1, r2;            // scale of a block's input over the scale of its output
     int64_t B;
+    int units;               // compute units: workgroup b of the resident ones is number b / units on its unit
 };
 
 constexpr int st_up16(int v) { return (v + 15) / 16 * 16; }
@@ -142,6 +143,21 @@ __device__ __forceinline__ StBytes st_pack(const int (&q)[4]) {
 // 1.5 * 2^23 + sum as a float.  Three stacks at 16384 states, in turn on one card: 583, 592, 594 -> 576, 581, 585 us.  A
 // bias can take a layer out of these ranges (no weights of these sizes can); such a network converts.
 constexpr int ST_MAGIC = 0x4B400000;
+
+// The workgroups of a unit take turns at being first.  Between wavefronts of equal priority a SIMD issues the oldest one's instructions, so
+// the workgroup that came first runs through its images and leaves the unit to the others, which cannot fill it: of two (first stack, 16384
+// states) one was through after 202 us and the other after 308, of four (second stack) after 99, 116, 157 and 179.  A turn is 2^LOG clocks
+// of the unit's counter, which all see alike; the third stack, whose workgroups do not come in equal numbers, gains nothing.
+// Traces in turn on one card, us, without / with: first stack 2048 states 49.7 / 48.1, 4096 95.2 / 92.6, 16384 335 / 326; second 31.6 / 30.4,
+// 57.6 / 56.0, 194 / 181 (turns of 2^12 335 / 187 at 16384 states, 2^16 as long as 2^15).
+template <int SLOTS, int LOG>
+__device__ __forceinline__ void st_turn(int slot) {
+    const int t = ((int)(__builtin_readcyclecounter() >> LOG) + slot) & (SLOTS - 1);
+    if (t == 0) __builtin_amdgcn_s_setprio(0);
+    else if (t == 1) __builtin_amdgcn_s_setprio(1);
+    else if (t == 2) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(3);
+}
 template <bool BITS>
 __device__ __forceinline__ float st_float(int acc) { return BITS ? __int_as_float(acc) - 12582912.0f : (float)acc; }
 
@@ -314,7 +330,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     }
     __syncthreads();
 
+    const int slot = blockIdx.x / (uint32_t)p.units;
+    auto turn = [&]() {
+        if constexpr (S::P == 2) st_turn<2, 14>(slot);
+        else if constexpr (CI == 8) st_turn<4, 13>(slot);
+    };
     for (; batch < n_batch; batch += gridDim.x) {
+        turn();
         commit(batch);
         __syncthreads();
         const int64_t b0 = batch * G;
@@ -524,6 +546,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         };
         // The pooled stream waits where the inner tensor will be: its pixels' owners take it into registers before they
         // write there, and it stays in registers from then on.
+        turn();
         v4i wA[S::NWB], wB[S::NWB];
 #pragma unroll
         for (int k = 0; k < S::R; ++k) x[k] = *(const uint32_t*)(tM + bown + k * S::PITCH_B);
@@ -533,6 +556,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
         __syncthreads();
         conv_b(wB, 2, p.r1, std::false_type{});
         weights(std::integral_constant<int, 2>{}, wA);
+        turn();
         __syncthreads();
         conv_a(wA, 3);
         weights(std::integral_constant<int, 3>{}, wB);
@@ -607,7 +631,7 @@ hipError_t launch_stack(const ConvParams& c, const ConvParams& a1, const ConvPar
     p.in = c.in; p.rows = c.rows; p.out = (int8_t*)b2.out;
     const ConvParams* cv[5] = {&c, &a1, &b1, &a2, &b2};
     for (int i = 0; i < 5; ++i) { p.w[i] = (const v4i*)cv[i]->wfrag; p.bias[i] = (const int*)cv[i]->bias; p.mult[i] = cv[i]->mult; }
-    p.r1 = b1.r; p.r2 = b2.r; p.B = c.B;
+    p.r1 = b1.r; p.r2 = b2.r; p.B = c.B; p.units = (int)conv_num_cus();
     static const bool no_p23 = getenv("ACCERL_NO_P23") != nullptr;
     const bool bits = a1.pos23 && a2.pos23 && c.mag22 && b1.mag22 && b2.mag22 && !no_p23;
 #define X(U8, CI, HIN, C, G, SEG, PSEG, NW, WL, MINB)                                                              \
