@@ -102,6 +102,11 @@ struct StShape {
     static constexpr int NWB = P == 2 ? 4 : 3;                 // fragments of a block convolution
     static constexpr int WB = P == 2 ? 4096 : 9 * 256;         // their bytes in LDS (three lane groups of 16-channel layers)
     static constexpr int NWP = P == 2 ? 2 : CI == 8 ? 8 : 6;   // fragments of the stack convolution
+    // The products of a row are issued between the vector instructions of the row above, their fragments read before that.  Left to itself
+    // the compiler keeps every read behind the stores of the row above and waits for it and then for the products.  For the third stack,
+    // whose LDS leaves a SIMD two wavefronts (1024 states 12.3 -> 11.1 us, 4096 29.5 -> 28.3, 16384 79.3 -> 75.6; the blocks alone 11.4, 28.8,
+    // 77.5); the others' four cover each other and have no registers for it (first 333 / 333, second 188 / 190 with spills).
+    static constexpr bool AHEAD = CI == 16;
     // LDS layout (bytes)
     static constexpr int O_TX = st_up16(G * TILE_IN + 64);
     static constexpr int O_TM = O_TX + G * TILE_B;
@@ -449,41 +454,55 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                         cE = e1; cO = o1; f0 = f1;
                     }
                 } else {
+                    static_assert(S::AHEAD, "16 input channels");
                     auto conv = [&](const v4i* w, v4i r0, v4i r1, v4i r2) { return st_mfma(w[2], r2, st_mfma(w[1], r1, st_mfma(w[0], r0, biC))); };
                     auto row = [&](int y) { return *(const v4i*)(a + y * S::PITCH_IN); };
-                    v4i f0 = row(0), f1 = row(1), cE, cO;
+                    constexpr auto below = [](int k) { return !(HIN & 1) || k + 1 < S::RP; };    // (odd sizes: no conv row below the last)
+                    v4i f0 = row(0), f1 = row(1), f2 = row(2), f3 = row(3), cE, cO;
                     {
                         const char* m = a + pfirst;
                         const v4i m1 = *(const v4i*)(m + S::PITCH_IN), m2 = *(const v4i*)(m + 2 * S::PITCH_IN), m3 = *(const v4i*)(m + 3 * S::PITCH_IN);
                         cE = conv(wP, m1, m2, m3);
                         cO = conv(wP + 3, m1, m2, m3);
                     }
+                    v4i e0 = conv(wP, f0, f1, f2), o0 = conv(wP + 3, f0, f1, f2), e1 = conv(wP, f1, f2, f3), o1 = conv(wP + 3, f1, f2, f3);
+                    f0 = f2; f1 = f3; f2 = row(4); f3 = row(5);
 #pragma unroll
                     for (int k = 0; k < S::RP; ++k) {
-                        const v4i f2 = row(2 * k + 2);
-                        const v4i e0 = conv(wP, f0, f1, f2), o0 = conv(wP + 3, f0, f1, f2);
-                        v4i e1 = e0, o1 = o0, f3 = f2;
-                        if (!(HIN & 1) || k + 1 < S::RP) {
-                            f3 = row(2 * k + 3);
-                            e1 = conv(wP, f1, f2, f3);
-                            o1 = conv(wP + 3, f1, f2, f3);
-                        }                                            // (odd sizes: no conv row below the last)
-                        out(k, max3(cE, e0, e1), max3(cO, o0, o1));
-                        cE = e1; cO = o1; f0 = f2; f1 = f3;
+                        const v4i mE = max3(cE, e0, e1), mO = max3(cO, o0, o1);
+                        cE = e1; cO = o1;
+                        if (k + 1 < S::RP) {
+                            e0 = conv(wP, f0, f1, f2); o0 = conv(wP + 3, f0, f1, f2);
+                            e1 = e0; o1 = o0;
+                            if (below(k + 1)) { e1 = conv(wP, f1, f2, f3); o1 = conv(wP + 3, f1, f2, f3); }
+                            f0 = f2; f1 = f3;
+                            if (k + 2 < S::RP) { f2 = row(2 * k + 6); if (below(k + 2)) f3 = row(2 * k + 7); }
+                        }
+                        out(k, mE, mO);
+                        if (k + 1 < S::RP) {
+#pragma unroll
+                            for (int m = 0; m < (below(k + 1) ? 12 : 6); ++m) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
                     }
                 }
             }
         }
         __syncthreads();
 
-        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k
-        auto walk = [&](const char* src, const v4i (&w)[S::NWB], v4i b, auto&& done) {
+        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k in V vector instructions
+        auto walk = [&](const char* src, const v4i (&w)[S::NWB], v4i b, auto per_row, auto&& done) {
+            constexpr int V = decltype(per_row)::value;
             const char* a = src + boff;
+            auto row = [&](int y) { return *(const v4i*)(a + y * S::PITCH_B); };
             if constexpr (S::P == 2) {
-                v4i f0 = *(const v4i*)a;
+                v4i f0 = row(0);
 #pragma unroll
                 for (int k = 0; k < S::R; k += 2) {
-                    const v4i f1 = *(const v4i*)(a + (k + 2) * S::PITCH_B);
+                    const v4i f1 = row(k + 2);
                     const v4i u = st_mfma(w[1], f1, st_mfma(w[0], f0, b));
                     if (k + 1 < S::R) {
                         const v4i l = st_mfma(w[3], f1, st_mfma(w[2], f0, b));
@@ -494,14 +513,35 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                     }
                     f0 = f1;
                 }
-            } else {
-                auto row = [&](int y) { return *(const v4i*)(a + y * S::PITCH_B); };
+            } else if constexpr (!S::AHEAD) {
                 v4i f0 = row(0), f1 = row(1);
 #pragma unroll
                 for (int k = 0; k < S::R; ++k) {
                     const v4i f2 = row(k + 2);
                     done(k, st_mfma(w[2], f2, st_mfma(w[1], f1, st_mfma(w[0], f0, b))));
                     f0 = f1; f1 = f2;
+                }
+            } else {
+                v4i f0 = row(0), f1 = row(1), f2 = row(2), f3 = row(3);
+                v4i acc = st_mfma(w[2], f2, st_mfma(w[1], f1, st_mfma(w[0], f0, b)));
+#pragma unroll
+                for (int k = 0; k < S::R; ++k) {
+                    v4i next = acc, f4 = f3;
+                    if (k + 1 < S::R) {
+                        if (k + 2 < S::R) f4 = row(k + 4);
+                        next = st_mfma(w[2], f3, st_mfma(w[1], f2, st_mfma(w[0], f1, b)));
+                    }
+                    done(k, acc);
+                    if (k + 1 < S::R) {
+#pragma unroll
+                        for (int m = 0; m < 3; ++m) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            if (m == 0 && k + 2 < S::R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x002, V / 3, 0);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc = next; f1 = f2; f2 = f3; f3 = f4;
                 }
             }
         };
@@ -510,7 +550,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             const v4i bi = *(const v4i*)(cst + cv * 32 + 4 * g) + (BITS ? P23_MAGIC : 0);
             const v4f ml = *(const v4f*)(cst + cv * 32 + 16 + 4 * g);
             const v4f cc = ml * -8388608.0f;
-            walk(tX, w, bi, [&](int k, v4i acc) {
+            walk(tX, w, bi, std::integral_constant<int, BITS ? 12 : 16>{}, [&](int k, v4i acc) {
                 const uint32_t y = requant_relu4_p23<BITS>(acc, ml, cc);
                 *(uint32_t*)(tM + bown + k * S::PITCH_B) = y;
             });
@@ -527,7 +567,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             // branch around the phase would leave the matrix instructions with some of a wavefront's lanes only.  Rows by the scalar
             // offset: added to the lanes' they took a register and an instruction each)
             const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((char*)p.out + b0 * (int64_t)S::IMG, 0, gc * S::IMG, 0x00027000);
-            walk(tM, w, bi, [&](int k, v4i acc) {
+            walk(tM, w, bi, std::integral_constant<int, LAST ? 27 : 29>{}, [&](int k, v4i acc) {
                 int q[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
