@@ -78,13 +78,16 @@ struct BsShape {
     static constexpr int IMG = H * H * C * 2;
     // conv + pool items: column tiles of pooled pixels (14 of observations, else seven) x row segments x images
     static constexpr int CT = U8 ? (H + 13) / 14 : (H + 6) / 7, RP = (H + PSEG - 1) / PSEG, ITEMS = CT * PSEG * G;
+    static constexpr int PAST = SEG * R - H;                   // rows that the last segment's lanes walk past the image
     // the inner tensor takes the place of the observation tile, which is dead once it has been pooled
     static constexpr bool OVER = U8;
     static constexpr int O_IN = G * TILE, O_M = O_IN;
-    static constexpr int LDS = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);   // dynamic; besides S_IN
+    // where lanes that own no pooled pixel store (a branch around the store would end the compiler's view at every row)
+    static constexpr int O_DUMP = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);
+    static constexpr int LDS = O_DUMP + RP * ROWB + 512;       // dynamic; besides S_IN
     // bf16 inputs: an LDS array of their own, filled from memory without passing through registers (a load of 64 chunks each)
     static constexpr int S_IN = OVER ? 16 : G * TILE_IN, NLOAD = (S_IN / 16 + THREADS - 1) / THREADS;
-    static_assert(C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS + S_IN <= 160 * 1024, "shape");
+    static_assert(PAST <= 1 && C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS + S_IN <= 160 * 1024, "shape");
 };
 
 __device__ __forceinline__ v4f bs_mfma(v4i a, v4i b, v4f c) {
@@ -119,21 +122,35 @@ __device__ __forceinline__ void bs_load(BsRow& r, const char* a, const char* m, 
     r.f[1] = CIN == 16 ? *(const v4i*)(m + off) : *(const v4i*)(a + off + 16);
     r.f[2] = *(const v4i*)(a + off + (CIN == 16 ? 16 : 32));
 }
-// what an input row adds to the output row whose first / middle / last window row it is
+// What an input row adds to the output rows whose last / middle / first window row it is: three chains, one product of each in turn.  A chain
+// that is not wanted costs nothing once inlined.
 template <int CIN>
-__device__ __forceinline__ v4f bs_top(const v4i* w, const BsRow& r, v4f acc) {
-    if constexpr (CIN == 16) return bs_mfma(w[0], r.f[0], acc);
-    else return bs_mfma(w[2], r.f[2], bs_mfma(w[1], r.f[1], bs_mfma(w[0], r.f[0], acc)));
+__device__ __forceinline__ void bs_row(const v4i* w, const BsRow& r, v4f& bottom, v4f& mid, v4f& top) {
+    if constexpr (CIN == 16) {
+        bottom = bs_mfma(w[3], r.f[0], bottom);
+        top = bs_mfma(w[0], r.f[0], top);
+        mid = bs_mfma(w[1], r.f[1], mid);
+        bottom = bs_mfma(w[4], r.f[2], bottom);
+        mid = bs_mfma(w[2], r.f[2], mid);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            bottom = bs_mfma(w[6 + q], r.f[q], bottom);
+            mid = bs_mfma(w[3 + q], r.f[q], mid);
+            top = bs_mfma(w[q], r.f[q], top);
+        }
+    }
 }
-template <int CIN>
-__device__ __forceinline__ v4f bs_mid(const v4i* w, const BsRow& r, v4f acc) {
-    if constexpr (CIN == 16) return bs_mfma(w[2], r.f[2], bs_mfma(w[1], r.f[1], acc));
-    else return bs_mfma(w[5], r.f[2], bs_mfma(w[4], r.f[1], bs_mfma(w[3], r.f[0], acc)));
-}
-template <int CIN>
-__device__ __forceinline__ v4f bs_bottom(const v4i* w, const BsRow& r, v4f acc) {
-    if constexpr (CIN == 16) return bs_mfma(w[4], r.f[2], bs_mfma(w[3], r.f[0], acc));
-    else return bs_mfma(w[8], r.f[2], bs_mfma(w[7], r.f[1], bs_mfma(w[6], r.f[0], acc)));
+// The order of a stretch of code without branches: R reads, then M times one product and V vector instructions.  Two wavefronts share a SIMD;
+// left to itself the compiler puts a row's reads, products and vector instructions behind one another and waits between them.
+template <int R, int M, int V>
+__device__ __forceinline__ void bs_order() {
+    __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
 }
 
 // ROWS: observations through the row list (as a test in the kernel it cost the others 0.5 us of 169 at 1024 states)
@@ -259,6 +276,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     const int offA = pos + (C == 16 ? (g & 1) * S::PLANE + (g >> 1) * 16 : g * S::PLANE);
     const int offM = pos + (g & 1) * S::PLANE + (g < 2 ? 32 - S::ROWB : 0);       // 16 channels only
     const int own = pos + S::ROWB + 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
+    const int past = S::PAST && seg == SEG - 1 ? S::ROWB : 0;
     __syncthreads();
 
     for (; batch < n_batch; batch += gridDim.x) {
@@ -272,8 +290,8 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
         for (int it = tile; it < S::ITEMS; it += S::TW) {
             const int im = it / (S::CT * PSEG), ps = (it - im * S::CT * PSEG) % PSEG, ct = (it - im * S::CT * PSEG) / PSEG;
             const int p0 = min(ps * S::RP, S::H - S::RP);        // segments may overlap: the same bytes twice
-            auto dst_of = [&](int px) {
-                return tX + im * S::TILE + (p0 + 1) * S::ROWB + (px + 1) * 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
+            auto dst_of = [&](int px, bool ok) {
+                return !ok ? smem + S::O_DUMP + 8 * lane : tX + im * S::TILE + (p0 + 1) * S::ROWB + (px + 1) * 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
             };
             const v4f none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             if constexpr (U8) {
@@ -281,8 +299,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                 // accumulators; the left neighbour's O completes the window, so the first lane only serves its neighbour.
                 // (Columns outside the image repeat one of the same window.)
                 const int px = 14 * ct - 1 + j, pc = min(max(px, 0), S::H - 1);
-                const bool st_ok = j >= 1 && j <= 14 && px < S::H;
-                char* dst = dst_of(px);
+                char* dst = dst_of(px, j >= 1 && j <= 14 && px < S::H);
                 // window rows y, y + 1 in the two halves of a fragment: F(y) is step 0 of conv row y and step 1 of row y - 2
                 const char* a = tin + (2 * p0 + (g >> 1)) * S::IROW + 2 * pc * 8 + (g & 1) * 16;
                 auto even = [&](int row) { return *(const v4i*)(a + row * S::IROW); };
@@ -292,32 +309,41 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                 v4i e0 = even(0), e1 = even(1), o0 = odd(0), o1 = odd(1);
                 v4f carryE = none, carryO = none;
                 if (p0 > 0) { carryE = conv(even(-1), e1); carryO = conv(odd(-1), o1); }
+                v4i e2 = even(2), e3 = even(3), o2 = odd(2), o3 = odd(3);
+                v4f cE0 = conv(e0, e2), cO0 = conv(o0, o2), cE1 = conv(e1, e3), cO1 = conv(o1, o3);
 #pragma unroll
                 for (int k = 0; k < S::RP; ++k) {
-                    const v4i e2 = even(2 * k + 2), e3 = even(2 * k + 3), o2 = odd(2 * k + 2), o3 = odd(2 * k + 3);
-                    const v4f cE0 = conv(e0, e2), cO0 = conv(o0, o2), cE1 = conv(e1, e3), cO1 = conv(o1, o3);
+                    v4f mO, mE;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        mO[r] = bs_max3(carryO[r], cO0[r], cO1[r]);
+                        mE[r] = bs_max3(carryE[r], cE0[r], cE1[r]);
+                    }
+                    carryE = cE1; carryO = cO1;
+                    if (k + 1 < S::RP) {                  // the next row's products go between this one's maxima
+                        e0 = e2; e1 = e3; o0 = o2; o1 = o3;
+                        e2 = even(2 * k + 4); e3 = even(2 * k + 5); o2 = odd(2 * k + 4); o3 = odd(2 * k + 5);
+                        cE0 = conv(e0, e2); cO0 = conv(o0, o2); cE1 = conv(e1, e3); cO1 = conv(o1, o3);
+                    }
                     v4f m;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float vO = bs_max3(carryO[r], cO0[r], cO1[r]);
-                        const int i = __float_as_int(vO);
-                        const float left = __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false));
-                        m[r] = bs_max3(bs_max3(carryE[r], cE0[r], cE1[r]), vO, left);
+                        const int i = __float_as_int(mO[r]);
+                        m[r] = bs_max3(mE[r], mO[r], __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false)));
                     }
-                    if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
-                    carryE = cE1; carryO = cO1;
-                    e0 = e2; e1 = e3; o0 = o2; o1 = o3;
+                    *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+                    if (k + 1 < S::RP) bs_order<4, 8, 3>();
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
                 const int x = min(max(14 * ct - 1 + j, 0), HIN - 1);  // columns outside repeat the outermost one
                 const int px = 7 * ct + (j >> 1);
-                const bool st_ok = (j & 1) && j < 14 && px < S::H;
-                char* dst = dst_of(px);
+                char* dst = dst_of(px, (j & 1) && j < 14 && px < S::H);
                 auto store = [&](int k, v4f v) {
                     v4f m;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) m[r] = bs_max_neighbours(v[r]);
-                    if (st_ok) *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
+                    *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
                 };
                 v4f carry = none;
                 const int base = im * S::TILE_IN + 2 * p0 * S::IROW + x * 16;
@@ -325,36 +351,50 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                 const char* m = tin + base + (g & 1) * S::IPLANE + (g < 2 ? 32 - S::IROW : 0);
                 BsRow r0, r1;                             // input rows 2 p0, 2 p0 + 1
                 bs_load<CI>(r1, a, m, S::IROW);
-                v4f a1, a2;
+                v4f a1, a2, unused = none;
                 if (p0 > 0) {                             // conv row 2 p0 - 1, kept for the first pooled row
                     BsRow rm;
                     bs_load<CI>(rm, a, a, -S::IROW);      // (its f1 is not used with 16 channels)
                     bs_load<CI>(r0, a, m, 0);
-                    carry = bs_bottom<CI>(wC, r1, bs_mid<CI>(wC, r0, bs_top<CI>(wC, rm, bias[0])));
+                    carry = bias[0];
+                    bs_row<CI>(wC, rm, unused, unused, carry);
+                    a2 = a1 = bias[0];
+                    bs_row<CI>(wC, r0, unused, carry, a2);
+                    bs_row<CI>(wC, r1, carry, a2, a1);
                 } else {
                     bs_load<CI>(r0, a, a, 0);
+                    a2 = a1 = bias[0];
+                    bs_row<CI>(wC, r0, unused, unused, a2);
+                    bs_row<CI>(wC, r1, unused, a2, a1);
                 }
-                a2 = bs_mid<CI>(wC, r1, bs_top<CI>(wC, r0, bias[0]));
-                a1 = bs_top<CI>(wC, r1, bias[0]);
+                constexpr int NM = CI == 16 ? 5 : 9;
+                BsRow r2, r3;
+                bs_load<CI>(r2, a, m, 2 * S::IROW);
+                v4f v = none;
 #pragma unroll
                 for (int k = 0; k < S::RP; ++k) {
-                    BsRow r2, r3;
                     const bool low = (HIN & 1) == 0 || k + 1 < S::RP || p0 + k < S::H - 1;   // conv row 2 py + 1 exists
-                    bs_load<CI>(r2, a, m, (2 * k + 2) * S::IROW);
-                    const v4f c0 = bs_bottom<CI>(wC, r2, a2);
-                    v4f c1 = c0;
-                    if (low) {
-                        bs_load<CI>(r3, a, m, (2 * k + 3) * S::IROW);
-                        c1 = bs_bottom<CI>(wC, r3, bs_mid<CI>(wC, r2, a1));
-                        a2 = bs_mid<CI>(wC, r3, bs_top<CI>(wC, r2, bias[0]));
-                        a1 = bs_top<CI>(wC, r3, bias[0]);
-                    }
-                    v4f v;
+                    // conv row 2 py is complete with row 2, the next two are under way; the maximum of the row above follows the products
+                    if (low) bs_load<CI>(r3, a, m, (2 * k + 3) * S::IROW);
+                    v4f c0 = a2, c1 = a1, top = bias[0];
+                    bs_row<CI>(wC, r2, c0, c1, top);
+                    if (k > 0) store(k - 1, v);
+                    if (low) bs_order<3, NM, CI == 16 ? 5 : 3>();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k + 1 < S::RP) bs_load<CI>(r2, a, m, (2 * k + 4) * S::IROW);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = bs_max3(carry[r], c0[r], c1[r]);
-                    carry = c1;
-                    store(k, v);
+                    for (int r = 0; r < 4; ++r) v[r] = fmaxf(carry[r], c0[r]);
+                    if (low) {
+                        a2 = top; a1 = bias[0];
+                        bs_row<CI>(wC, r3, c1, a2, a1);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], c1[r]);
+                        carry = c1;
+                    }
+                    if (k + 1 < S::RP) bs_order<3, NM, 1>();
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                store(S::RP - 1, v);
             }
         }
         __syncthreads();
@@ -368,10 +408,10 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
             }
         }
 
-        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k, one row late
-        const bool live = n < S::NCOL && img < gc;
-        auto walk = [&](const char* src, const v4i* w, v4f b, auto relu, auto&& done) {
+        // ---- one block convolution: walk down this lane's column; done(k, acc) takes output row k, one row late, and before(k) what it will need
+        auto walk = [&](const char* src, const v4i* w, v4f b, auto relu, auto&& before, auto&& done) {
             constexpr bool RELU = decltype(relu)::value;
+            constexpr int NM = C == 16 ? 5 : 9;
             const char* a = src + offA;
             const char* m = src + offM;
             BsRow cur, nxt;
@@ -384,41 +424,56 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
             bs_load<C>(cur, a, a, 0);                     // (f1 of the first row is not used with 16 channels)
             bs_load<C>(nxt, a, m, S::ROWB);
             rect(cur);
-            v4f a1 = bs_top<C>(w, cur, b), a2 = a1, out = a1;
+            v4f a2 = b, a1 = b, out = b, unused = b;
+            bs_row<C>(w, cur, unused, unused, a1);
 #pragma unroll
             for (int i = 1; i < S::R + 2; ++i) {
                 cur = nxt;
                 if (i + 1 < S::R + 2) bs_load<C>(nxt, a, m, (i + 1) * S::ROWB);
+                if (i >= 2) before(i - 2);
                 rect(cur);
-                v4f o = out;
-                if (i >= 2) o = bs_bottom<C>(w, cur, a2);
-                if (i < S::R + 1) a2 = bs_mid<C>(w, cur, a1);
-                if (i < S::R) a1 = bs_top<C>(w, cur, b);
+                // (chains of rows above the first and past the last are not used)
+                v4f o = a2, mid = a1, top = b;
+                bs_row<C>(w, cur, o, mid, top);
                 if (i >= 3) done(i - 3, out);
-                out = o;
+                if (i >= 3 && i < S::R) {
+                    if constexpr (RELU) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                    bs_order<RELU ? 3 : 4, NM, C == 16 ? (RELU ? 3 : 2) : (RELU ? 2 : 1)>();
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                out = o; a2 = mid; a1 = top;
             }
             done(S::R - 1, out);
         };
-        auto row_ok = [&](int k) { return live && (SEG * S::R == S::H || row0 + k < S::H); };
+        // Lanes past the last column repeat it, those of images past the batch work on what is there: no predicates.  The row that the last
+        // segment's lanes walk past the image goes to the row behind the border, which meets no pixel of the image.
+        auto at = [&](int k) { return own + (k + 1 == S::R ? past : 0) + k * S::ROWB; };
         auto conv_a = [&](const v4i* w, v4f b) {          // inner tensor = relu(conv(relu(stream)))
             if (tile * 16 >= S::NCOL) return;
-            walk(tX, w, b, std::true_type{}, [&](int k, v4f acc) {
+            walk(tX, w, b, std::true_type{}, [](int) {}, [&](int k, v4f acc) {
                 typedef short v4s __attribute__((ext_vector_type(4)));
                 const v4s q = __builtin_elementwise_max(__builtin_bit_cast(v4s, bs_pack(acc)), (v4s){0, 0, 0, 0});
-                if (row_ok(k)) *(v2i*)(tM + own + k * S::ROWB) = __builtin_bit_cast(v2i, q);
+                *(v2i*)(tM + at(k)) = __builtin_bit_cast(v2i, q);
             });
         };
         auto conv_b = [&](const v4i* w, v4f b, auto last) {   // stream += conv(inner tensor), in place or to memory
             constexpr bool LAST = decltype(last)::value;
             if (tile * 16 >= S::NCOL) return;
-            char* outp = p.out + b0 * (int64_t)S::IMG + (uint32_t)((img * S::H + row0) * S::H + col) * (C * 2) + (C == 16 ? 8 * g : 16 * g + 8 * half);
-            walk(tM, w, b, std::false_type{}, [&](int k, v4f acc) {
-                const v2i x = *(const v2i*)(tX + own + k * S::ROWB);
-                const v4f y = {bf2f((uint32_t)x[0] & 0xffffu) + acc[0], __int_as_float(x[0] & (int)0xffff0000) + acc[1],
-                               bf2f((uint32_t)x[1] & 0xffffu) + acc[2], __int_as_float(x[1] & (int)0xffff0000) + acc[3]};
-                if (!row_ok(k)) return;
-                if constexpr (LAST) *(v2i*)(outp + k * S::H * C * 2) = bs_pack(y);
-                else *(v2i*)(tX + own + k * S::ROWB) = bs_pack(y);
+            const int offp = ((img * S::H + row0) * S::H + col) * (C * 2) + (C == 16 ? 8 * g : 16 * g + 8 * half);
+            char* outp = p.out + b0 * (int64_t)S::IMG + (uint32_t)offp;
+            // (the buffer ends with the batch's last image: what is stored behind it is dropped)
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(p.out + b0 * (int64_t)S::IMG, 0, gc * S::IMG, 0x00027000);
+            v2i x[2];
+            walk(tM, w, b, std::false_type{}, [&](int k) { x[k & 1] = *(const v2i*)(tX + own + k * S::ROWB); }, [&](int k, v4f acc) {
+                const v2i q = x[k & 1];
+                const v4f y = {bf2f((uint32_t)q[0] & 0xffffu) + acc[0], __int_as_float(q[0] & (int)0xffff0000) + acc[1],
+                               bf2f((uint32_t)q[1] & 0xffffu) + acc[2], __int_as_float(q[1] & (int)0xffff0000) + acc[3]};
+                if constexpr (!LAST) *(v2i*)(tX + at(k)) = bs_pack(y);
+                else if constexpr (G == 1 && S::PAST == 0) *(v2i*)(outp + k * S::H * C * 2) = bs_pack(y);
+                else {
+                    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, bs_pack(y)), rsrc, k + 1 == S::R && past ? 0x7fffff00 : offp, k * S::H * C * 2, 0);
+                }
             });
         };
         // the next batch's input, a third of the loads at a time: the memory queue of a compute unit holds a wavefront that
