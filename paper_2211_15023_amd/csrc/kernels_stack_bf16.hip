@@ -84,9 +84,11 @@ struct BsShape {
     static constexpr int O_IN = G * TILE, O_M = O_IN;
     // where lanes that own no pooled pixel store (a branch around the store would end the compiler's view at every row)
     static constexpr int O_DUMP = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);
-    static constexpr int LDS = O_DUMP + RP * ROWB + 512;       // dynamic; besides S_IN
+    static constexpr int O_TAB = O_DUMP + RP * ROWB + 512;
     // bf16 inputs: an LDS array of their own, filled from memory without passing through registers (a load of 64 chunks each)
-    static constexpr int S_IN = OVER ? 16 : G * TILE_IN, NLOAD = (S_IN / 16 + THREADS - 1) / THREADS;
+    // and a table of where its chunks come from
+    static constexpr int NLOAD = OVER ? 0 : (G * TILE_IN / 16 + THREADS - 1) / THREADS, S_IN = OVER ? 16 : NLOAD * THREADS * 16;
+    static constexpr int LDS = O_TAB + NLOAD * THREADS * 4;    // dynamic; besides S_IN
     static_assert(PAST <= 1 && C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS + S_IN <= 160 * 1024, "shape");
 };
 
@@ -110,6 +112,13 @@ __device__ __forceinline__ float bs_max_neighbours(float v) {
     const int i = __float_as_int(v);
     return bs_max3(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false)),
                    __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x101, 0xf, 0xf, false)));
+}
+
+// 16 bytes a lane from the buffer to 1 KiB of LDS (the compiler's host pass does not know the builtin and would drop the kernel)
+__device__ __forceinline__ void bs_load_lds(__amdgpu_buffer_rsrc_t src, char* lds, int off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lds, 16, off, 0, 0, 0);
+#endif
 }
 
 // The fragments of one input row under a lane's 3-wide window.
@@ -205,34 +214,29 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
         }
         for (int i = tid; i < 2 * HIN; i += T) *(v2i*)(tin + (1 + (i >> 1)) * S::IROW + (i & 1) * (HIN + 1) * 8) = (v2i){0, 0};
     };
-    // ---- staging of bf16 inputs: memory to the planes of s_in directly.  Chunk (wave + NW * i) * 64 + l of s_in comes from
-    //      source(i, l) of the batch or, at borders and padding, from nowhere (they stay zero).
-    auto source = [&](int i, int l) -> int {
-        const int q = (wave + i * S::NW) * 64 + l;
-        const int im = q / (S::TILE_IN / 16), r1 = q - im * (S::TILE_IN / 16), cb = r1 / (S::IPLANE / 16), r2 = r1 - cb * (S::IPLANE / 16);
-        const int row = r2 / S::IPB, col = r2 - row * S::IPB;
-        return im < G && row >= 1 && row <= HIN && col >= 1 && col <= HIN ? im * S::IMG_IN + ((row - 1) * HIN + col - 1) * (CI * 2) + cb * 16 : -1;
-    };
+    // ---- staging of bf16 inputs: memory to the planes of s_in directly.  Chunk i * T + tid of s_in comes from tab[i * T + tid] of the
+    //      batch; those of borders and padding, and of images past the batch, are out of the buffer's range: zeros.  (Worked out for every
+    //      load, a third of the loads cost their phase 1 100 clocks of 4 000.)
+    int* tab = (int*)(smem + S::O_TAB);
     auto fetch = [&](int64_t batch, int i0, int i1) {
         if constexpr (!U8) {
             const int64_t b0 = batch * G;
-            const int lim = (int)min(p.B - b0, (int64_t)G) * S::IMG_IN;      // images past the batch: not fetched, never stored
-            const char* src = (const char*)p.in + b0 * (int64_t)S::IMG_IN;
-            int l = lane;
-            asm volatile("" : "+v"(l));                  // worked out anew for every batch: registers are short
+            const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + b0 * (int64_t)S::IMG_IN, 0, (int)min(p.B - b0, (int64_t)G) * S::IMG_IN, 0x00027000);
 #pragma unroll
-            for (int i = i0; i < i1; ++i) {
-                const int at = i < S::NLOAD ? source(i, l) : -1;
-                if (at >= 0 && at < lim)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (uint32_t)at),
-                                                     (__attribute__((address_space(3))) void*)(s_in + (wave + i * S::NW) * 1024), 16, 0, 0);
-            }
+            for (int i = i0; i < i1; ++i)
+                if (i < S::NLOAD)
+                    bs_load_lds(src, s_in + (wave + i * S::NW) * 1024, tab[i * T + tid]);
         }
     };
     if constexpr (!U8) {
+#pragma unroll
         for (int i = 0; i < S::NLOAD; ++i) {
-            const int q = (wave + i * S::NW) * 64 + lane;
-            if (source(i, lane) < 0 && q < S::S_IN / 16) ((v4i*)s_in)[q] = (v4i){0, 0, 0, 0};
+            const int q = tid + i * T;
+            const int im = q / (S::TILE_IN / 16), r1 = q - im * (S::TILE_IN / 16), cb = r1 / (S::IPLANE / 16), r2 = r1 - cb * (S::IPLANE / 16);
+            const int row = r2 / S::IPB, col = r2 - row * S::IPB;
+            const bool pixel = im < G && row >= 1 && row <= HIN && col >= 1 && col <= HIN;
+            tab[q] = pixel ? im * S::IMG_IN + ((row - 1) * HIN + col - 1) * (CI * 2) + cb * 16 : 0x7fffff00;
+            if (!pixel) ((v4i*)s_in)[q] = (v4i){0, 0, 0, 0};
         }
     }
 
@@ -266,7 +270,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
 #pragma unroll
         for (int cv = 0; cv < 5; ++cv) bias[cv] = *(const v4f*)(p.bias[cv] + 4 * NH * g + 4 * half);
     }
-    for (int i = tid; i < S::LDS / 16; i += T) ((v4i*)smem)[i] = (v4i){0, 0, 0, 0};
+    for (int i = tid; i < S::O_TAB / 16; i += T) ((v4i*)smem)[i] = (v4i){0, 0, 0, 0};
 
     // ---- this lane's column of the blocks' tiles
     const int n = tile * 16 + j, nc = min(n, S::NCOL - 1);
