@@ -7,7 +7,9 @@
 // Here a lane is a *column* of the image and walks down it: the fragments of an input row (three reads) serve the output
 // rows above, at and below it, so a row of 16 pixels costs three reads and five (16 channels) or nine (32 channels) MFMAs
 // per 16 output channels.  The three output rows in flight are three independent accumulator chains.  Measured at 1024
-// states: the three stacks 66 / 63 / 31 us (72 / 68 / 33 on another card) where the layer-by-layer kernels took 283 / 163 / 85 us.
+// states: the three stacks 66 / 63 / 31 us where the layer-by-layer kernels took 283 / 163 / 85 us; on another card 73-76 / 66-70 / 33-35 -> 69.6 /
+// 63.4 / 31.5 with the order of bs_order and the input's chunks from a table.  What bounds it now: LDS in the first stack's blocks (3 200 of
+// 4 000 clocks a phase), matrix cores in the others' (2 000 of 2 850), the pooling of all at 60-75 % of either.
 //
 //  * Lanes.  A workgroup of eight wavefronts owns G images.  The lanes of the blocks' tiles are (image, segment of rows,
 //    column) triples: 3 x 42, 3 x 21 and 2 x 2 x 11 of them fill 126 of 128, 63 of 64 and 44 of 48 lanes.  32-channel
@@ -16,16 +18,17 @@
 //  * LDS layout.  Planes of eight channels, [channel block][row][column][16 B]: the 16 lanes of a K group read 256
 //    consecutive bytes, and planes a multiple of 256 bytes apart keep the four groups of a read off each other's banks.
 //  * Convolution + pooling.  First stack: lanes are pooled pixels, the even and the odd column under each two sets of
-//    accumulators (74 -> 71 us against seven pooled pixels per tile, which took twice the vector instructions per pixel).
+//    accumulators (74 -> 71 us against seven pooled pixels per tile, which took twice the vector instructions per pixel); the odd
+//    window is put together from the lane's even one and its neighbour's (read as well it was half of the phase's LDS clocks).
 //    Others: lanes are convolution columns 14 t - 1 .. 14 t + 14 (seven pooled pixels).  The vertical
 //    maximum runs over the rows as they are produced (row 2 py + 1 is kept for the next pooled row), the horizontal one
 //    over the two neighbour lanes (DPP).  Rounding to bf16 is monotone, so it follows the maximum.
 //  * The stream is kept un-rectified (the skip connection needs it) and rectified as fragments are read: one packed
 //    16-bit integer maximum per dword, since a negative bf16 is a negative 16-bit integer (the NaN that the matrix cores
 //    produce, 0xffc0, is one too and becomes 0 as in fmaxf).
-//  * bf16 inputs go from memory to LDS without passing through registers, a third of the next batch at the start of each of
+//  * Inputs go from memory to LDS without passing through registers, a third of the next batch at the start of each of
 //    three phases: loads into registers held their wavefront for 6 000 clocks of 34 000 in a full memory queue and storing
-//    them took another 4 000 (second stack 80 -> 67 us, third 39 -> 32 us at 1024 states).
+//    them took another 4 000 (second stack 80 -> 67 us, third 39 -> 32 us at 1024 states; the first with its odd windows 72.4 -> 69.6).
 //
 // Arithmetic: the planner's weight fragments, the bias in the accumulator and the K steps of every output in the planner's
 // order, so results are bit-identical to the layer-by-layer kernels (conv_kernel.h), which the debug taps still run.  (The
@@ -73,7 +76,7 @@ struct BsShape {
     static constexpr int TILE_IN = U8 ? bs_up((HIN + 3) * IROW, 256) : CI / 8 * IPLANE;
     static constexpr int KS_C = U8 ? 2 : CI == 16 ? 5 : 9, KS_B = C == 16 ? 5 : 9;
     static constexpr int UNITS = HIN * HIN / 4;                // observations only
-    static constexpr int PF = U8 ? (UNITS + THREADS - 1) / THREADS : 1;
+    static constexpr int PF = (UNITS + THREADS - 1) / THREADS;
     static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI * 2;
     static constexpr int IMG = H * H * C * 2;
     // conv + pool items: column tiles of pooled pixels (14 of observations, else seven) x row segments x images
@@ -85,10 +88,10 @@ struct BsShape {
     // where lanes that own no pooled pixel store (a branch around the store would end the compiler's view at every row)
     static constexpr int O_DUMP = O_M + (G * TILE > TILE_IN || !OVER ? G * TILE : TILE_IN);
     static constexpr int O_TAB = O_DUMP + RP * ROWB + 512;
-    // bf16 inputs: an LDS array of their own, filled from memory without passing through registers (a load of 64 chunks each)
-    // and a table of where its chunks come from
-    static constexpr int NLOAD = OVER ? 0 : (G * TILE_IN / 16 + THREADS - 1) / THREADS, S_IN = OVER ? 16 : NLOAD * THREADS * 16;
-    static constexpr int LDS = O_TAB + NLOAD * THREADS * 4;    // dynamic; besides S_IN
+    // inputs: an LDS array of their own, filled from memory without passing through registers (a load of 64 chunks each): the observation's
+    // bytes as they are, or the planes and a table of where their chunks come from
+    static constexpr int NLOAD = ((U8 ? IMG_IN : G * TILE_IN) / 16 + THREADS - 1) / THREADS, S_IN = U8 ? bs_up(IMG_IN, 1024) : NLOAD * THREADS * 16;
+    static constexpr int LDS = O_TAB + (U8 ? 0 : NLOAD * THREADS * 4);    // dynamic; besides S_IN
     static_assert(PAST <= 1 && C % 16 == 0 && NCOL <= TW * 16 && (!U8 || (G == 1 && CI == 4)) && LDS + S_IN <= 160 * 1024, "shape");
 };
 
@@ -179,16 +182,6 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     constexpr int NH = S::NH;
 
     // ---- staging of observations: unit u is one dword of each of the four planes
-    v4i pre[S::PF];
-    auto prefetch = [&](int64_t batch) {
-        const char* src = (const char*)p.in + (ROWS ? (int64_t)p.rows[batch] : batch) * (int64_t)S::IMG_IN;
-#pragma unroll
-        for (int i = 0; i < S::PF; ++i) {
-            const int u = min(tid + i * T, S::UNITS - 1);    // a unit that does not exist re-reads the last one
-#pragma unroll
-            for (int c = 0; c < 4; ++c) pre[i][c] = *(const int*)(src + (uint32_t)(c * HIN * HIN + 4 * u));
-        }
-    };
     auto commit = [&]() {
 #pragma unroll
         for (int i = 0; i < S::PF; ++i) {
@@ -196,14 +189,17 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
             if (u >= S::UNITS) continue;
             constexpr int RU = HIN / 4;
             const int row = u / RU, cu = u - row * RU;
+            int v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = *(const int*)(s_in + c * HIN * HIN + 4 * u);
             typedef float v2f __attribute__((ext_vector_type(2)));
             typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
             const float k255 = 1.0f / 255.0f;            // bf16(v / 255) = bf16(v * (1 / 255)): checked for all 256 values
             char* d = tin + (row + 1) * S::IROW + (1 + 4 * cu) * 8;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const v2f lo = {(float)((pre[i][0] >> (8 * e)) & 0xff) * k255, (float)((pre[i][1] >> (8 * e)) & 0xff) * k255};
-                const v2f hi = {(float)((pre[i][2] >> (8 * e)) & 0xff) * k255, (float)((pre[i][3] >> (8 * e)) & 0xff) * k255};
+                const v2f lo = {(float)((v[0] >> (8 * e)) & 0xff) * k255, (float)((v[1] >> (8 * e)) & 0xff) * k255};
+                const v2f hi = {(float)((v[2] >> (8 * e)) & 0xff) * k255, (float)((v[3] >> (8 * e)) & 0xff) * k255};
                 *(v2i*)(d + 8 * e) = (v2i){__builtin_bit_cast(int, __builtin_convertvector(lo, v2bf)),
                                            __builtin_bit_cast(int, __builtin_convertvector(hi, v2bf))};
             }
@@ -214,18 +210,20 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
         }
         for (int i = tid; i < 2 * HIN; i += T) *(v2i*)(tin + (1 + (i >> 1)) * S::IROW + (i & 1) * (HIN + 1) * 8) = (v2i){0, 0};
     };
-    // ---- staging of bf16 inputs: memory to the planes of s_in directly.  Chunk i * T + tid of s_in comes from tab[i * T + tid] of the
-    //      batch; those of borders and padding, and of images past the batch, are out of the buffer's range: zeros.  (Worked out for every
-    //      load, a third of the loads cost their phase 1 100 clocks of 4 000.)
+    // ---- memory to s_in directly.  Observations: chunk by chunk (into registers, with their 16 loads in the last phase, they held it for
+    //      2 300 clocks of 5 900).  bf16: chunk i * T + tid of the planes comes from tab[i * T + tid] of the batch; those of borders and padding, and
+    //      of images past the batch, are out of the buffer's range: zeros.  (Worked out for every load, a third of the loads cost their
+    //      phase 1 100 clocks of 4 000.)
     int* tab = (int*)(smem + S::O_TAB);
     auto fetch = [&](int64_t batch, int i0, int i1) {
-        if constexpr (!U8) {
-            const int64_t b0 = batch * G;
-            const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + b0 * (int64_t)S::IMG_IN, 0, (int)min(p.B - b0, (int64_t)G) * S::IMG_IN, 0x00027000);
+        const int64_t b0 = batch * G;
+        const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + (ROWS ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN, 0,
+                                                           (int)min(p.B - b0, (int64_t)G) * S::IMG_IN, 0x00027000);
 #pragma unroll
-            for (int i = i0; i < i1; ++i)
-                if (i < S::NLOAD)
-                    bs_load_lds(src, s_in + (wave + i * S::NW) * 1024, tab[i * T + tid]);
+        for (int i = i0; i < i1; ++i) {
+            if (i >= S::NLOAD) continue;
+            if constexpr (!U8) bs_load_lds(src, s_in + (wave + i * S::NW) * 1024, tab[i * T + tid]);
+            else if ((i + 1) * T * 16 <= S::S_IN || (wave + i * S::NW) * 1024 < S::S_IN) bs_load_lds(src, s_in + (wave + i * S::NW) * 1024, (i * T + tid) * 16);
         }
     };
     if constexpr (!U8) {
@@ -243,8 +241,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     const int64_t n_batch = (p.B + G - 1) / G;
     int64_t batch = blockIdx.x;
     if (batch < n_batch) {
-        if constexpr (U8) prefetch(batch);
-        else fetch(batch, 0, S::NLOAD);
+        fetch(batch, 0, S::NLOAD);
     }
 
     // ---- weights of all five convolutions, in registers for the whole kernel
@@ -281,6 +278,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     const int offM = pos + (g & 1) * S::PLANE + (g < 2 ? 32 - S::ROWB : 0);       // 16 channels only
     const int own = pos + S::ROWB + 16 + (C == 16 ? (g >> 1) * S::PLANE + (g & 1) * 8 : g * S::PLANE + half * 8);
     const int past = S::PAST && seg == SEG - 1 ? S::ROWB : 0;
+    if constexpr (U8) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // (see the loop's end)
     __syncthreads();
 
     for (; batch < n_batch; batch += gridDim.x) {
@@ -299,21 +297,24 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
             };
             const v4f none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             if constexpr (U8) {
-                // Lanes are pooled pixels 14 ct - 1 .. 14 ct + 14 with the even and the odd column (E, O) as two sets of
-                // accumulators; the left neighbour's O completes the window, so the first lane only serves its neighbour.
-                // (Columns outside the image repeat one of the same window.)
-                const int px = 14 * ct - 1 + j, pc = min(max(px, 0), S::H - 1);
-                char* dst = dst_of(px, j >= 1 && j <= 14 && px < S::H);
+                // Lanes are pooled pixels 14 ct .. 14 ct + 15 with the even and the odd column (E, O) as two sets of accumulators; the
+                // left neighbour's O completes the window (the first pixel of all needs none), the right one's fragment is the second
+                // half of the odd column's: the first and the last lane only serve their neighbours.
+                const int px = 14 * ct + j, pc = min(px, S::H);
+                char* dst = dst_of(px, (ct == 0 || j >= 1) && j <= 14 && px < S::H);
                 // window rows y, y + 1 in the two halves of a fragment: F(y) is step 0 of conv row y and step 1 of row y - 2
                 const char* a = tin + (2 * p0 + (g >> 1)) * S::IROW + 2 * pc * 8 + (g & 1) * 16;
                 auto even = [&](int row) { return *(const v4i*)(a + row * S::IROW); };
-                auto odd = [&](int row) { return read_chunk<8>(a + row * S::IROW + 8); };
+                auto odd = [&](v4i e) {
+                    return (v4i){e[2], e[3], __builtin_amdgcn_update_dpp(e[2], e[0], 0x101, 0xf, 0xf, false), __builtin_amdgcn_update_dpp(e[3], e[1], 0x101, 0xf, 0xf, false)};
+                };
                 static_assert(S::IROW % 16 == 0 && HIN % 2 == 0, "whole chunks under even columns");
                 auto conv = [&](v4i lo, v4i hi) { return bs_mfma(wC[1], hi, bs_mfma(wC[0], lo, bias[0])); };
-                v4i e0 = even(0), e1 = even(1), o0 = odd(0), o1 = odd(1);
+                v4i e0 = even(0), e1 = even(1), o0 = odd(e0), o1 = odd(e1);
                 v4f carryE = none, carryO = none;
-                if (p0 > 0) { carryE = conv(even(-1), e1); carryO = conv(odd(-1), o1); }
-                v4i e2 = even(2), e3 = even(3), o2 = odd(2), o3 = odd(3);
+                if (p0 > 0) { carryE = conv(even(-1), e1); carryO = conv(odd(even(-1)), o1); }
+                v4i e2 = even(2), e3 = even(3), o2 = odd(e2), o3 = odd(e3);
+                v4i eN = even(4), fN = even(5);
                 v4f cE0 = conv(e0, e2), cO0 = conv(o0, o2), cE1 = conv(e1, e3), cO1 = conv(o1, o3);
 #pragma unroll
                 for (int k = 0; k < S::RP; ++k) {
@@ -326,8 +327,10 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                     carryE = cE1; carryO = cO1;
                     if (k + 1 < S::RP) {                  // the next row's products go between this one's maxima
                         e0 = e2; e1 = e3; o0 = o2; o1 = o3;
-                        e2 = even(2 * k + 4); e3 = even(2 * k + 5); o2 = odd(2 * k + 4); o3 = odd(2 * k + 5);
-                        cE0 = conv(e0, e2); cO0 = conv(o0, o2); cE1 = conv(e1, e3); cO1 = conv(o1, o3);
+                        e2 = eN; e3 = fN;
+                        if (k + 2 < S::RP) { eN = even(2 * k + 6); fN = even(2 * k + 7); }
+                        o2 = odd(e2); o3 = odd(e3);
+                        cE0 = conv(e0, e2); cE1 = conv(e1, e3); cO0 = conv(o0, o2); cO1 = conv(o1, o3);
                     }
                     v4f m;
 #pragma unroll
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
                         m[r] = bs_max3(mE[r], mO[r], __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x111, 0xf, 0xf, false)));
                     }
                     *(v2i*)(dst + k * S::ROWB) = bs_pack(m);
-                    if (k + 1 < S::RP) bs_order<4, 8, 3>();
+                    if (k + 1 < S::RP) bs_order<2, 8, 3>();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
@@ -493,10 +496,13 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
         if (next < n_batch) fetch(next, 2 * N3, S::NLOAD);
         conv_a(wA2, bias[3]);
         __syncthreads();
-        if constexpr (U8) { if (next < n_batch) prefetch(next); }
         conv_b(wB2, bias[4], std::true_type{});
-        // the observation tile takes the inner tensor's place; otherwise the barrier behind the next commit is enough
-        if constexpr (S::OVER) __syncthreads();
+        // the observation tile takes the inner tensor's place, and its bytes were fetched by all wavefronts; otherwise the barrier behind the
+        // next commit is enough
+        if constexpr (S::OVER) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
     }
 }
 
