@@ -126,6 +126,9 @@ hipError_t launch_conv_fused(const ConvParams& a, int NTA, const ConvParams& b, 
 // the same pair for exactly the paper's original network (84x84x4 -> 8x8/4 x32 -> 4x4/2 x64): sizes fixed at compile time
 bool conv_front_supported(const ConvParams& a, int NTA, const ConvParams& b);
 hipError_t launch_conv_front(const ConvParams& a, const ConvParams& b, hipStream_t s);
+// with the third layer behind them, for small calls (a.B is looked at)
+bool conv_front3_supported(const ConvParams& a, int NTA, const ConvParams& b, const ConvParams& c, int NTC);
+hipError_t launch_conv_front3(const ConvParams& a, const ConvParams& b, const ConvParams& c, hipStream_t s);
 // a residual block (ReLU - conv3x3 - ReLU - conv3x3 + skip) of the pruned IMPALA student in one kernel: a = first, b = second convolution
 bool resblock_supported(const ConvParams& a, int NTA, const ConvParams& b, int NTB);
 hipError_t launch_resblock(const ConvParams& a, const ConvParams& b, hipStream_t s);

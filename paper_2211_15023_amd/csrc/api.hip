@@ -1059,6 +1059,7 @@ int run(accerl_policy* p, const Call& c) {
         auto bufp = [&](int b) -> char* { return b < 0 ? const_cast<char*>(states) : p->ws + p->bufs[b].off; };
         bool pooled = false;   // the last conv step also did the max-pool that follows it
         bool conv_pair_done = false;   // the last conv step also did the conv that follows it
+        bool conv_third_done = false;  // and the one behind that
         bool packed = false;           // the last dense step also packed the LSTM's operand
         int stack_skip = 0;            // conv steps still to pass over: a stack kernel has done them
         hipEvent_t prof_prev = nullptr;
@@ -1115,6 +1116,7 @@ int run(accerl_policy* p, const Call& c) {
                         break;
                     }
                     if (s.fused_prev && conv_pair_done) { conv_pair_done = false; launched = false; break; }   // done by the step before
+                    if (conv_third_done) { conv_third_done = false; launched = false; break; }                 // and so is this one
                     if (s.fuse_next && !c.debug) {
                         const Step& nx = p->steps[si + 1];
                         ConvParams ca = s.cp, cb = nx.cp;
@@ -1125,9 +1127,21 @@ int run(accerl_policy* p, const Call& c) {
                         cb.in = nullptr; cb.out = bufp(nx.out_buf); cb.res = nullptr; cb.tap_acc = nullptr;
                         cb.wfrag = p->consts + nx.o_w; cb.bias = p->consts + nx.o_bias; cb.mult = nx.o_mult >= 0 ? (const float*)(p->consts + nx.o_mult) : nullptr;
                         cb.B = n;
+                        conv_pair_done = true;
+                        if (s.el == EL_I8 && !s.resblock && si + 2 <= last_step && p->steps[si + 2].kind == ST_CONV && p->steps[si + 2].in_buf == nx.out_buf &&
+                            p->steps[si + 2].res_buf < 0 && !p->steps[si + 2].fuse_next &&
+                            conv_front3_supported(ca, s.NT, cb, p->steps[si + 2].cp, p->steps[si + 2].NT)) {
+                            const Step& third = p->steps[si + 2];
+                            ConvParams cc = third.cp;
+                            cc.in = nullptr; cc.out = bufp(third.out_buf); cc.res = nullptr; cc.tap_acc = nullptr;
+                            cc.wfrag = p->consts + third.o_w; cc.bias = p->consts + third.o_bias; cc.mult = (const float*)(p->consts + third.o_mult);
+                            cc.B = n;
+                            e = launch_conv_front3(ca, cb, cc, c.stream);
+                            conv_third_done = true;
+                            break;
+                        }
                         e = s.resblock ? launch_resblock(ca, cb, c.stream)
                           : s.el == EL_BF16 ? launch_conv_front_bf16(ca, cb, c.stream) : launch_conv_fused(ca, s.NT, cb, c.stream);
-                        conv_pair_done = true;
                         break;
                     }
                     ConvParams cp = s.cp;

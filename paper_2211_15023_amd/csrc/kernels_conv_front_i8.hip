@@ -52,6 +52,9 @@ constexpr int FR_NPIX2 = 81, FR_PIX2_BYTES = 64;
 constexpr int FR_LDS = 2 * FR_TILE_A + 4 * FR_TILE_B;   // two observations; per observation two output tiles
 constexpr int FR_STAGERS = 256;                   // lanes that stage one observation (its four first-layer wavefronts)
 constexpr int FR_PF = (FR_UNITS + FR_STAGERS - 1) / FR_STAGERS;   // staging chunks per lane (7)
+// the third layer behind them: its input is planes of 16 channels, [channel block][pixel][16 B] (see kernels_conv_tail_i8.hip)
+constexpr int F3_PLANE = 1536, F3_TILE = 4 * F3_PLANE;
+constexpr int F3_LDS = FR_TILE_A + FR_TILE_B + F3_TILE;
 
 struct FrontParams {
     const uint8_t* obs;      // [B, 4, 84, 84]
@@ -61,6 +64,10 @@ struct FrontParams {
     const v4i* wB; const int* biasB; const float* multB;
     int64_t B;
     int per;                 // observations a workgroup takes at a time (1 or 2)
+    // THIRD: the layer behind them
+    int8_t* out3;            // [B, 7, 7, 64] or fragment order
+    const v4i* wC; const int* biasC; const float* multC;
+    int out_frag, frag_ks;
 };
 
 // 4x4 byte transpose of a 16-byte chunk
@@ -74,7 +81,11 @@ __device__ __forceinline__ v4i transpose4x4(v4i v) {
 
 // P23: both layers' accumulators stay below 2^23, so requantization takes the three-instruction form of requant_relu4_p23
 // ROWS: observations through the row list (as a test in the kernel it cost the others 1 us of 7.5 at 160 states)
-template <bool P23, bool ROWS>
+// THIRD: small calls, one observation per workgroup and no second tick: the wavefronts of the second slot compute the third layer from
+// what the second leaves in LDS.  Such a call is a chain of dependent steps, and this takes a launch and a round trip through memory
+// out of it (160 states: 6.2 + 4.1 us in two launches).  The weights of the third layer are requested when the observation has arrived: all
+// of them at once keep the observation waiting (twelve wavefronts on every layer, each with its own 25 KB of weights, took 9.5 us).
+template <bool P23, bool ROWS, bool THIRD>
 __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontParams p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     typedef int v2i __attribute__((ext_vector_type(2)));
@@ -82,7 +93,9 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
     // LDS: observation tile of slot 0, of slot 1, then the output tiles [slot][buffer]
-    char* tilesB = smem + 2 * FR_TILE_A;
+    char* tilesB = smem + (THIRD ? 1 : 2) * FR_TILE_A;
+    char* tileC = tilesB + FR_TILE_B;                    // THIRD only
+    constexpr int STAGERS = THIRD ? 512 : FR_STAGERS, PF = (FR_UNITS + STAGERS - 1) / STAGERS;
 
     // tick n of this workgroup: observations per * (blockIdx.x + n * gridDim.x) + {0, .., per - 1} ("pair" below, also where it is one)
     const int64_t stride = p.per * (int64_t)gridDim.x;
@@ -92,14 +105,14 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
 
     if (wave >= 4) {
         // ================= first-layer wavefronts of slot `slot` (they also stage its observations)
-        const int slot = (wave - 4) >> 2, aw = (wave - 4) & 3, stid = (tid - 256) & 255;
+        const int slot = THIRD ? 0 : (wave - 4) >> 2, aw = (wave - 4) & 3, stid = (tid - 256) & (STAGERS - 1);
         char* tileA = smem + slot * FR_TILE_A;
         char* tileB = tilesB + slot * (2 * FR_TILE_B);
         img += slot * second;                           // this group's observation of the current pair
         // staging: chunk u = dword u of the four planes
-        uint32_t pre[FR_PF][4];
+        uint32_t pre[PF][4];
         auto stage_load_part = [&](const uint8_t* src, int k) {
-            const int u = min(stid + k * FR_STAGERS, FR_UNITS - 1);
+            const int u = min(stid + k * STAGERS, FR_UNITS - 1);
 #pragma unroll
             for (int c = 0; c < 4; ++c) pre[k][c] = *(const uint32_t*)(src + c * FR_PLANE + 4 * u);
         };
@@ -110,12 +123,12 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
         auto stage_load = [&](int64_t im) {
             const uint8_t* src = obs_of(im);
 #pragma unroll
-            for (int k = 0; k < FR_PF; ++k) stage_load_part(src, k);
+            for (int k = 0; k < PF; ++k) stage_load_part(src, k);
         };
         auto stage_commit = [&]() {
 #pragma unroll
-            for (int k = 0; k < FR_PF; ++k) {
-                const int u = stid + k * FR_STAGERS;
+            for (int k = 0; k < PF; ++k) {
+                const int u = stid + k * STAGERS;
                 if (u < FR_UNITS)
                     *(v4i*)(tileA + 16 * u) = (v4i){(int)(pre[k][0] ^ 0x80808080u), (int)(pre[k][1] ^ 0x80808080u),
                                                     (int)(pre[k][2] ^ 0x80808080u), (int)(pre[k][3] ^ 0x80808080u)};
@@ -123,6 +136,50 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
         };
         const bool have0 = img < p.B;
         if (have0) stage_load(img);
+        if constexpr (THIRD) {
+            if (wave >= 8) {
+                // ============= third-layer wavefronts: half of the filters of two pixel tiles each
+                stage_commit();
+                __syncthreads();                         // observation tile complete
+                const int h = wave & 1, u0 = (wave - 8) & 2;
+                v4i w[9][2];
+#pragma unroll
+                for (int st = 0; st < 9; ++st)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) w[st][t] = p.wC[(st * 4 + 2 * h + t) * 64 + lane];
+                v4i bi[2], acc[2][2];
+                v4f ml[2];
+                const char* a[2];
+                int8_t* o[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    bi[t] = *(const v4i*)(p.biasC + 16 * g + 8 * h + 4 * t) + (P23 ? P23_MAGIC : 0);
+                    ml[t] = *(const v4f*)(p.multC + 16 * g + 8 * h + 4 * t);
+                }
+                int8_t* out = p.out_frag ? p.out3 + (img >> 4) * ((int64_t)p.frag_ks << 10) + (((int)img & 15) << 4) : p.out3 + img * (int64_t)(49 * 64);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {            // tile: two output rows, the last one rows 5 and 6; spare lanes repeat a pixel
+                    const int jj = min(j, 13), r = jj >= 7 ? 1 : 0, ox = jj - 7 * r, oy = (u0 + u < 3 ? 2 * (u0 + u) : 5) + r, px = oy * 7 + ox;
+                    a[u] = tileC + g * F3_PLANE + (oy * 9 + ox) * 16;
+                    o[u] = out + (p.out_frag ? px * 1024 + g * 256 : px * 64 + 16 * g) + 8 * h;
+                }
+                __syncthreads();                         // first layer's tile complete
+                __syncthreads();                         // second layer's tile complete
+#pragma unroll
+                for (int st = 0; st < 9; ++st)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const v4i f = *(const v4i*)(a[u] + ((st / 3) * 9 + st % 3) * 16);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) acc[u][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[st][t], f, st == 0 ? bi[t] : acc[u][t], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    *(v2i*)o[u] = (v2i){(int)requant_relu4_p23<P23>(acc[u][0], ml[0], ml[0] * -8388608.0f),
+                                        (int)requant_relu4_p23<P23>(acc[u][1], ml[1], ml[1] * -8388608.0f)};
+                return;
+            }
+        }
         v4i wA[4][2];
 #pragma unroll
         for (int st = 0; st < 4; ++st)
@@ -185,7 +242,7 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
             for (int r = 0; r < 6; ++r) {
                 v4i accN[2], fn[4];
                 mfma_a(f, accN);
-                stage_load_part(next, r);
+                if constexpr (!THIRD) stage_load_part(next, r);
                 // fragments of tile r+1: a chain tile inherits steps 0 and 1 from steps 2 and 3 of the tile above
                 if (r + 1 < 5) {
                     fn[0] = f[2]; fn[1] = f[3];
@@ -209,12 +266,12 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
                         __builtin_amdgcn_sched_group_barrier(0x002, P23 ? 6 : 8, 0);
                     }
                     __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
+                    if constexpr (!THIRD) __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             static_assert(FR_PF == 7, "six tiles carry one staging part each, the seventh follows");
-            stage_load_part(next, 6);
+            if constexpr (!THIRD) stage_load_part(next, 6);
             if (aw == 0) {                              // the fifth 4 x 4 tile
                 v4i accN[2];
                 mfma_a(f, accN);
@@ -233,6 +290,12 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
 
         if (have0) stage_commit();
         __syncthreads();                                 // observation tiles complete
+        if constexpr (THIRD) {
+            conv_a(tileB, nullptr);
+            __syncthreads();                             // first layer's tile complete
+            __syncthreads();                             // second layer's
+            return;
+        }
         const bool more = img + stride < p.B;
         if (have0) conv_a(tileB, obs_of(img + stride));  // the second pair's observation is in flight meanwhile
         __syncthreads();                                 // first output tiles complete, observation tiles free
@@ -266,7 +329,8 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
             const int oy = (px * 7282) >> 16, ox = px - oy * 9;       // px / 9 for px < 81
             rb[u] = oy * (2 * FR_ROW_B) + ox * 32 + (g >> 1) * FR_PLANE_B + (g & 1) * 16;
         }
-        const int oofs = (p0 + j) * FR_PIX2_BYTES + 16 * g + 8 * h;   // tile u adds 16 pixels
+        constexpr int PIX = THIRD ? 16 : FR_PIX2_BYTES;
+        const int oofs = (p0 + j) * PIX + (THIRD ? F3_PLANE : 16) * g + 8 * h;   // tile u adds 16 pixels
 
         // Three pixel tiles, one after the other: 16 MFMAs (8 K steps x 2 channel tiles) each, with the
         // requantization of the tile before interleaved.  Pixel fragments rotate through eight slots: the
@@ -278,11 +342,11 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
             const int u = q >> 3, st = q & 7;
             return *(const v4i*)(srcB + rb[u] + (st >> 1) * FR_ROW_B + (st & 1) * 32);
         };
-        auto store_b = [&](int8_t* outp, int u, const v4i (&acc)[2]) {
+        auto store_b = [&](auto* outp, int u, const v4i (&acc)[2]) {
             const uint32_t w0 = requant_relu4_p23<P23>(acc[0], m0, c0), w1 = requant_relu4_p23<P23>(acc[1], m1, c1);
-            *(v2i*)(outp + oofs + u * (16 * FR_PIX2_BYTES)) = (v2i){(int)w0, (int)w1};
+            *(v2i*)(outp + oofs + u * (16 * PIX)) = (v2i){(int)w0, (int)w1};
         };
-        auto conv_b = [&](const char* srcB, int8_t* outp) {
+        auto conv_b = [&](const char* srcB, auto* outp) {
             v4i gq[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) gq[q] = frag_b(srcB, q);
@@ -306,7 +370,7 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
                         if (u * 8 + k + 8 < 24) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                         __builtin_amdgcn_sched_group_barrier(0x002, P23 ? 3 : 4, 0);
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x040, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(THIRD ? 0x200 : 0x040, 1, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -314,6 +378,11 @@ __global__ __launch_bounds__(FR_THREADS, 3) void conv_front_kernel(const FrontPa
         };
         __syncthreads();
         __syncthreads();
+        if constexpr (THIRD) {
+            conv_b(tilesB, tileC);
+            __syncthreads();                             // second layer's tile complete
+            return;
+        }
         __syncthreads();
         for (int n = 0;; ++n, img += stride) {
             conv_b(tilesB + (n & 1) * FR_TILE_B, p.out + img * (int64_t)(FR_NPIX2 * FR_PIX2_BYTES));
@@ -341,10 +410,10 @@ template <bool P23, bool ROWS>
 static hipError_t front_go(const FrontParams& q, hipStream_t s) {
     static int occ = 0;
     if (!occ) {
-        hipError_t e = hipFuncSetAttribute((const void*)conv_front_kernel<P23, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, FR_LDS);
+        hipError_t e = hipFuncSetAttribute((const void*)conv_front_kernel<P23, ROWS, false>, hipFuncAttributeMaxDynamicSharedMemorySize, FR_LDS);
         if (e != hipSuccess) return e;
         int o = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, (const void*)conv_front_kernel<P23, ROWS>, FR_THREADS, FR_LDS);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, (const void*)conv_front_kernel<P23, ROWS, false>, FR_THREADS, FR_LDS);
         if (e != hipSuccess) return e;
         occ = o < 1 ? 1 : o;
     }
@@ -357,20 +426,49 @@ static hipError_t front_go(const FrontParams& q, hipStream_t s) {
     const int64_t pairs = (p.B + p.per - 1) / p.per;
     const int64_t rounds = (pairs + cap - 1) / cap;
     dim3 grid((unsigned)((pairs + rounds - 1) / rounds));
-    conv_front_kernel<P23, ROWS><<<grid, dim3(FR_THREADS), FR_LDS, s>>>(p);
+    conv_front_kernel<P23, ROWS, false><<<grid, dim3(FR_THREADS), FR_LDS, s>>>(p);
     return hipGetLastError();
 }
 
-hipError_t launch_conv_front(const ConvParams& a, const ConvParams& b, hipStream_t s) {
-    if (a.B <= 0) return hipSuccess;
-    FrontParams p;
+static FrontParams front_params(const ConvParams& a, const ConvParams& b) {
+    FrontParams p{};
     p.obs = (const uint8_t*)a.in; p.rows = a.rows; p.out = (int8_t*)b.out;
     p.wA = (const v4i*)a.wfrag; p.biasA = (const int*)a.bias; p.multA = a.mult;
     p.wB = (const v4i*)b.wfrag; p.biasB = (const int*)b.bias; p.multB = b.mult;
     p.B = a.B;
+    return p;
+}
+
+hipError_t launch_conv_front(const ConvParams& a, const ConvParams& b, hipStream_t s) {
+    if (a.B <= 0) return hipSuccess;
+    const FrontParams p = front_params(a, b);
     static const bool no_p23 = getenv("ACCERL_NO_P23") != nullptr;
     if (a.pos23 && b.pos23 && !no_p23) return p.rows ? front_go<true, true>(p, s) : front_go<true, false>(p, s);
     return p.rows ? front_go<false, true>(p, s) : front_go<false, false>(p, s);
+}
+
+// The third layer behind them in the same launch: for calls that leave every observation a compute unit of its own.
+bool conv_front3_supported(const ConvParams& a, int NTA, const ConvParams& b, const ConvParams& c, int NTC) {
+    static const bool off = getenv("ACCERL_NO_CONV_FRONT") || getenv("ACCERL_NO_CONV_TAIL");
+    return !off && a.B <= conv_num_cus() && conv_front_supported(a, NTA, b) && conv_tail_supported(c, NTC);
+}
+
+template <bool P23, bool ROWS>
+static hipError_t front3_go(const FrontParams& p, hipStream_t s) {
+    static_assert(F3_LDS <= 64 * 1024, "needs no attribute");
+    conv_front_kernel<P23, ROWS, true><<<dim3((unsigned)p.B), dim3(FR_THREADS), F3_LDS, s>>>(p);
+    return hipGetLastError();
+}
+
+hipError_t launch_conv_front3(const ConvParams& a, const ConvParams& b, const ConvParams& c, hipStream_t s) {
+    if (a.B <= 0) return hipSuccess;
+    FrontParams p = front_params(a, b);
+    p.per = 1;
+    p.out3 = (int8_t*)c.out; p.wC = (const v4i*)c.wfrag; p.biasC = (const int*)c.bias; p.multC = c.mult;
+    p.out_frag = c.out_frag; p.frag_ks = c.frag_ks;
+    static const bool no_p23 = getenv("ACCERL_NO_P23") != nullptr;
+    if (a.pos23 && b.pos23 && c.pos23 && !no_p23) return p.rows ? front3_go<true, true>(p, s) : front3_go<true, false>(p, s);
+    return p.rows ? front3_go<false, true>(p, s) : front3_go<false, false>(p, s);
 }
 
 }  // namespace accerl
