@@ -336,8 +336,11 @@ bool ksplit_small_i8(const GemmParams& p) {
     return !p.x_frag && p.n_tiles <= 16 && groups(p, 1, 2) > most_groups() && 2 * groups(p, 4, 4) < conv_num_cus();
 }
 
-// The smallest tile that gives at most about one workgroup per compute unit.  Measured on 3136 -> 512 (fragment order; us, tile
-// of states x features): bf16, 160 states 16x32 6.5, 16x16 7.2, 32x32 7.3; 500 states 32x32 7.8, 16x64 8.4, 32x64 9.8; 1000
+// The smallest tile that gives at most one workgroup per compute unit.  (An eighth more were let through once; the units with a second one
+// hold up the call.  us, with them / next tile: 3136 -> 512 bf16 140 states 7.7 / 7.0, 270 9.0 / 8.1, 525 11.4 / 10.1, 1100 16.1 / 12.8, 2200 24.4 /
+// 19.8; 3872 -> 256 bf16 272 8.9 / 7.8, 540 12.2 / 10.2, 1100 18.1 / 15.7, 2200 25.0 / 21.8; 1296 -> 128 bf16 560 5.4 / 4.4; int8 3136 -> 512
+// 140 5.4 / 5.1, 270 6.3 / 6.1, 540 7.9 / 7.5, 1100 10.6 / 9.5; 1936 -> 256 272 4.3 / 4.1, 540 5.7 / 5.4, 2200 10.8 / 10.2.)  Measured on
+// 3136 -> 512 (fragment order; us, tile of states x features): bf16, 160 states 16x32 6.5, 16x16 7.2, 32x32 7.3; 500 states 32x32 7.8, 16x64 8.4, 32x64 9.8; 1000
 // states 32x64 9.8, 32x32 11.4, 64x64 12.4; 2048 states 64x64 12.9, 32x64 16.1.  int8, 64
 // states 16x16 4.0, 16x32 4.3; 160 states 16x32 4.3, 16x16 4.5; 512 states 32x32 5.7, 16x64 6.2, 16x32 6.6; 1000 states 32x64 7.2,
 // 32x32 8.4; 2048 states 64x64 9.2, 32x64 10.8.  bf16 beyond one 64x64 workgroup per unit: 128x64, half the fetches of the weights (3136 -> 512
@@ -345,7 +348,7 @@ bool ksplit_small_i8(const GemmParams& p) {
 // whole forwards with row-major states, 3872 -> 256 at 5000 706 / 695, 6500 898 / 889, 8192 1107 / 1101).
 template <int EL, int EPI>
 hipError_t pick(const GemmParams& p, hipStream_t s) {
-    const int64_t most = most_groups();
+    const int64_t most = conv_num_cus();
     if (groups(p, 1, 1) <= most) return go<EL, EPI, 1, 1>(p, s);
     if (groups(p, 1, 2) <= most) return go<EL, EPI, 1, 2>(p, s);
     if constexpr (EL == EL_I8) {
