@@ -780,8 +780,12 @@ constexpr int conv_pt(int NT) { return NT == 4 ? 4 : 2; }
 // Tuned shared-batch variants: (element, NT, KS, RD, staging mode, PF).  KS > 0 keeps the weights in
 // registers and unrolls that many MFMA steps; KS = 0 reads them from LDS for any number of steps.
 // Last entry: 1 = residual join and fused pooling compiled in.
+// First layers of the paper's two-convolution networks (8x8/4 of 84x84x4 to 16, 8 or 4 filters, the latter pixel-packed: 4, 6, 10 steps; bf16 8, 12)
+// against the generic kernel, us: 8 filters int8 160 states 9.9 -> 7.4, 1000 16.7 -> 12.2, 8192 72 -> 54.6, through a row list (475 of 1000) 12.5 ->
+// 9.1; bf16 160 11.1 -> 7.7, 1000 23.8 -> 17.1, 8192 129 -> 98.7, the second layer (4 steps) 6.2 -> 4.9, 8.3 -> 5.8, 22.5 -> 19.0.
 #define ACCERL_TUNED_I8(X)                                                                                   \
-    X(EL_I8, 2, 4, 16, CM_U8T, 8, 0) X(EL_I8, 1, 4, 16, CM_U8T, 8, 0) X(EL_I8, 4, 0, 16, CM_FLAT, 8, 0)     \
+    X(EL_I8, 2, 4, 16, CM_U8T, 8, 0) X(EL_I8, 1, 4, 16, CM_U8T, 8, 0) X(EL_I8, 1, 6, 16, CM_U8T, 8, 0)     \
+    X(EL_I8, 1, 10, 16, CM_U8T, 8, 0) X(EL_I8, 4, 0, 16, CM_FLAT, 8, 0)                                      \
     X(EL_I8, 4, 0, 16, CM_FLAT, 10, 0) X(EL_I8, 2, 4, 16, CM_FLAT, 8, 0) X(EL_I8, 1, 2, 16, CM_FLAT, 8, 0)  \
     X(EL_I8, 1, 1, 8, CM_FLAT, 8, 0) X(EL_I8, 1, 1, 4, CM_U8T, 8, 1) X(EL_I8, 1, 1, 8, CM_U8T, 8, 1)        \
     X(EL_I8, 1, 1, 8, CM_U8T, 4, 1) X(EL_I8, 1, 2, 8, CM_ROWSV, 8, 1) X(EL_I8, 1, 2, 8, CM_ROWSV, 4, 1)     \
@@ -790,7 +794,8 @@ constexpr int conv_pt(int NT) { return NT == 4 ? 4 : 2; }
 #define ACCERL_TUNED_BF16(X)                                                                                 \
     X(EL_BF16, 2, 8, 16, CM_U8T, 8, 0) X(EL_BF16, 1, 2, 8, CM_U8T, 8, 1) X(EL_BF16, 1, 5, 16, CM_ROWSV, 16, 1) \
     X(EL_BF16, 2, 5, 16, CM_ROWSV, 16, 1) X(EL_BF16, 2, 9, 16, CM_ROWSV, 16, 1) X(EL_BF16, 2, 9, 16, CM_ROWSV, 8, 1) \
-    X(EL_BF16, 4, 0, 16, CM_FLAT, 8, 0)
+    X(EL_BF16, 4, 0, 16, CM_FLAT, 8, 0) X(EL_BF16, 1, 8, 16, CM_U8T, 4, 0) X(EL_BF16, 1, 12, 16, CM_U8T, 4, 0)  \
+    X(EL_BF16, 1, 4, 16, CM_FLAT, 10, 0)
 
 // Wave-private variants (8 wavefronts, weights in LDS, contiguous staging): (element, NT, RD, PF, PT)
 constexpr int CONV_WP_WAVES = 8;
