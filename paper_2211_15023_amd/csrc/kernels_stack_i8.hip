@@ -180,6 +180,77 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
 
+    // ---- staging: unit u of the batch is one dword of each of the four planes, or 16 bytes of the images
+    v4i pre[S::PF];
+    int doff[S::PF];
+#pragma unroll
+    for (int i = 0; i < S::PF; ++i) {
+        const int u = min(tid + i * T, G * S::UNITS_IN - 1);
+        const int img = u / S::UNITS_IN, w = u - img * S::UNITS_IN, row = w / S::UPR_IN, cu = w - row * S::UPR_IN;
+        doff[i] = img * S::TILE_IN + (row + 1) * S::PITCH_IN + CI + cu * 16;
+    }
+    const int64_t n_batch = (p.B + G - 1) / G;
+    auto prefetch = [&](int64_t batch) {
+        const int64_t b0 = batch * G;
+        const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
+        // (buffer loads: the plane is their scalar offset, and a unit that does not exist is out of the buffer's range and reads 0)
+        const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN, 0,
+                                                           gc * S::IMG_IN, 0x00027000);
+#pragma unroll
+        for (int i = 0; i < S::PF; ++i) {
+            if constexpr (U8) {
+                v4i v;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = (int)__builtin_amdgcn_raw_buffer_load_b32(src, 4 * (tid + i * T), c * HIN * HIN, 0);
+                pre[i] = v;
+            } else {
+                pre[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(src, 16 * (tid + i * T), 0, 0));
+            }
+        }
+    };
+    auto commit = [&](int64_t batch) {
+        const int64_t b0 = batch * G;
+        const int total = (G == 1 || p.B - b0 >= G ? G : (int)(p.B - b0)) * S::UNITS_IN;
+#pragma unroll
+        for (int i = 0; i < S::PF; ++i) {
+            if (tid + i * T >= total) break;
+            const v4i v = pre[i];
+            if constexpr (U8) {
+                // one dword (4 pixels) of each plane -> four channels-last pixels, stored as obs - 128
+                const uint32_t P0 = (uint32_t)v[0], P1 = (uint32_t)v[1], P2 = (uint32_t)v[2], P3 = (uint32_t)v[3];
+                const uint32_t lo01 = __builtin_amdgcn_perm(P1, P0, 0x05010400u), hi01 = __builtin_amdgcn_perm(P1, P0, 0x07030602u);
+                const uint32_t lo23 = __builtin_amdgcn_perm(P3, P2, 0x05010400u), hi23 = __builtin_amdgcn_perm(P3, P2, 0x07030602u);
+                uint32_t* d = (uint32_t*)(tin + doff[i]);
+                d[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
+                d[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
+                d[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
+                d[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u) ^ 0x80808080u;
+            } else if constexpr ((CI & 15) == 0) {
+                *(v4i*)(tin + doff[i]) = v;
+            } else {
+                *(v2i*)(tin + doff[i]) = (v2i){v[0], v[1]};
+                *(v2i*)(tin + doff[i] + 8) = (v2i){v[2], v[3]};
+            }
+        }
+    };
+
+    int64_t batch = blockIdx.x;
+    // before the weights, so that a small call waits for both at once, and the borders meanwhile (third stack 8 states 9.6 -> 8.4 us, 1024 11.1 -> 10.1,
+    // 4096 28.9 -> 26.6; first 160 states 11.8 -> 10.9)
+    if (batch < n_batch) prefetch(batch);
+
+    // ---- once per workgroup: borders (only interiors are written later), constants
+    {
+        const int padv = U8 ? (int)0x80808080u : 0;       // a padding pixel is the observation value 0
+        for (int i = tid; i < S::O_TX / 16; i += T) ((v4i*)tin)[i] = (v4i){padv, padv, padv, padv};
+        for (int i = tid; i < (S::O_W - S::O_TX) / 16; i += T) ((v4i*)tX)[i] = (v4i){0, 0, 0, 0};
+        for (int i = tid; i < 5 * 16; i += T) {
+            const int cv = i >> 4, n = i & 15;
+            cst[cv * 32 + n] = p.bias[cv][n];
+            ((float*)cst)[cv * 32 + 16 + n] = p.mult[cv][n];
+        }
+    }
+
     // ---- weights: those of the stack convolution and of the block convolutions WL .. 3 stay in registers, the others go to LDS
     v4i wP[S::NWP], wR[S::WL < 4 ? 4 - S::WL : 1][S::NWB];
     {
@@ -238,78 +309,10 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             if constexpr (cv >= S::WL) w[e] = wR[cv - S::WL][e];
             else w[e] = *(const v4i*)(smem + woff + cv * S::WB + e * (S::WB / S::NWB));
     };
-    // the weights are in their registers before any other load is issued: the waits the compiler places in the batch
-    // loop then only ever concern the loads of the next batch, not these
+    // the weights are in their registers before the loop: the waits the compiler places there then only ever concern the
+    // loads of the next batch, not these
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
 
-    // ---- staging: unit u of the batch is one dword of each of the four planes, or 16 bytes of the images
-    v4i pre[S::PF];
-    int doff[S::PF];
-#pragma unroll
-    for (int i = 0; i < S::PF; ++i) {
-        const int u = min(tid + i * T, G * S::UNITS_IN - 1);
-        const int img = u / S::UNITS_IN, w = u - img * S::UNITS_IN, row = w / S::UPR_IN, cu = w - row * S::UPR_IN;
-        doff[i] = img * S::TILE_IN + (row + 1) * S::PITCH_IN + CI + cu * 16;
-    }
-    const int64_t n_batch = (p.B + G - 1) / G;
-    auto prefetch = [&](int64_t batch) {
-        const int64_t b0 = batch * G;
-        const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
-        // (buffer loads: the plane is their scalar offset, and a unit that does not exist is out of the buffer's range and reads 0)
-        const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN, 0,
-                                                           gc * S::IMG_IN, 0x00027000);
-#pragma unroll
-        for (int i = 0; i < S::PF; ++i) {
-            if constexpr (U8) {
-                v4i v;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = (int)__builtin_amdgcn_raw_buffer_load_b32(src, 4 * (tid + i * T), c * HIN * HIN, 0);
-                pre[i] = v;
-            } else {
-                pre[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(src, 16 * (tid + i * T), 0, 0));
-            }
-        }
-    };
-    auto commit = [&](int64_t batch) {
-        const int64_t b0 = batch * G;
-        const int total = (G == 1 || p.B - b0 >= G ? G : (int)(p.B - b0)) * S::UNITS_IN;
-#pragma unroll
-        for (int i = 0; i < S::PF; ++i) {
-            if (tid + i * T >= total) break;
-            const v4i v = pre[i];
-            if constexpr (U8) {
-                // one dword (4 pixels) of each plane -> four channels-last pixels, stored as obs - 128
-                const uint32_t P0 = (uint32_t)v[0], P1 = (uint32_t)v[1], P2 = (uint32_t)v[2], P3 = (uint32_t)v[3];
-                const uint32_t lo01 = __builtin_amdgcn_perm(P1, P0, 0x05010400u), hi01 = __builtin_amdgcn_perm(P1, P0, 0x07030602u);
-                const uint32_t lo23 = __builtin_amdgcn_perm(P3, P2, 0x05010400u), hi23 = __builtin_amdgcn_perm(P3, P2, 0x07030602u);
-                uint32_t* d = (uint32_t*)(tin + doff[i]);
-                d[0] = __builtin_amdgcn_perm(lo23, lo01, 0x05040100u) ^ 0x80808080u;
-                d[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u) ^ 0x80808080u;
-                d[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u) ^ 0x80808080u;
-                d[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u) ^ 0x80808080u;
-            } else if constexpr ((CI & 15) == 0) {
-                *(v4i*)(tin + doff[i]) = v;
-            } else {
-                *(v2i*)(tin + doff[i]) = (v2i){v[0], v[1]};
-                *(v2i*)(tin + doff[i] + 8) = (v2i){v[2], v[3]};
-            }
-        }
-    };
-
-    int64_t batch = blockIdx.x;
-    if (batch < n_batch) prefetch(batch);
-
-    // ---- once per workgroup: borders (only interiors are written later), constants
-    {
-        const int padv = U8 ? (int)0x80808080u : 0;       // a padding pixel is the observation value 0
-        for (int i = tid; i < S::O_TX / 4; i += T) ((int*)tin)[i] = padv;
-        for (int i = tid; i < (S::O_W - S::O_TX) / 4; i += T) ((int*)tX)[i] = 0;
-        for (int i = tid; i < 5 * 16; i += T) {
-            const int cv = i >> 4, n = i & 15;
-            cst[cv * 32 + n] = p.bias[cv][n];
-            ((float*)cst)[cv * 32 + 16 + n] = p.mult[cv][n];
-        }
-    }
 
     // ---- this lane's column of the blocks; lanes past the last column repeat it (the same bytes written twice)
     const int n = wave * 16 + j, nc = min(n, S::NCOL - 1);
