@@ -82,6 +82,8 @@ struct StShape {
     static constexpr int UNITS_IN = HIN * UPR_IN;
     static constexpr int IMG_IN = U8 ? 4 * HIN * HIN : HIN * HIN * CI;
     static constexpr int PF = (G * UNITS_IN + THREADS - 1) / THREADS;
+    // the observation's unit that lane tid stages i-th; one that does not exist re-reads the last (three of a lane's four always exist)
+    static constexpr int unit(int tid, int i) { return (i + 1) * THREADS <= UNITS_IN || tid + i * THREADS < UNITS_IN ? tid + i * THREADS : UNITS_IN - 1; }
     static constexpr int CPR_C = ((3 + P - 1) * CI + 15) / 16;  // 16-byte chunks per kernel row of the planner's fragments
     static constexpr int KS_C = (3 * CPR_C + 3) / 4;
     // pooled stream
@@ -120,6 +122,15 @@ struct StShape {
     static_assert(LDS <= 160 * 1024 && WL <= 4 && SEG * R == H && (HIN % 2 == 0 || PSEG == 1), "LDS, rows");
     static_assert(NCOL > NW * 16 - 16, "every wavefront owns a column");
 };
+// The loads of an observation's planes have the plane as their scalar offset, which a buffer's range check may leave out: a lane's offset
+// stays inside a plane by itself.
+template <class S>
+constexpr bool st_units_in_plane(int plane) {
+    for (int i = 0; i < S::PF; ++i)
+        for (int tid = 0; tid < S::THREADS; ++tid)
+            if (4 * S::unit(tid, i) + 4 > plane) return false;
+    return true;
+}
 
 // v[r] = max(v[r], v[r] of the lane to its left in the same 16-lane row); lane 0 of a row keeps its value: a DPP lane without
 // a source is not written and keeps the destination's old value.  (The two idle cycles a DPP read needs after the vector
@@ -193,7 +204,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     auto prefetch = [&](int64_t batch) {
         const int64_t b0 = batch * G;
         const int gc = (int)((p.B - b0 < G) ? (p.B - b0) : G);
-        // (buffer loads: the plane is their scalar offset, and a unit that does not exist is out of the buffer's range and reads 0)
+        // (buffer loads: an observation's plane is their scalar offset; of int8 images, a unit that does not exist is out of the buffer's
+        // range and reads 0)
+        static_assert(!U8 || st_units_in_plane<S>(HIN * HIN), "no lane reads past a plane");
         const auto src = __builtin_amdgcn_make_buffer_rsrc((char*)p.in + (U8 && p.rows ? (int64_t)p.rows[b0] : b0) * (int64_t)S::IMG_IN, 0,
                                                            gc * S::IMG_IN, 0x00027000);
 #pragma unroll
@@ -201,7 +214,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
             if constexpr (U8) {
                 v4i v;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = (int)__builtin_amdgcn_raw_buffer_load_b32(src, 4 * (tid + i * T), c * HIN * HIN, 0);
+                for (int c = 0; c < 4; ++c) v[c] = (int)__builtin_amdgcn_raw_buffer_load_b32(src, 4 * S::unit(tid, i), c * HIN * HIN, 0);
                 pre[i] = v;
             } else {
                 pre[i] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(src, 16 * (tid + i * T), 0, 0));
