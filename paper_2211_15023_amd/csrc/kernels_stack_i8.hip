@@ -384,7 +384,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
                 // walks down runs of them: an item's windows are two fragments, and the lower conv row of the row above is the
                 // last product of the item before.  Runs that cross into the next strip do so at few places of the unrolled walk.
                 constexpr int NS = (S::H - 1 + 14) / 15, RPS = S::H / 2, N_IT = RPS * NS, PER = (N_IT + NW - 1) / NW;
-                static_assert((NW - 1) * PER < N_IT && PER <= RPS && N_IT > NW * PER - PER, "runs");
+                static_assert(N_IT >= NW * PER - 1 && PER <= RPS, "runs: only the last one may be short, by its last item");
                 constexpr auto crosses = [](int i) {
                     for (int w = 0; w < NW; ++w) if (i > 0 && (w * PER + i) % RPS == 0) return true;
                     return false;
