@@ -5,6 +5,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -14,23 +16,24 @@ using namespace accerl;
 
 namespace {
 
-thread_local std::string g_err;
+thread_local char g_err[512];            // (allocates nothing: it also says that an allocation failed)
 
 int fail(int code, const char* fmt, ...) {
-    char buf[512];
     va_list ap;
     va_start(ap, fmt);
-    vsnprintf(buf, sizeof buf, fmt, ap);
+    vsnprintf(g_err, sizeof g_err, fmt, ap);
     va_end(ap);
-    g_err = buf;
     return code;
 }
+
+// No exception leaves the C ABI: its callers are C, or call without the interpreter's lock.
+int host_fail(const std::exception& e) { return fail(ACCERL_ENOMEM, "on the host: %s", e.what()); }
 
 }  // namespace
 
 // error reporting for the other translation units of the C ABI
 int accerl::set_error(int code, const char* msg) {
-    g_err = msg;
+    snprintf(g_err, sizeof g_err, "%s", msg);
     return code;
 }
 
@@ -1280,13 +1283,15 @@ int check_common(accerl_policy* p, const void* states, int64_t B, bool need_outp
 
 extern "C" {
 
-int accerl_blob_sizes(const accerl_arch* arch, int64_t* weights_bytes, int64_t* n_scales) {
+int accerl_blob_sizes(const accerl_arch* arch, int64_t* weights_bytes, int64_t* n_scales) try {
     Parsed P;
     int rc = parse_arch(arch, P);
     if (rc) return rc;
     if (weights_bytes) *weights_bytes = P.weights_bytes;
     if (n_scales) *n_scales = P.n_scales;
     return ACCERL_OK;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 // Host half of policy creation: parse, check, build the plan and the host image of the constants.
@@ -1478,14 +1483,13 @@ static int create_host(const accerl_arch* arch, const void* weights, int64_t wei
 }
 
 int accerl_policy_create(const accerl_arch* arch, const void* weights, int64_t weights_bytes,
-                         const float* quant_scales, int64_t n_scales, accerl_policy** out) {
+                         const float* quant_scales, int64_t n_scales, accerl_policy** out) try {
     if (!out) return fail(ACCERL_EINVAL, "out is NULL");
     *out = nullptr;
-    accerl_policy* pol = new (std::nothrow) accerl_policy();
-    if (!pol) return fail(ACCERL_ENOMEM, "host allocation failed");
+    auto pol = std::make_unique<accerl_policy>();
     std::vector<char> cst;
-    int rc = create_host(arch, weights, weights_bytes, quant_scales, n_scales, pol, cst);
-    if (rc) { delete pol; return rc; }
+    int rc = create_host(arch, weights, weights_bytes, quant_scales, n_scales, pol.get(), cst);
+    if (rc) return rc;
     hipError_t e = hipGetDevice(&pol->device);
     if (e == hipSuccess) e = hipMalloc((void**)&pol->consts, cst.size() + 256);
     if (e == hipSuccess) e = hipMemcpy(pol->consts, cst.data(), cst.size(), hipMemcpyHostToDevice);
@@ -1493,15 +1497,16 @@ int accerl_policy_create(const accerl_arch* arch, const void* weights, int64_t w
         rc = fail(e == hipErrorOutOfMemory ? ACCERL_ENOMEM : ACCERL_EHIP, "uploading constants: %s", hipGetErrorString(e));
         (void)hipGetLastError();
         if (pol->consts) (void)hipFree(pol->consts);
-        delete pol;
         return rc;
     }
-    *out = pol;
+    *out = pol.release();
     return ACCERL_OK;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t weights_bytes,
-                         const float* quant_scales, int64_t n_scales, char* text, int64_t cap) {
+                         const float* quant_scales, int64_t n_scales, char* text, int64_t cap) try {
     if (!text || cap < 1) return fail(ACCERL_EINVAL, "text buffer is NULL or empty");
     accerl_policy pol;
     std::vector<char> cst;
@@ -1537,6 +1542,8 @@ int accerl_plan_describe(const accerl_arch* arch, const void* weights, int64_t w
     }
     snprintf(text, (size_t)cap, "%s", out.c_str());
     return ACCERL_OK;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 void accerl_policy_destroy(accerl_policy* p) {
@@ -1554,7 +1561,7 @@ void accerl_policy_destroy(accerl_policy* p) {
 }
 
 static int forward_impl(accerl_policy* p, bool want_student, const void* states, int64_t B, const float* uniforms,
-                        float* out_logits, float* out_value, int32_t* out_action, void* stream) {
+                        float* out_logits, float* out_value, int32_t* out_action, void* stream) try {
     int rc = check_common(p, states, B, true, uniforms, out_logits, out_value, out_action);
     if (rc) return rc;
     if (want_student != (p->arch.precision == ACCERL_INT8))
@@ -1562,6 +1569,8 @@ static int forward_impl(accerl_policy* p, bool want_student, const void* states,
     if (p->recurrent) return fail(ACCERL_EINVAL, "recurrent policy: use accerl_actor_forward_recurrent");
     Call c{states, B, uniforms, nullptr, nullptr, nullptr, out_logits, out_value, out_action, (hipStream_t)stream};
     return run(p, c);
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 int accerl_actor_forward(accerl_policy* p, const void* states, int64_t B, const float* uniforms,
@@ -1582,7 +1591,7 @@ double accerl_mixture_alpha(double kl_mean, double kl_lo, double kl_hi) {
 
 int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original, const void* states, int64_t B,
                                  const float* uniforms, const uint8_t* use_smaller,
-                                 float* out_logits, float* out_value, int32_t* out_action, void* stream) {
+                                 float* out_logits, float* out_value, int32_t* out_action, void* stream) try {
     int rc = check_common(smaller, states, B, true, uniforms, out_logits, out_value, out_action);
     if (rc) return rc;
     rc = check_common(original, states, B, true, uniforms, out_logits, out_value, out_action);
@@ -1666,11 +1675,13 @@ int accerl_actor_forward_mixture(accerl_policy* smaller, accerl_policy* original
     if (rc) return rc;
     if (!direct) HIP_TRY(launch_scatter_mix(d_logits, d_value, d_action, d_idx, B, ns, o2, A, out_logits, out_value, out_action, st));
     return ACCERL_OK;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 int accerl_actor_forward_recurrent(accerl_policy* p, const void* states, int64_t B, const float* uniforms,
                                    const uint8_t* done, float* h, float* c,
-                                   float* out_logits, float* out_value, int32_t* out_action, void* stream) {
+                                   float* out_logits, float* out_value, int32_t* out_action, void* stream) try {
     int rc = check_common(p, states, B, true, uniforms, out_logits, out_value, out_action);
     if (rc) return rc;
     if (!p->recurrent) return fail(ACCERL_EINVAL, "policy has no lstm layer");
@@ -1679,10 +1690,12 @@ int accerl_actor_forward_recurrent(accerl_policy* p, const void* states, int64_t
     if (((uintptr_t)h | (uintptr_t)c) & 15) return fail(ACCERL_EINVAL, "h or c is not 16-byte aligned");
     Call cl{states, B, uniforms, done, h, c, out_logits, out_value, out_action, (hipStream_t)stream};
     return run(p, cl);
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 int accerl_actor_forward_debug(accerl_policy* p, const void* states, int64_t B, int32_t layer, int32_t tap,
-                               void* out, int64_t out_bytes, void* stream) {
+                               void* out, int64_t out_bytes, void* stream) try {
     int rc = check_common(p, states, B, false, nullptr, nullptr, nullptr, nullptr);
     if (rc) return rc;
     if (B == 0) return ACCERL_OK;
@@ -1695,9 +1708,11 @@ int accerl_actor_forward_debug(accerl_policy* p, const void* states, int64_t B, 
     Call c{states, B, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream};
     c.debug = true; c.layer = layer; c.tap = tap; c.out = out; c.out_bytes = out_bytes;
     return run(p, c);
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
-int accerl_profile_begin(accerl_policy* p) {
+int accerl_profile_begin(accerl_policy* p) try {
     if (!p) return fail(ACCERL_EINVAL, "policy is NULL");
     for (auto& ev : p->events) (void)hipEventDestroy(ev.b);
     for (auto& ev : p->ev_starts) (void)hipEventDestroy(ev);
@@ -1705,10 +1720,12 @@ int accerl_profile_begin(accerl_policy* p) {
     p->ev_starts.clear();
     p->profiling = true;
     return ACCERL_OK;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
 int accerl_profile_end(accerl_policy* p, int32_t cap, int32_t* n_steps, float* total_ms, int64_t* launches,
-                       int32_t* layer, int32_t* kind) {
+                       int32_t* layer, int32_t* kind) try {
     if (!p || !n_steps) return fail(ACCERL_EINVAL, "policy or n_steps is NULL");
     p->profiling = false;
     const int n = (int)p->steps.size();
@@ -1731,8 +1748,10 @@ int accerl_profile_end(accerl_policy* p, int32_t cap, int32_t* n_steps, float* t
     p->events.clear();
     p->ev_starts.clear();
     return rc;
+} catch (const std::exception& e) {
+    return host_fail(e);
 }
 
-const char* accerl_last_error(void) { return g_err.c_str(); }
+const char* accerl_last_error(void) { return g_err; }
 
 }  // extern "C"
