@@ -46,19 +46,25 @@ def build(verbose=False):
     return SO
 
 
-def _build_args(verbose):
-    """The CPython module that takes torch tensors to pointers: host code, against torch's headers and libaccerl.so beside it."""
+def compile_module(src, out, extra=()):
+    """A CPython module on torch's headers and libaccerl.so: host code, by the host's compiler.  Returns what the compiler said."""
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
     rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
-    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE,
+    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE, *extra,
                         *(a for d in (f"{torch}/include", f"{torch}/include/torch/csrc/api/include", f"{rocm}/include",
                                       sysconfig.get_path("include")) for a in ("-isystem", d)),
-                        os.path.join(CSRC, "arguments.cpp"), "-o", ARGS_SO, "-L", HERE, "-l:libaccerl.so", "-L", f"{torch}/lib",
+                        src, "-o", out, "-L", HERE, "-l:libaccerl.so", "-L", f"{torch}/lib",
                         "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"], capture_output=True, text=True)
     if r.returncode:
-        raise RuntimeError("arguments.cpp failed:\n" + r.stderr)
-    if verbose and r.stderr.strip():
-        print(r.stderr)
+        raise RuntimeError(f"{os.path.basename(src)} failed:\n" + r.stderr)
+    return r.stderr
+
+
+def _build_args(verbose):
+    """The module that takes torch tensors to pointers."""
+    said = compile_module(os.path.join(CSRC, "arguments.cpp"), ARGS_SO)
+    if verbose and said.strip():
+        print(said)
 
 
 if __name__ == "__main__":

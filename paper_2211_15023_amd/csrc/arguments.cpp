@@ -83,10 +83,12 @@ PyObject* call(PyObject* const* argv, Py_ssize_t given, Py_ssize_t count, Parse&
         auto made = parse(a);
         if (PyErr_Occurred()) { PyErr_Clear(); a.plain = false; }
         if (!a.plain) Py_RETURN_NONE;
-        int rc;
+        int rc = 0;
+        bool threw = false;                      // (said only when the lock is held again, and never taken for arguments that are not plain)
         Py_BEGIN_ALLOW_THREADS
-        rc = made();
+        try { rc = made(); } catch (...) { threw = true; }
         Py_END_ALLOW_THREADS
+        if (threw) { PyErr_SetString(PyExc_RuntimeError, "the library threw an exception"); return nullptr; }
         return PyLong_FromLong(rc);
     } catch (const std::exception&) {            // a tensor without storage, for one: the general way says it
         PyErr_Clear();

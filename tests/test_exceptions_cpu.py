@@ -1,4 +1,5 @@
-"""C++ exceptions stay inside: an entry of the C ABI returns a status where the host's memory runs out."""
+"""C++ exceptions stay inside: an entry of the C ABI returns a status where the host's memory runs out, and the compiled marshalling
+takes an exception of the call it made neither for arguments that are not plain nor into the interpreter without its lock."""
 import os
 import subprocess
 import sys
@@ -26,6 +27,20 @@ for i in range(2):
 print("refused")
 """
 
+# the marshalling's own call(), around a call that throws
+THROWING = r"""
+#include <new>
+#include "arguments.cpp"
+static int calls = 0;
+static PyObject* throwing(PyObject*, PyObject* const* argv, Py_ssize_t n) {
+    return call(argv, n, 0, [](Args&) { return []() -> int { ++calls; throw std::bad_alloc(); }; });
+}
+static PyObject* count(PyObject*, PyObject*) { return PyLong_FromLong(calls); }
+static PyMethodDef table[] = {{"throwing", FAST(throwing)}, {"count", count, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+static PyModuleDef def = {PyModuleDef_HEAD_INIT, "throwing", nullptr, -1, table, nullptr, nullptr, nullptr, nullptr};
+PyMODINIT_FUNC PyInit_throwing() { return PyModule_Create(&def); }
+"""
+
 
 def _run(code):
     return subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=110)
@@ -34,3 +49,18 @@ def _run(code):
 def test_host_memory_running_out_is_a_status():
     r = _run(NO_MEMORY.format(root=ROOT))
     assert r.returncode == 0 and "refused" in r.stdout, (r.returncode, r.stderr[-2000:])
+
+
+def test_marshalling_survives_a_call_that_throws(tmp_path):
+    from paper_2211_15023_amd import build
+    src = tmp_path / "throwing.cpp"
+    src.write_text(THROWING)
+    build.compile_module(str(src), str(tmp_path / "throwing.so"), ["-I", build.CSRC])
+    r = _run(f"import sys; sys.path[:0] = [{ROOT!r}, {str(tmp_path)!r}]\n"
+             "import paper_2211_15023_amd as A; A.load_library()\n"
+             "import throwing\n"
+             "try: throwing.throwing()\n"
+             "except RuntimeError as e: assert 'exception' in str(e)\n"
+             "else: raise SystemExit('no error')\n"
+             "assert throwing.count() == 1; print('said')")
+    assert r.returncode == 0 and "said" in r.stdout, (r.returncode, r.stderr[-2000:])
