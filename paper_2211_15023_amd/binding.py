@@ -6,9 +6,10 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SO = os.path.join(_HERE, "libaccerl.so")
+_BUILD = "run `python -c 'import __graft_entry__ as g; g.build()'` (or paper_2211_15023_amd/build.py)"
 _lib = None
 torch = None            # set by load_library
-_args = None            # accerl_args, set by load_library
+_args = None            # accerl_args, set by _loaded
 
 INT8, FP32, BF16 = 0, 1, 2
 OBS_U8, OBS_F32 = 0, 1
@@ -35,14 +36,13 @@ class _Arch(C.Structure):
 
 def load_library():
     """Load libaccerl.so (after torch, so that both share one HIP runtime).  No fallback exists."""
-    global _lib, torch, _args
+    global _lib, torch
     if _lib is not None:
         return _lib
     import torch as _torch  # brings in the HIP runtime the library links against
     torch = _torch
     if not os.path.exists(_SO):
-        raise ImportError(f"{_SO} is missing: run `python -c 'import __graft_entry__ as g; g.build()'` "
-                          "(or paper_2211_15023_amd/build.py); there is no CPU fallback")
+        raise ImportError(f"{_SO} is missing: {_BUILD}; there is no CPU fallback")
     lib = C.CDLL(_SO)
     vp, i64, i32 = C.c_void_p, C.c_int64, C.c_int32
     lib.accerl_blob_sizes.argtypes = [C.POINTER(_Arch), C.POINTER(i64), C.POINTER(i64)]
@@ -81,15 +81,20 @@ def load_library():
               "accerl_actor_forward_recurrent", "accerl_actor_forward_debug", "accerl_profile_begin",
               "accerl_profile_end"):
         getattr(lib, f).restype = C.c_int
-    from . import accerl_args                # links against torch and the library loaded above
-    accerl_args.init(C.c_void_p)
-    _args = accerl_args
     _lib = lib
     return lib
 
 
 def _loaded():
-    load_library()
+    """accerl_args, for the calls made every step; host-only calls do without it."""
+    global _args
+    load_library()                           # accerl_args links against torch and the library
+    try:
+        from . import accerl_args
+    except ImportError as e:
+        raise ImportError(f"accerl_args.so is missing or of another torch or Python ({e}): {_BUILD}") from e
+    accerl_args.init(C.c_void_p)
+    _args = accerl_args
     return _args
 
 

@@ -14,6 +14,7 @@ ARGS_SO = os.path.join(HERE, "accerl_args.so")
 OBJ = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-command-line-argument", "-I", INCLUDE, "-I", CSRC]
@@ -50,7 +51,7 @@ def compile_module(src, out, extra=()):
     """A CPython module on torch's headers and libaccerl.so: host code, by the host's compiler.  Returns what the compiler said."""
     torch = os.path.dirname(importlib.util.find_spec("torch").origin)
     rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
-    r = subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE, *extra,
+    r = subprocess.run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE, *extra,
                         *(a for d in (f"{torch}/include", f"{torch}/include/torch/csrc/api/include", f"{rocm}/include",
                                       sysconfig.get_path("include")) for a in ("-isystem", d)),
                         src, "-o", out, "-L", HERE, "-l:libaccerl.so", "-L", f"{torch}/lib",

@@ -55,6 +55,7 @@ def test_marshalling_survives_a_call_that_throws(tmp_path):
     from paper_2211_15023_amd import build
     src = tmp_path / "throwing.cpp"
     src.write_text(THROWING)
+    os.symlink(build.SO, tmp_path / "libaccerl.so")
     build.compile_module(str(src), str(tmp_path / "throwing.so"), ["-I", build.CSRC])
     r = _run(f"import sys; sys.path[:0] = [{ROOT!r}, {str(tmp_path)!r}]\n"
              "import paper_2211_15023_amd as A; A.load_library()\n"
