@@ -82,6 +82,10 @@ def load_library():
               "accerl_profile_end"):
         getattr(lib, f).restype = C.c_int
     _lib = lib
+    try:
+        _loaded()                            # here and not in the first step's call, which says it if there is none
+    except ImportError:
+        pass
     return lib
 
 
