@@ -330,10 +330,11 @@ int64_t groups(const GemmParams& p, int rt, int nt) { return ((p.B + 16 * rt - 1
 // Row-major int8 layers of at most 256 features between the batches that 16 x 32 tiles cover with one workgroup per compute
 // unit and those with one 64 x 64 workgroup per two.  us, this kernel / the tile that the rule below would take (rocprofv3):
 // 1936 -> 256, ReLU on the input: 600 states 4.9 / 6.0, 1000 5.1 / 5.6, 1500 7.0 / 7.6, 1800 7.0 / 8.0; 1296 -> 128: 1800 states
-// 4.8 / 5.3, 3000 5.7 / 6.2, 3500 5.8 / 6.4.  Smaller batches: 1936 -> 256 at 256 states 4.6 / 4.6, 512 4.6 / 4.2.  Wide layers:
+// 4.8 / 5.3, 3000 5.7 / 6.2, 3500 5.8 / 6.4; just beyond the 16 x 32 tiles, 1936 -> 256 at 513 5.0 / 5.4, 576 5.0 / 5.4, 1296 -> 128 at 1025 4.5 /
+// 4.8, 1152 4.4 / 4.9, 3600 -> 240 at 576 6.7 / 7.2.  Smaller batches: 1936 -> 256 at 256 states 4.6 / 4.6, 512 4.6 / 4.2.  Wide layers:
 // 1936 -> 2048 at 160 states 8.6 / 6.9.
 bool ksplit_small_i8(const GemmParams& p) {
-    return !p.x_frag && p.n_tiles <= 16 && groups(p, 1, 2) > most_groups() && 2 * groups(p, 4, 4) < conv_num_cus();
+    return !p.x_frag && p.n_tiles <= 16 && groups(p, 1, 2) > conv_num_cus() && 2 * groups(p, 4, 4) < conv_num_cus();
 }
 
 // The smallest tile that gives at most one workgroup per compute unit.  (An eighth more were let through once; the units with a second one

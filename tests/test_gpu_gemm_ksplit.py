@@ -1,6 +1,6 @@
 """The dense kernels whose wavefronts split K, at every tile they can take: the batch picks the tile (layers of about 512
 features: 1, 100 states 16x16; 160 16x32; 500 32x32; 900 32x64; 2000 64x64; bf16 at 2400 128x64 or, with fewer than 64 steps, the
-kernel that walks K in one wavefront; int8 layers of at most 256 features: 16x64 from 577 or, of 128, from 1153 states on), the
+kernel that walks K in one wavefront; int8 layers of at most 256 features: 16x64 from 513 or, of 128, from 1025 states on), the
 layer's rows end inside a 16-byte chunk or inside an MFMA step, with and without a ReLU on the input, with a
 partly filled last feature tile.  int8: the oracle's bits.  bf16: the oracle's tolerance, and a state's result does not depend on the tile or the kernel (the split of K and the order of its sums are fixed)."""
 import numpy as np
