@@ -376,7 +376,10 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 // 4 MB of an XCD's second-level cache, the streaming kernel is already the faster one when 32 x 64 tiles no longer fit (3136 ->
 // 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
 // bf16 layers beyond one 64 x 64 workgroup per compute unit (128 x 64 tiles) stay here while the eighth of K that a wavefront walks is at
-// least eight steps (1296 -> 128 at 10000 20.5 / 16.5) and the rounds of workgroups are full enough.  States in fragment order: one round, or
+// least eight steps (1296 -> 128 at 10000 20.5 / 16.5), five and a half up to an eighth more than one workgroup (900 -> 512, 28 steps of K, at 2049
+// states 14.1 / 12.0, 2304 13.6 / 12.3; 1296 -> 128, 41, at 8193 16.6 / 14.8, 9216 17.9 / 15.2; 1452 -> 256, 46, at 4097 19.0 / 20.8, 4608 18.4 / 19.7;
+// 1568 -> 256, 49, 16.9 / 21.2, 16.8 / 21.0; 1800 -> 256, 57, 21.7 / 23.7, 21.2 / 23.0; 1936 -> 256, 61, 21.8 / 25.3, 21.0 / 24.1), and the rounds of
+// workgroups are full enough.  States in fragment order: one round, or
 // weights of at most 8 MB (us, this / gemm_kernel: 3136 -> 512 at 3000 states 18.1 / 28.3, 4096 18.7 / 27.1, 4500, two rounds, 33.9 / 42.5, 6000
 // 35.2 / 38.9, 12000 52.6 / 77.0; 2304 -> 512 at 4500 27.8 / 31.7, 6000 28.9 / 28.3; 3136 -> 1024 at 2100 34.5 / 34.6, 4096 36.0 / 42.7), or 85 %
 // of the rounds (3136 -> 2048 at 1050, 56 %, 37.9 / 35.3, 3300, 81 %, 79.1 / 71.5, 2600 60.7 / 82.0, 4096 69.2 / 80.1).  Row-major states:
@@ -387,9 +390,9 @@ bool gemm_ksplit_supported(const GemmParams& p, Elem el, GemmEpi epi) {
     const int64_t cus = conv_num_cus();
     if (el == EL_BF16) {
         if (epi != EPI_BF16) return false;
-        if (groups(p, 4, 4) <= most_groups()) return true;
+        if (groups(p, 4, 4) <= cus) return true;
         const int64_t g = groups(p, 8, 4), rounds = (g + cus - 1) / cus;
-        if (p.k_steps < 8 * KSPLIT_PARTS) return false;
+        if (2 * p.k_steps < (groups(p, 4, 4) <= most_groups() ? 11 : 16) * KSPLIT_PARTS) return false;
         if (rounds == 1) return true;
         if (!p.x_frag) return rounds <= 4 && 10 * g >= 9 * rounds * cus;
         return (int64_t)p.n_tiles * p.k_steps * 1024 <= 8 << 20 || 20 * g >= 17 * rounds * cus;

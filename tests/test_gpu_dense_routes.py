@@ -35,6 +35,11 @@ ROUTES = [
     ("int8", lambda: _row_major(16, 11, 256), [(_full(16, 8), "ksplit_kernel<0, 0, 1, 2,"), (_full(16, 8) + 1, "ksplit_small_i8_kernel"),
                                                (_full(16, 8) + 64, "ksplit_small_i8_kernel")]),
     ("int8", lambda: wl.configs.PAPER_STUDENTS["net2"], [(_full(16, 4), "ksplit_kernel<0, 0, 1, 2,"), (_full(16, 4) + 1, "ksplit_small_i8_kernel")]),
+    # bf16 beyond one 64 x 64 tile per compute unit: 41 steps of K go to the kernel that walks K in one wavefront, 61 stay (128 x 64 tiles) up
+    # to an eighth more
+    ("bf16", lambda: wl.configs.PAPER_STUDENTS["net2"], [(_full(64, 2), "ksplit_kernel<1, 2, 4, 4,"), (_full(64, 2) + 1, "gemm_kernel<1, 2, 8>")]),
+    ("bf16", lambda: _row_major(16, 11, 256), [(_full(64, 4), "ksplit_kernel<1, 2, 4, 4,"), (_full(64, 4) + 1, "ksplit_kernel<1, 2, 8, 4,"),
+                                               (_full(72, 4), "ksplit_kernel<1, 2, 8, 4,"), (_full(72, 4) + 1, "gemm_kernel<1, 2, 8>")]),
 ]
 
 
