@@ -7,8 +7,8 @@
 // however many loads its wavefronts keep open, so the tile is the smallest that still gives every unit one workgroup: more units
 // pull, and none of them twice; beyond that the largest, whose operands are fetched least often.  The kernel this replaces walked K alone in each 64 x 64 workgroup
 // (64 workgroups on 256 units for 1024 states of a 3872 -> 256 layer): 41 -> 10.2 us there; 3136 -> 512 at 500 states
-// 28 -> 8 us (526 states, where sixteen units get a second workgroup, 14.6), at 4096 states 33 -> 28 us, 25 with two 64 x 64 tiles per
-// unit, 20 with one of 128 x 64 (13 of it the fetches, 3 the partial sums in LDS).
+// 28 -> 8 us, at 4096 states 33 -> 28 us, 25 with two 64 x 64 tiles per unit, 18.7 with one of 128 x 64 (13 of it the fetches, 3 the partial
+// sums in LDS).
 #include <type_traits>
 
 #include "gemm_epilogue.h"
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64 * KS_W) void gemm_ksplit_kernel(const GemmParams
     lstm.store();
 }
 
-// about one workgroup per compute unit
+// An eighth more than one workgroup per compute unit: where the three rules below that name it end (pick's tiles end at one).
 int64_t most_groups() { return conv_num_cus() * 9 / 8; }
 
 // Whether gemm_tile orders by XCD.  In the grid's own order the workgroups of one group of states meet on an XCD only if the groups are a
@@ -239,6 +239,8 @@ int64_t most_groups() { return conv_num_cus() * 9 / 8; }
 // states 20.2 / 22.9, whole forwards 35.0 / 37.0, at 2048 24.6 / 25.9; -> 24 at 3000, 188 groups, 23.7 / 26.3) -- except beyond one round,
 // where a group's first and last features no longer run together, as long as the weights then stay in the 4 MB of an XCD's second-level
 // cache (3600 -> 500 at 16384 states 186 / 173, 2304 -> 512 124 / 116; 3600 -> 2048 at 4096 161 / 169, -> 1500 126 / 130).
+// An eighth more workgroups than units is not beyond one round yet: 16 x 64 tiles of the small kernel run two to a unit (whole int8 forwards, grid / XCD:
+// 1296 -> 128 at 2176, 272 workgroups, 29.5 / 30.0, 1936 -> 256 at 1152, 288, 15.5 / 16.3; 128 x 64 tiles 124.9 / 123.8, 3136 -> 576 at 4096, 288).
 // All states of one group of features before the next, whose weights are then fetched once: no faster than the grid's order at the
 // small batches where weights are the larger part, 160 states 16.6 -> 17.1.
 bool by_xcd(const GemmParams& p, dim3 grid) {
@@ -373,8 +375,9 @@ hipError_t pick(const GemmParams& p, hipStream_t s) {
 // int8 layers only up to one 64 x 64 workgroup per compute unit: beyond that the kernels that share the weights through LDS are
 // faster (us, this / theirs: 3136 -> 2048 at 575 states, 288 workgroups, 21.4 / 18.2; 1936 -> 2048 there 19.3 / 16.3; at 256
 // workgroups 3136 -> 512 9.2 / 9.6, 1936 -> 256 10.4 / 14.1, 1296 -> 128 at 8192 states 9.1 / 9.5).  Where the weights exceed the
-// 4 MB of an XCD's second-level cache, the streaming kernel is already the faster one when 32 x 64 tiles no longer fit (3136 ->
-// 2048: 300 states 11.2 / 11.0, 400 13.7 / 12.9, 500 13.6 / 13.2; 160 states, 32 x 64 tiles, 8.0 / 10.4).
+// 4 MB of an XCD's second-level cache, the streaming kernel is as fast from an eighth more 32 x 64 tiles than compute units on (3136 -> 2048:
+// 160 states, 32 x 64 tiles, 8.0 / 10.4; 257, 64 x 64 tiles from here on, 9.9 / 10.3, 288 10.0 / 10.2, 300 10.9 / 10.6, 400 12.5 / 12.2, 500 13.6 /
+// 13.2; -> 1536: 321 9.7 / 9.9, 384 9.9 / 10.1; -> 1344: 385 9.9 / 10.6, 416 9.9 / 11.3).
 // bf16 layers beyond one 64 x 64 workgroup per compute unit (128 x 64 tiles) stay here while the eighth of K that a wavefront walks is at
 // least eight steps (1296 -> 128 at 10000 20.5 / 16.5), five and a half up to an eighth more than one workgroup (900 -> 512, 28 steps of K, at 2049
 // states 14.1 / 12.0, 2304 13.6 / 12.3; 1296 -> 128, 41, at 8193 16.6 / 14.8, 9216 17.9 / 15.2; 1452 -> 256, 46, at 4097 19.0 / 20.8, 4608 18.4 / 19.7;

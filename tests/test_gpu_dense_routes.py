@@ -35,6 +35,9 @@ ROUTES = [
     ("int8", lambda: _row_major(16, 11, 256), [(_full(16, 8), "ksplit_kernel<0, 0, 1, 2,"), (_full(16, 8) + 1, "ksplit_small_i8_kernel"),
                                                (_full(16, 8) + 64, "ksplit_small_i8_kernel")]),
     ("int8", lambda: wl.configs.PAPER_STUDENTS["net2"], [(_full(16, 4), "ksplit_kernel<0, 0, 1, 2,"), (_full(16, 4) + 1, "ksplit_small_i8_kernel")]),
+    # int8 with more than 4 MB of weights: 64 x 64 tiles beyond one 32 x 64 tile per compute unit, the streaming kernel beyond an eighth more
+    ("int8", lambda: wl.nature_cnn("wide", fc=2048), [(_full(32, 32), "ksplit_kernel<0, 0, 2, 4,"), (_full(32, 32) + 1, "ksplit_kernel<0, 0, 4, 4,"),
+                                                      (_full(36, 32), "ksplit_kernel<0, 0, 4, 4,"), (_full(36, 32) + 1, "gemm_stream_i8_kernel")]),
     # bf16 beyond one 64 x 64 tile per compute unit: 41 steps of K go to the kernel that walks K in one wavefront, 61 stay (128 x 64 tiles) up
     # to an eighth more
     ("bf16", lambda: wl.configs.PAPER_STUDENTS["net2"], [(_full(64, 2), "ksplit_kernel<1, 2, 4, 4,"), (_full(64, 2) + 1, "gemm_kernel<1, 2, 8>")]),
