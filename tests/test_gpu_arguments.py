@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import workloads as wl
-from helpers import make_states, teacher_tensors
+from helpers import make_states, policies, student_tensors, teacher_tensors
 
 pytestmark = pytest.mark.gpu
 
@@ -84,3 +84,95 @@ def test_corrector_either_way():
         with pytest.raises(ValueError):
             A.accerl_vtrace(*k.values(), 1.0, 1.0, *outs)
     A.accerl_vtrace(o, s, act, r, d, v, boot, 1.0, 1.0, outs[0], None, outs[2])    # advantages are optional
+
+
+def _tables(T, B, acts):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    o, s = (torch.randn(T, B, acts, device="cuda", generator=g) for _ in range(2))
+    act = torch.randint(0, acts, (T, B), dtype=torch.int32, device="cuda", generator=g)
+    r, d, v = (torch.rand(T, B, device="cuda", generator=g) for _ in range(3))
+    return o, s, act, r, d, v, torch.rand(B, device="cuda", generator=g)
+
+
+def test_compiled_way_takes_plain_arguments_and_leaves_the_others():
+    """The status of the compiled functions themselves: 0 where the call was made there, None where it was left to Python."""
+    A, net, pol, x, u = _policy()
+    out = pol.alloc_outputs(40)
+    args = A.binding._loaded()
+    plain = [pol.handle, x, u, *out, None]
+
+    def with_(base, i, value):
+        return [*base[:i], value, *base[i + 1:]]
+    assert args.forward_teacher(*plain) == 0
+    assert args.forward_teacher(*with_(plain, 6, torch.cuda.current_stream().cuda_stream)) == 0
+    for i, value in ((0, pol), (1, x.as_subclass(Sub)), (1, torch.nn.Parameter(x)), (1, x.cpu()), (1, x.t()), (1, None), (2, u.double()), (5, out[2].long()),
+                     (6, torch.cuda.current_stream())):
+        assert args.forward_teacher(*with_(plain, i, value)) is None, i
+    with torch.overrides.BaseTorchFunctionMode():
+        assert args.forward_teacher(*plain) is None
+    assert args.forward_teacher(*with_(plain, 4, None)) < 0         # the library's own refusal
+    assert args.forward(*plain) < 0                                # an fp32 policy
+
+    o, s, act, r, d, v, boot = _tables(7, 33, 5)
+    two = [t.view(7 * 33, 5) for t in (o, s)]
+    kl, ent, st = torch.empty(7 * 33, device="cuda"), torch.empty(7 * 33, device="cuda"), torch.empty(4, dtype=torch.float64, device="cuda")
+    for f in (args.monitor_kl, args.monitor_kl_noalloc):
+        assert f(*two, kl, ent, st, None) == 0
+        for bad in ((two[0], two[1][:-1], kl, ent, st), (o, s, kl, ent, st), (two[0].double(), two[1], kl, ent, st), (*two, kl, ent, st.float()),
+                    (*two, kl.as_subclass(Sub), ent, st)):
+            assert f(*bad, None) is None
+    outs = [torch.empty(7, 33, device="cuda") for _ in range(3)]
+    base = [o, s, act, r, d, v, boot, 1.0, 1.0, *outs, None]
+    assert args.vtrace(*base) == 0
+    for i, value in ((2, act.float()), (2, act[:-1]), (3, r.t()), (7, 1), (9, outs[0].as_subclass(Sub))):
+        assert args.vtrace(*with_(base, i, value)) is None, i
+    torch.cuda.synchronize()
+
+
+def test_noalloc_either_way():
+    import paper_2211_15023_amd as A
+    o, s = (t.view(7 * 33, 5) for t in _tables(7, 33, 5)[:2])
+
+    def run(wrap):
+        kl, ent, st = torch.empty(7 * 33, device="cuda"), torch.empty(7 * 33, device="cuda"), torch.empty(4, dtype=torch.float64, device="cuda")
+        A.accerl_monitor_kl_noalloc(wrap(o), s, kl, ent, st)
+        return kl, ent, st
+    for a, b in zip(run(lambda t: t), run(lambda t: t.as_subclass(Sub))):
+        assert torch.equal(a, b)
+    kl, st = torch.empty(7 * 33, device="cuda"), torch.empty(4, dtype=torch.float64, device="cuda")
+    for bad in ((o, s[:-1]), (o.double(), s), (o.t(), s.t()), (o.cpu(), s)):
+        with pytest.raises(ValueError):
+            A.accerl_monitor_kl_noalloc(*bad, kl, kl, st)
+
+
+def test_recurrent_either_way():
+    import paper_2211_15023_amd as A
+    nt, pt, ns, ps, qp = policies(4)
+    pol = A.Policy(ns, "int8", student_tensors(qp), qp.act_scales)
+    B = 12
+    x, u = torch.from_numpy(make_states(ns, B, wl.STREAM["states"])).cuda(), torch.from_numpy(wl.make_uniforms(B)).cuda()
+    h0, c0 = (torch.from_numpy(t).cuda() for t in wl.make_hc(B, 256))
+    done = torch.tensor([0, 1, 0] * 4, dtype=torch.uint8, device="cuda")
+
+    def run(wrap, done, stream):
+        h, c = h0.clone(), c0.clone()
+        out = pol.forward(wrap(x), u, done=done, h=wrap(h), c=c, stream=stream)
+        torch.cuda.synchronize()
+        return *out, h, c
+    args = A.binding._loaded()
+    out = pol.alloc_outputs(B)
+    assert args.forward_recurrent(pol.handle, x, u, done, h0.clone(), c0.clone(), *out, None) == 0
+    assert args.forward_recurrent(pol.handle, x, u, done.bool(), h0, c0, *out, None) is None
+    assert args.forward_recurrent(pol.handle, x, u, done, h0.half(), c0, *out, None) is None
+    for dn in (done, None):
+        for a, b in zip(run(lambda t: t, dn, None), run(lambda t: t.as_subclass(Sub), dn, torch.cuda.current_stream())):
+            assert torch.equal(a, b)
+    for bad in (dict(done=done.bool()), dict(h=h0.half()), dict(c=c0.t())):
+        with pytest.raises(ValueError):
+            pol.forward(x, u, **{**dict(done=done, h=h0, c=c0), **bad})
+    for bad in (dict(h=None), dict(c=None)):
+        with pytest.raises(A.AccerlError):
+            pol.forward(x, u, **{**dict(done=done, h=h0, c=c0), **bad})
+    with pytest.raises(A.AccerlError):
+        A.accerl_actor_forward(pol.handle, x, u, *out)              # a recurrent policy
+    pol.close()
