@@ -77,3 +77,12 @@ def check_sampler_self_consistency(got_action, got_logits, u, delta=1e-5):
     u = np.ascontiguousarray(u, np.float32)
     want = L.softmax_sample(got_logits, u)
     return check_actions(got_action, want, got_logits, u, delta)
+
+
+def kernel_names(call):
+    """call()'s result and the names of the kernels it launched, from a kernel trace."""
+    import torch
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA], acc_events=True) as prof:
+        out = call()
+        torch.cuda.synchronize()
+    return out, [e.key for e in prof.key_averages()]

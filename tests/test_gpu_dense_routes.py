@@ -6,7 +6,7 @@ import torch
 import oracle
 import workloads as wl
 from workloads import Net, conv, dense, relu, flatten
-from helpers import make_states, student_tensors, teacher_tensors
+from helpers import kernel_names, make_states, student_tensors, teacher_tensors
 
 pytestmark = pytest.mark.gpu
 
@@ -16,13 +16,6 @@ CUS = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is
 def _row_major(cout, side, width):
     return Net("routes", "u8", (4, side + 1, side + 1), 5,
                [conv(4, cout, 2, 1, 0, False), relu(), flatten(), dense(cout * side * side, width, True)])
-
-
-def _kernels(pol, x, u):
-    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
-        out = pol.forward(x, u)
-        torch.cuda.synchronize()
-    return out, [e.key for e in prof.key_averages() if "gemm" in e.key]
 
 
 # states at which `per` workgroups a tile of `rows` states fill the compute units once
@@ -64,7 +57,7 @@ def test_route(case):
     dx, du, ref = torch.cat([dx] * times), torch.cat([du] * times), [torch.cat([t] * times) for t in ref]
     for B, kernel in lines:
         print(f"{net.name} {precision} B={B}: {kernel}", flush=True)
-        out, names = _kernels(pol, dx[:B], du[:B])
+        out, names = kernel_names(lambda: pol.forward(dx[:B], du[:B]))
         assert any(kernel in n for n in names), names
         for got, want in zip(out, ref):
             assert torch.equal(got, want[:B])
