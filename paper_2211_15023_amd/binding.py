@@ -1,4 +1,4 @@
-"""Binding of include/accerl.h (ctypes; the calls made every step through the compiled accerl_args): same names, argument marshalling only."""
+"""Binding of include/accerl.h (ctypes; forwards, V-trace and the KL indicators through the compiled accerl_args): same names, argument marshalling only."""
 import ctypes as C
 import os
 
@@ -83,14 +83,14 @@ def load_library():
         getattr(lib, f).restype = C.c_int
     _lib = lib
     try:
-        _loaded()                            # here and not in the first step's call, which says it if there is none
+        _loaded()                            # here and not in the first call that needs it, which says it if there is none
     except ImportError:
         pass
     return lib
 
 
 def _loaded():
-    """accerl_args, for the calls made every step; host-only calls do without it."""
+    """accerl_args, for the calls that go through it; the others, and host-only ones, do without it."""
     global _args
     load_library()                           # accerl_args links against torch and the library
     try:
@@ -199,8 +199,9 @@ def accerl_policy_destroy(handle):
 
 
 # Marshalling is most of what a small call costs the host (32 states of the 64-unit MLP, time between calls: 5.8 us through ctypes from
-# the code below, 3.6 through accerl_args; the kernel takes 2.5).  The calls made every step go through accerl_args and come here
-# where it returns None, because an argument is not a plain tensor: an error to raise, a subclass of torch.Tensor, a stream object.
+# the code below, 3.6 through accerl_args; the kernel takes 2.5).  A policy's forwards, V-trace and the KL indicators go through
+# accerl_args and come here where it returns None, because an argument is not a plain tensor: an error to raise, a subclass of torch.Tensor,
+# a stream object.  The mixture and the distillation loss always come here.
 def _ptr(t, dtype=None):
     if t is None:
         return None

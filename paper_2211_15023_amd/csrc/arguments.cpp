@@ -1,4 +1,4 @@
-// Argument marshalling of the calls that are made every step, as a CPython module: tensors are checked and taken to pointers here, and
+// Argument marshalling of a policy's forwards, V-trace and the KL indicators, as a CPython module: tensors are checked and taken to pointers here, and
 // the library is called without the interpreter's lock.  A call of 32 states on the 64-unit MLP costs the host what the checks, the
 // conversions of eight ctypes arguments and the launch cost; the kernel takes 2.5 us.
 //

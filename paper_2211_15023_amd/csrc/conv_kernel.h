@@ -156,8 +156,8 @@ constexpr int conv_min_blocks(int NT, int KS, int PF, int PT, int NW, int MODE, 
 // EX: residual join and fused max-pooling compiled in (kernels for layers that need neither do without their registers).
 // ROWS: observations through the row list, 1 = a batch is one image, 2 = any number, every unit looks its image up.  As a test in the
 // kernel the list cost those with their weights in registers up to 0.8 us (20x20x4, 4096 states, 12.3 -> 13.1 us); in the others
-// (KS = 0) it costs nothing and is one (net2's first layer at 160 states 12.3 us without, 11.8 with it).  Both forms of the list in one
-// instance take registers that leave two workgroups per compute unit for three (mixture with net2, 4096 rows, 101 -> 112 us).
+// (KS = 0) it costs nothing and is one (an 8-filter first layer with its weights in LDS at 160 states 12.3 us without, 11.8 with it).  Both forms of the list in one
+// instance take registers that leave two workgroups per compute unit for three (a mixture with that layer, 4096 rows, 101 -> 112 us).
 template <int EL, int NT, int KS, int RD, int MODE, int PF, int PT, int NW, bool WP, bool EX, int ROWS>
 __global__ __launch_bounds__(NW * 64, conv_min_blocks(NT, KS, PF, PT, NW, MODE, ROWS)) void conv_kernel(const ConvParams p) {
     constexpr int CONV_THREADS = NW * 64;

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(512, 2) void stack_bf16_kernel(const BStackParams p
     v4f bias[5];
     {
         auto frag = [&](int cv, int st, int ks) -> v4i {
-            if (ks == 5 && st == 4) {                    // the two chunks of the last step in the upper half (see bs_bottom)
+            if (ks == 5 && st == 4) {                    // the two chunks of the last step in the upper half (bs_row multiplies it with pixels 1, 2)
                 const v4i v = p.w[cv][(st * NH + half) * 64 + (lane & 31)];
                 return g >= 2 ? v : (v4i){0, 0, 0, 0};
             }

@@ -40,9 +40,11 @@
 //    is what limits the workgroups.
 //  * the next batch's input bytes are requested at the start of the current batch's last phase and land while it runs.
 //
-// Measured at 16384 states (kernel traces): 429 / 270 / 95 -> 325 / 182 / 72 us (320 / 180 / 71 without conversions, see
-// BITS).  Vector issue 80 / 69 / 56 % of the clocks,
-// LDS pipe 56 / 42 / 36 %, matrix cores 27 / 39 / 35 %.
+// Measured at 16384 states (kernel traces): 429 / 270 / 95 us with tiles in raster order, now 295-309 / 165-173 / 67-69 (two cards).
+// Vector instructions at four clocks each 85 / 80 / 61 % of the clocks (an overstatement, see above), LDS pipe 60 / 49 / 40 %, matrix
+// cores 29 / 46 / 39 %.  What the clocks go to is not settled by that: the first stack, 330 us, took 270 without its requantizations,
+// 270 without its products and 228 without either, 325 without the LDS reads of the walks and 326 without barriers.  The 228 -- pooling
+// maxima, the skip connection's unpacking, staging, LDS stores, addresses -- have not been taken apart.
 //
 // Arithmetic and constants are those of the layer-by-layer kernels (conv_kernel.h), so results are bit-identical; the debug
 // taps still run that path.  Network: the benchmark's IMPALA configuration (three such stacks).
@@ -325,7 +327,6 @@ __global__ __launch_bounds__(NW * 64, MINB) void stack_kernel(const StackParams 
     // the weights are in their registers before the loop: the waits the compiler places there then only ever concern the
     // loads of the next batch, not these
     __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
-
 
     // ---- this lane's column of the blocks; lanes past the last column repeat it (the same bytes written twice)
     const int n = wave * 16 + j, nc = min(n, S::NCOL - 1);

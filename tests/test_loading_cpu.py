@@ -1,4 +1,4 @@
-"""What needs which file: host-only calls take libaccerl.so alone, the calls made every step say how to build accerl_args.so where it is
+"""What needs which file: host-only calls take libaccerl.so alone, the calls that go through accerl_args.so say how to build it where it is
 missing or of another torch or Python."""
 import os
 import shutil
